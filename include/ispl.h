@@ -102,7 +102,10 @@ ispl_status ispl_create(const ispl_config* cfg, ispl_ctx** out);
  *   accumulate  0: spectra = sum;  1: spectra += sum (resumable integration).
  *   n_pulses  0 <= n_pulses <= max_pulses.  With 0 pulses the sum is empty:
  *             spectra is zeroed (accumulate = 0) or left as is (accumulate = 1).
- * Arithmetic: decode, transform, power and accumulation in FP32.
+ * Arithmetic: decode, transform, power and accumulation in FP32.  Codes of at
+ * most 1024 samples are summed over the pulses on a grid of 2^m >= 2 L - 1
+ * frequencies, from which the N bins follow exactly (|X|^2 of L samples has 2 L - 1
+ * coefficients); S >= 0 as in the direct form.
  */
 ispl_status ispl_integrate_spectra(ispl_ctx* ctx, const void* samples,
                                    const float* tx_code, int32_t tx_per_pulse,
@@ -474,8 +477,8 @@ ispl_status ispl_stream_submit(ispl_stream* st, int32_t slot, int32_t n_pulses,
                                void* stream);
 ispl_status ispl_stream_sync(ispl_stream* st);
 
-/* Launch plan the library would use for n_pulses pulses with this config;
- * host-only (no device call), for tests and tooling.  Fills, when non-NULL:
+/* Launch plan of the direct N-point transform for n_pulses pulses with this config
+ * (calls that sum on a shorter grid plan that launch by themselves); host-only (no device call), for tests and tooling.  Fills, when non-NULL:
  * chunks = number of pulse chunks integrated side by side (1 = no partial
  * buffers), waves_per_block, blocks = workgroups of the fused launch. */
 ispl_status ispl_plan(const ispl_config* cfg, int32_t n_pulses, int32_t* chunks,

@@ -31,6 +31,10 @@ struct ispl_ctx {
   // codes of L > 2 SUB as sign bits (long-code kernel), max_pulses rows
   uint16_t* code_bits;  // [max_pulses][CODE_BITS_WORDS]
   int32_t* code_binary; // [max_pulses]
+  float* grid;          // folded integration: scratch of grid_bytes (nullptr: never folds)
+  int64_t grid_bytes;
+  uint32_t* grid_bits;  // codes as sign bits [max_pulses][64] and flags [max_pulses]
+  int32_t* grid_binary;
 };
 
 namespace {
@@ -96,6 +100,10 @@ constexpr int kMaxWavesPerBlock = ISPL_MAX_WAVES_PER_BLOCK;
 static_assert(kMaxWavesPerBlock <= ispl::MAX_WAVES_PER_BLOCK, "at most 16 waves per block");
 constexpr int64_t kMaxPartialBytes = int64_t{1} << 30;
 
+// Fewest pulses that fold: the expansion costs each gate about as much as one
+// pulse's N-point transform, and a launch.
+constexpr int kMinFoldPulses = 3;
+
 struct Plan {
   int sub_len;    // M: points of one sub-transform (1024, or 16384 for L > 1024)
   int r;          // R = N / M sub-transforms (bin classes) per spectrum
@@ -137,6 +145,93 @@ Plan make_plan(const ispl_config& c, int32_t n_pulses, int32_t force_rw = 0,
   pl.chunks = static_cast<int>(chunks);
   pl.blocks = base * pl.chunks;
   return pl;
+}
+
+// Folded integration: fewest points of a grid that holds |X|^2 of an L-sample
+// row, a power of two >= 2 L - 1 (at least 128), or 0 when the N bins are fewer
+// or the code has no grid kernel.
+int grid_length(const ispl_config& c) {
+  if (c.code_len > ispl::SUB) return 0;
+  int m = 128;
+  while (m < 2 * c.code_len - 1) m *= 2;
+  return m <= c.fft_len ? m : 0;
+}
+
+// Fewest pulse-gate transforms whose launch first packs the codes into sign
+// bits (a pass of its own over the codes).
+constexpr int64_t kMinBitsPulseGates = 32768;
+
+struct GridPlan {
+  int len;     // 0: the direct transform
+  int waves;   // per workgroup
+  int chunks;  // pulse chunks, each a workgroup per gate
+};
+
+constexpr int64_t kGridBytes = int64_t{64} << 20;       // most grid scratch
+constexpr int64_t kGridChunkBytes = int64_t{32} << 20;  // most of it for several chunks
+
+// Waves per workgroup and pulse chunks on a grid of `len` points with the
+// least estimated time (us, fitted to measurements), and that time: rounds of
+// workgroups over the chip, each a fixed cost and its steps; a step takes
+// longer the more waves share a SIMD.
+double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force_chunks,
+                  GridPlan* out) {
+  const int classes = len > ispl::SUB ? len / ispl::SUB : 1;
+  const int per_step = len < ispl::SUB ? ispl::SUB / len : 1;  // pulses a wave takes at once
+  const int64_t steps = (n_pulses + per_step - 1) / per_step;
+  const int64_t row = int64_t{4} * len * c.n_gates;
+  double best = 0.0;
+  out->len = 0;
+  for (int waves = 8; waves <= 16; waves *= 2) {
+    const int runs = waves / classes;
+    int64_t lo = 1, hi = std::min<int64_t>(64, (steps + runs - 1) / runs);
+    hi = std::max<int64_t>(1, std::min(hi, kGridChunkBytes / row));
+    if (force_chunks > 0) {
+      lo = hi = std::min<int64_t>(force_chunks, kMaxChunks);
+      if (len == c.fft_len) lo = hi = std::max<int64_t>(1, std::min(hi, kGridChunkBytes / row));
+    }
+    for (int64_t chunks = lo; chunks <= hi; ++chunks) {
+      const int64_t wgs = chunks * c.n_gates, per_cu = kMaxWavesPerCu / waves;
+      const int64_t rounds = (wgs + kComputeUnits * per_cu - 1) / (kComputeUnits * per_cu);
+      const int64_t resident = std::min(per_cu, (wgs + kComputeUnits - 1) / kComputeUnits);
+      const int64_t iters = (steps + chunks * runs - 1) / (chunks * runs);
+      const double step_us = std::max(1.6, 0.85 * static_cast<double>(resident * waves) / 4);
+      const double us = rounds * (iters * step_us + 3.0) + chunks * (row / 2e6 + 0.1) +
+                        (len == c.fft_len && chunks > 1 ? 4.0 : 0.0);
+      if (out->len == 0 || us < best) {
+        *out = GridPlan{len, waves, static_cast<int>(chunks)};
+        best = us;
+      }
+    }
+  }
+  return best;
+}
+
+GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks = 0) {
+  GridPlan fold{}, whole{};
+  const int len = grid_length(c);
+  if (len == 0 || n_pulses < 1) return fold;
+  // a grid of all the bins needs no expansion
+  const double whole_us = c.fft_len <= 2 * ispl::SUB && c.fft_len >= ispl::SUB
+                              ? grid_split(c, c.fft_len, n_pulses, force_chunks, &whole)
+                              : 0.0;
+  if (len == c.fft_len) return whole;
+  const double fold_us = grid_split(c, len, n_pulses, force_chunks, &fold);
+  // the expansion: two workgroups per compute unit
+  const double expand_us = 9.0 + 6.0 * ((c.n_gates - 1) / (2 * kComputeUnits));
+  if (whole.len > 0) return fold_us + expand_us < whole_us ? fold : whole;
+  return n_pulses >= kMinFoldPulses ? fold : GridPlan{};
+}
+
+// Scratch of a context whose calls run on a grid (0: they never do): the chunk
+// partials of every gate when they fit, else of as many gates as do (any chunk
+// count of a plan fits for one gate).
+int64_t grid_scratch_bytes(const ispl_config& c) {
+  const int64_t len = grid_length(c);
+  if (len == 0) return 0;
+  const int64_t most = c.fft_len <= 2 * ispl::SUB ? c.fft_len : len;  // longest grid of a plan
+  const int64_t all = 4 * most * c.n_gates;
+  return std::min(kGridBytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), kMaxChunks * 4 * most}));
 }
 
 ispl_status validate_config(const ispl_config* c) {
@@ -415,6 +510,22 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
                   hipGetErrorString(e));
     }
   }
+  ctx->grid_bytes = grid_scratch_bytes(*cfg);
+  if (ctx->grid_bytes > 0) {
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->grid), static_cast<size_t>(ctx->grid_bytes));
+    if (e == hipSuccess)  // the sign bits and their flags in one block
+      e = hipMalloc(reinterpret_cast<void**>(&ctx->grid_bits),
+                    static_cast<size_t>(cfg->max_pulses) * 65 * sizeof(uint32_t));
+    if (e != hipSuccess) {
+      if (ctx->grid) (void)hipFree(ctx->grid);
+      if (ctx->partial) (void)hipFree(ctx->partial);
+      (void)hipFree(ctx->twiddle);
+      delete ctx;
+      return fail(ISPL_ERR_OUT_OF_MEMORY, "grid scratch: %s", hipGetErrorString(e));
+    }
+    ctx->grid_binary =
+        reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(cfg->max_pulses) * 64);
+  }
   if (cfg->code_len > 2 * ispl::SUB) {  // the long-code kernel reads binary codes as sign bits
     const size_t rows = static_cast<size_t>(cfg->max_pulses);
     e = hipMalloc(reinterpret_cast<void**>(&ctx->code_bits),
@@ -424,6 +535,8 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
     if (e != hipSuccess) {
       if (ctx->code_bits) (void)hipFree(ctx->code_bits);
       if (ctx->partial) (void)hipFree(ctx->partial);
+      if (ctx->grid) (void)hipFree(ctx->grid);
+      if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
       (void)hipFree(ctx->twiddle);
       delete ctx;
       return fail(ISPL_ERR_OUT_OF_MEMORY, "code sign bits: %s", hipGetErrorString(e));
@@ -446,6 +559,8 @@ void ispl_destroy(ispl_ctx* ctx) {
     if (ctx->twiddle) (void)hipFree(ctx->twiddle);
     if (ctx->code_bits) (void)hipFree(ctx->code_bits);
     if (ctx->code_binary) (void)hipFree(ctx->code_binary);
+    if (ctx->grid) (void)hipFree(ctx->grid);
+    if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
   }
   delete ctx;
 }
@@ -559,6 +674,25 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
   a.waves_per_block = pl.rw;
   a.gate_list = gate_list;
   a.gate_count = gate_count;
+  GridPlan gp{};
+  if (ctx->grid && !adapt && !deferred_chunks) gp = grid_plan(c, n_pulses, ctx->force_chunks);
+  if (gp.len > 0) {
+    a.out = spectra;
+    a.chunks = 1;
+    a.grid = ctx->grid;
+    a.grid_len = gp.len;
+    a.grid_chunks = gp.chunks;
+    a.grid_waves = gp.waves;
+    a.grid_rows = static_cast<int32_t>(
+        std::min<int64_t>(c.n_gates, ctx->grid_bytes / (int64_t{4} * gp.len * gp.chunks)));
+    if (static_cast<int64_t>(n_pulses) * c.n_gates >= kMinBitsPulseGates) {
+      a.grid_bits = ctx->grid_bits;
+      a.grid_binary = ctx->grid_binary;
+    }
+    e = ispl::launch_fused(a, s);
+    if (e != hipSuccess) return hip_fail(e, "folded launch");
+    return ok();
+  }
   if (adapt) {
     a.out = spectra;
     a.chunks = 1;
@@ -659,6 +793,8 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
   tmp.partial = pl.chunks > 1 ? reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES)
                               : nullptr;
   tmp.min_chunk_pulses = kMinChunkPulses;
+  tmp.grid_bytes = grid_scratch_bytes(*cfg);
+  if (tmp.grid_bytes > 0) tmp.grid = reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES);
   if (n_pulses > 0) {
     e = ispl::launch_build_twiddles(tmp.twiddle, cfg->fft_len, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "twiddle launch");

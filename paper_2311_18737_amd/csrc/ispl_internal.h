@@ -76,6 +76,20 @@ struct FusedArgs {
   // launch_pack_code_bits for the same tx; NULL = always read tx.
   const uint16_t* code_bits;     // [rows][SUB]: bit j of word lg is code[lg + SUB j] == -1
   const int32_t* code_binary;    // [rows]: 1 when every code of the row is +-1 + 0i
+  // Folded integration (grid_len 0 = off): the pulses are summed on a grid of
+  // grid_len >= 2 L - 1 points, which is then expanded to the N bins of `out`
+  // (`chunks` and `waves_per_block` are not read); grid_len = N sums the bins
+  // themselves.  `grid` holds the chunk partials of grid_rows gates at a time,
+  // [grid_chunks][grid_rows][grid_len] floats (grid_len = N: of all gates, and
+  // one chunk needs none).  grid_bits / grid_binary (both or neither):
+  // [code rows][64] words and [code rows] flags for the codes' sign bits.
+  float* grid;
+  uint32_t* grid_bits;
+  int32_t* grid_binary;
+  int32_t grid_len;
+  int32_t grid_chunks;
+  int32_t grid_waves;
+  int32_t grid_rows;
 };
 
 // Words of one code row in the sign-bit form (one per first-pass thread).
@@ -95,6 +109,27 @@ constexpr int MAX_BATCH_MODES = 8;
 int fused_lds_bytes(int rw, int sub_len);
 
 hipError_t launch_fused(const FusedArgs& a, hipStream_t stream);
+
+// Folded integration of one run of gates: slots slot0 .. slot0 + rows - 1 of
+// all gates or of the list.
+struct FoldArgs {
+  const void* samples;
+  const float* tx;
+  const float* twiddle;      // W_N^i, i < N
+  const uint32_t* code_bits; // [code rows][64] sign bits (NULL: read tx), see pack_grid_bits
+  const int32_t* code_binary;
+  float* grid;               // [chunks][rows][M]
+  float* out;                // [G][N]
+  int64_t stride;
+  int32_t n_fft, grid_len, code_len;
+  int32_t n_gates, gate_step, first_gate, n_pulses;
+  int32_t chunks, waves, tx_per_pulse, accumulate;
+  const int32_t* gate_list;
+  const int32_t* gate_count;
+  int32_t slot0, rows;
+};
+// The whole folded integration of a.grid_len > 0.
+hipError_t launch_folded(const FusedArgs& a, hipStream_t stream);
 
 // S[g][k] = (accumulate ? S[g][k] : 0) + sum_{c < C} partial[c][g][k], c ascending.
 // spectra (+)= sum over chunks of partial; with a list, only the rows of the

@@ -1,0 +1,168 @@
+"""Folded integration: pulses summed on a grid of M >= 2 L - 1 points, expanded
+to the N bins once per gate, against the FP64 oracle where the path changes
+form: code lengths on both sides of every grid length, pulse counts around the
+pulses that one wave takes at once, every expansion factor (one and several
+rounds of bin classes), codes read as sign bits and as complex numbers in one
+call, more gates than the scratch holds, and powers beyond the FP32 range.
+
+Tolerance: the plain path's 1e-5 of max(S, mean S) per bin (parity_util)."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import integrate_spectra as oracle_spectra  # noqa: E402
+from synth import random_inputs  # noqa: E402
+from tests.conftest import ensure_library  # noqa: E402
+from tests.parity_util import assert_spectra_match  # noqa: E402
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def ispl():
+    ensure_library()
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2311_18737_amd as pkg
+
+    return pkg
+
+
+def test_a_grid_of_2l_minus_1_points_holds_the_spectrum():
+    """The identity itself, in FP64: lags from the M-point power spectrum, then the N bins."""
+    rng = np.random.default_rng(1)
+    for L, M, N in ((1, 128, 1024), (64, 128, 1024), (65, 256, 2048), (1000, 2048, 16384)):
+        y = rng.standard_normal((3, L)) + 1j * rng.standard_normal((3, L))
+        grid = (np.abs(np.fft.fft(y, M)) ** 2).sum(axis=0)
+        r = np.fft.ifft(grid)
+        lags = np.zeros(N, dtype=complex)
+        lags[:L] = r[:L]
+        lags[N - L + 1:] = r[M - L + 1:]
+        want = (np.abs(np.fft.fft(y, N)) ** 2).sum(axis=0)
+        assert np.max(np.abs(np.fft.fft(lags).real - want)) <= 1e-12 * want.max() * N
+
+
+CASES = [
+    # N,    L,    G,  P, type,  per-pulse code, code kind
+    (1024, 1, 2, 9, "c64", True, "phase"),
+    (1024, 64, 3, 17, "ci16", True, "bpsk"),
+    (1024, 65, 3, 8, "c64", False, "gauss"),
+    (1024, 512, 5, 7, "c64", True, "phase"),
+    (1024, 256, 300, 120, "ci16", True, "bpsk"),
+    (2048, 128, 4, 5, "ci16", False, "bpsk"),
+    (2048, 129, 4, 6, "c64", True, "phase"),
+    (2048, 1024, 2, 4, "c64", True, "gauss"),
+    (2048, 513, 260, 130, "c64", True, "bpsk"),
+    (4096, 256, 3, 3, "c64", True, "bpsk"),
+    (4096, 257, 3, 4, "ci16", True, "phase"),
+    (8192, 512, 2, 5, "c64", False, "phase"),
+    (16384, 513, 2, 3, "ci16", True, "bpsk"),
+    (16384, 200, 40, 900, "c64", True, "bpsk"),
+    (32768, 100, 2, 12, "ci16", True, "phase"),
+    (32768, 1024, 2, 3, "c64", True, "phase"),
+    (65536, 512, 2, 3, "c64", True, "gauss"),
+    (65536, 30, 1, 40, "c64", True, "phase"),
+    (65536, 1000, 1, 2, "ci16", True, "bpsk"),
+]
+
+
+def run(ispl, samples, tx, out=None, accumulate=False, **geo):
+    ctx = ispl.Context(max_pulses=max(1, samples.shape[0]), **geo)
+    xs = torch.from_numpy(np.ascontiguousarray(samples)).to(DEV)
+    xt = torch.from_numpy(np.ascontiguousarray(tx)).to(DEV)
+    out = ctx.integrate_spectra(xs, xt, out=out, accumulate=accumulate)
+    torch.cuda.synchronize()
+    ctx.close()
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=lambda t: "N{}_L{}_G{}_P{}_{}_{}_{}".format(*t))
+def test_folded_integration_matches_oracle(ispl, case):
+    N, L, G, P, st, per_pulse, kind = case
+    print(f"case {case}", flush=True)
+    stride = 3 + (G - 1) * 7 + L + 2
+    samples, tx = random_inputs(P, stride, L, sample_type=st, code_kind=kind,
+                                tx_rows=None if per_pulse else 1, seed=N + L + P,
+                                amplitude=3000.0 if st == "ci16" else 1.0)
+    geo = dict(code_len=L, fft_len=N, n_gates=G, gate_step=7, first_gate=3, pulse_stride=stride,
+               sample_type=st)
+    out = run(ispl, samples, tx, **geo)
+    ref = oracle_spectra(samples, tx, n_gates=G, gate_step=7, first_gate=3, fft_len=N,
+                         tx_per_pulse=per_pulse)
+    assert_spectra_match(out.cpu().numpy(), ref, what=str(case))
+    assert bool((out >= 0).all())
+    again = run(ispl, samples, tx, out=out.clone(), accumulate=True, **geo)
+    assert torch.equal(again, 2 * out)
+
+
+@pytest.mark.gpu
+def test_sign_bits_and_complex_codes_in_one_call(ispl):
+    """Enough pulse-gate pairs for the sign-bit pass; some rows binary, some not."""
+    L, N, G, P = 300, 4096, 64, 600
+    stride = (G - 1) * 5 + L
+    samples, tx = random_inputs(P, stride, L, code_kind="bpsk", seed=5)
+    _, phase = random_inputs(P, stride, L, code_kind="phase", seed=6)
+    tx = tx.copy()
+    tx[100:107] = phase[100:107]
+    tx[401, L - 1] = 1.0 + 0.25j
+    tx[402, 7] = -0.0 + 1.0j
+    out = run(ispl, samples, tx, code_len=L, fft_len=N, n_gates=G, gate_step=5, pulse_stride=stride)
+    ref = oracle_spectra(samples, tx, n_gates=G, gate_step=5, first_gate=0, fft_len=N,
+                         tx_per_pulse=True)
+    assert_spectra_match(out.cpu().numpy(), ref, what="binary and complex rows")
+
+
+@pytest.mark.gpu
+def test_more_gates_than_the_scratch_holds(ispl):
+    """9000 gates x 2048 grid points (74 MB) run in two slices; a gate list through both."""
+    L, N, G, P, s = 600, 4096, 9000, 3, 2
+    stride = (G - 1) * s + L
+    samples, tx = random_inputs(P, stride, L, code_kind="phase", seed=8)
+    geo = dict(code_len=L, fft_len=N, n_gates=G, gate_step=s, pulse_stride=stride)
+    out = run(ispl, samples, tx, **geo)
+    gates = [0, 1, 4095, 8190, 8191, 8192, 8193, 8999]
+    ref = oracle_spectra(samples, tx, n_gates=G, gate_step=s, first_gate=0, fft_len=N,
+                         tx_per_pulse=True, gates=gates)
+    assert_spectra_match(out[gates].cpu().numpy(), ref, what="sliced")
+    ctx = ispl.Context(max_pulses=P, **geo)
+    lst = torch.arange(G - 1, -1, -1, dtype=torch.int32, device=DEV)
+    part = torch.full((G, N), -1.0, device=DEV)
+    ctx.integrate_spectra(torch.from_numpy(samples).to(DEV), torch.from_numpy(tx).to(DEV), out=part,
+                          gates=(lst, torch.tensor([8500], dtype=torch.int32, device=DEV)))
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.equal(part[500:], out[500:])
+    assert bool((part[:500] == -1.0).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,N", [(100, 2048), (700, 16384)])
+def test_powers_beyond_fp32_and_nan(ispl, L, N):
+    """Bins whose power overflows are infinite and the others keep their values;
+    a NaN sample spoils exactly the gates that read it; all-zero gates are zero."""
+    G, P, s = 6, 5, L
+    stride = G * s
+    samples, tx = random_inputs(P, stride, L, code_kind="bpsk", seed=9)
+    n = np.arange(L)
+    tone = np.exp(2j * np.pi * 0.125 * n)
+    samples[:, s:2 * s] = samples[:, s:2 * s] * 1e16 + 3e18 * tx * tone  # gate 1: overflows at its line
+    samples[:, 2 * s:3 * s] *= 1e-18                                     # gate 2: tiny powers
+    samples[:, 3 * s:4 * s] = 0                                          # gate 3: no echo at all
+    samples[2, 4 * s + 5] = np.nan                                       # gate 4
+    out = run(ispl, samples, tx, code_len=L, fft_len=N, n_gates=G, gate_step=s, pulse_stride=stride)
+    got = out.cpu().numpy().astype(np.float64)
+    with np.errstate(all="ignore"):
+        ref = oracle_spectra(samples, tx, n_gates=G, gate_step=s, first_gate=0, fft_len=N,
+                             tx_per_pulse=True)
+    big = float(np.finfo(np.float32).max)
+    over, under = ref[1] > 1.0001 * big, ref[1] < 0.9999 * big
+    assert over.any() and under.any()
+    assert np.isinf(got[1][over]).all() and np.isfinite(got[1][under]).all()
+    # within a wide margin below the line the rounding is relative to the line's amplitude
+    near = np.abs(got[1][under] - ref[1][under]) / np.sqrt(ref[1][under] * (3e18 * L) ** 2 * P)
+    assert near.max() <= 1e-5
+    assert_spectra_match(got[[0, 2, 5]], ref[[0, 2, 5]], what="ordinary and tiny gates")
+    assert (got[3] == 0).all() and np.isnan(got[4]).all()
