@@ -33,6 +33,7 @@ struct ispl_ctx {
   int32_t* code_binary; // [max_pulses]
   float* grid;          // folded integration: scratch of grid_bytes (nullptr: never folds)
   int64_t grid_bytes;
+  double* twiddle64;    // the twiddle table in double
   uint32_t* grid_bits;  // codes as sign bits [max_pulses][64] and flags [max_pulses]
   int32_t* grid_binary;
 };
@@ -151,7 +152,7 @@ Plan make_plan(const ispl_config& c, int32_t n_pulses, int32_t force_rw = 0,
 // row, a power of two >= 2 L - 1 (at least 128), or 0 when the N bins are fewer
 // or the code has no grid kernel.
 int grid_length(const ispl_config& c) {
-  if (c.code_len > ispl::SUB) return 0;
+  if (c.code_len > 8 * ispl::SUB) return 0;
   int m = 128;
   while (m < 2 * c.code_len - 1) m *= 2;
   return m <= c.fft_len ? m : 0;
@@ -167,7 +168,9 @@ struct GridPlan {
   int chunks;  // pulse chunks, each a workgroup per gate
 };
 
-constexpr int64_t kGridBytes = int64_t{64} << 20;       // most grid scratch
+constexpr int64_t kGridBytes = int64_t{63} << 20;       // most grid scratch
+static_assert(kGridBytes + ispl::NOALLOC_TWIDDLE64_BYTES <= ispl::NOALLOC_PARTIAL_BYTES,
+              "the entry point that allocates nothing holds the grid scratch");
 constexpr int64_t kGridChunkBytes = int64_t{32} << 20;  // most of it for several chunks
 
 // Waves per workgroup and pulse chunks on a grid of `len` points with the
@@ -180,9 +183,10 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force
   const int per_step = len < ispl::SUB ? ispl::SUB / len : 1;  // pulses a wave takes at once
   const int64_t steps = (n_pulses + per_step - 1) / per_step;
   const int64_t row = int64_t{4} * len * c.n_gates;
+  const bool is_long = classes > 2;  // one wave per bin class, one pulse at a time
   double best = 0.0;
   out->len = 0;
-  for (int waves = 8; waves <= 16; waves *= 2) {
+  for (int waves = is_long ? classes : 8; waves <= 16; waves = is_long ? 32 : 2 * waves) {
     const int runs = waves / classes;
     int64_t lo = 1, hi = std::min<int64_t>(64, (steps + runs - 1) / runs);
     hi = std::max<int64_t>(1, std::min(hi, kGridChunkBytes / row));
@@ -212,7 +216,7 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks 
   const int len = grid_length(c);
   if (len == 0 || n_pulses < 1) return fold;
   // a grid of all the bins needs no expansion
-  const double whole_us = c.fft_len <= 2 * ispl::SUB && c.fft_len >= ispl::SUB
+  const double whole_us = c.fft_len <= 2 * ispl::SUB || len == c.fft_len
                               ? grid_split(c, c.fft_len, n_pulses, force_chunks, &whole)
                               : 0.0;
   if (len == c.fft_len) return whole;
@@ -229,7 +233,7 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks 
 int64_t grid_scratch_bytes(const ispl_config& c) {
   const int64_t len = grid_length(c);
   if (len == 0) return 0;
-  const int64_t most = c.fft_len <= 2 * ispl::SUB ? c.fft_len : len;  // longest grid of a plan
+  const int64_t most = c.fft_len <= 2 * ispl::SUB ? c.fft_len : len;  // longest of its grids
   const int64_t all = 4 * most * c.n_gates;
   return std::min(kGridBytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), kMaxChunks * 4 * most}));
 }
@@ -285,8 +289,8 @@ struct DeviceGuard {  // restores the caller's current device
 
 // W_N^i = exp(-2 pi i / N)^i for i < N, from double-precision cos/sin of the
 // first octant and exact symmetries (so 0, +-1 and the octant values are exact).
-std::vector<float> twiddle_table(int n) {
-  std::vector<float> t(2 * static_cast<size_t>(n));
+std::vector<double> twiddle_table(int n) {
+  std::vector<double> t(2 * static_cast<size_t>(n));
   const int quarter = n / 4, eighth = n / 8;
   for (int i = 0; i < n; ++i) {
     const int qd = i / quarter;        // quadrant of the angle 2 pi i / N
@@ -308,8 +312,8 @@ std::vector<float> twiddle_table(int n) {
       case 2: ci = -c; si = -s; break;
       default: ci = s; si = -c; break;
     }
-    t[2 * i] = static_cast<float>(ci);
-    t[2 * i + 1] = static_cast<float>(-si);
+    t[2 * i] = ci;
+    t[2 * i + 1] = -si;
   }
   return t;
 }
@@ -484,7 +488,8 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
   ctx->min_chunk_pulses = min_chunk_pulses;
   const Plan worst = make_plan(*cfg, cfg->max_pulses, 0, 0, min_chunk_pulses);
 
-  const std::vector<float> tw = twiddle_table(cfg->fft_len);
+  const std::vector<double> tw64 = twiddle_table(cfg->fft_len);
+  const std::vector<float> tw(tw64.begin(), tw64.end());  // rounded
   e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle), tw.size() * sizeof(float));
   if (e != hipSuccess) {
     delete ctx;
@@ -513,18 +518,24 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
   ctx->grid_bytes = grid_scratch_bytes(*cfg);
   if (ctx->grid_bytes > 0) {
     e = hipMalloc(reinterpret_cast<void**>(&ctx->grid), static_cast<size_t>(ctx->grid_bytes));
+    if (e == hipSuccess)
+      e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle64), tw64.size() * sizeof(double));
+    if (e == hipSuccess)
+      e = hipMemcpy(ctx->twiddle64, tw64.data(), tw64.size() * sizeof(double), hipMemcpyHostToDevice);
+    const size_t words = cfg->code_len > ispl::SUB ? ispl::SUB : 64;
     if (e == hipSuccess)  // the sign bits and their flags in one block
       e = hipMalloc(reinterpret_cast<void**>(&ctx->grid_bits),
-                    static_cast<size_t>(cfg->max_pulses) * 65 * sizeof(uint32_t));
+                    static_cast<size_t>(cfg->max_pulses) * (words + 1) * sizeof(uint32_t));
     if (e != hipSuccess) {
       if (ctx->grid) (void)hipFree(ctx->grid);
+      if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
       if (ctx->partial) (void)hipFree(ctx->partial);
       (void)hipFree(ctx->twiddle);
       delete ctx;
       return fail(ISPL_ERR_OUT_OF_MEMORY, "grid scratch: %s", hipGetErrorString(e));
     }
     ctx->grid_binary =
-        reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(cfg->max_pulses) * 64);
+        reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(cfg->max_pulses) * words);
   }
   if (cfg->code_len > 2 * ispl::SUB) {  // the long-code kernel reads binary codes as sign bits
     const size_t rows = static_cast<size_t>(cfg->max_pulses);
@@ -537,6 +548,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
       if (ctx->partial) (void)hipFree(ctx->partial);
       if (ctx->grid) (void)hipFree(ctx->grid);
       if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
+      if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
       (void)hipFree(ctx->twiddle);
       delete ctx;
       return fail(ISPL_ERR_OUT_OF_MEMORY, "code sign bits: %s", hipGetErrorString(e));
@@ -561,6 +573,7 @@ void ispl_destroy(ispl_ctx* ctx) {
     if (ctx->code_binary) (void)hipFree(ctx->code_binary);
     if (ctx->grid) (void)hipFree(ctx->grid);
     if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
+    if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
   }
   delete ctx;
 }
@@ -680,6 +693,7 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     a.out = spectra;
     a.chunks = 1;
     a.grid = ctx->grid;
+    a.twiddle64 = ctx->twiddle64;
     a.grid_len = gp.len;
     a.grid_chunks = gp.chunks;
     a.grid_waves = gp.waves;
@@ -794,7 +808,11 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
                               : nullptr;
   tmp.min_chunk_pulses = kMinChunkPulses;
   tmp.grid_bytes = grid_scratch_bytes(*cfg);
-  if (tmp.grid_bytes > 0) tmp.grid = reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES);
+  if (tmp.grid_bytes > 0) {
+    tmp.twiddle64 = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES);
+    tmp.grid = reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
+                                        ispl::NOALLOC_TWIDDLE64_BYTES);
+  }
   if (n_pulses > 0) {
     e = ispl::launch_build_twiddles(tmp.twiddle, cfg->fft_len, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "twiddle launch");

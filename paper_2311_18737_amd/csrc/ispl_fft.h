@@ -346,7 +346,14 @@ struct GridTwiddles {
   GeoTwiddles p2;
   float2 t3[4], t3sq[4];
 };
-// The same with pass 3's factors in LDS: t3[64 t] = (T_kc, T_kc^2) of this
+// The same, with pass 3's row exchange through LDS.
+struct GridTwiddlesRows : GridTwiddles {};
+// The same with T_kc^2 formed for each transform (8 registers less).
+struct GridTwiddlesRows1 {
+  GeoTwiddles p2;
+  float2 t3[4];
+};
+// The same with pass 3's factors in LDS too: t3[64 t] = (T_kc, T_kc^2) of this
 // lane (16 registers less, for kernels that keep the next pulse's samples in flight).
 struct GridTwiddlesLds {
   GeoTwiddles p2;
@@ -361,10 +368,24 @@ template <>
 inline constexpr bool kGeo<GridTwiddles> = true;
 template <>
 inline constexpr bool kGeo<GridTwiddlesLds> = true;
+template <>
+inline constexpr bool kGeo<GridTwiddlesRows> = true;
+template <>
+inline constexpr bool kGeo<GridTwiddlesRows1> = true;
 template <typename TW>
 inline constexpr bool kLds3 = false;
 template <>
 inline constexpr bool kLds3<GridTwiddlesLds> = true;
+template <typename TW>
+inline constexpr bool kRowsLds = kLds3<TW>;
+template <>
+inline constexpr bool kRowsLds<GridTwiddlesRows> = true;
+template <>
+inline constexpr bool kRowsLds<GridTwiddlesRows1> = true;
+template <typename TW>
+inline constexpr bool kSquare3 = false;
+template <>
+inline constexpr bool kSquare3<GridTwiddlesRows1> = true;
 
 // One wave's 1024-point transform and power accumulation.  On entry lane l
 // holds f[l + 64 j] in v[j]; xw is the wave's exchange buffer.  On exit
@@ -403,7 +424,7 @@ __device__ __forceinline__ void wave_passes_23(float2 (&v)[16], float2* xw, cons
   // pass 3: the 4-point DFT over r runs across the four 16-lane rows.  For
   // each t a row transpose hands row g the four values v_{ka,r}[4 g + t],
   // r = 0..3; then twiddle W_64^{r kc}, DFT over r.
-  if constexpr (kLds3<TW>) {
+  if constexpr (kRowsLds<TW>) {
     // rows exchange through LDS: a v_permlane swap holds the VALU for 8 cycles
 #pragma unroll
     for (int k = 0; k < 16; ++k) xw[64 * k + lane] = v[k];
@@ -416,7 +437,7 @@ __device__ __forceinline__ void wave_passes_23(float2 (&v)[16], float2* xw, cons
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     float2 c0, c1, c2, c3;
-    if constexpr (kLds3<TW>) {
+    if constexpr (kRowsLds<TW>) {
       c0 = v[4 * t], c1 = v[4 * t + 1], c2 = v[4 * t + 2], c3 = v[4 * t + 3];
     } else {
       float re[4] = {v[t].x, v[4 + t].x, v[8 + t].x, v[12 + t].x};
@@ -429,6 +450,10 @@ __device__ __forceinline__ void wave_passes_23(float2 (&v)[16], float2* xw, cons
     if constexpr (kLds3<TW>) {
       const float4 q = w.t3[64 * t];
       dft4_geo(c0, c1, c2, c3, make_float2(q.x, q.y), make_float2(q.z, q.w));
+    } else if constexpr (kSquare3<TW>) {
+      float2 u = w.t3[t];
+      asm volatile("" : "+v"(u.x), "+v"(u.y));  // (or the squares would be kept across pulses)
+      dft4_geo(c0, c1, c2, c3, u, make_float2(fmaf(u.x, u.x, -u.y * u.y), 2.f * u.x * u.y));
     } else if constexpr (kGeo<TW>) {
       dft4_geo(c0, c1, c2, c3, w.t3[t], w.t3sq[t]);
     } else {

@@ -11,8 +11,8 @@
 //   S[k] = r[0] + 2 Re sum_{0 < n < L} r[n] W_N^{k n}.
 //
 // At L = 1000, N = 16384 the pulse loop has 2 instead of 16 transforms of 1024
-// points per pulse and gate: 1000 pulses x 1000 gates (int16 samples) take 1.72 instead of
-// 11.45 ms.  The grid's mean is taken out before the inverse transform and r[0]
+// points per pulse and gate: 1000 pulses x 1000 gates (int16 samples) take 1.75 instead of
+// 11.49 ms.  The grid's mean is taken out before the inverse transform and r[0]
 // added back last, so rounding in the two transforms is relative to the
 // spectrum's fluctuation about its mean, not to the mean; the sums of a gate's
 // pulses are split over 8 or 16 waves, which halves their rounding (relative error against
@@ -21,9 +21,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include <algorithm>
 
 #include "ispl_fft.h"
+#include "ispl_fft64.h"
 #include "ispl_internal.h"
 
 namespace ispl {
@@ -55,6 +58,26 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // bits are brought up by additions, and pass 3's twiddles lie in LDS, which keeps
 // four waves per SIMD with the next pulse's samples in flight.
 
+// Pulses (or steps of several) that one FP32 sum takes before it is added to the
+// row in memory.  The rounding of a long sum grows with its length, and the
+// expansion spreads what a strong line leaves there over the bins around it: with 500
+// pulses in one sum the uneven batch's L = 2000 experiment had bins 3.6e-5
+// off, with 32 it is 5.7e-6.
+constexpr int RUN_STEPS = 32;
+
+// `steps` cut into `n` runs, the first steps % n of them one longer (a 32-bit
+// division: s * steps / n takes 64 bits and hundreds of instructions each).
+struct RunSplit {
+  uint32_t each, extra;
+  __device__ RunSplit(int steps, int n)
+      : each(static_cast<uint32_t>(steps) / static_cast<uint32_t>(n)),
+        extra(static_cast<uint32_t>(steps) - each * static_cast<uint32_t>(n)) {}
+  __device__ int begin(int s) const {
+    return static_cast<int>(static_cast<uint32_t>(s) * each + min(static_cast<uint32_t>(s), extra));
+  }
+  __device__ int longest() const { return static_cast<int>(each + (extra != 0 ? 1 : 0)); }
+};
+
 // Samples through a buffer descriptor: reads past the end of the code return
 // zero, so the row is zero-padded by the load itself.
 __device__ __forceinline__ auto row_desc(const void* base, int64_t elem, int size, int elems) {
@@ -64,6 +87,13 @@ __device__ __forceinline__ auto row_desc(const void* base, int64_t elem, int siz
   return __builtin_amdgcn_make_buffer_rsrc(
       reinterpret_cast<void*>((static_cast<uint64_t>(hi) << 32) | lo), 0,
       __builtin_amdgcn_readfirstlane(elems * size), 0x00020000);
+}
+
+// x, recomputed by the compiler wherever it is used (values formed from it are
+// not kept across a loop).
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 template <int ST>
@@ -210,7 +240,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   constexpr int JL = CLS > 1 ? 16 : J / 2;      // of which loaded
   constexpr int RUNS = W / CLS;
   // samples per pulse fetched a step ahead (all that four waves per SIMD have registers for)
-  constexpr int JP = CLS > 1 ? (ST == 0 ? 6 : 10) : JL;
+  constexpr int JP = CLS > 1 ? (ST == 0 ? 6 : 12) : JL;
   static_assert(CLS <= 2 && W % CLS == 0, "at most two bin classes");
   using IO = BufferSample<ST>;
   __shared__ float2 xs[W * XWAVE];
@@ -253,15 +283,17 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
   const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
-  const int steps = (a.n_pulses + Q - 1) / Q;
-  const int64_t s = static_cast<int64_t>(c) * RUNS + run, all = static_cast<int64_t>(a.chunks) * RUNS;
-  const int i0 = static_cast<int>(s * steps / all), i1 = static_cast<int>((s + 1) * steps / all);
+  const RunSplit runs((a.n_pulses + Q - 1) / Q, a.chunks * RUNS);
+  const int i0 = runs.begin(c * RUNS + run), i1 = runs.begin(c * RUNS + run + 1);
   float2* xw = xs + wave * XWAVE;
 
   typename IO::raw_t raw[Q * JL];
   uint32_t bits[Q];
   // samples j0 <= j < j1 of each pulse of step i (zero past the last pulse)
   auto fetch = [&](int i, int j0, int j1) {
+    // formed here, the offsets fold into the loads; hoisted out of the loop they
+    // would take a register each
+    const int so = opaque(lane * IO::SIZE);
 #pragma unroll
     for (int t = 0; t < Q; ++t) {
       const int p = i * Q + t;
@@ -269,7 +301,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
                               p < a.n_pulses && i < i1 ? L : 0);
 #pragma unroll
       for (int j = 0; j < JL; ++j)
-        if (j >= j0 && j < j1) raw[t * JL + j] = IO::load(d, (lane + 64 * j) * IO::SIZE);
+        if (j >= j0 && j < j1) raw[t * JL + j] = IO::load(d, so + 64 * IO::SIZE * j);
     }
   };
   auto fetch_bits = [&](int i) {
@@ -301,12 +333,23 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
       binary = a.code_binary[0] != 0;
     }
   }
+  // the chunk's partial row; on a grid of all N bins by gate, and with one
+  // chunk the gate's row of the result itself
+  const bool whole = a.grid_len == a.n_fft, last = whole && a.chunks == 1;
+  float* out = last ? a.out + static_cast<int64_t>(g) * M
+                    : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
+  bool add = last && a.accumulate;
+  // at most RUN_STEPS steps go into one FP32 sum (the same number of sums for
+  // every run, which meet at its end)
+  const int n_sums = max(1, (runs.longest() + RUN_STEPS - 1) / RUN_STEPS);
+  for (int u = 0; u < n_sums; ++u) {
+  const int b0 = min(i0 + u * RUN_STEPS, i1), b1 = min(b0 + RUN_STEPS, i1);
   if (binary) {
-    if (i0 < i1) {
-      fetch(i0, 0, JP);
-      fetch_bits(i0);
+    if (b0 < b1) {
+      fetch(b0, 0, JP);
+      fetch_bits(b0);
     }
-    for (int i = i0; i < i1; ++i) {
+    for (int i = b0; i < b1; ++i) {
       float2 v[16];
       if constexpr (JP < JL) fetch(i, JP, JL);
 #pragma unroll
@@ -328,9 +371,12 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
       transform(v);
     }
   } else {
-    for (int i = i0; i < i1; ++i) {
+    // (the two bin classes of M = 2048 have no registers for a prefetch beside the codes)
+    if (CLS == 1 && b0 < b1) fetch(b0, 0, JL);
+    for (int i = b0; i < b1; ++i) {
       float2 v[16];
-      fetch(i, 0, JL);
+      if constexpr (CLS > 1) fetch(i, 0, JL);
+      const int co = opaque(lane * 8);
 #pragma unroll
       for (int t = 0; t < Q; ++t) {
         const int p = i * Q + t;
@@ -338,10 +384,14 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
                                 p < a.n_pulses ? L : 0);
 #pragma unroll
         for (int j = 0; j < JL; ++j) {
-          const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(d, (lane + 64 * j) * 8, 0, 0);
+          const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(d, co + 512 * j, 0, 0);
           v[t * J + j] = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)),
                                   IO::cvt(raw[t * JL + j]));
         }
+      }
+      if constexpr (CLS == 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(i + 1, 0, JL);
       }
       transform(v);
     }
@@ -350,25 +400,24 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   // the workgroup's sums: each wave lays its bins out in its own region, then
   // every bin is added over runs and side-by-side transforms in fixed order
   wave_lds_sync();
-  float* st = reinterpret_cast<float*>(xw);
+  // (addresses formed here each time: kept across the pulse loop they would
+  // take its registers)
+  const int ft = opaque(tid), fl = ft & 63;
+  float* st = reinterpret_cast<float*>(xs) + (ft >> 6) * (2 * XWAVE);
   {
-    const int ka = lane & 15, row = lane >> 4;
+    const int ka = fl & 15, row = fl >> 4;
     const int base = CLS > 1 ? ka : (ka / J) * M + (ka & (J - 1));
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int kd = 0; kd < 4; ++kd)
+      for (int kd = 0; kd < 4; ++kd) {
         st[base + J * (4 * row + t + 16 * kd)] = acc[4 * t + kd];
+        acc[4 * t + kd] = 0.f;
+      }
   }
   __syncthreads();
   const float* all_st = reinterpret_cast<const float*>(xs);
-  // the chunk's partial row; on a grid of all N bins by gate, and with one
-  // chunk the gate's row of the result itself
-  const bool whole = a.grid_len == a.n_fft, last = whole && a.chunks == 1;
-  float* out = last ? a.out + static_cast<int64_t>(g) * M
-                    : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
-  const bool add = last && a.accumulate;
-  for (int e = tid; e < M; e += 64 * W) {
+  for (int e = ft; e < M; e += 64 * W) {
     float sum = 0.f;
 #pragma unroll
     for (int r = 0; r < RUNS; ++r) {
@@ -382,37 +431,299 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
     }
     out[e] = add ? out[e] + sum : sum;
   }
+  add = true;
+  if (u + 1 < n_sums) __syncthreads();  // the regions are exchange buffers again
+  }
 }
 
 // ---------------------------------------------------------------------------
-// Expansion of the summed grid to N = 1024 R bins, L <= 1024.
+// Grid pass, 1024 < L <= 8192: M = 1024 J points, J = 4, 8 or 16 >= L / 512.
+//
+// A workgroup of J waves transforms one pulse at a time.  With n = lg + 1024 j
+// the first pass is a J-point DFT over j for every lg < 1024 (half of its inputs
+// lie past the code), 16 / J values of lg per thread; an exchange through LDS hands wave k1 the
+// outputs k1 of all lg, and its 1024-point transform with the factors
+// W_M^{k1 lg} gives bins k1 + J kb.  The factors are a geometric progression in
+// every pass, so none costs a multiplication of its own.
+//
+// VALU issue bounds it like the short grid, with two barriers a pulse; registers
+// decide what is kept in flight: all eight int16 samples of the next pulse, half
+// of the complex64 ones (all of them spill, and a reload waits for every load
+// before it).  200 pulses x 500 gates at L = 4000, N = 16384, phase codes (int16)
+// take 1.04 ms, 2.24 by direct transforms; the uneven batch, of which
+// L = 2000 is the longest part, 6.2 instead of 40 ms.
+
+// Code rows as sign bits for the long grid: word lg of a row holds in bit
+// 31 - j whether code sample lg + 1024 j is -1.  One workgroup per row.
+__global__ void __launch_bounds__(256)
+pack_long_grid_bits(const float2* __restrict__ tx, int32_t code_len, uint32_t* __restrict__ bits,
+                    int32_t* __restrict__ binary) {
+  const int row = blockIdx.x;
+  bool ok = true;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int lg = static_cast<int>(threadIdx.x) + 256 * t;
+    u32x2 c[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const auto d = row_desc(tx, static_cast<int64_t>(row) * code_len + SUB * j, 8,
+                              max(0, code_len - SUB * j));
+      c[j] = __builtin_amdgcn_raw_buffer_load_b64(d, 8 * lg, 0, 0);
+    }
+    uint32_t word = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float x = __uint_as_float(c[j].x), y = __uint_as_float(c[j].y);
+      ok = ok && (lg + SUB * j >= code_len || ((x == 1.f || x == -1.f) && y == 0.f));
+      word |= (x < 0.f ? 1u : 0u) << (31 - j);
+    }
+    bits[static_cast<int64_t>(row) * SUB + lg] = word;
+  }
+  ok = __syncthreads_and(ok);
+  if (threadIdx.x == 0) binary[row] = ok ? 1 : 0;
+}
+
+template <int J, int ST>
+__global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
+  constexpr int NT = 64 * J, PER = 16 / J, JL = J / 2;
+  constexpr int JP = ST == 0 ? JL / 2 : JL;  // of each thread's samples, fetched a pulse ahead
+  using IO = BufferSample<ST>;
+  __shared__ float2 xs[J * XWAVE];
+  __shared__ GeoTwiddles p1s[J];  // pass-1 progression W_M^{64 k1} of each wave
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
+  const int c = bid % a.chunks, slot = bid / a.chunks;
+  int g = a.slot0 + slot;
+  if (a.gate_list) {
+    if (g >= *a.gate_count) return;  // uniform, before any barrier
+    g = a.gate_list[g];
+    if (g < 0 || g >= a.n_gates) return;
+  }
+  const int L = a.code_len, M = SUB * J, step = a.n_fft / M, nmask = a.n_fft - 1;
+  const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
+  // (complex64 samples in flight take 16 registers)
+  std::conditional_t<ST == 0, GridTwiddlesRows1, GridTwiddlesRows> wt;
+  {
+    const int q = wave + J * (lane & 15);
+    load_geo(wt.p2, tw, a.n_fft, 4 * step * q);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int e = step * (q + 16 * J * (4 * (lane >> 4) + t));
+      wt.t3[t] = tw[e & nmask];
+      if constexpr (ST == 1) wt.t3sq[t] = tw[(2 * e) & nmask];
+    }
+    if (lane == 0) load_geo(p1s[wave], tw, a.n_fft, 64 * step * wave);
+  }
+  const Dft16Consts dk = dft16_consts();
+  float acc[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+
+  const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
+  const RunSplit runs(a.n_pulses, a.chunks);
+  const int p0 = runs.begin(c), p1 = runs.begin(c + 1);
+  float2* xw = xs + wave * XWAVE;
+
+  typename IO::raw_t raw[8];  // sample tid + NT t + 1024 j in raw[t JL + j]
+  uint32_t bits[PER];
+  auto fetch = [&](int p, int j0, int j1) {
+    const int so = opaque(tid * IO::SIZE);  // (as in grid_spectra)
+#pragma unroll
+    for (int j = 0; j < JL; ++j) {
+      if (j < j0 || j >= j1) continue;
+      const auto d = row_desc(a.samples, static_cast<int64_t>(p) * a.stride + gate_off + SUB * j,
+                              IO::SIZE, p < p1 ? max(0, L - SUB * j) : 0);
+#pragma unroll
+      for (int t = 0; t < PER; ++t) raw[t * JL + j] = IO::load(d, so + NT * IO::SIZE * t);
+    }
+  };
+  auto fetch_bits = [&](int p) {
+    const uint32_t* row = a.code_bits + (a.tx_per_pulse ? static_cast<int64_t>(min(p, p1 - 1)) * SUB : 0);
+#pragma unroll
+    for (int t = 0; t < PER; ++t) bits[t] = row[tid + NT * t];
+  };
+  // first pass in place: outputs k1 of thread value t in v[t J + k1]
+  auto first_pass = [&](float2 (&v)[16]) {
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+      if constexpr (J == 4) {
+        const float2 x = v[4 * t], y = v[4 * t + 1];
+        v[4 * t] = make_float2(x.x + y.x, x.y + y.y);
+        v[4 * t + 1] = make_float2(x.x + y.y, x.y - y.x);
+        v[4 * t + 2] = make_float2(x.x - y.x, x.y - y.y);
+        v[4 * t + 3] = make_float2(x.x - y.y, x.y + y.x);
+      } else if constexpr (J == 8) {
+        dft8_first4(v + 8 * t, dk);
+      } else {
+        dft16_first8(v, dk);
+      }
+    }
+  };
+  auto transform = [&](float2 (&v)[16]) {
+    __syncthreads();  // every wave has finished its exchanges of the previous pulse
+#pragma unroll
+    for (int t = 0; t < PER; ++t)
+#pragma unroll
+      for (int k = 0; k < J; ++k) xs[k * XWAVE + tid + NT * t] = v[t * J + k];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = xw[lane + 64 * i];
+    wave_lds_sync();  // read before this wave reuses its region for its own exchange
+    dft16_geo(v, p1s[wave]);
+    wave_passes_23(v, xw, wt, dk, lane, NoHook{}, PowerSink{acc});
+  };
+
+  // codes of this workgroup's pulses all +-1: conj(c) x is a sign flip
+  bool binary = a.code_bits != nullptr;
+  if (binary) {
+    if (a.tx_per_pulse) {
+      bool ok = true;
+      for (int p = p0 + lane; p < p1; p += 64) ok = ok && a.code_binary[p] != 0;
+      binary = __all(ok);  // every wave reads the same flags
+    } else {
+      binary = a.code_binary[0] != 0;
+    }
+  }
+  // the chunk's partial row, or the result's (as in grid_spectra)
+  const bool whole = a.grid_len == a.n_fft, last = whole && a.chunks == 1;
+  float* out = last ? a.out + static_cast<int64_t>(g) * M
+                    : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
+  bool add = last && a.accumulate;
+  for (int q0 = p0; q0 == p0 || q0 < p1; q0 += RUN_STEPS) {  // one FP32 sum each
+    const int q1 = min(q0 + RUN_STEPS, p1);
+    if (binary) {
+      if (q0 < q1) {
+        fetch(q0, 0, JP);
+        fetch_bits(q0);
+      }
+      for (int p = q0; p < q1; ++p) {
+        float2 v[16];
+        if constexpr (JP < JL) fetch(p, JP, JL);
+#pragma unroll
+        for (int t = 0; t < PER; ++t) {
+          uint32_t b = bits[t];
+#pragma unroll
+          for (int j = 0; j < JL; ++j) {
+            const float2 x = IO::cvt(raw[t * JL + j]);
+            const uint32_t sgn = b & 0x80000000u;
+            v[t * J + j] = make_float2(__uint_as_float(__float_as_uint(x.x) ^ sgn),
+                                       __uint_as_float(__float_as_uint(x.y) ^ sgn));
+            asm("v_add_u32 %0, %0, %0" : "+v"(b));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(p + 1, 0, JP);
+        fetch_bits(p + 1);
+        first_pass(v);
+        transform(v);
+      }
+    } else {
+      // (complex64 samples have no registers for a prefetch beside the codes)
+      if (ST == 1 && q0 < q1) fetch(q0, 0, JL);
+      for (int p = q0; p < q1; ++p) {
+        float2 v[16];
+        if constexpr (ST == 0) fetch(p, 0, JL);
+        const int co = opaque(tid * 8);
+#pragma unroll
+        for (int j = 0; j < JL; ++j) {
+          const auto d = row_desc(a.tx, (a.tx_per_pulse ? static_cast<int64_t>(p) * L : 0) + SUB * j, 8,
+                                  max(0, L - SUB * j));
+#pragma unroll
+          for (int t = 0; t < PER; ++t) {
+            const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(d, co + 8 * NT * t, 0, 0);
+            v[t * J + j] = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)),
+                                    IO::cvt(raw[t * JL + j]));
+          }
+        }
+        if constexpr (ST == 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          fetch(p + 1, 0, JL);
+        }
+        first_pass(v);
+        transform(v);
+      }
+    }
+
+    // the sums in bin order through LDS (bin k1 + J kb of wave k1), stored in runs
+    __syncthreads();
+    // (addresses formed here each time: kept across the pulse loop they would
+    // take its registers)
+    const int ft = opaque(tid), fl = ft & 63;
+    float* st = reinterpret_cast<float*>(xs) + (ft >> 6) * (2 * XWAVE);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r4 = fl >> 4;
+      st[(fl & 15) + 64 * r4 + 16 * ((i >> 2) ^ r4) + 256 * (i & 3)] = acc[i];  // staged(bin_of)
+      acc[i] = 0.f;
+    }
+    __syncthreads();
+    const float* all_st = reinterpret_cast<const float*>(xs);
+    for (int e = ft; e < M; e += NT) {
+      const int kb = e / J;
+      const float s = all_st[(e & (J - 1)) * (2 * XWAVE) + (kb ^ ((kb >> 2) & 48))];
+      out[e] = add ? out[e] + s : s;
+    }
+    add = true;  // (the next pulse's first barrier frees the regions)
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Expansion of the summed grid to N = 1024 R bins.
 //
 // With the two-sided lags R[n] = rho[n] + i tau[n] (rho even, tau odd) and the
 // real sequence q[n] = rho[n] + tau[n], H[k] = sum_{0 < |n| < L} q[n] W_N^{k n}
 // gives two bins at once, S[k] = r0 + Re H - Im H and S[-k] = r0 + Re H + Im H.  Folded
 // to 1024 points, bin class k1 (bins k1 + R kk) is the 1024-point transform of
-//   h[n] = q[n] + e^{2 pi i k1 / R} q[n - 1024], 0 <= n < 1024,
-// with the class's twiddles, and also yields class R - k1: the classes
-// 0 ... R / 2 are all the transforms there are.  Bins on the grid are copied.
+//   h[n] = sum_s q[n + 1024 s] W_R^{k1 s} + q[n - 1024 (s + 1)] W_R^{-k1 (s + 1)},
+// 0 <= n < 1024, s < max(1, M / 2048), with the class's twiddles, and also
+// yields class R - k1: the classes 0 ... R / 2 are all the transforms there
+// are.  Bins on the grid are copied, and classes wholly on it not transformed.
 //
-// One workgroup of eight waves per gate (two fit a compute unit): all waves sum
-// the gate's chunk partials, wave 0 runs the inverse transform (for M < 1024
-// also class 0, which makes the grid one of 1024 points), then each wave transforms one class and
+// One workgroup of eight waves per gate: all waves sum the gate's chunk
+// partials, the inverse transform (up to M = 2048 by wave 0, for M < 1024 with
+// class 0, which makes the grid one of 1024 points; longer grids as M / 2048 classes
+// of one wave each) leaves q in LDS, then each wave transforms one class and
 // lays its two rows out in its own exchange buffer, from which the workgroup
-// stores whole rows.  Everything between the partials and the result stays in LDS.
+// stores whole rows.
+//
+// The transforms run in double precision: a line of power S_l leaves rounding of
+// about 1e-7 S_l at its mirror frequency and other places of an FP32
+// transform's structure, where S may be a hundred times smaller, which no direct
+// transform does.  (With FP32 transforms the largest error of the uneven batch's
+// L = 2000 experiment was 3.5e-5 of the larger of S and its mean, now 5.7e-6; 1000
+// gates of N = 16384 take 68 us instead of 50.)  Lags and grid stay FP32:
+// their rounding is spread evenly over all bins.
 
-// Factors of passes 2 and 3 for bin class kappa of n = 1024 S points; `tw` is
-// the table of `table` >= n points.
-__device__ __forceinline__ void load_class_twiddles(GridTwiddles& w, const float2* __restrict__ tw,
-                                                    int n, int table, int kappa, int lane) {
-  const int step = table / n, mask = table - 1, S = n >> 10;
-  const int row = lane >> 4, q = kappa + S * (lane & 15);
-  load_geo(w.p2, tw, table, 4 * step * q);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int e = step * (q + 16 * S * (4 * row + t));
-    w.t3[t] = tw[e & mask];
-    w.t3sq[t] = tw[(2 * e) & mask];
+// SG-point DFT in place, natural order (SG = 2, 4 or 8).
+template <int SG>
+__device__ __forceinline__ void dft_small64(complex64d (&z)[SG]) {
+  auto add = [](complex64d a, complex64d b) { return complex64d{a.x + b.x, a.y + b.y}; };
+  auto sub = [](complex64d a, complex64d b) { return complex64d{a.x - b.x, a.y - b.y}; };
+  auto four = [&](complex64d& a0, complex64d& a1, complex64d& a2, complex64d& a3) {
+    const complex64d s02 = add(a0, a2), d02 = sub(a0, a2), s13 = add(a1, a3), d13 = sub(a1, a3);
+    a0 = add(s02, s13);
+    a2 = sub(s02, s13);
+    a1 = complex64d{d02.x + d13.y, d02.y - d13.x};
+    a3 = complex64d{d02.x - d13.y, d02.y + d13.x};
+  };
+  if constexpr (SG == 2) {
+    const complex64d a = z[0], b = z[1];
+    z[0] = add(a, b);
+    z[1] = sub(a, b);
+  } else if constexpr (SG == 4) {
+    four(z[0], z[1], z[2], z[3]);
+  } else {
+    constexpr double r2 = 0.70710678118654752440;  // cos(pi / 4)
+    complex64d e0 = z[0], e1 = z[2], e2 = z[4], e3 = z[6], o0 = z[1], o1 = z[3], o2 = z[5], o3 = z[7];
+    four(e0, e1, e2, e3);
+    four(o0, o1, o2, o3);
+    o1 = complex64d{r2 * (o1.x + o1.y), r2 * (o1.y - o1.x)};   // W_8
+    o2 = complex64d{o2.y, -o2.x};                              // -i
+    o3 = complex64d{r2 * (o3.y - o3.x), -r2 * (o3.x + o3.y)};  // W_8^3
+    z[0] = add(e0, o0), z[4] = sub(e0, o0), z[1] = add(e1, o1), z[5] = sub(e1, o1);
+    z[2] = add(e2, o2), z[6] = sub(e2, o2), z[3] = add(e3, o3), z[7] = sub(e3, o3);
   }
 }
 
@@ -441,8 +752,8 @@ struct alignas(4) Float4u {
 
 // Whether the grid's sums can be expanded: finite, and far enough from the ends
 // of the FP32 range that the transforms stay inside it.
-__device__ __forceinline__ bool expandable(float mean) {
-  return mean == 0.f || (mean > 1e-30f && mean < 1e30f);
+__device__ __forceinline__ bool expandable(double mean) {
+  return mean == 0.0 || (mean > 1e-30 && mean < 1e30);
 }
 
 // The N bins of gate g straight from its pulses, for a grid that cannot be
@@ -470,14 +781,23 @@ __device__ void direct_row(const FoldArgs& a, int g, float2* xs, const Dft16Cons
       for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll 1
       for (int p = 0; p < a.n_pulses; ++p) {
-        const auto ds = row_desc(a.samples, static_cast<int64_t>(p) * a.stride + gate_off, IO::SIZE, L);
-        const auto dc = row_desc(a.tx, a.tx_per_pulse ? static_cast<int64_t>(p) * L : 0, 8, L);
         float2 v[16];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const auto x = IO::load(ds, (lane + 64 * j) * IO::SIZE);
-          const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(dc, (lane + 64 * j) * 8, 0, 0);
-          v[j] = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)), IO::cvt(x));
+        for (int j = 0; j < 16; ++j) v[j] = make_float2(0.f, 0.f);
+#pragma unroll 1
+        for (int s = 0; s * SUB < L; ++s) {  // 1024 samples at a time, folded by W_R^{k1 s}
+          const auto ds = row_desc(a.samples, static_cast<int64_t>(p) * a.stride + gate_off + SUB * s,
+                                   IO::SIZE, L - SUB * s);
+          const auto dc = row_desc(a.tx, (a.tx_per_pulse ? static_cast<int64_t>(p) * L : 0) + SUB * s,
+                                   8, L - SUB * s);
+          const float2 f = uniform_twiddle(tw, (SUB * k1 * s) & (N - 1));
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const auto x = IO::load(ds, (lane + 64 * j) * IO::SIZE);
+            const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(dc, (lane + 64 * j) * 8, 0, 0);
+            const float2 y = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)), IO::cvt(x));
+            v[j] = s == 0 ? y : cmuladd(v[j], f, y);
+          }
         }
         wave_fft_accumulate(v, xw, w, dk, acc, lane);
       }
@@ -495,22 +815,26 @@ __device__ void direct_row(const FoldArgs& a, int g, float2* xs, const Dft16Cons
   }
 }
 
-template <int ST>
-__global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_grid(FoldArgs a) {
+// SG: M / 2048 segments of 1024 lags each way (0: M <= 1024).
+template <int ST, int SG>
+__global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(FoldArgs a) {
   constexpr int W = EXP_WAVES, NT = 64 * W;
   constexpr int UP = SUB + 4;  // aux: 1024-point grid of M < 1024
+  constexpr bool WIDE = SG == 1, LONG = SG > 1;
   __shared__ __attribute__((aligned(16))) float2 xs[W * XWAVE];
-  __shared__ __attribute__((aligned(16))) float aux[2 * SUB + 8];
-  __shared__ float red[W];
+  __shared__ __attribute__((aligned(16))) float aux[LONG ? 4 : 2 * SUB + 8];
+  __shared__ float2 lags[LONG ? SG * SUB + 1 : 1];
+  __shared__ double red[W];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = a.grid_len, N = a.n_fft, L = a.code_len, R = N / SUB;
   const int lr = __builtin_ctz(R);
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
-  const Dft16Consts dk = dft16_consts();
+  const double* tw64 = a.twiddle64;
   float* xf = reinterpret_cast<float*>(xs);
   float2* xw = xs + wave * XWAVE;
+  double* xd = reinterpret_cast<double*>(xw);
 
   const int slot = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
   int g = a.slot0 + slot;
@@ -519,19 +843,97 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_grid(FoldArgs a) {
     g = a.gate_list[g];
     if (g < 0 || g >= a.n_gates) return;
   }
+  float* const row = a.grid + static_cast<int64_t>(slot) * M;
+  const int64_t cs = static_cast<int64_t>(a.rows) * M;
+  const float scale = 1.f / static_cast<float>(M);
 
-  // the classes 1, 2, ... last (class 0, and R / 2 at M = 2048, lie on the
-  // grid), one per wave and round; at M = 2048 wave 0 runs the inverse transform only
-  const bool wide = M == 2 * SUB;
-  const int last = wide ? R / 2 - 1 : R / 2, per_round = wide ? W - 1 : W;
-  const int task = wide ? wave - 1 : wave;
-  const bool one_round = last <= per_round;
+  // Mean of the grid from each thread's part of its sum.
+  auto block_mean = [&](double part) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+    if (lane == 0) red[wave] = part;
+    __syncthreads();
+    double m = 0.0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) m += red[i];
+    return m / static_cast<double>(M);
+  };
+  // The lags n and m = n_cpx - n in place of F[n], F[m] (F: the transform of the
+  // complex points z[2 a] + i z[2 a + 1]); with r = conj(DFT) / M
+  // qs[n] = (q[n], q[-n]) = (Re r + Im r, Re r - Im r).
+  auto untangle = [&](float2* qs, int n, float2 p, float2 m) {
+    float2 f = make_float2(0.f, 0.f);
+    if (n > 0 && n < L) {
+      const float2 E = make_float2(0.5f * (p.x + m.x), 0.5f * (p.y - m.y));
+      const float2 O = make_float2(0.5f * (p.y + m.y), 0.5f * (m.x - p.x));
+      f = cmuladd(E, tw[n * (N / M)], O);
+    }
+    qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
+  };
 
-  // ---- the grid, chunk sums in ascending order, into aux; its mean
-  float part = 0.f;
-  {
-    const float* row = a.grid + static_cast<int64_t>(slot) * M;
-    const int64_t cs = static_cast<int64_t>(a.rows) * M;
+  double mean;
+  float2* qs;  // (q[n], q[-n]), n < M / 2, and one zero more
+  if constexpr (LONG) {
+    // ---- chunk sums in ascending order (left in chunk 0's row), two times SG
+    // complex points per thread, and the first pass of the inverse transform:
+    // SG-point DFTs over points lg + 1024 j
+    complex64d z[2][SG];
+    double part = 0.0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < SG; ++j) {
+        float2* at = reinterpret_cast<float2*>(row) + tid + NT * t + SUB * j;
+        float2 s = *at;
+        for (int c = 1; c < a.chunks; ++c) {
+          const float2 q = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(at) + c * cs);
+          s.x += q.x;
+          s.y += q.y;
+        }
+        if (a.chunks > 1) *at = s;
+        z[t][j] = complex64d{s.x, s.y};
+        part += static_cast<double>(s.x) + static_cast<double>(s.y);
+      }
+    mean = block_mean(part);
+    qs = lags;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int j = 0; j < SG; ++j) z[t][j] = complex64d{z[t][j].x - mean, z[t][j].y - mean};
+      dft_small64(z[t]);
+    }
+    // class `wave` of the SG 1024-point complex transforms, real and imaginary
+    // parts handed over one after the other
+    complex64d v[16];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half == 1) __syncthreads();
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < SG; ++k)
+          reinterpret_cast<double*>(xs + k * XWAVE)[tid + NT * t] = half == 0 ? z[t][k].x : z[t][k].y;
+      __syncthreads();
+      if (wave < SG)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) (half == 0 ? v[j].x : v[j].y) = xd[lane + 64 * j];
+    }
+    if (wave < SG) {
+      wave_lds_sync();
+      class_transform64(v, xd, tw64, M / 2, N, wave, lane, [&](int i, complex64d f) {
+        lags[wave + SG * bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
+      });
+    }
+    __syncthreads();
+    constexpr int NC = SG * SUB;
+    for (int n = tid; n <= NC / 2; n += NT) {
+      const float2 A = lags[n], B = lags[n == 0 ? 0 : NC - n];
+      untangle(lags, n, A, B);
+      untangle(lags, NC - n, B, A);  // n = 0: the zero past the last lag
+    }
+  } else {
+    // ---- the grid, chunk sums in ascending order, into aux
+    double part = 0.0;
     for (int k = 4 * tid; k < M; k += 4 * NT) {
       float4 s = *reinterpret_cast<const float4*>(row + k);
       for (int c0 = 1; c0 < a.chunks; c0 += 8) {
@@ -549,140 +951,126 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_grid(FoldArgs a) {
           }
       }
       *reinterpret_cast<float4*>(aux + k) = s;
-      part += (s.x + s.y) + (s.z + s.w);
+      part += (static_cast<double>(s.x) + static_cast<double>(s.y)) +
+              (static_cast<double>(s.z) + static_cast<double>(s.w));
     }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-  if (lane == 0) red[wave] = part;
-  __syncthreads();
-  float mean = 0.f;
-#pragma unroll
-  for (int i = 0; i < W; ++i) mean += red[i];
-  mean *= 1.f / static_cast<float>(M);
-  const bool ok = expandable(mean);
+    mean = block_mean(part);
 
-  // ---- lags: up to conjugation and 1 / M the forward DFT of the real grid,
-  // M <= 1024 zero-interleaved to 1024 points (which repeats its spectrum),
-  // M = 2048 as 1024 complex points z[2 a] + i z[2 a + 1]; with r = conj(F) / M
-  // qs[n] = (q[n], q[-n]) = (Re r + Im r, Re r - Im r), n < M / 2, and one zero
-  // more: behind the grid in aux, at M = 2048 in wave 0's own region
-  const float scale = 1.f / static_cast<float>(M);
-  float2* qs = wide ? xs : reinterpret_cast<float2*>(aux + M);
-  if (wave == 0) {
-    GridTwiddles w;
-    load_class_twiddles(w, tw, SUB, N, 0, lane);
-    float2 v[16];
-    if (wide) {
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const float2 p = reinterpret_cast<const float2*>(aux)[lane + 64 * j];
-        v[j] = make_float2(p.x - mean, p.y - mean);
-      }
-      dft16(v, dk);
-      // (this wave's reads of its exchange buffer are all issued by then)
-      wave_passes_23(v, xw, w, dk, lane, NoHook{},
-                     [&](int i, float2 f) { xw[bin_of(i, lane)] = f; });
-    } else {
-      const int lup = __builtin_ctz(SUB / M), up = (1 << lup) - 1;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int n = lane + 64 * j;
-        v[j] = make_float2((n & up) == 0 ? aux[n >> lup] - mean : 0.f, 0.f);
-      }
-      dft16(v, dk);
-      wave_passes_23(v, xw, w, dk, lane, NoHook{},
-                     [&](int i, float2 f) { xw[bin_of(i, lane)] = f; });
-      wave_lds_sync();
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int n = lane + 64 * j;
-        const float2 f = n > 0 && n < L ? xw[n] : make_float2(0.f, 0.f);
-        if (n < M / 2) qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
-      }
-      if (lane == 0) qs[M / 2] = make_float2(0.f, 0.f);
-      if (M < SUB) {  // class 0
-        wave_lds_sync();
+    // ---- lags: up to conjugation and 1 / M the forward DFT of the real grid,
+    // M <= 1024 zero-interleaved to 1024 points (which repeats its spectrum),
+    // M = 2048 as complex points; left behind the grid in aux, at M = 2048 in
+    // wave 0's own region
+    qs = WIDE ? xs : reinterpret_cast<float2*>(aux + M);
+    if (wave == 0) {
+      // (the sinks write into the wave's own exchange buffer, whose reads are
+      // all issued by then)
+      complex64d v[16];
+      if constexpr (WIDE) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-          const int n = lane + 64 * j, m = SUB - n;
-          const float qp = 64 * j < M / 2 ? qs[n].x : 0.f;
-          const float qm = 64 * (15 - j) < M / 2 ? qs[m].y : 0.f;
-          v[j] = make_float2(qp + qm, 0.f);
+          const float2 p = reinterpret_cast<const float2*>(aux)[lane + 64 * j];
+          v[j] = complex64d{p.x - mean, p.y - mean};
         }
-        wave_lds_sync();
-        dft16(v, dk);
-        wave_passes_23(v, xw, w, dk, lane, NoHook{}, [&](int i, float2 F) {
-          const int k = bin_of(i, lane);
-          float s = F.x - F.y + mean;
-          s = s < 0.f ? 0.f : s;  // S >= 0: a rounded zero stays one
-          aux[UP + k] = (k & up) == 0 ? aux[k >> lup] : s;
+        class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d f) {
+          xw[bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
         });
+      } else {
+        const int lup = __builtin_ctz(SUB / M), up = (1 << lup) - 1;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const int n = lane + 64 * j;
+          v[j] = complex64d{(n & up) == 0 ? aux[n >> lup] - mean : 0.0, 0.0};
+        }
+        class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d f) {
+          xw[bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
+        });
+        wave_lds_sync();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int n = lane + 64 * j;
+          const float2 f = n > 0 && n < L ? xw[n] : make_float2(0.f, 0.f);
+          if (n < M / 2) qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
+        }
+        if (lane == 0) qs[M / 2] = make_float2(0.f, 0.f);
+        if (M < SUB) {  // class 0
+          wave_lds_sync();
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int n = lane + 64 * j, m = SUB - n;
+            const float qp = 64 * j < M / 2 ? qs[n].x : 0.f;
+            const float qm = 64 * (15 - j) < M / 2 ? qs[m].y : 0.f;
+            v[j] = complex64d{static_cast<double>(qp) + static_cast<double>(qm), 0.0};
+          }
+          class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d F) {
+            const int k = bin_of(i, lane);
+            const float s = static_cast<float>(F.x - F.y + mean);
+            // S >= 0: a rounded zero stays one
+            aux[UP + k] = (k & up) == 0 ? aux[k >> lup] : s < 0.f ? 0.f : s;
+          });
+        }
       }
     }
-  }
-  if (wide) {
-    __syncthreads();
-    // thread n turns F[n], F[1024 - n] into the lags n and 1024 - n in place
-    static_assert(NT == SUB / 2, "a pair of lags per thread, thread 0 also the middle one");
-    {
+    if constexpr (WIDE) {
+      __syncthreads();
+      static_assert(NT == SUB / 2, "a pair of lags per thread, thread 0 also the middle one");
       const float2 A = xs[tid], B = xs[tid == 0 ? SUB / 2 : SUB - tid];
-      auto lag = [&](int n, float2 p, float2 m) {  // p = F[n], m = F[1024 - n]
-        float2 f = make_float2(0.f, 0.f);
-        if (n > 0 && n < L) {
-          const float2 E = make_float2(0.5f * (p.x + m.x), 0.5f * (p.y - m.y));
-          const float2 O = make_float2(0.5f * (p.y + m.y), 0.5f * (m.x - p.x));
-          f = cmuladd(E, tw[n * (N / (2 * SUB))], O);
-        }
-        qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
-      };
-      lag(tid, A, B);
-      lag(SUB - tid, B, A);  // tid = 0: the zero past the last lag
-      if (tid == 0) lag(SUB / 2, B, B);
+      untangle(qs, tid, A, B);
+      untangle(qs, SUB - tid, B, A);  // tid = 0: the zero past the last lag
+      if (tid == 0) untangle(qs, SUB / 2, B, B);
     }
   }
 
-  // ---- the classes
-  const float* grid = M < SUB ? aux + UP : aux;
-  const int lratio = __builtin_ctz(N / max(M, SUB)), rmask = (1 << lratio) - 1;
-  for (int z0 = 1; z0 == 1 || z0 <= last; z0 += per_round) {
-    const int n_cls = min(per_round, last - z0 + 1);  // 0: every bin is on the grid
+  // ---- the classes 1 ... R / 2 that do not lie on the grid (multiples of
+  // `ratio` do), one per wave and round; at M = 2048 the lags keep wave 0's region
+  const bool ok = expandable(mean);
+  const float* grid = LONG ? row : M < SUB ? aux + UP : aux;
+  const int ratio = N / max(M, SUB), lratio = __builtin_ctz(ratio), rmask = ratio - 1;
+  const int n_tasks = ratio == 1 ? 0 : R / 2 - ((R / 2) >> lratio);
+  constexpr int FIRST = WIDE ? 1 : 0, PER_ROUND = W - FIRST;
+  const bool one_round = n_tasks <= PER_ROUND;
+  for (int z0 = 0; z0 == 0 || z0 < n_tasks; z0 += PER_ROUND) {
+    const int n_cls = min(PER_ROUND, n_tasks - z0);  // 0: every bin is on the grid
+    const int task = wave - FIRST;
     const bool mine = task >= 0 && task < n_cls;
-    const int k1 = z0 + task;
-    GridTwiddles w;
-    float2 pre[16];
-    float2 rot = make_float2(1.f, 0.f);  // e^{2 pi i k1 / R}
-    if (mine) {
-      load_class_twiddles(w, tw, N, N, k1, lane);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) pre[j] = uniform_twiddle(tw, (64 * k1 * j) & (N - 1));
-      const float2 r = uniform_twiddle(tw, (SUB * k1) & (N - 1));
-      rot = make_float2(r.x, -r.y);
-    }
+    const int k1 = mine ? z0 + task + 1 + (z0 + task) / rmask : 0;
     __syncthreads();  // the lags (first round) are written, the regions free
     if (mine) {
-      float2 v[16];
+      complex64d v[16];
+      const complex64d r1 = uniform_twiddle64(tw64, (SUB * k1) & (N - 1));  // W_R^{k1}
 #pragma unroll
       for (int j = 0; j < 16; ++j) {  // q[n] and q[n - 1024], n = lane + 64 j
         const int n = lane + 64 * j, m = SUB - n;
-        const float qp = 64 * j < M / 2 ? qs[n].x : 0.f;
-        const float qm = 64 * (15 - j) < M / 2 ? qs[m].y : 0.f;
-        v[j] = make_float2(fmaf(rot.x, qm, qp), rot.y * qm);
+        const double qp = LONG || 64 * j < M / 2 ? qs[n].x : 0.f;
+        const double qm = LONG || 64 * (15 - j) < M / 2 ? qs[m].y : 0.f;
+        v[j] = complex64d{fma(r1.x, qm, qp), -r1.y * qm};
       }
-      dft16_pre1(v, pre, dk);
+      if constexpr (LONG) {
+#pragma unroll 1
+        for (int s = 1; s < SG; ++s) {
+          const complex64d f = uniform_twiddle64(tw64, (SUB * k1 * s) & (N - 1));
+          const complex64d b = uniform_twiddle64(tw64, (SUB * k1 * (s + 1)) & (N - 1));
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int n = lane + 64 * j + SUB * s, m = SUB * (s + 1) - lane - 64 * j;
+            const double qp = qs[n].x, qm = qs[m].y;
+            v[j].x = fma(b.x, qm, fma(f.x, qp, v[j].x));
+            v[j].y = fma(-b.y, qm, fma(f.y, qp, v[j].y));
+          }
+        }
+      }
       float* own = reinterpret_cast<float*>(xw);
-      wave_passes_23(v, xw, w, dk, lane, NoHook{}, [&](int i, float2 f) {
+      class_transform64(v, xd, tw64, N, N, k1, lane, [&](int i, complex64d f) {
         // staged(bin_of(i, lane)), with the register's kd as a constant offset
         const int r4 = lane >> 4;
         const int at = (lane & 15) + 64 * r4 + 16 * ((i >> 2) ^ r4);
-        own[at + 256 * (i & 3)] = f.x - f.y;
-        own[at + 256 * (i & 3) + MIRROR] = f.x + f.y;
+        own[at + 256 * (i & 3)] = static_cast<float>(f.x - f.y + mean);
+        own[at + 256 * (i & 3) + MIRROR] = static_cast<float>(f.x + f.y + mean);
       });
     }
     __syncthreads();
     if (ok) {
-      // the four bins k = 4 tid + u (+ 4 NT per step) this thread stores:
-      // their staged rows, or -1: not of this round, or grid points
+      // the four bins k = 4 tid + u (+ 4 NT per step) this thread stores: their
+      // staged rows, or -1: not of this round, or grid points
       int base[4];
       bool grid_pt[4], mirror[4];
 #pragma unroll
@@ -690,11 +1078,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_grid(FoldArgs a) {
         const int k = 4 * tid + u, cl = k & (R - 1);
         grid_pt[u] = (k & rmask) == 0;
         mirror[u] = 2 * cl > R;
-        const int i = (mirror[u] ? R - cl : cl) - z0;
-        base[u] = i >= 0 && i < n_cls
-                      ? (i + (wide ? 1 : 0)) * 2 * XWAVE + (mirror[u] ? MIRROR : 0)
-                      : -1;
-        if (grid_pt[u]) base[u] = z0 == 1 ? 0 : -1;
+        const int kc = mirror[u] ? R - cl : cl;
+        const int i = kc - 1 - (kc >> lratio) - z0;
+        base[u] = i >= 0 && i < n_cls ? (i + FIRST) * 2 * XWAVE + (mirror[u] ? MIRROR : 0) : -1;
+        if (grid_pt[u]) base[u] = z0 == 0 ? 0 : -1;
       }
       float* out = a.out + static_cast<int64_t>(g) * N;
       for (int k0 = 4 * tid; k0 < N; k0 += 4 * NT) {
@@ -708,8 +1095,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_grid(FoldArgs a) {
           } else if (base[u] >= 0) {
             // class R - k1 holds bin -(k1 + R kk), i.e. its own entry 1023 - kk
             const int kb = (k0 + u) >> lr;
-            x = xf[base[u] + staged(mirror[u] ? SUB - 1 - kb : kb)] + mean;
-            x = x < 0.f ? 0.f : x;
+            x = xf[base[u] + staged(mirror[u] ? SUB - 1 - kb : kb)];
+            x = x < 0.f ? 0.f : x;  // S >= 0: a rounded zero stays one
           }
           s.v[u] = a.accumulate ? s.v[u] + x : x;
         }
@@ -722,9 +1109,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_grid(FoldArgs a) {
         }
       }
     }
-    if (z0 + per_round <= last) __syncthreads();
+    if (z0 + PER_ROUND < n_tasks) __syncthreads();
   }
-  if (!ok) direct_row<ST>(a, g, xs, dk, tid);
+  if (!ok) direct_row<ST>(a, g, xs, dft16_consts(), tid);
 }
 
 template <int LOGM, int ST>
@@ -740,20 +1127,32 @@ hipError_t launch_grid_w(const FoldArgs& a, hipStream_t s) {
 
 template <int ST>
 hipError_t launch_grid(const FoldArgs& a, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.chunks));
   switch (a.grid_len) {
     case 128: return launch_grid_w<7, ST>(a, s);
     case 256: return launch_grid_w<8, ST>(a, s);
     case 512: return launch_grid_w<9, ST>(a, s);
     case 1024: return launch_grid_w<10, ST>(a, s);
     case 2048: return launch_grid_w<11, ST>(a, s);
+    case 4096: hipLaunchKernelGGL((grid_long<4, ST>), grid, dim3(256), 0, s, a); break;
+    case 8192: hipLaunchKernelGGL((grid_long<8, ST>), grid, dim3(512), 0, s, a); break;
+    case 16384: hipLaunchKernelGGL((grid_long<16, ST>), grid, dim3(1024), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
 }
 
 template <int ST>
 hipError_t launch_expand(const FoldArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(expand_grid<ST>, dim3(static_cast<unsigned>(a.rows)), dim3(64 * EXP_WAVES), 0,
-                     s, a);
+  const dim3 grid(static_cast<unsigned>(a.rows)), block(64 * EXP_WAVES);
+  switch (a.grid_len / (2 * SUB)) {
+    case 0: hipLaunchKernelGGL((expand_grid<ST, 0>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((expand_grid<ST, 1>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((expand_grid<ST, 2>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((expand_grid<ST, 4>), grid, block, 0, s, a); break;
+    case 8: hipLaunchKernelGGL((expand_grid<ST, 8>), grid, block, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -764,6 +1163,7 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.samples = f.samples;
   a.tx = f.tx;
   a.twiddle = f.twiddle;
+  a.twiddle64 = f.twiddle64;
   a.grid = f.grid;
   a.out = f.out;
   a.stride = f.stride;
@@ -782,9 +1182,14 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.gate_count = f.gate_count;
   if (f.grid_bits) {
     const int rows = f.tx_per_pulse ? f.n_pulses : 1;
-    hipLaunchKernelGGL(pack_grid_bits, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, s,
-                       reinterpret_cast<const float2*>(f.tx), rows, f.code_len, f.grid_bits,
-                       f.grid_binary);
+    if (f.code_len > SUB)
+      hipLaunchKernelGGL(pack_long_grid_bits, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
+                         reinterpret_cast<const float2*>(f.tx), f.code_len, f.grid_bits,
+                         f.grid_binary);
+    else
+      hipLaunchKernelGGL(pack_grid_bits, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0,
+                         s, reinterpret_cast<const float2*>(f.tx), rows, f.code_len, f.grid_bits,
+                         f.grid_binary);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     a.code_bits = f.grid_bits;

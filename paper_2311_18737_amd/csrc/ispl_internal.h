@@ -82,8 +82,10 @@ struct FusedArgs {
   // themselves.  `grid` holds the chunk partials of grid_rows gates at a time,
   // [grid_chunks][grid_rows][grid_len] floats (grid_len = N: of all gates, and
   // one chunk needs none).  grid_bits / grid_binary (both or neither):
-  // [code rows][64] words and [code rows] flags for the codes' sign bits.
+  // [code rows][L <= SUB ? 64 : SUB] words and [code rows] flags for the codes'
+  // sign bits.
   float* grid;
+  const double* twiddle64;  // W_N^i, i < N, complex128 pairs
   uint32_t* grid_bits;
   int32_t* grid_binary;
   int32_t grid_len;
@@ -116,7 +118,8 @@ struct FoldArgs {
   const void* samples;
   const float* tx;
   const float* twiddle;      // W_N^i, i < N
-  const uint32_t* code_bits; // [code rows][64] sign bits (NULL: read tx), see pack_grid_bits
+  const double* twiddle64;   // the same in double
+  const uint32_t* code_bits; // sign bits of the code rows (NULL: read tx), see the packing kernels
   const int32_t* code_binary;
   float* grid;               // [chunks][rows][M]
   float* out;                // [G][N]
@@ -139,13 +142,16 @@ hipError_t launch_reduce_chunks(const float* partial, float* spectra, int64_t el
                                 const int32_t* list, const int32_t* count, hipStream_t stream);
 
 // Static scratch of ispl_integrate_spectra_noalloc: twiddle table first, the
-// chunk partials after it.
+// chunk partials after it.  Calls that run on a grid use the second part as the twiddle
+// table in double (NOALLOC_TWIDDLE64_BYTES) and the grid scratch after it.
 constexpr size_t NOALLOC_TWIDDLE_BYTES = size_t{512} << 10;  // N <= 65536 complex64
 constexpr size_t NOALLOC_PARTIAL_BYTES = ISPL_NOALLOC_SCRATCH_BYTES - NOALLOC_TWIDDLE_BYTES;
+constexpr size_t NOALLOC_TWIDDLE64_BYTES = size_t{1} << 20;  // N <= 65536 complex128
 // This GPU's copy of the array (`device` must be current); looked up once per
 // device.
 hipError_t noalloc_scratch(int device, unsigned char** base);
-// W_N^i, i < n_fft, into `table` (complex64 pairs), as the context builds it.
+// W_N^i, i < n_fft, as the context builds them: into `table` (complex64 pairs) and in
+// double into the NOALLOC_TWIDDLE64_BYTES that follow its NOALLOC_TWIDDLE_BYTES.
 hipError_t launch_build_twiddles(float* table, int32_t n_fft, hipStream_t stream);
 
 hipError_t launch_fill_zero(float* dst, int64_t elems, hipStream_t stream);

@@ -6,7 +6,8 @@
 //
 // Layout of the array (ISPL_NOALLOC_SCRATCH_BYTES):
 //   [0, 512 KiB)        twiddle table W_N^i, i < N <= 65536, complex64
-//   [512 KiB, end)      chunk partials [C][G][N] float32 (64 MiB)
+//   [512 KiB, end)      chunk partials [C][G][N] float32 (64 MiB), or the twiddle table
+//                       in double (1 MiB) and the grid scratch
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -48,6 +49,7 @@ __global__ void __launch_bounds__(256) build_twiddles(float* __restrict__ table,
   }
   table[2 * i] = static_cast<float>(ci);
   table[2 * i + 1] = static_cast<float>(-si);
+  reinterpret_cast<double2*>(table + NOALLOC_TWIDDLE_BYTES / sizeof(float))[i] = make_double2(ci, -si);
 }
 
 constexpr int kMaxDevices = 64;

@@ -166,3 +166,32 @@ def test_powers_beyond_fp32_and_nan(ispl, L, N):
     assert near.max() <= 1e-5
     assert_spectra_match(got[[0, 2, 5]], ref[[0, 2, 5]], what="ordinary and tiny gates")
     assert (got[3] == 0).all() and np.isnan(got[4]).all()
+
+
+LONG_CASES = [
+    # N,     L,    G,  P, type,  per-pulse code, code kind
+    (16384, 1025, 3, 4, "c64", True, "phase"),
+    (16384, 2048, 2, 5, "ci16", False, "bpsk"),
+    (16384, 2049, 2, 3, "c64", True, "gauss"),
+    (16384, 4096, 3, 6, "ci16", True, "phase"),
+    (16384, 4097, 2, 4, "c64", True, "bpsk"),
+    (16384, 8192, 2, 2, "ci16", False, "phase"),
+    (32768, 2000, 70, 480, "c64", True, "bpsk"),
+    (32768, 4000, 1, 7, "ci16", True, "bpsk"),
+    (32768, 8191, 2, 3, "c64", True, "phase"),
+    (65536, 1500, 1, 3, "ci16", True, "phase"),
+    (65536, 3000, 2, 9, "c64", False, "bpsk"),
+    (65536, 8192, 1, 3, "c64", True, "gauss"),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", LONG_CASES, ids=lambda t: "N{}_L{}_G{}_P{}_{}_{}_{}".format(*t))
+def test_long_folded_integration_matches_oracle(ispl, case):
+    test_folded_integration_matches_oracle(ispl, case)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,N", [(1500, 16384), (7000, 32768)])
+def test_long_powers_beyond_fp32_and_nan(ispl, L, N):
+    test_powers_beyond_fp32_and_nan(ispl, L, N)
