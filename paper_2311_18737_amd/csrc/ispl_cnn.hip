@@ -1,14 +1,13 @@
-// Window-proposal network of the learned zoom: training kernels (FP32 on
-// the vector ALUs).
+// Window-proposal network of the learned zoom: training kernels (FP32: the
+// 32 -> 32 layers on the matrix cores' FP32 products, the rest on the vector ALUs).
 //
 // The network maps one gate's coarse spectrum feature
 // x[t] = log(max(S[t] / mean S, 1e-30)), t < T = 1024, to one logit per coarse bin through four circular 7-tap 1-D
 // convolutions, 1 -> 32 -> 32 -> 32 -> 1 channels with ReLU after the first
 // three.  Training minimises the softmax cross entropy against a two-hot
 // target at the line's coarse position u (1 - frac(u) on floor(u), frac(u)
-// on floor(u) + 1, modulo T).  One workgroup handles one gate; per-gate
-// weight gradients are summed over the batch in a fixed order (no atomics),
-// so a training step is bit-reproducible.
+// on floor(u) + 1, modulo T).  Per-gate weight gradients are summed over the
+// batch in a fixed order (no atomics), so a training step is bit-reproducible.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -37,138 +36,257 @@ __device__ __forceinline__ void window10(const float* row, int j, float (&w)[10]
   w[7] = r.x; w[8] = r.y; w[9] = r.z;
 }
 
-// z[co][t] = b[co] + sum_{ci,k} W[co][ci][k] a[ci][(t + k - 3) mod T]; out = relu(z) or z.
-template <int CIN, int COUT, bool RELU>
-__global__ void __launch_bounds__(NT) conv_fwd(const float* __restrict__ in,
-                                               const float* __restrict__ params, int w_off,
-                                               float* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) float a_s[CIN][T];
-  const int b = blockIdx.x, j = threadIdx.x;
-  const float* src = in + static_cast<int64_t>(b) * CIN * T;
-  for (int i = j; i < CIN * T / 4; i += NT)
-    reinterpret_cast<float4*>(&a_s[0][0])[i] = reinterpret_cast<const float4*>(src)[i];
-  __syncthreads();
+// ---------------------------------------------------------------------------
+// 32 -> 32 layers and their data gradients as FP32 matrix products
+// (v_mfma_f32_32x32x2_f32): rows are the 32 output channels, columns 32
+// positions, the reduction 16 channel pairs x 7 taps.
+//
+// One workgroup of eight waves per 256 positions of a gate, one 32-position
+// tile per wave.  The inputs (with the 3 + 3 neighbours, wrapped) and the
+// weights lie in LDS; a step's operands are one 4-byte read each, which the
+// 64-cycle products of four waves per SIMD (two workgroups per CU) hide.  At 256
+// gates a layer takes 43 to 46 us (128-position workgroups 50; on the vector ALUs, one
+// workgroup per gate, 150 to 230), the products alone 24, its bytes 15.
+// Weight rows have an odd pitch, input rows one of half the banks.
+constexpr int TILE = 256;
+constexpr int TNT = 2 * TILE;      // threads: a wave per 32 positions
+constexpr int ROW = 288;           // pitch of an input row; entry i is position t0 - 4 + i
+constexpr int USED = TILE + 8;     // entries of it
+constexpr int WPITCH = 32 * TAPS + 1;
+
+typedef float f32x16t __attribute__((ext_vector_type(16)));
+
+// Row (channel) of accumulator i in lane half h.
+__device__ __forceinline__ int acc_row(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }
+
+enum ConvKind {
+  kFirstTwo,  // layers 1 and 2: in = x [B][T]; layer 1 is also written to a1
+  kForward,   // a 32 -> 32 layer with ReLU
+  kData       // its data gradient: in = dz, da[ci][t] = sum_{co,k} W[co][ci][k] dz[co][t - k + 3],
+              // out = da where a1 (the layer's input activation) > 0, else 0
+};
+
+template <ConvKind KIND>
+__global__ void __launch_bounds__(TNT) conv_tile(const float* __restrict__ in,
+                                                const float* __restrict__ params, int w_off,
+                                                float* __restrict__ a1, float* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) float in_s[32][ROW];
+  __shared__ float w_s[32 * WPITCH];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.x / (T / TILE), t0 = TILE * (blockIdx.x % (T / TILE));
   const float* W = params + w_off;
-  const float* bias = W + COUT * CIN * TAPS;
-  float* dst = out + static_cast<int64_t>(b) * COUT * T;
-  for (int co = 0; co < COUT; ++co) {
-    float acc[4];
+  const int64_t rows = static_cast<int64_t>(b) * 32 * T;
+
 #pragma unroll
-    for (int m = 0; m < 4; ++m) acc[m] = bias[co];
-    for (int ci = 0; ci < CIN; ++ci) {
-      float w[10];
-      window10(a_s[ci], j, w);
-      const float* wk = W + (co * CIN + ci) * TAPS;
-#pragma unroll
-      for (int k = 0; k < TAPS; ++k)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) acc[m] = fmaf(wk[k], w[m + k], acc[m]);
-    }
-    float4 o;
-    o.x = RELU ? fmaxf(acc[0], 0.f) : acc[0];
-    o.y = RELU ? fmaxf(acc[1], 0.f) : acc[1];
-    o.z = RELU ? fmaxf(acc[2], 0.f) : acc[2];
-    o.w = RELU ? fmaxf(acc[3], 0.f) : acc[3];
-    *reinterpret_cast<float4*>(dst + co * T + 4 * j) = o;
+  for (int i = 0; i < 32 * 32 * TAPS / TNT; ++i) {
+    const int e = tid + TNT * i, r = e / (32 * TAPS);
+    w_s[e + r] = W[e];
   }
-}
-
-// Data gradient: da[ci][t] = sum_{co,k} W[co][ci][k] dz[co][(t - k + 3) mod T],
-// returned as the pre-activation gradient dz_in = da * (a_in > 0).
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(NT) conv_bwd_data(const float* __restrict__ dz,
-                                                    const float* __restrict__ params, int w_off,
-                                                    const float* __restrict__ a_in,
-                                                    float* __restrict__ dz_in) {
-  __shared__ __attribute__((aligned(16))) float d_s[COUT][T];
-  const int b = blockIdx.x, j = threadIdx.x;
-  const float* src = dz + static_cast<int64_t>(b) * COUT * T;
-  for (int i = j; i < COUT * T / 4; i += NT)
-    reinterpret_cast<float4*>(&d_s[0][0])[i] = reinterpret_cast<const float4*>(src)[i];
-  __syncthreads();
-  const float* W = params + w_off;
-  const float* mask = a_in + static_cast<int64_t>(b) * CIN * T;
-  float* dst = dz_in + static_cast<int64_t>(b) * CIN * T;
-  for (int ci = 0; ci < CIN; ++ci) {
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int co = 0; co < COUT; ++co) {
-      float w[10];  // w[i] = dz[co][4 j - 3 + i]
-      window10(d_s[co], j, w);
-      const float* wk = W + (co * CIN + ci) * TAPS;
-      // t = 4 j + m needs dz[t - k + 3] = w[m - k + 6]
-#pragma unroll
-      for (int k = 0; k < TAPS; ++k)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) acc[m] = fmaf(wk[k], w[m - k + 6], acc[m]);
-    }
-    const float4 a = ld4(mask + ci * T + 4 * j);
-    float4 o;
-    o.x = a.x > 0.f ? acc[0] : 0.f;
-    o.y = a.y > 0.f ? acc[1] : 0.f;
-    o.z = a.z > 0.f ? acc[2] : 0.f;
-    o.w = a.w > 0.f ? acc[3] : 0.f;
-    *reinterpret_cast<float4*>(dst + ci * T + 4 * j) = o;
-  }
-}
-
-// Weight gradient of one gate: dW[co][ci][k] = sum_t dz[co][t] a[ci][(t + k - 3) mod T],
-// db[co] = sum_t dz[co][t], written to that gate's row of the partial buffer
-// (layer segment at w_off, flat parameter order).  Positions are swept in
-// chunks of 256 staged in LDS; each thread owns fixed (co, ci) pairs.
-constexpr int WCH = 256;
-constexpr int APITCH = WCH + 7;  // 263: odd pitch spreads the 32 rows over the banks
-
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(NT) conv_bwd_weight(const float* __restrict__ dz,
-                                                      const float* __restrict__ a_in,
-                                                      int w_off, int n_params,
-                                                      float* __restrict__ part) {
-  constexpr int PAIRS = CIN * COUT;
-  constexpr int PER = (PAIRS + NT - 1) / NT;
-  __shared__ float d_s[COUT][WCH];
-  __shared__ float a_s[CIN][APITCH];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const float* dzb = dz + static_cast<int64_t>(b) * COUT * T;
-  const float* ab = a_in + static_cast<int64_t>(b) * CIN * T;
-  float acc[PER][TAPS];
-  float bacc = 0.f;
-#pragma unroll
-  for (int q = 0; q < PER; ++q)
-#pragma unroll
-    for (int k = 0; k < TAPS; ++k) acc[q][k] = 0.f;
-
-  for (int t0 = 0; t0 < T; t0 += WCH) {
+  if constexpr (KIND == kFirstTwo) {
+    __shared__ float x_s[USED + 8];  // entry i is position t0 - 8 + i
+    if (tid < USED + 8) x_s[tid] = in[static_cast<int64_t>(b) * T + ((t0 - 8 + tid) & (T - 1))];
     __syncthreads();
-    for (int i = tid; i < COUT * WCH; i += NT) d_s[i / WCH][i % WCH] = dzb[(i / WCH) * T + t0 + i % WCH];
-    for (int i = tid; i < CIN * (WCH + 6); i += NT) {
-      const int ci = i / (WCH + 6), tt = i % (WCH + 6);
-      a_s[ci][tt] = ab[ci * T + ((t0 + tt - PAD) & (T - 1))];  // a[ci][t0 + tt - 3]
+    const float* W1 = params;
+    for (int e = tid; e < 32 * USED; e += TNT) {
+      const int co = e / USED, i = e % USED;
+      float z = W1[32 * TAPS + co];
+#pragma unroll
+      for (int k = 0; k < TAPS; ++k) z = fmaf(W1[co * TAPS + k], x_s[i + k + 1], z);
+      z = fmaxf(z, 0.f);
+      in_s[co][i] = z;
+      if (i >= 4 && i < 4 + TILE) a1[rows + co * T + t0 - 4 + i] = z;
     }
-    __syncthreads();
+  } else {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int pr = tid + NT * q;
-      if (pr < PAIRS) {
-        const int co = pr / CIN, ci = pr % CIN;
-        for (int tt = 0; tt < WCH; ++tt) {
-          const float d = d_s[co][tt];
-#pragma unroll
-          for (int k = 0; k < TAPS; ++k) acc[q][k] = fmaf(d, a_s[ci][tt + k], acc[q][k]);
-        }
+    for (int u = 0; u < (32 * USED / 4 + TNT - 1) / TNT; ++u) {
+      const int e = tid + TNT * u;
+      if (e < 32 * USED / 4) {
+        const int r = e / (USED / 4), i = 4 * (e % (USED / 4));
+        *reinterpret_cast<float4*>(&in_s[r][i]) = ld4(in + rows + r * T + ((t0 - 4 + i) & (T - 1)));
       }
     }
-    if (tid < COUT)
-      for (int tt = 0; tt < WCH; ++tt) bacc += d_s[tid][tt];
   }
-  float* out = part + static_cast<int64_t>(b) * n_params + w_off;
+  __syncthreads();
+
+  const int col = lane & 31, h = lane >> 5;
+  f32x16t acc;
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int pr = tid + NT * q;
-    if (pr < PAIRS)
+  for (int i = 0; i < 16; ++i) acc[i] = KIND == kData ? 0.f : W[32 * 32 * TAPS + acc_row(i, h)];
+  // product step (pair c, tap k): channel 2 c + h of both operands
+  const float* wp = w_s + (KIND == kData ? h * WPITCH + col * TAPS : col * WPITCH + h * TAPS);
+  const float* ip = &in_s[h][32 * wave + col];
+#pragma unroll 4
+  for (int c = 0; c < 16; ++c)
 #pragma unroll
-      for (int k = 0; k < TAPS; ++k) out[pr * TAPS + k] = acc[q][k];
+    for (int k = 0; k < TAPS; ++k)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(
+          wp[(KIND == kData ? 2 * WPITCH : 2 * TAPS) * c + k],
+          ip[2 * ROW * c + (KIND == kData ? 7 - k : 1 + k)], acc, 0, 0, 0);
+  const int64_t at = rows + t0 + 32 * wave + col;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t o = at + acc_row(i, h) * T;
+    if constexpr (KIND == kData)
+      out[o] = a1[o] > 0.f ? acc[i] : 0.f;
+    else
+      out[o] = fmaxf(acc[i], 0.f);
   }
-  if (tid < COUT) out[PAIRS * TAPS + tid] = bacc;
+}
+
+// Sums over the 64 lanes of 64 values per lane, value i left in lane i: each
+// step hands half of the values to the lane's partner (63 exchanges, not 6 x 64).
+template <int N = 32>
+__device__ __forceinline__ float lane_sums(float (&v)[64], int lane) {
+  const bool up = (lane & N) != 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float keep = up ? v[i + N] : v[i], send = up ? v[i] : v[i + N];
+    v[i] = keep + __shfl_xor(send, N);
+  }
+  if constexpr (N > 1)
+    return lane_sums<N / 2>(v, lane);
+  else
+    return v[0];
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients dW[co][ci][k] = sum_t dz[co][t] a[ci][(t + k - 3) mod T],
+// db[co] = sum_t dz[co][t] of one gate, written to that gate's row of the partial
+// buffer (layer segment at w_off, flat parameter order).
+//
+// A 32 -> 32 layer: seven FP32 matrix products (one per tap) over the
+// positions, all seven accumulators in registers.  Wave w takes positions 128 w ...
+// 128 w + 127, lane half h their half 64 h ..., so that each lane walks its own
+// rows of dz and a in order: 16-byte loads, no LDS, and the taps' operands are a
+// sliding window over a in registers.  At 256 gates the three layers take 100 us (the
+// vector ALU form with a (co, ci) pair's taps per thread 530), of which the products are
+// 48; accumulators leave two waves per SIMD, so a workgroup's first loads are not hidden.
+constexpr int WG_WAVES = 8;
+
+__device__ void weight_grad32(const float* __restrict__ dz, const float* __restrict__ a,
+                              float* __restrict__ out, float (&buf)[2][WG_WAVES][1024]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 31, h = lane >> 5;
+  const int t0 = 128 * wave + 64 * h;
+  const float* dr = dz + r * T + t0;
+  const float* ar = a + r * T;
+  f32x16t acc[TAPS];
+#pragma unroll
+  for (int k = 0; k < TAPS; ++k)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[k][i] = 0.f;
+  float db = 0.f;
+  // sixteen positions at a time, the next ones in flight
+  float w[22], next[16], dv[16], dn[16];  // w[i]: position base - 3 + i of a
+  auto load16 = [](float (&to)[16], const float* from) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 f = ld4(from + 4 * q);
+      to[4 * q] = f.x, to[4 * q + 1] = f.y, to[4 * q + 2] = f.z, to[4 * q + 3] = f.w;
+    }
+  };
+  {
+    const float4 l = ld4(ar + ((t0 - 4) & (T - 1)));
+    w[0] = l.y, w[1] = l.z, w[2] = l.w;
+  }
+  load16(next, ar + t0);
+  load16(dn, dr);
+#pragma unroll 1
+  for (int it = 0; it < 4; ++it) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[3 + i] = next[i], dv[i] = dn[i];
+    load16(next, ar + ((t0 + 16 * it + 16) & (T - 1)));
+    if (it < 3) load16(dn, dr + 16 * it + 16);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if (j == 13) w[19] = next[0], w[20] = next[1], w[21] = next[2];
+#pragma unroll
+      for (int k = 0; k < TAPS; ++k)
+        acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(dv[j], w[j + k], acc[k], 0, 0, 0);
+      db += dv[j];
+    }
+    w[0] = w[16], w[1] = w[17], w[2] = w[18];
+  }
+  // the waves' sums, tap by tap through LDS
+  float sum[TAPS][2];
+#pragma unroll
+  for (int k = 0; k < TAPS; ++k) {
+    float (&half)[WG_WAVES][1024] = buf[k & 1];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) half[wave][32 * acc_row(i, h) + r] = acc[k][i];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < WG_WAVES; ++w) s += half[w][tid + 512 * u];
+      sum[k][u] = s;
+    }
+  }
+  db += __shfl_xor(db, 32);
+  __syncthreads();  // (both halves read)
+  float* flat = &buf[0][0][0];
+  float* bias = &buf[1][0][0];
+  static_assert(32 * 32 * TAPS <= WG_WAVES * 1024, "a gate's weights in one half");
+#pragma unroll
+  for (int k = 0; k < TAPS; ++k)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) flat[(tid + 512 * u) * TAPS + k] = sum[k][u];
+  if (lane < 32) bias[32 * wave + lane] = db;
+  __syncthreads();
+  for (int i = tid; i < 32 * 32 * TAPS; i += 64 * WG_WAVES) out[i] = flat[i];
+  if (tid < 32) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < WG_WAVES; ++w) s += bias[32 * w + tid];
+    out[32 * 32 * TAPS + tid] = s;
+  }
+}
+
+// Layer 1 (one input channel): four output channels per wave, 16 positions per lane.
+__device__ void weight_grad1(const float* __restrict__ dz, const float* __restrict__ x,
+                             float* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float v[64];  // 8 values (taps, bias) of 4 channels; the upper half stays zero
+#pragma unroll
+  for (int i = 0; i < 64; ++i) v[i] = 0.f;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int j = lane + 64 * s;
+    float w[10];
+    window10(x, j, w);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float4 d4 = ld4(dz + (4 * wave + c) * T + 4 * j);
+      const float d[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+#pragma unroll
+        for (int k = 0; k < TAPS; ++k) v[8 * c + k] = fmaf(d[m], w[m + k], v[8 * c + k]);
+        v[8 * c + 7] += d[m];
+      }
+    }
+  }
+  const float s = lane_sums(v, lane);
+  const int co = 4 * wave + (lane >> 3), k = lane & 7;
+  if (lane < 32) out[k < TAPS ? co * TAPS + k : 32 * TAPS + co] = s;
+}
+
+// Layers 3, 2 and 1 in one launch (the long ones first).
+__global__ void __launch_bounds__(64 * WG_WAVES)
+weight_grads(const float* __restrict__ dz3, const float* __restrict__ a2,
+             const float* __restrict__ dz2, const float* __restrict__ a1,
+             const float* __restrict__ dz1, const float* __restrict__ x, int batch, int off3,
+             int off2, int off1, int n_params, float* __restrict__ part) {
+  __shared__ float buf[2][WG_WAVES][1024];
+  const int layer = blockIdx.x / batch, b = blockIdx.x % batch;
+  const int64_t rows = static_cast<int64_t>(b) * 32 * T;
+  float* out = part + static_cast<int64_t>(b) * n_params;
+  if (layer == 2)
+    weight_grad1(dz1 + rows, x + static_cast<int64_t>(b) * T, out + off1);
+  else
+    weight_grad32((layer == 0 ? dz3 : dz2) + rows, (layer == 0 ? a2 : a1) + rows,
+                  out + (layer == 0 ? off3 : off2), buf);
 }
 
 // Fixed-order block reduction helpers (256 threads).
@@ -179,57 +297,145 @@ __device__ float block_sum(float v, float* red) {
   __syncthreads();
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
-__device__ float block_max(float v, float* red) {
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+
+// Sum or maximum over a workgroup of 16 waves, in a fixed order.
+template <bool MAX>
+__device__ __forceinline__ float block16(float v, float* red) {
+  for (int off = 32; off > 0; off >>= 1) {
+    const float o = __shfl_xor(v, off);
+    v = MAX ? fmaxf(v, o) : v + o;
+  }
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-
-// Softmax cross entropy against the two-hot target at coarse position u[b];
-// dlogits = softmax - target, loss[b].
-__global__ void __launch_bounds__(NT) softmax_ce(const float* __restrict__ logits,
-                                                 const float* __restrict__ target_pos,
-                                                 float* __restrict__ dlogits,
-                                                 float* __restrict__ loss) {
-  __shared__ float red[4];
-  const int b = blockIdx.x, j = threadIdx.x;
-  const float4 z = ld4(logits + static_cast<int64_t>(b) * T + 4 * j);
-  const float mx = block_max(fmaxf(fmaxf(z.x, z.y), fmaxf(z.z, z.w)), red);
-  const float e0 = expf(z.x - mx), e1 = expf(z.y - mx), e2 = expf(z.z - mx), e3 = expf(z.w - mx);
-  const float sum = block_sum((e0 + e1) + (e2 + e3), red);
-  const float u = target_pos[b];
-  const float fl = floorf(u);
-  const float f = u - fl;
-  const int lo = static_cast<int>(fl) & (T - 1), hi = (lo + 1) & (T - 1);
-  const float inv = 1.f / sum;
-  float e[4] = {e0, e1, e2, e3};
-  float4 d;
-  float* dp = &d.x;
+  float r = red[0];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int t = 4 * j + m;
-    const float tgt = (t == lo ? 1.f - f : 0.f) + (t == hi ? f : 0.f);
-    dp[m] = e[m] * inv - tgt;
+  for (int i = 1; i < 16; ++i) r = MAX ? fmaxf(r, red[i]) : r + red[i];
+  return r;
+}
+
+// Layer 4 (32 -> 1) of one gate: logits; with GRAD instead the softmax cross
+// entropy against the two-hot target at coarse position target_pos[b] (loss[b]) and,
+// with dz4 = softmax - target, the gradients of the layer's weights (into the gate's
+// partial row) and its data gradient dz3, in one pass over a3 each: four
+// kernels and two passes of 128 KB per gate less.  1024 threads: four positions of
+// eight channels each.
+template <bool GRAD>
+__global__ void __launch_bounds__(1024) last_layer(const float* __restrict__ a3,
+                                                   const float* __restrict__ params, int w_off,
+                                                   const float* __restrict__ target_pos,
+                                                   float* __restrict__ logits,
+                                                   float* __restrict__ loss, int n_params,
+                                                   float* __restrict__ part,
+                                                   float* __restrict__ dz3) {
+  __shared__ __attribute__((aligned(16))) float z_s[4][T];
+  __shared__ __attribute__((aligned(16))) float d_s[T];
+  __shared__ float red[16], wsum[16][64];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = tid & (NT - 1), grp = __builtin_amdgcn_readfirstlane(tid / NT);
+  const float* W = params + w_off;
+  const int64_t rows = static_cast<int64_t>(b) * 32 * T;
+  const float* a = a3 + rows + 8 * grp * T;
+  const float* wg = W + 8 * grp * TAPS;
+  {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      float w[10];
+      window10(a + c * T, j, w);
+#pragma unroll
+      for (int k = 0; k < TAPS; ++k)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[m] = fmaf(wg[c * TAPS + k], w[m + k], acc[m]);
+    }
+    *reinterpret_cast<float4*>(&z_s[grp][4 * j]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   }
-  *reinterpret_cast<float4*>(dlogits + static_cast<int64_t>(b) * T + 4 * j) = d;
-  if (j == 0) {
-    const float lse = mx + logf(sum);  // -log p[t] = lse - z[t]
-    const float zlo = logits[static_cast<int64_t>(b) * T + lo];
-    const float zhi = logits[static_cast<int64_t>(b) * T + hi];
-    loss[b] = (1.f - f) * (lse - zlo) + f * (lse - zhi);
+  __syncthreads();
+  const float z = W[32 * TAPS] + ((z_s[0][tid] + z_s[1][tid]) + (z_s[2][tid] + z_s[3][tid]));
+  if constexpr (!GRAD) {
+    logits[static_cast<int64_t>(b) * T + tid] = z;
+  } else {
+    const float mx = block16<true>(z, red);
+    const float e = expf(z - mx);
+    const float sum = block16<false>(e, red);
+    const float u = target_pos[b];
+    const float fl = floorf(u);
+    const float f = u - fl;
+    const int lo = static_cast<int>(fl) & (T - 1), hi = (lo + 1) & (T - 1);
+    const float tgt = (tid == lo ? 1.f - f : 0.f) + (tid == hi ? f : 0.f);
+    d_s[tid] = e * (1.f / sum) - tgt;
+    z_s[0][tid] = z;  // (read by this thread alone before)
+    __syncthreads();
+    if (tid == 0) {
+      const float lse = mx + logf(sum);  // -log p[t] = lse - z[t]
+      loss[b] = (1.f - f) * (lse - z_s[0][lo]) + f * (lse - z_s[0][hi]);
+    }
+    float dw[10];  // dw[i] = dz4[4 j - 3 + i]
+    window10(d_s, j, dw);
+    float v[64];   // 7 taps of 8 channels; 56: the bias
+#pragma unroll
+    for (int i = 0; i < 64; ++i) v[i] = 0.f;
+    float* dst = dz3 + rows + 8 * grp * T;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      float w[10];
+      window10(a + c * T, j, w);
+      float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < TAPS; ++k)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          v[c * TAPS + k] = fmaf(dw[m + 3], w[m + k], v[c * TAPS + k]);
+          o[m] = fmaf(wg[c * TAPS + k], dw[m - k + 6], o[m]);
+        }
+      *reinterpret_cast<float4*>(dst + c * T + 4 * j) =
+          make_float4(w[3] > 0.f ? o[0] : 0.f, w[4] > 0.f ? o[1] : 0.f, w[5] > 0.f ? o[2] : 0.f,
+                      w[6] > 0.f ? o[3] : 0.f);
+    }
+    v[56] = (dw[3] + dw[4]) + (dw[5] + dw[6]);
+    wsum[wave][lane] = lane_sums(v, lane);
+    __syncthreads();
+    if (tid < 32 * TAPS + 1) {  // waves 4 grp ... 4 grp + 3 hold channels 8 grp ...
+      const int q = tid < 32 * TAPS ? tid / 56 : 0, i = tid < 32 * TAPS ? tid % 56 : 56;
+      part[static_cast<int64_t>(b) * n_params + w_off + tid] =
+          (wsum[4 * q][i] + wsum[4 * q + 1][i]) + (wsum[4 * q + 2][i] + wsum[4 * q + 3][i]);
+    }
   }
 }
 
-// grad[i] = (1 / B) sum_b part[b][i] in increasing b; loss_mean likewise.
+// grad[i] = (1 / B) sum_b part[b][i], and in the last workgroup the mean of the
+// losses: 32 columns and 8 interleaved runs of rows per workgroup, the runs'
+// sums added in order.  (One thread per column has 59 workgroups walk the
+// rows: 62 us at 256 rows.)
 __global__ void __launch_bounds__(256) mean_rows(const float* __restrict__ part, int rows,
-                                                 int cols, float* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= cols) return;
+                                                 int cols, const float* __restrict__ loss,
+                                                 float* __restrict__ out,
+                                                 float* __restrict__ loss_mean) {
+  __shared__ float run_s[8][32];
+  const int c = threadIdx.x & 31, run = threadIdx.x >> 5;
+  const bool of_loss = blockIdx.x == gridDim.x - 1;
+  const int i = of_loss ? c : 32 * static_cast<int>(blockIdx.x) + c, n = of_loss ? 1 : cols;
+  const float* src = of_loss ? loss : part;
   float s = 0.f;
-  for (int r = 0; r < rows; ++r) s += part[static_cast<int64_t>(r) * cols + i];
-  out[i] = s / static_cast<float>(rows);
+  if (i < n) {
+    int r = run;
+    for (; r + 24 < rows; r += 32) {
+      float q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q[u] = src[static_cast<int64_t>(r + 8 * u) * n + i];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += q[u];
+    }
+    for (; r < rows; r += 8) s += src[static_cast<int64_t>(r) * n + i];
+  }
+  run_s[run][c] = s;
+  __syncthreads();
+  if (run == 0 && i < n) {
+    s = run_s[0][c];
+#pragma unroll
+    for (int u = 1; u < 8; ++u) s += run_s[u][c];
+    (of_loss ? loss_mean : out)[i] = s / static_cast<float>(rows);
+  }
 }
 
 __global__ void __launch_bounds__(256) adam_update(float* __restrict__ params,
@@ -275,30 +481,40 @@ hipError_t launch_net_features(const float* spectra, int rows, float* out, hipSt
   return hipGetLastError();
 }
 
+namespace {
+
+// layers 1 to 3: a1, a2, a3
+void launch_trunk(const NetWork& w, const float* x, int batch, hipStream_t s) {
+  const dim3 tiles(batch * (T / TILE));
+  hipLaunchKernelGGL((conv_tile<kFirstTwo>), tiles, dim3(TNT), 0, s, x, w.params, L2_OFF, w.a1, w.a2);
+  hipLaunchKernelGGL((conv_tile<kForward>), tiles, dim3(TNT), 0, s, w.a2, w.params, L3_OFF,
+                     static_cast<float*>(nullptr), w.a3);
+}
+
+}  // namespace
+
 hipError_t launch_net_forward_f32(const NetWork& w, const float* x, int batch, float* logits,
                                   hipStream_t s) {
-  hipLaunchKernelGGL((conv_fwd<1, 32, true>), dim3(batch), dim3(NT), 0, s, x, w.params, L1_OFF, w.a1);
-  hipLaunchKernelGGL((conv_fwd<32, 32, true>), dim3(batch), dim3(NT), 0, s, w.a1, w.params, L2_OFF, w.a2);
-  hipLaunchKernelGGL((conv_fwd<32, 32, true>), dim3(batch), dim3(NT), 0, s, w.a2, w.params, L3_OFF, w.a3);
-  hipLaunchKernelGGL((conv_fwd<32, 1, false>), dim3(batch), dim3(NT), 0, s, w.a3, w.params, L4_OFF, logits);
+  launch_trunk(w, x, batch, s);
+  hipLaunchKernelGGL((last_layer<false>), dim3(batch), dim3(1024), 0, s, w.a3, w.params, L4_OFF,
+                     static_cast<const float*>(nullptr), logits, static_cast<float*>(nullptr), 0,
+                     static_cast<float*>(nullptr), static_cast<float*>(nullptr));
   return hipGetLastError();
 }
 
 hipError_t launch_net_loss_grad(const NetWork& w, const float* x, const float* target_pos,
                                 int batch, float* grad, float* loss_mean, hipStream_t s) {
-  hipError_t e = launch_net_forward_f32(w, x, batch, w.logits, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(softmax_ce, dim3(batch), dim3(NT), 0, s, w.logits, target_pos, w.dz4, w.loss);
-  // layer 4 (32 -> 1), then 3, 2, 1
-  hipLaunchKernelGGL((conv_bwd_weight<32, 1>), dim3(batch), dim3(NT), 0, s, w.dz4, w.a3, L4_OFF, NET_PARAMS, w.part);
-  hipLaunchKernelGGL((conv_bwd_data<32, 1>), dim3(batch), dim3(NT), 0, s, w.dz4, w.params, L4_OFF, w.a3, w.dzA);
-  hipLaunchKernelGGL((conv_bwd_weight<32, 32>), dim3(batch), dim3(NT), 0, s, w.dzA, w.a2, L3_OFF, NET_PARAMS, w.part);
-  hipLaunchKernelGGL((conv_bwd_data<32, 32>), dim3(batch), dim3(NT), 0, s, w.dzA, w.params, L3_OFF, w.a2, w.dzB);
-  hipLaunchKernelGGL((conv_bwd_weight<32, 32>), dim3(batch), dim3(NT), 0, s, w.dzB, w.a1, L2_OFF, NET_PARAMS, w.part);
-  hipLaunchKernelGGL((conv_bwd_data<32, 32>), dim3(batch), dim3(NT), 0, s, w.dzB, w.params, L2_OFF, w.a1, w.dzA);
-  hipLaunchKernelGGL((conv_bwd_weight<1, 32>), dim3(batch), dim3(NT), 0, s, w.dzA, x, L1_OFF, NET_PARAMS, w.part);
-  hipLaunchKernelGGL(mean_rows, dim3((NET_PARAMS + 255) / 256), dim3(256), 0, s, w.part, batch, NET_PARAMS, grad);
-  hipLaunchKernelGGL(mean_rows, dim3(1), dim3(256), 0, s, w.loss, batch, 1, loss_mean);
+  launch_trunk(w, x, batch, s);
+  hipLaunchKernelGGL((last_layer<true>), dim3(batch), dim3(1024), 0, s, w.a3, w.params, L4_OFF,
+                     target_pos, static_cast<float*>(nullptr), w.loss, NET_PARAMS, w.part, w.dzA);
+  // data gradients: dz3 in dzA, dz2 in dzB, dz1 in a3 (no longer needed)
+  const dim3 tiles(batch * (T / TILE));
+  hipLaunchKernelGGL((conv_tile<kData>), tiles, dim3(TNT), 0, s, w.dzA, w.params, L3_OFF, w.a2, w.dzB);
+  hipLaunchKernelGGL((conv_tile<kData>), tiles, dim3(TNT), 0, s, w.dzB, w.params, L2_OFF, w.a1, w.a3);
+  hipLaunchKernelGGL(weight_grads, dim3(3 * batch), dim3(64 * WG_WAVES), 0, s, w.dzA, w.a2, w.dzB,
+                     w.a1, w.a3, x, batch, L3_OFF, L2_OFF, L1_OFF, NET_PARAMS, w.part);
+  hipLaunchKernelGGL(mean_rows, dim3((NET_PARAMS + 31) / 32 + 1), dim3(256), 0, s, w.part, batch,
+                     NET_PARAMS, w.loss, grad, loss_mean);
   return hipGetLastError();
 }
 

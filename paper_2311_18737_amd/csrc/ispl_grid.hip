@@ -73,7 +73,8 @@ struct RunSplit {
       : each(static_cast<uint32_t>(steps) / static_cast<uint32_t>(n)),
         extra(static_cast<uint32_t>(steps) - each * static_cast<uint32_t>(n)) {}
   __device__ int begin(int s) const {
-    return static_cast<int>(static_cast<uint32_t>(s) * each + min(static_cast<uint32_t>(s), extra));
+    return __builtin_amdgcn_readfirstlane(
+        static_cast<int>(static_cast<uint32_t>(s) * each + min(static_cast<uint32_t>(s), extra)));
   }
   __device__ int longest() const { return static_cast<int>(each + (extra != 0 ? 1 : 0)); }
 };
