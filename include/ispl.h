@@ -189,7 +189,10 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
  * high and low halves (three split products each, FP32 accumulation);
  * decode, shift and the pulse sum stay FP32.  The result is the same
  * quantity as ispl_integrate_spectra at those bins (Section 2.2, Eqs. 7-8),
- * at the precision of the chosen split.
+ * at the precision of the chosen split.  Codes of at most 1024 samples sum the
+ * pulses in FP32 on a grid of 2^m >= 2 L - 1 points instead and take the
+ * windows from it in double precision, for either precision (relative error
+ * about 1e-7, that of ispl_integrate_spectra).
  */
 typedef enum {
   ISPL_ZOOM_BF16X3 = 0,  /* BF16 hi/lo split: ~16 significant bits per product */
@@ -202,7 +205,7 @@ typedef struct ispl_zoom ispl_zoom; /* opaque; must not outlive its context */
  * 128, at most fft_len) of ctx's geometry: two halves of 6 * n_bins *
  * round_up(code_len, 64) bytes each; ISPL_ERR_UNSUPPORTED above 512 MiB per
  * half.  Also holds the per-call scratch: FP16 exponents and the sign bits of
- * +-1 codes for max_pulses pulses. */
+ * +-1 codes for max_pulses pulses, and up to 63 MiB for the grid. */
 ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
                              ispl_zoom** out);
 
@@ -309,7 +312,7 @@ ispl_status ispl_net_select(ispl_net* net, const float* logits, int32_t n_gates,
 /*
  * Learned zoom: peak frequency of every gate without the full-resolution
  * spectrum of every gate.  One call runs, on `stream`, what these calls
- * compute one after another (in six launches):
+ * compute one after another (in six launches, seven with a zoom from the grid):
  *   1. ispl_integrate_spectra at N_c = 1024 (the coarse spectra; its pulses
  *      are split into chunks of at least 4, so the coarse sums may differ
  *      from a context's own in rounding);
@@ -333,7 +336,7 @@ ispl_status ispl_net_select(ispl_net* net, const float* logits, int32_t n_gates,
  * window_bins <= fft_len; zoom_precision an ispl_zoom_precision; threshold
  * in (0, 1].  `net` stays owned by the caller, must outlive the object and
  * be on cfg->device; its current parameters are used at every call.  The
- * object owns two contexts, a zoom table, [n_gates] x (2 * 1024 +
+ * object owns two contexts, a zoom object, [n_gates] x (2 * 1024 +
  * window_bins + fft_len) floats of buffers and up to 16 MiB of fallback
  * chunk partials.  Not thread-safe, and calls on
  * one object must not overlap on different streams (it owns the scratch and

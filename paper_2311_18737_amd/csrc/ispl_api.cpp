@@ -33,6 +33,7 @@ struct ispl_ctx {
   int32_t* code_binary; // [max_pulses]
   float* grid;          // folded integration: scratch of grid_bytes (nullptr: never folds)
   int64_t grid_bytes;
+  const float* deferred; // where the last call's chunk partials lie that its caller sums
   double* twiddle64;    // the twiddle table in double
   uint32_t* grid_bits;  // codes as sign bits [max_pulses][64] and flags [max_pulses]
   int32_t* grid_binary;
@@ -388,6 +389,10 @@ struct ispl_zoom {
   int32_t* col_exp;  // [max_pulses] (FP16 only)
   uint32_t* code_bits;    // [max_pulses][code_pad / 32] sign bits of +-1 codes
   int32_t* code_binary;   // [max_pulses]
+  float* grid;            // scratch of calls from the summed grid (NULL: none of this zoom's are)
+  int64_t grid_bytes;
+  uint32_t* grid_bits;    // [max_pulses][64]
+  int32_t* grid_binary;   // [max_pulses]
 };
 
 namespace {
@@ -414,10 +419,23 @@ ZoomPlan zoom_plan(int32_t n_gates, int32_t n_bins, int32_t n_pulses) {
   return z;
 }
 
+// The grid plan of a zoom call, or none (then matrix products): one transform of
+// >= 2 L - 1 points per pulse is less than K L products already for the smallest
+// window.  Measured (pulses x gates, L, N, K: us by products, on the grid):
+// 1 x 64, 256, 16384, 256: 16.8, 13.7; 3 x 300, 1000, 16384, 16384: 8250, 1210;
+// 1000 x 16, 256, 16384, 256: 46, 28; 4000 gates of 1 pulse, L = 16: 119, 94.
+GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_pulses) {
+  GridPlan gp{};
+  const int len = c.code_len <= ispl::SUB ? grid_length(c) : 0;
+  if (len > 0 && n_pulses >= 1) grid_split(c, len, n_pulses, 0, &gp);
+  return gp;
+}
+
 }  // namespace
 
 static void zoom_free(ispl_zoom* z) {
-  void* bufs[] = {z->a_hi, z->a_lo, z->partial, z->col_exp, z->code_bits, z->code_binary};
+  void* bufs[] = {z->a_hi,      z->a_lo, z->partial,   z->col_exp,    z->code_bits,
+                  z->code_binary, z->grid, z->grid_bits, z->grid_binary};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
 }
@@ -689,9 +707,15 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
   a.gate_count = gate_count;
   GridPlan gp{};
   if (ctx->grid && !adapt && !deferred_chunks) gp = grid_plan(c, n_pulses, ctx->force_chunks);
+  // chunk partials that the caller sums: on a grid of all the bins (100 pulses of 64
+  // gates at N = 1024 take 13.9 us, 16.4 by the direct kernel)
+  if (ctx->grid && deferred_chunks && !adapt && !gate_list && !accumulate &&
+      c.fft_len <= 2 * ispl::SUB && grid_length(c) > 0)
+    grid_split(c, c.fft_len, n_pulses, 0, &gp);
   if (gp.len > 0) {
     a.out = spectra;
     a.chunks = 1;
+    a.grid_defer = deferred_chunks ? 1 : 0;
     a.grid = ctx->grid;
     a.twiddle64 = ctx->twiddle64;
     a.grid_len = gp.len;
@@ -705,6 +729,10 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     }
     e = ispl::launch_fused(a, s);
     if (e != hipSuccess) return hip_fail(e, "folded launch");
+    if (deferred_chunks) {
+      *deferred_chunks = gp.chunks;
+      ctx->deferred = ctx->grid;
+    }
     return ok();
   }
   if (adapt) {
@@ -732,6 +760,7 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
   if (pl.chunks > 1) {
     if (deferred_chunks && !accumulate) {
       *deferred_chunks = pl.chunks;
+      ctx->deferred = ctx->partial;
       return ok();
     }
     e = ispl::launch_reduce_chunks(ctx->partial, spectra, elems, pl.chunks, accumulate,
@@ -860,6 +889,14 @@ ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
                                      static_cast<size_t>(code_pad / 32));
   if (e == hipSuccess)
     e = hipMalloc(&z->code_binary, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
+  // (a call of fewer pulses gains less from the grid)
+  if (e == hipSuccess && ctx->twiddle64 && zoom_grid_plan(c, c.max_pulses).len > 0) {
+    z->grid_bytes = grid_scratch_bytes(c);
+    e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes));
+    if (e == hipSuccess) e = hipMalloc(&z->grid_bits, size_t{256} * static_cast<size_t>(c.max_pulses));
+    if (e == hipSuccess)
+      e = hipMalloc(&z->grid_binary, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
+  }
   if (e != hipSuccess) {
     zoom_free(z);
     delete z;
@@ -961,8 +998,25 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
   a.row_lo = c.first_gate;
   a.row_hi = static_cast<int64_t>(c.first_gate) + static_cast<int64_t>(c.n_gates - 1) * c.gate_step +
              c.code_len;
+  GridPlan gp{};
+  if (z->grid) gp = zoom_grid_plan(c, n_pulses);
+  if (gp.len > 0) {
+    a.chunks = 1;
+    a.grid = z->grid;
+    a.twiddle64 = z->ctx->twiddle64;
+    a.grid_len = gp.len;
+    a.grid_chunks = gp.chunks;
+    a.grid_waves = gp.waves;
+    a.grid_rows = static_cast<int32_t>(
+        std::min<int64_t>(c.n_gates, z->grid_bytes / (int64_t{4} * gp.len * gp.chunks)));
+    if (static_cast<int64_t>(n_pulses) * c.n_gates >= kMinBitsPulseGates) {
+      a.grid_bits = z->grid_bits;
+      a.grid_binary = z->grid_binary;
+    }
+  }
   hipError_t e = ispl::launch_zoom(a, s, !exponents_ready);
   if (e != hipSuccess) return hip_fail(e, "zoom launch");
+  if (gp.len > 0) return ok();
   if (zp.chunks > 1 && deferred_chunks && !accumulate) {
     *deferred_chunks = zp.chunks;
     return ok();
@@ -1422,7 +1476,7 @@ ispl_status ispl_lzoom_peaks(ispl_lzoom* z, const void* samples, const float* tx
   bf16_table_ready(z->net, s, &e);
   if (e == hipSuccess)
     e = ispl::launch_net_forward_bf16(z->net->bf16_weights, z->coarse_spectra, G, z->logits, s,
-                                      true, z->coarse->partial, coarse_chunks, z->coarse_spectra);
+                                      true, z->coarse->deferred, coarse_chunks, z->coarse_spectra);
   if (e == hipSuccess) {
     ispl::PulseExpArgs pe{};
     pe.samples = samples;
@@ -1438,7 +1492,9 @@ ispl_status ispl_lzoom_peaks(ispl_lzoom* z, const void* samples, const float* tx
     pe.sample_type = c.sample_type;
     pe.code_len = c.code_len;
     pe.tx_per_pulse = tx_per_pulse;
-    pe.n_pulses = n_pulses > 0 ? n_pulses : 0;
+    // (a zoom from the grid needs neither exponents nor these sign bits)
+    const bool folds = z->zoom->grid && zoom_grid_plan(c, n_pulses).len > 0;
+    pe.n_pulses = n_pulses > 0 && !folds ? n_pulses : 0;
     e = ispl::launch_select_and_exponents(z->logits, G, c.fft_len, z->window_bins, z->threshold,
                                           z->bin_start, z->confidence, z->flag, z->zoom_list,
                                           z->fallback_list, z->counts, z->done, pe,

@@ -45,20 +45,26 @@ __device__ __forceinline__ complex64d uniform_twiddle64(const double* tw, int i)
   return {w.x, w.y};
 }
 
-// sum_j v[j] P^j W_16^{j k} into v[k] for P = W_N^e (see dft16_geo and
-// load_geo of the FP32 form); tw(i) is W_N^{i mod N}.
-template <typename TW>
-__device__ __forceinline__ void dft16_geo64(complex64d (&v)[16], int e, int n_fft, TW tw) {
-  const int n16 = n_fft >> 4;
-  {
-    const complex64d g = tw(4 * e), g2 = tw(8 * e);
+__device__ __forceinline__ complex64d cmul(complex64d a, complex64d b) {
+  return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+}
+__device__ __forceinline__ complex64d square(complex64d a) {
+  return {fma(a.x, a.x, -(a.y * a.y)), 2.0 * (a.x * a.y)};
+}
+
+// sum_j v[j] P^j W_16^{j k} into v[k], natural order (see dft16_geo of the FP32
+// form), from P, P^2, P^4 and P^8: P^j W_16^{k1} and its square by constants.
+__device__ __forceinline__ void dft16_geo64(complex64d (&v)[16], complex64d p, complex64d p2,
+                                            complex64d p4, complex64d p8) {
 #pragma unroll
-    for (int j1 = 0; j1 < 4; ++j1) dft4_geo(v[j1], v[j1 + 4], v[j1 + 8], v[j1 + 12], g, g2);
-  }
-#pragma unroll
-  for (int k1 = 0; k1 < 4; ++k1)
-    dft4_geo(v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3], tw(e + k1 * n16),
-             tw(2 * e + 2 * k1 * n16));
+  for (int j1 = 0; j1 < 4; ++j1) dft4_geo(v[j1], v[j1 + 4], v[j1 + 8], v[j1 + 12], p4, p8);
+  // W_16^{k1} and W_8^{k1}
+  constexpr double c = 0.92387953251128675613, s = 0.38268343236508977173;  // cos, sin(pi / 8)
+  constexpr double r = 0.70710678118654752440;                              // cos(pi / 4)
+  dft4_geo(v[0], v[1], v[2], v[3], p, p2);
+  dft4_geo(v[4], v[5], v[6], v[7], cmul(p, {c, -s}), cmul(p2, {r, -r}));
+  dft4_geo(v[8], v[9], v[10], v[11], cmul(p, {r, -r}), {p2.y, -p2.x});
+  dft4_geo(v[12], v[13], v[14], v[15], cmul(p, {s, -c}), cmul(p2, {-r, -r}));
   complex64d t[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) t[i] = v[4 * (i & 3) + (i >> 2)];
@@ -75,8 +81,14 @@ __device__ __forceinline__ void class_transform64(complex64d (&v)[16], double* x
                                                   int n, int table, int kappa, int lane, Sink sink) {
   const int step = table / n, mask = table - 1, S = n >> 10;
   const int ka = lane & 15, row = lane >> 4, q = step * (kappa + S * ka);
-  dft16_geo64(v, 64 * step * kappa, table,
-              [&](int i) { return uniform_twiddle64(tw, i & mask); });
+  // the lane's two twiddles; their powers are formed (each 64-lane gather holds the CU's
+  // address unit for 64 cycles, and eight waves share it)
+  const complex64d w = twiddle64(tw, q & mask), w16 = twiddle64(tw, (table >> 4) * row);
+  {
+    const int e = 64 * step * kappa;
+    dft16_geo64(v, uniform_twiddle64(tw, e & mask), uniform_twiddle64(tw, (2 * e) & mask),
+                uniform_twiddle64(tw, (4 * e) & mask), uniform_twiddle64(tw, (8 * e) & mask));
+  }
   const int p2base = ka * XPITCH + row;
 #pragma unroll
   for (int k = 0; k < 16; ++k) xd[k * XPITCH + lane] = v[k].x;
@@ -89,7 +101,8 @@ __device__ __forceinline__ void class_transform64(complex64d (&v)[16], double* x
   wave_lds_sync();
 #pragma unroll
   for (int m = 0; m < 16; ++m) v[m].y = xd[p2base + 4 * m];
-  dft16_geo64(v, 4 * q, table, [&](int i) { return twiddle64(tw, i & mask); });
+  const complex64d p4 = square(square(w)), p8 = square(p4), p16 = square(p8);
+  dft16_geo64(v, p4, p8, p16, square(p16));
   wave_lds_sync();
 #pragma unroll
   for (int k = 0; k < 16; ++k) xd[64 * k + lane] = v[k].x;
@@ -107,11 +120,14 @@ __device__ __forceinline__ void class_transform64(complex64d (&v)[16], double* x
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[4 * t + r].y = xd[64 * (4 * row + t) + 16 * r + ka];
   wave_lds_sync();
+  const complex64d w3 = cmul(w, w16);  // W^q W_64^{kc}, kc = 4 row + t
+  // W_64^t
+  constexpr double c64[4] = {1.0, 0.99518472667219688624, 0.98078528040323044913, 0.95694033573220886494};
+  constexpr double s64[4] = {0.0, 0.09801714032956060199, 0.19509032201612826785, 0.29028467725446236764};
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int e = q + (table >> 6) * (4 * row + t);  // W_n^{q} W_64^{kc}
-    dft4_geo(v[4 * t], v[4 * t + 1], v[4 * t + 2], v[4 * t + 3], twiddle64(tw, e & mask),
-             twiddle64(tw, (2 * e) & mask));
+    const complex64d f = t == 0 ? w3 : cmul(w3, {c64[t], -s64[t]});
+    dft4_geo(v[4 * t], v[4 * t + 1], v[4 * t + 2], v[4 * t + 3], f, square(f));
 #pragma unroll
     for (int kd = 0; kd < 4; ++kd) sink(4 * t + kd, v[4 * t + kd]);
   }

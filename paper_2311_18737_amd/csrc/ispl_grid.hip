@@ -122,6 +122,15 @@ struct BufferSample<1> {
   __device__ static float2 cvt(raw_t r) { return SampleIO<1>::cvt(r); }
 };
 
+// The gate of a workgroup's slot, or -1 (uniform, before any barrier).
+__device__ __forceinline__ int gate_of(const FoldArgs& a, int slot) {
+  const int g = a.slot0 + slot;
+  if (!a.gate_list) return g;
+  if (g >= *a.gate_count) return -1;
+  const int listed = a.gate_list[g];
+  return listed < a.n_gates ? listed : -1;
+}
+
 // 8-point DFT of (v0, v1, v2, v3, 0, 0, 0, 0): even outputs are the 4-point
 // DFT of v, odd ones that of v_j W_8^j.
 __device__ __forceinline__ void dft8_first4(float2* v, const Dft16Consts& k) {
@@ -253,12 +262,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   const int run = wave / CLS;
   const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
   const int c = bid % a.chunks, slot = bid / a.chunks;
-  int g = a.slot0 + slot;
-  if (a.gate_list) {
-    if (g >= *a.gate_count) return;  // uniform, before any barrier
-    g = a.gate_list[g];
-    if (g < 0 || g >= a.n_gates) return;
-  }
+  const int g = gate_of(a, slot);
+  if (g < 0) return;
   const int L = a.code_len;
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   // pass-2 column k1 of this lane (bins k1 + (M / 64) (kc + 16 kd)) and its
@@ -336,7 +341,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   }
   // the chunk's partial row; on a grid of all N bins by gate, and with one
   // chunk the gate's row of the result itself
-  const bool whole = a.grid_len == a.n_fft, last = whole && a.chunks == 1;
+  const bool whole = a.grid_len == a.n_fft && !a.partials, last = whole && a.chunks == 1;
   float* out = last ? a.out + static_cast<int64_t>(g) * M
                     : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
   bool add = last && a.accumulate;
@@ -496,12 +501,8 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
   const int c = bid % a.chunks, slot = bid / a.chunks;
-  int g = a.slot0 + slot;
-  if (a.gate_list) {
-    if (g >= *a.gate_count) return;  // uniform, before any barrier
-    g = a.gate_list[g];
-    if (g < 0 || g >= a.n_gates) return;
-  }
+  const int g = gate_of(a, slot);
+  if (g < 0) return;
   const int L = a.code_len, M = SUB * J, step = a.n_fft / M, nmask = a.n_fft - 1;
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   // (complex64 samples in flight take 16 registers)
@@ -588,7 +589,7 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
     }
   }
   // the chunk's partial row, or the result's (as in grid_spectra)
-  const bool whole = a.grid_len == a.n_fft, last = whole && a.chunks == 1;
+  const bool whole = a.grid_len == a.n_fft && !a.partials, last = whole && a.chunks == 1;
   float* out = last ? a.out + static_cast<int64_t>(g) * M
                     : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
   bool add = last && a.accumulate;
@@ -694,7 +695,7 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
 // transform's structure, where S may be a hundred times smaller, which no direct
 // transform does.  (With FP32 transforms the largest error of the uneven batch's
 // L = 2000 experiment was 3.5e-5 of the larger of S and its mean, now 5.7e-6; 1000
-// gates of N = 16384 take 68 us instead of 50.)  Lags and grid stay FP32:
+// gates of N = 16384 take 67 us, in FP32 50.)  Lags and grid stay FP32:
 // their rounding is spread evenly over all bins.
 
 // SG-point DFT in place, natural order (SG = 2, 4 or 8).
@@ -816,9 +817,51 @@ __device__ void direct_row(const FoldArgs& a, int g, float2* xs, const Dft16Cons
   }
 }
 
-// SG: M / 2048 segments of 1024 lags each way (0: M <= 1024).
+// Mean of a gate's grid of m points from each thread's part of its sum.
+__device__ __forceinline__ double block_mean(double part, double* red, int m) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < EXP_WAVES; ++i) s += red[i];
+  return s / static_cast<double>(m);
+}
+
+// A gate's grid of M <= 2048 points into `to`, its chunk partials (cs floats apart)
+// summed in ascending order; returns this thread's part of the sum over the grid.
+__device__ __forceinline__ double gather_grid(const FoldArgs& a, const float* row, int64_t cs,
+                                              float* to, int tid) {
+  double part = 0.0;
+  for (int k = 4 * tid; k < a.grid_len; k += 4 * 64 * EXP_WAVES) {
+    float4 s = *reinterpret_cast<const float4*>(row + k);
+    for (int c0 = 1; c0 < a.chunks; c0 += 8) {
+      float4 q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        q[u] = *reinterpret_cast<const float4*>(row + min(c0 + u, a.chunks - 1) * cs + k);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (c0 + u < a.chunks) {
+          s.x += q[u].x;
+          s.y += q[u].y;
+          s.z += q[u].z;
+          s.w += q[u].w;
+        }
+    }
+    *reinterpret_cast<float4*>(to + k) = s;
+    part += (static_cast<double>(s.x) + static_cast<double>(s.y)) +
+            (static_cast<double>(s.z) + static_cast<double>(s.w));
+  }
+  return part;
+}
+
+// SG: M / 2048 segments of 1024 lags each way (0: M <= 1024).  Two waves per SIMD:
+// with four (two workgroups on a CU) the double-precision transforms spill, 71
+// against 67 us at 1000 gates of N = 16384.
 template <int ST, int SG>
-__global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(FoldArgs a) {
+__global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   constexpr int W = EXP_WAVES, NT = 64 * W;
   constexpr int UP = SUB + 4;  // aux: 1024-point grid of M < 1024
   constexpr bool WIDE = SG == 1, LONG = SG > 1;
@@ -838,27 +881,12 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(Fo
   double* xd = reinterpret_cast<double*>(xw);
 
   const int slot = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
-  int g = a.slot0 + slot;
-  if (a.gate_list) {
-    if (g >= *a.gate_count) return;  // uniform, before any barrier
-    g = a.gate_list[g];
-    if (g < 0 || g >= a.n_gates) return;
-  }
+  const int g = gate_of(a, slot);
+  if (g < 0) return;
   float* const row = a.grid + static_cast<int64_t>(slot) * M;
   const int64_t cs = static_cast<int64_t>(a.rows) * M;
   const float scale = 1.f / static_cast<float>(M);
 
-  // Mean of the grid from each thread's part of its sum.
-  auto block_mean = [&](double part) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    if (lane == 0) red[wave] = part;
-    __syncthreads();
-    double m = 0.0;
-#pragma unroll
-    for (int i = 0; i < W; ++i) m += red[i];
-    return m / static_cast<double>(M);
-  };
   // The lags n and m = n_cpx - n in place of F[n], F[m] (F: the transform of the
   // complex points z[2 a] + i z[2 a + 1]); with r = conj(DFT) / M
   // qs[n] = (q[n], q[-n]) = (Re r + Im r, Re r - Im r).
@@ -871,6 +899,13 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(Fo
     }
     qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
   };
+
+  // the classes 1 ... R / 2 that do not lie on the grid (multiples of `ratio` do),
+  // one per wave and round; at M = 2048 the lags keep wave 0's region
+  const int ratio = N / max(M, SUB), lratio = __builtin_ctz(ratio), rmask = ratio - 1;
+  const int n_tasks = ratio == 1 ? 0 : R / 2 - ((R / 2) >> lratio);
+  constexpr int FIRST = WIDE ? 1 : 0, PER_ROUND = W - FIRST;
+  auto class_of = [&](int task) { return task + 1 + task / rmask; };
 
   double mean;
   float2* qs;  // (q[n], q[-n]), n < M / 2, and one zero more
@@ -895,7 +930,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(Fo
         z[t][j] = complex64d{s.x, s.y};
         part += static_cast<double>(s.x) + static_cast<double>(s.y);
       }
-    mean = block_mean(part);
+    mean = block_mean(part, red, M);
     qs = lags;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -934,28 +969,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(Fo
     }
   } else {
     // ---- the grid, chunk sums in ascending order, into aux
-    double part = 0.0;
-    for (int k = 4 * tid; k < M; k += 4 * NT) {
-      float4 s = *reinterpret_cast<const float4*>(row + k);
-      for (int c0 = 1; c0 < a.chunks; c0 += 8) {
-        float4 q[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          q[u] = *reinterpret_cast<const float4*>(row + min(c0 + u, a.chunks - 1) * cs + k);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (c0 + u < a.chunks) {
-            s.x += q[u].x;
-            s.y += q[u].y;
-            s.z += q[u].z;
-            s.w += q[u].w;
-          }
-      }
-      *reinterpret_cast<float4*>(aux + k) = s;
-      part += (static_cast<double>(s.x) + static_cast<double>(s.y)) +
-              (static_cast<double>(s.z) + static_cast<double>(s.w));
-    }
-    mean = block_mean(part);
+    mean = block_mean(gather_grid(a, row, cs, aux, tid), red, M);
 
     // ---- lags: up to conjugation and 1 / M the forward DFT of the real grid,
     // M <= 1024 zero-interleaved to 1024 points (which repeats its spectrum),
@@ -1021,19 +1035,15 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(Fo
     }
   }
 
-  // ---- the classes 1 ... R / 2 that do not lie on the grid (multiples of
-  // `ratio` do), one per wave and round; at M = 2048 the lags keep wave 0's region
+  // ---- the classes
   const bool ok = expandable(mean);
   const float* grid = LONG ? row : M < SUB ? aux + UP : aux;
-  const int ratio = N / max(M, SUB), lratio = __builtin_ctz(ratio), rmask = ratio - 1;
-  const int n_tasks = ratio == 1 ? 0 : R / 2 - ((R / 2) >> lratio);
-  constexpr int FIRST = WIDE ? 1 : 0, PER_ROUND = W - FIRST;
   const bool one_round = n_tasks <= PER_ROUND;
   for (int z0 = 0; z0 == 0 || z0 < n_tasks; z0 += PER_ROUND) {
     const int n_cls = min(PER_ROUND, n_tasks - z0);  // 0: every bin is on the grid
     const int task = wave - FIRST;
     const bool mine = task >= 0 && task < n_cls;
-    const int k1 = mine ? z0 + task + 1 + (z0 + task) / rmask : 0;
+    const int k1 = mine ? class_of(z0 + task) : 0;
     __syncthreads();  // the lags (first round) are written, the regions free
     if (mine) {
       complex64d v[16];
@@ -1115,6 +1125,145 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, SG > 1 ? 2 : 4) expand_grid(Fo
   if (!ok) direct_row<ST>(a, g, xs, dft16_consts(), tid);
 }
 
+// ---------------------------------------------------------------------------
+// A window of K bins of the N-point spectrum from the summed grid (M <= 2048).
+//
+// The lags r[n] as in expand_grid, kept in double, then
+//   S[k] = r0 + 2 Re sum_{0 < n < L} r[n] z^n,  z = W_N^k,
+// by Horner's rule: wave w takes an eighth of the lags for 128 bins, two per lane
+// (the lag is one broadcast LDS read for eight multiply-adds), the eighths
+// meet in LDS.  4 K L double multiply-adds a gate are little beside a transform
+// of N points and need no window-sized table.  1000 pulses x 1000 gates, L = 256, K = 256
+// of N = 16384: the pulse pass 400 us, the windows 27; by matrix products (each
+// pulse's K L) 1180.  100 x 64: 16.8 us against 23, latency of the two kernels.
+
+// Bins k0 + j, j0 <= j < j1, of gate g straight from its pulses (see direct_row).
+template <int ST>
+__device__ void direct_window(const FoldArgs& a, int g, int k0, int j0, int j1, int tid) {
+  using IO = BufferSample<ST>;
+  const int N = a.n_fft, L = a.code_len;
+  const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
+  float* out = a.out + static_cast<int64_t>(g) * a.n_bins;
+  for (int j = j0 + tid; j < j1; j += 64 * EXP_WAVES) {
+    const complex64d z = twiddle64(a.twiddle64, (k0 + j) & (N - 1));
+    float s = a.accumulate ? out[j] : 0.f;
+    for (int p = 0; p < a.n_pulses; ++p) {
+      const auto ds = row_desc(a.samples, static_cast<int64_t>(p) * a.stride + gate_off, IO::SIZE, L);
+      const auto dc = row_desc(a.tx, a.tx_per_pulse ? static_cast<int64_t>(p) * L : 0, 8, L);
+      complex64d h{0.0, 0.0};
+      for (int n = L - 1; n >= 0; --n) {
+        const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(dc, 8 * n, 0, 0);
+        const float2 y = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)),
+                                  IO::cvt(IO::load(ds, IO::SIZE * n)));
+        h = cmuladd(complex64d{y.x, y.y}, h, z);
+      }
+      s += static_cast<float>(h.x * h.x + h.y * h.y);
+    }
+    out[j] = s;
+  }
+}
+
+template <int ST, bool WIDE>
+__global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
+  __shared__ __attribute__((aligned(16))) float grid[WIDE ? 2 * SUB : SUB];
+  __shared__ __attribute__((aligned(16))) complex64d lags[SUB + 1];
+  __shared__ __attribute__((aligned(16))) double xd[XWAVE];
+  __shared__ double red[EXP_WAVES], sums[EXP_WAVES][128];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int M = a.grid_len, N = a.n_fft, L = a.code_len, K = a.n_bins;
+  const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
+  const int slot = bid / a.blocks, part = bid % a.blocks;  // of the window, in runs of 128 bins
+  const int g = gate_of(a, slot);
+  if (g < 0) return;
+  const int r0 = K / 128 * part / a.blocks, r1 = K / 128 * (part + 1) / a.blocks;
+  const int k0 = a.bin_start[g];
+  const float* row = a.grid + static_cast<int64_t>(slot) * M;
+  const double mean = block_mean(
+      gather_grid(a, row, static_cast<int64_t>(a.rows) * M, grid, tid), red, M);
+  if (!expandable(mean)) {  // uniform
+    direct_window<ST>(a, g, k0, 128 * r0, 128 * r1, tid);
+    return;
+  }
+
+  // z and z^n0 of the lane's two bins in the run from j0 on (for the first run read
+  // before the lags are there)
+  const int per = (L - 1 + EXP_WAVES - 1) / EXP_WAVES;
+  const int n0 = 1 + wave * per, n1 = min(n0 + per, L);
+  complex64d za, zb, sa, sb;
+  auto load_factors = [&](int j0) {
+    const uint32_t ka = static_cast<uint32_t>(k0 + j0 + lane), kb = ka + 64, mask = N - 1;
+    za = twiddle64(a.twiddle64, ka & mask), sa = twiddle64(a.twiddle64, (ka * n0) & mask);
+    zb = twiddle64(a.twiddle64, kb & mask), sb = twiddle64(a.twiddle64, (kb * n0) & mask);
+  };
+  if (wave > 0) load_factors(128 * r0);
+
+  // lags[n] = r[n] = conj(DFT of the grid)[n] / M, 0 < n < L
+  const double scale = 1.0 / static_cast<double>(M);
+  if (wave == 0) {
+    complex64d v[16];
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float2 p = reinterpret_cast<const float2*>(grid)[lane + 64 * j];
+        v[j] = complex64d{p.x - mean, p.y - mean};
+      }
+      class_transform64(v, xd, a.twiddle64, SUB, N, 0, lane,
+                        [&](int i, complex64d f) { lags[bin_of(i, lane)] = f; });
+    } else {
+      const int lup = __builtin_ctz(SUB / M), up = (1 << lup) - 1;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int n = lane + 64 * j;
+        v[j] = complex64d{(n & up) == 0 ? grid[n >> lup] - mean : 0.0, 0.0};
+      }
+      class_transform64(v, xd, a.twiddle64, SUB, N, 0, lane, [&](int i, complex64d f) {
+        lags[bin_of(i, lane)] = complex64d{scale * f.x, -scale * f.y};
+      });
+    }
+  }
+  __syncthreads();
+  if constexpr (WIDE) {  // from the transform of the complex points grid[2 a] + i grid[2 a + 1]
+    auto untangle = [&](int n, complex64d p, complex64d m) {
+      const complex64d E{0.5 * (p.x + m.x), 0.5 * (p.y - m.y)};
+      const complex64d O{0.5 * (p.y + m.y), 0.5 * (m.x - p.x)};
+      const complex64d f = cmuladd(E, twiddle64(a.twiddle64, n * (N / M)), O);
+      lags[n] = complex64d{scale * f.x, -scale * f.y};
+    };
+    const int n = tid == 0 ? SUB / 2 : tid;  // a pair of lags per thread (n = 0 is not used)
+    const complex64d A = lags[n], B = lags[SUB - n];
+    __syncthreads();
+    untangle(n, A, B);
+    if (tid != 0) untangle(SUB - n, B, A);
+    __syncthreads();
+  }
+
+  if (wave == 0) load_factors(128 * r0);  // (no registers for them beside the transform)
+  float* out = a.out + static_cast<int64_t>(g) * K;
+  for (int j0 = 128 * r0; j0 < 128 * r1; j0 += 128) {
+    complex64d ha{0.0, 0.0}, hb{0.0, 0.0};
+#pragma unroll 4
+    for (int n = n1 - 1; n >= n0; --n) {
+      const complex64d r = lags[n];
+      ha = cmuladd(r, ha, za);
+      hb = cmuladd(r, hb, zb);
+    }
+    sums[wave][lane] = ha.x * sa.x - ha.y * sa.y;
+    sums[wave][lane + 64] = hb.x * sb.x - hb.y * sb.y;
+    __syncthreads();
+    if (tid < 128) {
+      double s = sums[0][tid];
+#pragma unroll
+      for (int w = 1; w < EXP_WAVES; ++w) s += sums[w][tid];
+      const float x = static_cast<float>(fma(2.0, s, mean));
+      const float y = x < 0.f ? 0.f : x;  // S >= 0: a rounded zero stays one
+      out[j0 + tid] = a.accumulate ? out[j0 + tid] + y : y;
+    }
+    if (j0 + 128 < 128 * r1) load_factors(j0 + 128);
+    __syncthreads();
+  }
+}
+
 template <int LOGM, int ST>
 hipError_t launch_grid_w(const FoldArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.chunks));
@@ -1157,6 +1306,31 @@ hipError_t launch_expand(const FoldArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Sign bits of the call's code rows, if it has room for them.
+hipError_t pack_bits(FoldArgs& a, uint32_t* bits, int32_t* binary, hipStream_t s) {
+  if (!bits) return hipSuccess;
+  const int rows = a.tx_per_pulse ? a.n_pulses : 1;
+  if (a.code_len > SUB)
+    hipLaunchKernelGGL(pack_long_grid_bits, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
+                       reinterpret_cast<const float2*>(a.tx), a.code_len, bits, binary);
+  else
+    hipLaunchKernelGGL(pack_grid_bits, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, s,
+                       reinterpret_cast<const float2*>(a.tx), rows, a.code_len, bits, binary);
+  a.code_bits = bits;
+  a.code_binary = binary;
+  return hipGetLastError();
+}
+
+template <int ST>
+hipError_t launch_window(const FoldArgs& a, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.blocks)), block(64 * EXP_WAVES);
+  if (a.grid_len > SUB)
+    hipLaunchKernelGGL((expand_window<ST, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((expand_window<ST, false>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
@@ -1181,25 +1355,12 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.accumulate = f.accumulate;
   a.gate_list = f.gate_list;
   a.gate_count = f.gate_count;
-  if (f.grid_bits) {
-    const int rows = f.tx_per_pulse ? f.n_pulses : 1;
-    if (f.code_len > SUB)
-      hipLaunchKernelGGL(pack_long_grid_bits, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
-                         reinterpret_cast<const float2*>(f.tx), f.code_len, f.grid_bits,
-                         f.grid_binary);
-    else
-      hipLaunchKernelGGL(pack_grid_bits, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0,
-                         s, reinterpret_cast<const float2*>(f.tx), rows, f.code_len, f.grid_bits,
-                         f.grid_binary);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    a.code_bits = f.grid_bits;
-    a.code_binary = f.grid_binary;
-  }
+  hipError_t e = pack_bits(a, f.grid_bits, f.grid_binary, s);
+  if (e != hipSuccess) return e;
   if (a.grid_len == a.n_fft) {  // every bin is on the grid: partials by gate, no expansion
     a.rows = f.n_gates;
-    hipError_t e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
-    if (e == hipSuccess && a.chunks > 1)
+    e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+    if (e == hipSuccess && a.chunks > 1 && !f.grid_defer)
       e = launch_reduce_chunks(a.grid, a.out, static_cast<int64_t>(f.n_gates) * f.n_fft, a.chunks,
                                a.accumulate, a.n_fft, a.gate_list, a.gate_count, s);
     return e;
@@ -1208,12 +1369,49 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   for (int32_t s0 = 0; s0 < f.n_gates; s0 += f.grid_rows) {
     a.slot0 = s0;
     a.rows = std::min(f.n_gates - s0, f.grid_rows);
-    hipError_t e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+    e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
     if (e == hipSuccess)
       e = f.sample_type == 1 ? launch_expand<1>(a, s) : launch_expand<0>(a, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
+  FoldArgs a{};
+  a.samples = z.samples;
+  a.tx = z.tx;
+  a.twiddle = z.twiddle;
+  a.twiddle64 = z.twiddle64;
+  a.grid = z.grid;
+  a.out = z.out;
+  a.stride = z.stride;
+  a.n_fft = z.n_fft;
+  a.grid_len = z.grid_len;
+  a.code_len = z.code_len;
+  a.n_gates = z.n_gates;
+  a.gate_step = z.gate_step;
+  a.first_gate = z.first_gate;
+  a.n_pulses = z.n_pulses;
+  a.chunks = z.grid_chunks;
+  a.waves = z.grid_waves;
+  a.tx_per_pulse = z.tx_per_pulse;
+  a.accumulate = z.accumulate;
+  a.gate_list = z.gate_list;
+  a.gate_count = z.gate_count;
+  a.bin_start = z.bin_start;
+  a.n_bins = z.n_bins;
+  a.partials = 1;
+  hipError_t e = pack_bits(a, z.grid_bits, z.grid_binary, s);
+  for (int32_t s0 = 0; e == hipSuccess && s0 < z.n_gates; s0 += z.grid_rows) {
+    a.slot0 = s0;
+    a.rows = std::min(z.n_gates - s0, z.grid_rows);
+    // a workgroup or more per gate, up to two per CU (each forms the gate's lags)
+    a.blocks = std::max(1, std::min(z.n_bins / 128, 512 / a.rows));
+    e = z.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+    if (e == hipSuccess) e = z.sample_type == 1 ? launch_window<1>(a, s) : launch_window<0>(a, s);
+  }
+  return e;
 }
 
 }  // namespace ispl

@@ -92,6 +92,7 @@ struct FusedArgs {
   int32_t grid_chunks;
   int32_t grid_waves;
   int32_t grid_rows;
+  int32_t grid_defer;        // grid_len = N: leave the chunk partials in `grid`
 };
 
 // Words of one code row in the sign-bit form (one per first-pass thread).
@@ -130,6 +131,10 @@ struct FoldArgs {
   const int32_t* gate_list;
   const int32_t* gate_count;
   int32_t slot0, rows;
+  // a window of n_bins bins per gate from bin_start[gate] on (out [G][n_bins])
+  const int32_t* bin_start;
+  int32_t n_bins, blocks;    // workgroups a window is split over
+  int32_t partials;          // leave the sums in `grid` also where M = N
 };
 // The whole folded integration of a.grid_len > 0.
 hipError_t launch_folded(const FusedArgs& a, hipStream_t stream);
@@ -194,7 +199,15 @@ struct ZoomArgs {
   // set when code[32 w + b] == -1, and per row 1 when the whole row is +-1.
   uint32_t* code_bits;
   int32_t* code_binary;
+  // Zoom from the pulse-summed grid of grid_len points instead (0: matrix
+  // products); see FusedArgs and launch_zoom_folded.  chunks is 1 then.
+  float* grid;
+  uint32_t* grid_bits;
+  int32_t* grid_binary;
+  const double* twiddle64;
+  int32_t grid_len, grid_chunks, grid_waves, grid_rows;
 };
+hipError_t launch_zoom_folded(const ZoomArgs& a, hipStream_t stream);
 
 // With prep = false the FP16 column exponents (FP16) and the code sign bits
 // (a.code_bits) must already be written (launch_select_and_exponents does).

@@ -741,6 +741,7 @@ hipError_t launch_zoom_t(const ZoomArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_zoom(const ZoomArgs& a, hipStream_t stream, bool prep) {
+  if (a.grid_len > 0) return launch_zoom_folded(a, stream);
   int32_t* exps = a.precision == 1 ? a.col_exp : nullptr;
   if (prep && (exps || a.code_bits)) {
     hipLaunchKernelGGL(pulse_prep, dim3(static_cast<unsigned>(a.n_pulses)), dim3(256), 0, stream,
