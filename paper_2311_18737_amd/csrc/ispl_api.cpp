@@ -102,10 +102,6 @@ constexpr int kMaxWavesPerBlock = ISPL_MAX_WAVES_PER_BLOCK;
 static_assert(kMaxWavesPerBlock <= ispl::MAX_WAVES_PER_BLOCK, "at most 16 waves per block");
 constexpr int64_t kMaxPartialBytes = int64_t{1} << 30;
 
-// Fewest pulses that fold: the expansion costs each gate about as much as one
-// pulse's N-point transform, and a launch.
-constexpr int kMinFoldPulses = 3;
-
 struct Plan {
   int sub_len;    // M: points of one sub-transform (1024, or 16384 for L > 1024)
   int r;          // R = N / M sub-transforms (bin classes) per spectrum
@@ -202,7 +198,7 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force
       const int64_t iters = (steps + chunks * runs - 1) / (chunks * runs);
       const double step_us = std::max(1.6, 0.85 * static_cast<double>(resident * waves) / 4);
       const double us = rounds * (iters * step_us + 3.0) + chunks * (row / 2e6 + 0.1) +
-                        (len == c.fft_len && chunks > 1 ? 4.0 : 0.0);
+                        (chunks > 1 && (len == c.fft_len || is_long) ? 4.0 : 0.0);
       if (out->len == 0 || us < best) {
         *out = GridPlan{len, waves, static_cast<int>(chunks)};
         best = us;
@@ -210,6 +206,35 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force
     }
   }
   return best;
+}
+
+// Estimated time of the expansion (see launch_expand): rounds of eight bin
+// classes, a gate's rounds by several workgroups when there are few gates.
+double expand_us(const ispl_config& c, int len) {
+  const int ratio = c.fft_len / std::max<int>(len, ispl::SUB), half = c.fft_len / ispl::SUB / 2;
+  const int tasks = ratio == 1 ? 0 : half - half / ratio;
+  const int per_round = len == 2 * ispl::SUB ? 7 : 8;
+  const int rounds = std::max(1, (tasks + per_round - 1) / per_round);
+  const int blocks = std::max(1, std::min(rounds, kComputeUnits / c.n_gates));
+  const int64_t passes = (static_cast<int64_t>(c.n_gates) * blocks + kComputeUnits - 1) / kComputeUnits;
+  return 4.0 + passes * (6.0 + len / 1024.0 + ((rounds + blocks - 1) / blocks) * (5.0 + c.fft_len / 4300.0));
+}
+
+// Estimated time of the direct transform: rounds of its plan's workgroups, a fixed
+// cost and the pulses of a chunk each; a pulse takes longer the more waves share a CU,
+// a long code's the longer the code.  Folding by this rule instead of from three
+// pulses on: one gate of three pulses at N = 65536 24 us, folded 104; at N = 4096 9.7, 16.6.
+double direct_us(const ispl_config& c, int32_t n_pulses) {
+  const Plan pl = make_plan(c, n_pulses);
+  const bool is_long = pl.sub_len > ispl::SUB;
+  const int64_t per_cu = is_long ? 1 : kMaxWavesPerCu / pl.rw;
+  const int64_t rounds = (pl.blocks + kComputeUnits * per_cu - 1) / (kComputeUnits * per_cu);
+  const int64_t resident = std::min(per_cu, (pl.blocks + kComputeUnits - 1) / kComputeUnits);
+  const double pulse_us = is_long ? 3.2 + 0.4e-3 * c.code_len
+                                  : std::max(1.5, 0.235 * static_cast<double>(resident * pl.rw));
+  const int iters = (n_pulses + pl.chunks - 1) / pl.chunks;
+  return 2.0 + rounds * ((is_long ? 12.0 : 2.5 + 0.5 * pl.rw) + iters * pulse_us) +
+         (pl.chunks > 1 ? 4.0 + 2e-7 * pl.chunks * c.n_gates * c.fft_len * 4.0 : 0.0);
 }
 
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks = 0) {
@@ -221,22 +246,20 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks 
                               ? grid_split(c, c.fft_len, n_pulses, force_chunks, &whole)
                               : 0.0;
   if (len == c.fft_len) return whole;
-  const double fold_us = grid_split(c, len, n_pulses, force_chunks, &fold);
-  // the expansion: two workgroups per compute unit
-  const double expand_us = 9.0 + 6.0 * ((c.n_gates - 1) / (2 * kComputeUnits));
-  if (whole.len > 0) return fold_us + expand_us < whole_us ? fold : whole;
-  return n_pulses >= kMinFoldPulses ? fold : GridPlan{};
+  const double fold_us = grid_split(c, len, n_pulses, force_chunks, &fold) + expand_us(c, len);
+  if (whole.len > 0) return fold_us < whole_us ? fold : whole;
+  return fold_us < direct_us(c, n_pulses) ? fold : GridPlan{};
 }
 
 // Scratch of a context whose calls run on a grid (0: they never do): the chunk
 // partials of every gate when they fit, else of as many gates as do (any chunk
-// count of a plan fits for one gate).
+// count of a plan fits for one gate, and a long grid's sums).
 int64_t grid_scratch_bytes(const ispl_config& c) {
   const int64_t len = grid_length(c);
   if (len == 0) return 0;
   const int64_t most = c.fft_len <= 2 * ispl::SUB ? c.fft_len : len;  // longest of its grids
   const int64_t all = 4 * most * c.n_gates;
-  return std::min(kGridBytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), kMaxChunks * 4 * most}));
+  return std::min(kGridBytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), (kMaxChunks + 1) * 4 * most}));
 }
 
 ispl_status validate_config(const ispl_config* c) {
@@ -721,8 +744,10 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     a.grid_len = gp.len;
     a.grid_chunks = gp.chunks;
     a.grid_waves = gp.waves;
+    // (a long grid's chunk partials are summed behind them)
+    const int64_t sets = gp.chunks + (gp.len > 2 * ispl::SUB && gp.chunks > 1 ? 1 : 0);
     a.grid_rows = static_cast<int32_t>(
-        std::min<int64_t>(c.n_gates, ctx->grid_bytes / (int64_t{4} * gp.len * gp.chunks)));
+        std::min<int64_t>(c.n_gates, ctx->grid_bytes / (int64_t{4} * gp.len * sets)));
     if (static_cast<int64_t>(n_pulses) * c.n_gates >= kMinBitsPulseGates) {
       a.grid_bits = ctx->grid_bits;
       a.grid_binary = ctx->grid_binary;

@@ -880,10 +880,11 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   float2* xw = xs + wave * XWAVE;
   double* xd = reinterpret_cast<double*>(xw);
 
-  const int slot = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
+  const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
+  const int slot = bid / a.blocks, share = bid % a.blocks;  // of the gate's rounds of classes
   const int g = gate_of(a, slot);
   if (g < 0) return;
-  float* const row = a.grid + static_cast<int64_t>(slot) * M;
+  const float* const row = a.grid + static_cast<int64_t>(slot) * M;
   const int64_t cs = static_cast<int64_t>(a.rows) * M;
   const float scale = 1.f / static_cast<float>(M);
 
@@ -910,8 +911,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   double mean;
   float2* qs;  // (q[n], q[-n]), n < M / 2, and one zero more
   if constexpr (LONG) {
-    // ---- chunk sums in ascending order (left in chunk 0's row), two times SG
-    // complex points per thread, and the first pass of the inverse transform:
+    // ---- the grid (its chunk sums are formed by then), two times SG complex points per thread, and the first pass of the inverse transform:
     // SG-point DFTs over points lg + 1024 j
     complex64d z[2][SG];
     double part = 0.0;
@@ -919,14 +919,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int j = 0; j < SG; ++j) {
-        float2* at = reinterpret_cast<float2*>(row) + tid + NT * t + SUB * j;
-        float2 s = *at;
-        for (int c = 1; c < a.chunks; ++c) {
-          const float2 q = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(at) + c * cs);
-          s.x += q.x;
-          s.y += q.y;
-        }
-        if (a.chunks > 1) *at = s;
+        const float2 s = reinterpret_cast<const float2*>(row)[tid + NT * t + SUB * j];
         z[t][j] = complex64d{s.x, s.y};
         part += static_cast<double>(s.x) + static_cast<double>(s.y);
       }
@@ -1039,7 +1032,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   const bool ok = expandable(mean);
   const float* grid = LONG ? row : M < SUB ? aux + UP : aux;
   const bool one_round = n_tasks <= PER_ROUND;
-  for (int z0 = 0; z0 == 0 || z0 < n_tasks; z0 += PER_ROUND) {
+  for (int z0 = PER_ROUND * share; z0 == 0 || z0 < n_tasks; z0 += PER_ROUND * a.blocks) {
     const int n_cls = min(PER_ROUND, n_tasks - z0);  // 0: every bin is on the grid
     const int task = wave - FIRST;
     const bool mine = task >= 0 && task < n_cls;
@@ -1120,9 +1113,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
         }
       }
     }
-    if (z0 + PER_ROUND < n_tasks) __syncthreads();
+    if (z0 + PER_ROUND * a.blocks < n_tasks) __syncthreads();
   }
-  if (!ok) direct_row<ST>(a, g, xs, dft16_consts(), tid);
+  if (!ok && share == 0) direct_row<ST>(a, g, xs, dft16_consts(), tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1293,8 +1286,14 @@ hipError_t launch_grid(const FoldArgs& a, hipStream_t s) {
 }
 
 template <int ST>
-hipError_t launch_expand(const FoldArgs& a, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(a.rows)), block(64 * EXP_WAVES);
+hipError_t launch_expand(FoldArgs a, hipStream_t s) {
+  // with fewer gates than compute units a gate's rounds of classes go to several
+  // workgroups, each forming the lags (N = 65536, one gate: 93 us by one)
+  const int ratio = a.n_fft / std::max(a.grid_len, SUB), half = a.n_fft / SUB / 2;
+  const int tasks = ratio == 1 ? 0 : half - half / ratio;
+  const int per_round = a.grid_len == 2 * SUB ? EXP_WAVES - 1 : EXP_WAVES;
+  a.blocks = std::max(1, std::min((tasks + per_round - 1) / per_round, 256 / a.rows));
+  const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.blocks)), block(64 * EXP_WAVES);
   switch (a.grid_len / (2 * SUB)) {
     case 0: hipLaunchKernelGGL((expand_grid<ST, 0>), grid, block, 0, s, a); break;
     case 1: hipLaunchKernelGGL((expand_grid<ST, 1>), grid, block, 0, s, a); break;
@@ -1370,8 +1369,17 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
     a.slot0 = s0;
     a.rows = std::min(f.n_gates - s0, f.grid_rows);
     e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+    FoldArgs x = a;
+    if (e == hipSuccess && a.grid_len > 2 * SUB && a.chunks > 1) {
+      // a long grid's chunk partials by a launch of their own, behind them (the expansion's
+      // workgroups have too few threads for their latency: 80 pulses of one gate, 60 us more)
+      const int64_t elems = static_cast<int64_t>(a.rows) * a.grid_len;
+      x.grid = a.grid + a.chunks * elems;
+      x.chunks = 1;
+      e = launch_reduce_chunks(a.grid, x.grid, elems, a.chunks, 0, a.grid_len, nullptr, nullptr, s);
+    }
     if (e == hipSuccess)
-      e = f.sample_type == 1 ? launch_expand<1>(a, s) : launch_expand<0>(a, s);
+      e = f.sample_type == 1 ? launch_expand<1>(x, s) : launch_expand<0>(x, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

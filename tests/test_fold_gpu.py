@@ -195,3 +195,35 @@ def test_long_folded_integration_matches_oracle(ispl, case):
 @pytest.mark.parametrize("L,N", [(1500, 16384), (7000, 32768)])
 def test_long_powers_beyond_fp32_and_nan(ispl, L, N):
     test_powers_beyond_fp32_and_nan(ispl, L, N)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # few gates: an expansion's rounds of classes by several workgroups, each power beyond FP32
+    # recomputed by one of them; several chunks of a long grid summed behind them
+    (65536, 30, 1, 40, "c64", True, "phase"),
+    (65536, 1000, 2, 200, "ci16", True, "bpsk"),
+    (32768, 700, 3, 90, "c64", True, "bpsk"),
+    (65536, 3000, 1, 90, "c64", True, "bpsk"),
+    (65536, 8000, 2, 60, "ci16", False, "phase"),
+], ids=lambda t: "N{}_L{}_G{}_P{}_{}_{}_{}".format(*t))
+def test_few_gates_match_oracle(ispl, case):
+    test_folded_integration_matches_oracle(ispl, case)
+
+
+@pytest.mark.gpu
+def test_direct_and_folded_calls_of_one_context_agree(ispl):
+    """Few pulses take the direct transform, many the grid: the same spectra."""
+    L, N, G, P = 200, 16384, 64, 120
+    stride = (G - 1) * 9 + L
+    samples, tx = random_inputs(P, stride, L, code_kind="bpsk", seed=12)
+    ctx = ispl.Context(code_len=L, fft_len=N, n_gates=G, gate_step=9, pulse_stride=stride, max_pulses=P)
+    xs, xt = torch.from_numpy(samples).to(DEV), torch.from_numpy(tx).to(DEV)
+    whole = ctx.integrate_spectra(xs, xt)
+    parts = torch.zeros_like(whole)
+    for p in range(0, P, 2):
+        ctx.integrate_spectra(xs[p:p + 2], xt[p:p + 2], out=parts, accumulate=True)
+    torch.cuda.synchronize()
+    ctx.close()
+    scale = torch.maximum(whole, whole.mean(dim=1, keepdim=True))
+    assert float(((whole - parts).abs() / scale).max()) <= 1e-5
