@@ -103,9 +103,10 @@ ispl_status ispl_create(const ispl_config* cfg, ispl_ctx** out);
  *   n_pulses  0 <= n_pulses <= max_pulses.  With 0 pulses the sum is empty:
  *             spectra is zeroed (accumulate = 0) or left as is (accumulate = 1).
  * Arithmetic: decode, transform, power and accumulation in FP32.  Codes of at
- * most 1024 samples are summed over the pulses on a grid of 2^m >= 2 L - 1
- * frequencies, from which the N bins follow exactly (|X|^2 of L samples has 2 L - 1
- * coefficients); S >= 0 as in the direct form.
+ * most 8192 samples may be summed over the pulses on a grid of 2^m >= 2 L - 1
+ * frequencies (where that is estimated to be faster), from which the N bins follow
+ * exactly (|X|^2 of L samples has 2 L - 1 coefficients; this step in double precision);
+ * S >= 0 as in the direct form.
  */
 ispl_status ispl_integrate_spectra(ispl_ctx* ctx, const void* samples,
                                    const float* tx_code, int32_t tx_per_pulse,
