@@ -259,7 +259,7 @@ void ispl_zoom_destroy(ispl_zoom* zoom);
 typedef struct ispl_net ispl_net;
 
 typedef enum {
-  ISPL_NET_FP32 = 0,  /* vector-ALU forward, FP32 weights and activations */
+  ISPL_NET_FP32 = 0,  /* FP32 weights, activations and products */
   ISPL_NET_BF16 = 1   /* matrix-core forward, BF16 weights and activations, FP32 accumulation */
 } ispl_net_precision;
 

@@ -221,8 +221,8 @@ struct NetWork {  // device buffers of a training batch (FP32)
   float* params;  // [NET_PARAMS]
   float* a1;      // [B][32][T] activations after layers 1..3
   float* a2;
-  float* a3;
-  float* logits;  // [B][T]
+  float* a3;      // the layer 1 gradient after the loss
+  float* logits;  // [B][T] (the loss needs neither this nor dz4 in memory)
   float* dz4;     // [B][T]
   float* dzA;     // [B][32][T] gradient ping-pong
   float* dzB;

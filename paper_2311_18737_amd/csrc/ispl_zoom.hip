@@ -1,4 +1,5 @@
-// Zoom DFT on the matrix cores (gfx950 MFMA): a window of K bins of the
+// Zoom DFT on the matrix cores (gfx950 MFMA), for codes of more than 1024 samples and
+// those too long for a grid of 2 L - 1 <= N points (the others: ispl_grid.hip): a window of K bins of the
 // N-point spectrum of every gate, S[g][j] = sum_p |Z_{p,g}[j]|^2 with
 //
 //   Z_{p,g}[j] = sum_{n < L} y'_{p,g}[n] W_N^{j n},
