@@ -35,8 +35,9 @@ struct ispl_ctx {
   int64_t grid_bytes;
   const float* deferred; // where the last call's chunk partials lie that its caller sums
   double* twiddle64;    // the twiddle table in double
-  uint32_t* grid_bits;  // codes as sign bits [max_pulses][64] and flags [max_pulses]
+  uint32_t* grid_bits;  // codes as sign bits, grid_bits_rows rows, and their flags
   int32_t* grid_binary;
+  int32_t grid_bits_rows;
 };
 
 namespace {
@@ -158,6 +159,20 @@ int grid_length(const ispl_config& c) {
 // Fewest pulse-gate transforms whose launch first packs the codes into sign
 // bits (a pass of its own over the codes).
 constexpr int64_t kMinBitsPulseGates = 32768;
+
+// Words of one code row's sign bits for the grid pass, and the rows there is room for: every
+// pulse's up to 64 MiB (258000 codes of L <= 1024, 16300 longer ones).  A call with more codes
+// reads them as complex numbers, so a large max_pulses costs no memory.
+int grid_bits_words(const ispl_config& c) { return c.code_len > ispl::SUB ? ispl::SUB : 64; }
+int32_t grid_bits_rows(const ispl_config& c) {
+  const int64_t row = int64_t{4} * (grid_bits_words(c) + 1);  // with its flag
+  return static_cast<int32_t>(std::min<int64_t>(c.max_pulses, (int64_t{64} << 20) / row));
+}
+// Whether a call packs its codes into `rows` rows of sign bits.
+bool packs_bits(const ispl_config& c, int32_t tx_per_pulse, int32_t n_pulses, int32_t rows) {
+  return (tx_per_pulse ? n_pulses : 1) <= rows &&
+         static_cast<int64_t>(n_pulses) * c.n_gates >= kMinBitsPulseGates;
+}
 
 struct GridPlan {
   int len;     // 0: the direct transform
@@ -414,8 +429,9 @@ struct ispl_zoom {
   int32_t* code_binary;   // [max_pulses]
   float* grid;            // scratch of calls from the summed grid (NULL: none of this zoom's are)
   int64_t grid_bytes;
-  uint32_t* grid_bits;    // [max_pulses][64]
-  int32_t* grid_binary;   // [max_pulses]
+  uint32_t* grid_bits;    // [grid_bits_rows][64], and the rows' flags behind them
+  int32_t* grid_binary;
+  int32_t grid_bits_rows;
 };
 
 namespace {
@@ -458,7 +474,7 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_pulses) {
 
 static void zoom_free(ispl_zoom* z) {
   void* bufs[] = {z->a_hi,      z->a_lo, z->partial,   z->col_exp,    z->code_bits,
-                  z->code_binary, z->grid, z->grid_bits, z->grid_binary};
+                  z->code_binary, z->grid, z->grid_bits};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
 }
@@ -563,10 +579,11 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
       e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle64), tw64.size() * sizeof(double));
     if (e == hipSuccess)
       e = hipMemcpy(ctx->twiddle64, tw64.data(), tw64.size() * sizeof(double), hipMemcpyHostToDevice);
-    const size_t words = cfg->code_len > ispl::SUB ? ispl::SUB : 64;
+    const size_t words = grid_bits_words(*cfg);
+    ctx->grid_bits_rows = grid_bits_rows(*cfg);
     if (e == hipSuccess)  // the sign bits and their flags in one block
       e = hipMalloc(reinterpret_cast<void**>(&ctx->grid_bits),
-                    static_cast<size_t>(cfg->max_pulses) * (words + 1) * sizeof(uint32_t));
+                    static_cast<size_t>(ctx->grid_bits_rows) * (words + 1) * sizeof(uint32_t));
     if (e != hipSuccess) {
       if (ctx->grid) (void)hipFree(ctx->grid);
       if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
@@ -576,7 +593,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
       return fail(ISPL_ERR_OUT_OF_MEMORY, "grid scratch: %s", hipGetErrorString(e));
     }
     ctx->grid_binary =
-        reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(cfg->max_pulses) * words);
+        reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(ctx->grid_bits_rows) * words);
   }
   if (cfg->code_len > 2 * ispl::SUB) {  // the long-code kernel reads binary codes as sign bits
     const size_t rows = static_cast<size_t>(cfg->max_pulses);
@@ -748,7 +765,7 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     const int64_t sets = gp.chunks + (gp.len > 2 * ispl::SUB && gp.chunks > 1 ? 1 : 0);
     a.grid_rows = static_cast<int32_t>(
         std::min<int64_t>(c.n_gates, ctx->grid_bytes / (int64_t{4} * gp.len * sets)));
-    if (static_cast<int64_t>(n_pulses) * c.n_gates >= kMinBitsPulseGates) {
+    if (packs_bits(c, tx_per_pulse, n_pulses, ctx->grid_bits_rows)) {
       a.grid_bits = ctx->grid_bits;
       a.grid_binary = ctx->grid_binary;
     }
@@ -918,9 +935,11 @@ ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
   if (e == hipSuccess && ctx->twiddle64 && zoom_grid_plan(c, c.max_pulses).len > 0) {
     z->grid_bytes = grid_scratch_bytes(c);
     e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes));
-    if (e == hipSuccess) e = hipMalloc(&z->grid_bits, size_t{256} * static_cast<size_t>(c.max_pulses));
+    z->grid_bits_rows = grid_bits_rows(c);
+    const size_t words = static_cast<size_t>(z->grid_bits_rows) * grid_bits_words(c);
     if (e == hipSuccess)
-      e = hipMalloc(&z->grid_binary, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
+      e = hipMalloc(&z->grid_bits, sizeof(uint32_t) * (words + static_cast<size_t>(z->grid_bits_rows)));
+    z->grid_binary = reinterpret_cast<int32_t*>(z->grid_bits + words);
   }
   if (e != hipSuccess) {
     zoom_free(z);
@@ -1034,7 +1053,7 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
     a.grid_waves = gp.waves;
     a.grid_rows = static_cast<int32_t>(
         std::min<int64_t>(c.n_gates, z->grid_bytes / (int64_t{4} * gp.len * gp.chunks)));
-    if (static_cast<int64_t>(n_pulses) * c.n_gates >= kMinBitsPulseGates) {
+    if (packs_bits(c, tx_per_pulse, n_pulses, z->grid_bits_rows)) {
       a.grid_bits = z->grid_bits;
       a.grid_binary = z->grid_binary;
     }

@@ -233,7 +233,7 @@ pack_grid_bits(const float2* __restrict__ tx, int32_t rows, int32_t code_len,
     ok = ok && (lane + 64 * j >= code_len || ((x == 1.f || x == -1.f) && y == 0.f));
     word |= (x < 0.f ? 1u : 0u) << (31 - j);
   }
-  bits[64 * row + lane] = word;
+  bits[64 * static_cast<int64_t>(row) + lane] = word;
   const bool all = __all(ok);
   if (lane == 0) binary[row] = all ? 1 : 0;
 }
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
 #pragma unroll
     for (int t = 0; t < Q; ++t) {
       const int p = min(i * Q + t, a.n_pulses - 1);
-      bits[t] = a.code_bits[(a.tx_per_pulse ? 64 * p : 0) + lane];
+      bits[t] = a.code_bits[(a.tx_per_pulse ? 64 * static_cast<int64_t>(p) : 0) + lane];
     }
   };
   auto transform = [&](float2 (&v)[16]) {
