@@ -206,7 +206,7 @@ typedef struct ispl_zoom ispl_zoom; /* opaque; must not outlive its context */
  * 128, at most fft_len) of ctx's geometry: two halves of 6 * n_bins *
  * round_up(code_len, 64) bytes each; ISPL_ERR_UNSUPPORTED above 512 MiB per
  * half.  Also holds the per-call scratch: FP16 exponents and the sign bits of
- * +-1 codes for max_pulses pulses, and up to 63 MiB for the grid. */
+ * +-1 codes for max_pulses pulses, and up to 128 MiB for the grid. */
 ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
                              ispl_zoom** out);
 

@@ -18,6 +18,7 @@
 #include <string>
 #include <vector>
 
+#include "ispl_gain.h"
 #include "ispl_internal.h"
 
 struct ispl_ctx {
@@ -31,10 +32,12 @@ struct ispl_ctx {
   // codes of L > 2 SUB as sign bits (long-code kernel), max_pulses rows
   uint16_t* code_bits;  // [max_pulses][CODE_BITS_WORDS]
   int32_t* code_binary; // [max_pulses]
-  float* grid;          // folded integration: scratch of grid_bytes (nullptr: never folds)
+  double* grid;         // folded integration: scratch of grid_bytes (nullptr: never folds)
   int64_t grid_bytes;
   const float* deferred; // where the last call's chunk partials lie that its caller sums
   double* twiddle64;    // the twiddle table in double
+  double* grid_gain;    // gains of the grid's points, behind it
+  bool gain_missing;    // (static scratch: written by the call)
   uint32_t* grid_bits;  // codes as sign bits, grid_bits_rows rows, and their flags
   int32_t* grid_binary;
   int32_t grid_bits_rows;
@@ -180,8 +183,12 @@ struct GridPlan {
   int chunks;  // pulse chunks, each a workgroup per gate
 };
 
-constexpr int64_t kGridBytes = int64_t{63} << 20;       // most grid scratch
-static_assert(kGridBytes + ispl::NOALLOC_TWIDDLE64_BYTES <= ispl::NOALLOC_PARTIAL_BYTES,
+// Most grid scratch of a context (2000 gates of L = 2000 in one run: in two 5.6 ms, 5.1 in one),
+// and of the static array.
+constexpr int64_t kGridBytes = int64_t{128} << 20;
+constexpr int64_t kNoallocGridBytes = int64_t{62} << 20;
+static_assert(kNoallocGridBytes + ispl::NOALLOC_TWIDDLE64_BYTES + ispl::NOALLOC_GAIN_BYTES <=
+                  ispl::NOALLOC_PARTIAL_BYTES,
               "the entry point that allocates nothing holds the grid scratch");
 constexpr int64_t kGridChunkBytes = int64_t{32} << 20;  // most of it for several chunks
 
@@ -194,7 +201,8 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force
   const int classes = len > ispl::SUB ? len / ispl::SUB : 1;
   const int per_step = len < ispl::SUB ? ispl::SUB / len : 1;  // pulses a wave takes at once
   const int64_t steps = (n_pulses + per_step - 1) / per_step;
-  const int64_t row = int64_t{4} * len * c.n_gates;
+  // FP32 partials on a grid of the N bins, doubles on a shorter one
+  const int64_t row = int64_t{len == c.fft_len ? 4 : 8} * len * c.n_gates;
   const bool is_long = classes > 2;  // one wave per bin class, one pulse at a time
   double best = 0.0;
   out->len = 0;
@@ -252,6 +260,14 @@ double direct_us(const ispl_config& c, int32_t n_pulses) {
          (pl.chunks > 1 ? 4.0 + 2e-7 * pl.chunks * c.n_gates * c.fft_len * 4.0 : 0.0);
 }
 
+// Gates whose sums are held at a time when there is room for `most`: as many runs of them
+// as that makes, all of one length (a short last run takes as long as a full one).
+int32_t grid_run(int32_t n_gates, int64_t most) {
+  if (most >= n_gates) return n_gates;
+  const int64_t runs = (n_gates + most - 1) / most;
+  return static_cast<int32_t>((n_gates + runs - 1) / runs);
+}
+
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks = 0) {
   GridPlan fold{}, whole{};
   const int len = grid_length(c);
@@ -269,12 +285,13 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks 
 // Scratch of a context whose calls run on a grid (0: they never do): the chunk
 // partials of every gate when they fit, else of as many gates as do (any chunk
 // count of a plan fits for one gate, and a long grid's sums).
-int64_t grid_scratch_bytes(const ispl_config& c) {
+int64_t grid_scratch_bytes(const ispl_config& c, int64_t most_bytes = kGridBytes) {
   const int64_t len = grid_length(c);
   if (len == 0) return 0;
-  const int64_t most = c.fft_len <= 2 * ispl::SUB ? c.fft_len : len;  // longest of its grids
-  const int64_t all = 4 * most * c.n_gates;
-  return std::min(kGridBytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), (kMaxChunks + 1) * 4 * most}));
+  // the larger row of its grids
+  const int64_t row = std::max<int64_t>(8 * len, c.fft_len <= 2 * ispl::SUB ? 4 * c.fft_len : 0);
+  const int64_t all = row * c.n_gates;
+  return std::min(most_bytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), (kMaxChunks + 1) * row}));
 }
 
 ispl_status validate_config(const ispl_config* c) {
@@ -427,7 +444,7 @@ struct ispl_zoom {
   int32_t* col_exp;  // [max_pulses] (FP16 only)
   uint32_t* code_bits;    // [max_pulses][code_pad / 32] sign bits of +-1 codes
   int32_t* code_binary;   // [max_pulses]
-  float* grid;            // scratch of calls from the summed grid (NULL: none of this zoom's are)
+  double* grid;           // scratch of calls from the summed grid (NULL: none of this zoom's are)
   int64_t grid_bytes;
   uint32_t* grid_bits;    // [grid_bits_rows][64], and the rows' flags behind them
   int32_t* grid_binary;
@@ -576,9 +593,18 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
   if (ctx->grid_bytes > 0) {
     e = hipMalloc(reinterpret_cast<void**>(&ctx->grid), static_cast<size_t>(ctx->grid_bytes));
     if (e == hipSuccess)
-      e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle64), tw64.size() * sizeof(double));
+      e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle64),
+                    (tw64.size() + grid_length(*cfg)) * sizeof(double));
     if (e == hipSuccess)
       e = hipMemcpy(ctx->twiddle64, tw64.data(), tw64.size() * sizeof(double), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+      std::vector<double> gain(grid_length(*cfg));
+      for (size_t k = 0; k < gain.size(); ++k)
+        gain[k] = ispl::grid_gain(tw64.data(), cfg->fft_len, static_cast<int32_t>(gain.size()),
+                                  static_cast<int32_t>(k));
+      ctx->grid_gain = ctx->twiddle64 + tw64.size();
+      e = hipMemcpy(ctx->grid_gain, gain.data(), gain.size() * sizeof(double), hipMemcpyHostToDevice);
+    }
     const size_t words = grid_bits_words(*cfg);
     ctx->grid_bits_rows = grid_bits_rows(*cfg);
     if (e == hipSuccess)  // the sign bits and their flags in one block
@@ -758,13 +784,14 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     a.grid_defer = deferred_chunks ? 1 : 0;
     a.grid = ctx->grid;
     a.twiddle64 = ctx->twiddle64;
+    a.grid_gain = ctx->grid_gain;
+    a.grid_gain_missing = ctx->gain_missing ? 1 : 0;
     a.grid_len = gp.len;
     a.grid_chunks = gp.chunks;
     a.grid_waves = gp.waves;
     // (a long grid's chunk partials are summed behind them)
     const int64_t sets = gp.chunks + (gp.len > 2 * ispl::SUB && gp.chunks > 1 ? 1 : 0);
-    a.grid_rows = static_cast<int32_t>(
-        std::min<int64_t>(c.n_gates, ctx->grid_bytes / (int64_t{4} * gp.len * sets)));
+    a.grid_rows = grid_run(c.n_gates, ctx->grid_bytes / (int64_t{8} * gp.len * sets));
     if (packs_bits(c, tx_per_pulse, n_pulses, ctx->grid_bits_rows)) {
       a.grid_bits = ctx->grid_bits;
       a.grid_binary = ctx->grid_binary;
@@ -773,7 +800,7 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     if (e != hipSuccess) return hip_fail(e, "folded launch");
     if (deferred_chunks) {
       *deferred_chunks = gp.chunks;
-      ctx->deferred = ctx->grid;
+      ctx->deferred = reinterpret_cast<const float*>(ctx->grid);
     }
     return ok();
   }
@@ -878,11 +905,14 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
   tmp.partial = pl.chunks > 1 ? reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES)
                               : nullptr;
   tmp.min_chunk_pulses = kMinChunkPulses;
-  tmp.grid_bytes = grid_scratch_bytes(*cfg);
+  tmp.grid_bytes = grid_scratch_bytes(*cfg, kNoallocGridBytes);
   if (tmp.grid_bytes > 0) {
     tmp.twiddle64 = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES);
-    tmp.grid = reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
-                                        ispl::NOALLOC_TWIDDLE64_BYTES);
+    tmp.grid_gain = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
+                                              ispl::NOALLOC_TWIDDLE64_BYTES);
+    tmp.gain_missing = true;
+    tmp.grid = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
+                                         ispl::NOALLOC_TWIDDLE64_BYTES + ispl::NOALLOC_GAIN_BYTES);
   }
   if (n_pulses > 0) {
     e = ispl::launch_build_twiddles(tmp.twiddle, cfg->fft_len, static_cast<hipStream_t>(stream));
@@ -1048,11 +1078,11 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
     a.chunks = 1;
     a.grid = z->grid;
     a.twiddle64 = z->ctx->twiddle64;
+    a.grid_gain = z->ctx->grid_gain;
     a.grid_len = gp.len;
     a.grid_chunks = gp.chunks;
     a.grid_waves = gp.waves;
-    a.grid_rows = static_cast<int32_t>(
-        std::min<int64_t>(c.n_gates, z->grid_bytes / (int64_t{4} * gp.len * gp.chunks)));
+    a.grid_rows = grid_run(c.n_gates, z->grid_bytes / (int64_t{8} * gp.len * gp.chunks));
     if (packs_bits(c, tx_per_pulse, n_pulses, z->grid_bits_rows)) {
       a.grid_bits = z->grid_bits;
       a.grid_binary = z->grid_binary;

@@ -359,6 +359,46 @@ struct GridTwiddlesLds {
   GeoTwiddles p2;
   const float4* t3;
 };
+// Pass 2's factors of one lane's column in LDS: p2[0] = (G, G^2), p2[16 (1 + k1)] =
+// (H_k1, H_k1^2); 20 registers less, for kernels whose sums take 32.
+struct GeoLds {
+  const float4* p;
+};
+__device__ __forceinline__ void dft16_geo(float2 (&v)[16], const GeoLds& w) {
+  {
+    const float4 g = w.p[0];
+#pragma unroll
+    for (int j1 = 0; j1 < 4; ++j1)
+      dft4_geo(v[j1], v[j1 + 4], v[j1 + 8], v[j1 + 12], make_float2(g.x, g.y), make_float2(g.z, g.w));
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < 4; ++k1) {
+    const float4 h = w.p[16 * (1 + k1)];
+    dft4_geo(v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3], make_float2(h.x, h.y),
+             make_float2(h.z, h.w));
+  }
+  float2 t[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) t[i] = v[4 * (i & 3) + (i >> 2)];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = t[i];
+}
+// Part t < 5 of the progression P = W_N^e as GeoLds reads it.
+__device__ __forceinline__ float4 geo_part(const float2* __restrict__ tw, int n_fft, int e, int t) {
+  const int nmask = n_fft - 1, i = t == 0 ? 4 * e : e + (t - 1) * (n_fft >> 4);
+  const float2 u = tw[i & nmask], u2 = tw[(2 * i) & nmask];
+  return make_float4(u.x, u.y, u2.x, u2.y);
+}
+// Both in LDS.
+struct GridTwiddlesLds2 {
+  GeoLds p2;
+  const float4* t3;
+};
+// Pass 2's in LDS, pass 3's T_kc in registers and squared for each transform.
+struct GridTwiddlesRows2 {
+  GeoLds p2;
+  float2 t3[4];
+};
 
 template <typename TW>
 inline constexpr bool kGeo = false;
@@ -372,20 +412,30 @@ template <>
 inline constexpr bool kGeo<GridTwiddlesRows> = true;
 template <>
 inline constexpr bool kGeo<GridTwiddlesRows1> = true;
+template <>
+inline constexpr bool kGeo<GridTwiddlesLds2> = true;
+template <>
+inline constexpr bool kGeo<GridTwiddlesRows2> = true;
 template <typename TW>
 inline constexpr bool kLds3 = false;
 template <>
 inline constexpr bool kLds3<GridTwiddlesLds> = true;
+template <>
+inline constexpr bool kLds3<GridTwiddlesLds2> = true;
 template <typename TW>
 inline constexpr bool kRowsLds = kLds3<TW>;
 template <>
 inline constexpr bool kRowsLds<GridTwiddlesRows> = true;
 template <>
 inline constexpr bool kRowsLds<GridTwiddlesRows1> = true;
+template <>
+inline constexpr bool kRowsLds<GridTwiddlesRows2> = true;
 template <typename TW>
 inline constexpr bool kSquare3 = false;
 template <>
 inline constexpr bool kSquare3<GridTwiddlesRows1> = true;
+template <>
+inline constexpr bool kSquare3<GridTwiddlesRows2> = true;
 
 // One wave's 1024-point transform and power accumulation.  On entry lane l
 // holds f[l + 64 j] in v[j]; xw is the wave's exchange buffer.  On exit
@@ -471,6 +521,16 @@ struct PowerSink {
   float (&acc)[16];
   __device__ __forceinline__ void operator()(int i, float2 c) const {
     acc[i] = fmaf(c.y, c.y, fmaf(c.x, c.x, acc[i]));
+  }
+};
+
+// The same in double: squares and sums of FP32 bins lose nothing to rounding or to the
+// range of FP32.
+struct PowerSink64 {
+  double (&acc)[16];
+  __device__ __forceinline__ void operator()(int i, float2 c) const {
+    const double x = c.x, y = c.y;
+    acc[i] = fma(y, y, fma(x, x, acc[i]));
   }
 };
 

@@ -11,12 +11,18 @@
 //   S[k] = r[0] + 2 Re sum_{0 < n < L} r[n] W_N^{k n}.
 //
 // At L = 1000, N = 16384 the pulse loop has 2 instead of 16 transforms of 1024
-// points per pulse and gate: 1000 pulses x 1000 gates (int16 samples) take 1.75 instead of
-// 11.49 ms.  The grid's mean is taken out before the inverse transform and r[0]
+// points per pulse and gate: 1000 pulses x 1000 gates (int16 samples) take 1.92 instead of
+// 11.45 ms.  The grid's mean is taken out before the inverse transform and r[0]
 // added back last, so rounding in the two transforms is relative to the
-// spectrum's fluctuation about its mean, not to the mean; the sums of a gate's
-// pulses are split over 8 or 16 waves, which halves their rounding (relative error against
-// FP64 1.8e-7 there, 6.1e-7 before).
+// spectrum's fluctuation about its mean, not to the mean.
+//
+// What is wrong at a strong grid point is spread over its neighbours by the expansion, as
+// 1 / (pi x distance): a direct transform's rounding stays at the line.  So the
+// powers are squared and summed in double (7 to 10 % of the pass; sums of 32 pulses in FP32
+// before that), and a point's sum is multiplied by the known gain of its FP32 twiddles
+// (ispl_gain.h).  Largest error over max(S, mean S) with a line at -10 dB per sample, L = 1000 /
+// 2000 / 4000: 7e-7 / 1.1e-6 / 1.7e-6 (FP32 sums 3.1e-6 / 7.5e-6 / 1.2e-5, double ones
+// without the gain 2.0e-6 / 5.7e-6 / 1.7e-5); without a line 1.0e-7 to 1.4e-7, direct 4e-7 to 6e-7.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -27,6 +33,7 @@
 
 #include "ispl_fft.h"
 #include "ispl_fft64.h"
+#include "ispl_gain.h"
 #include "ispl_internal.h"
 
 namespace ispl {
@@ -55,14 +62,12 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // ones (8 bytes) at 0.34, and conversions, shifts and anything reading a scalar
 // register at 0.22, a v_permlane swap at 0.12.  Hence pass 3's exchange between
 // lane rows goes through LDS (12 % fewer cycles than with swaps), the code
-// bits are brought up by additions, and pass 3's twiddles lie in LDS, which keeps
-// four waves per SIMD with the next pulse's samples in flight.
+// bits are brought up by additions, and pass 3's twiddles lie in LDS (beside double sums, which
+// take 32 registers, pass 2's too), which keeps four waves per SIMD with the next pulse's
+// samples in flight.
 
 // Pulses (or steps of several) that one FP32 sum takes before it is added to the
-// row in memory.  The rounding of a long sum grows with its length, and the
-// expansion spreads what a strong line leaves there over the bins around it: with 500
-// pulses in one sum the uneven batch's L = 2000 experiment had bins 3.6e-5
-// off, with 32 it is 5.7e-6.
+// row in memory, on a grid of all N bins (the rounding of a long sum grows with its length).
 constexpr int RUN_STEPS = 32;
 
 // `steps` cut into `n` runs, the first steps % n of them one longer (a 32-bit
@@ -211,6 +216,24 @@ __device__ __forceinline__ void dft16_w32(float2 (&v)[16], const Dft16Consts& k)
   for (int i = 0; i < 16; ++i) v[i] = t[i];
 }
 
+// Where chunk c of a gate's sums goes: the chunk's partial row by slot; on a grid of all N
+// bins (WHOLE, FP32) by gate, and with one chunk the gate's row of the result itself.
+template <bool WHOLE>
+__device__ __forceinline__ auto out_row(const FoldArgs& a, int g, int slot, int c) {
+  const int64_t row = static_cast<int64_t>(c) * a.rows + (WHOLE ? g : slot);
+  if constexpr (WHOLE)
+    return a.chunks == 1 ? a.out + static_cast<int64_t>(g) * a.grid_len : a.partial + row * a.grid_len;
+  else
+    return a.grid + row * a.grid_len;
+}
+
+// The gains of a grid's points (a context's are written on the host).
+__global__ void __launch_bounds__(256)
+build_gains(const double* __restrict__ tw64, int32_t n_fft, int32_t len, double* __restrict__ gain) {
+  const int k = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
+  if (k < len) gain[k] = grid_gain(tw64, n_fft, len, k);
+}
+
 // Code rows as sign bits: word lane of a row holds in bit 31 - j whether code
 // sample lane + 64 j is -1; binary[row] tells whether the whole row is
 // +-1 + 0i.  One wave per row, all its loads in flight at once.
@@ -240,8 +263,9 @@ pack_grid_bits(const float2* __restrict__ tx, int32_t rows, int32_t code_len,
 
 // LOGM: log2 of the grid; W: waves per workgroup.  The workgroup's waves take
 // W runs of pulses (LOGM = 11: W / 2 runs, each by one wave per bin class); with
-// C chunks the run count is C times that.
-template <int LOGM, int ST, int W>
+// C chunks the run count is C times that.  WHOLE: the grid is the N bins themselves, summed
+// in FP32 as the direct transform's are.
+template <int LOGM, int ST, int W, bool WHOLE>
 __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   constexpr int M = 1 << LOGM;
   constexpr int CLS = M > SUB ? M / SUB : 1;    // bin classes
@@ -251,10 +275,12 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   constexpr int RUNS = W / CLS;
   // samples per pulse fetched a step ahead (all that four waves per SIMD have registers for)
   constexpr int JP = CLS > 1 ? (ST == 0 ? 6 : 12) : JL;
+  using sum_t = std::conditional_t<WHOLE, float, double>;
   static_assert(CLS <= 2 && W % CLS == 0, "at most two bin classes");
   using IO = BufferSample<ST>;
   __shared__ float2 xs[W * XWAVE];
   __shared__ float4 t3s[CLS][4][64];  // pass-3 twiddles of each class
+  __shared__ float4 p2s[WHOLE ? 1 : CLS][5][16];  // and pass 2's (beside double sums)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -268,11 +294,14 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   // pass-2 column k1 of this lane (bins k1 + (M / 64) (kc + 16 kd)) and its
   // progressions W_M^{4 k1 m} (pass 2) and (W_M^{k1} W_64^{kc})^r (pass 3)
-  GridTwiddlesLds wt;
+  std::conditional_t<WHOLE, GridTwiddlesLds, GridTwiddlesLds2> wt;
   {
     const int step = a.n_fft >> LOGM, k1 = CLS > 1 ? cls + CLS * (lane & 15) : lane & (J - 1);
-    load_geo(wt.p2, tw, a.n_fft, 4 * step * k1);
+    if constexpr (WHOLE) load_geo(wt.p2, tw, a.n_fft, 4 * step * k1);
     if (wave < CLS) {
+      if constexpr (!WHOLE)
+        for (int t = lane >> 4; t < 5; t += 4)
+          p2s[wave][t][lane & 15] = geo_part(tw, a.n_fft, 4 * step * k1, t);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int e = step * k1 + (a.n_fft >> 6) * (4 * (lane >> 4) + t);
@@ -281,12 +310,13 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
       }
     }
     wt.t3 = &t3s[cls][0][lane];
+    if constexpr (!WHOLE) wt.p2.p = &p2s[cls][0][lane & 15];
     __syncthreads();
   }
   const Dft16Consts dk = dft16_consts();
-  float acc[16];
+  sum_t acc[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int i = 0; i < 16; ++i) acc[i] = 0;
 
   const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
   const RunSplit runs((a.n_pulses + Q - 1) / Q, a.chunks * RUNS);
@@ -324,7 +354,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
       dft16(v, dk);
     else
       dft16_w32(v, dk);
-    wave_passes_23(v, xw, wt, dk, lane, NoHook{}, PowerSink{acc});
+    wave_passes_23(v, xw, wt, dk, lane, NoHook{},
+                   std::conditional_t<WHOLE, PowerSink, PowerSink64>{acc});
   };
 
   // codes of this wave's pulses all +-1: conj(c) x is a sign flip
@@ -339,17 +370,15 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
       binary = a.code_binary[0] != 0;
     }
   }
-  // the chunk's partial row; on a grid of all N bins by gate, and with one
-  // chunk the gate's row of the result itself
-  const bool whole = a.grid_len == a.n_fft && !a.partials, last = whole && a.chunks == 1;
-  float* out = last ? a.out + static_cast<int64_t>(g) * M
-                    : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
+  sum_t* out = out_row<WHOLE>(a, g, slot, c);
+  const bool last = WHOLE && a.chunks == 1;
   bool add = last && a.accumulate;
   // at most RUN_STEPS steps go into one FP32 sum (the same number of sums for
-  // every run, which meet at its end)
-  const int n_sums = max(1, (runs.longest() + RUN_STEPS - 1) / RUN_STEPS);
+  // every run, which meet at its end), all into one double
+  const int per_sum = WHOLE ? RUN_STEPS : max(1, runs.longest());
+  const int n_sums = WHOLE ? max(1, (runs.longest() + RUN_STEPS - 1) / RUN_STEPS) : 1;
   for (int u = 0; u < n_sums; ++u) {
-  const int b0 = min(i0 + u * RUN_STEPS, i1), b1 = min(b0 + RUN_STEPS, i1);
+  const int b0 = min(i0 + u * per_sum, i1), b1 = min(b0 + per_sum, i1);
   if (binary) {
     if (b0 < b1) {
       fetch(b0, 0, JP);
@@ -409,7 +438,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   // (addresses formed here each time: kept across the pulse loop they would
   // take its registers)
   const int ft = opaque(tid), fl = ft & 63;
-  float* st = reinterpret_cast<float*>(xs) + (ft >> 6) * (2 * XWAVE);
+  constexpr int REGION = XWAVE * sizeof(float2) / sizeof(sum_t);
+  sum_t* st = reinterpret_cast<sum_t*>(xs) + (ft >> 6) * REGION;
   {
     const int ka = fl & 15, row = fl >> 4;
     const int base = CLS > 1 ? ka : (ka / J) * M + (ka & (J - 1));
@@ -418,16 +448,17 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
 #pragma unroll
       for (int kd = 0; kd < 4; ++kd) {
         st[base + J * (4 * row + t + 16 * kd)] = acc[4 * t + kd];
-        acc[4 * t + kd] = 0.f;
+        acc[4 * t + kd] = 0;
       }
   }
   __syncthreads();
-  const float* all_st = reinterpret_cast<const float*>(xs);
+  const sum_t* all_st = reinterpret_cast<const sum_t*>(xs);
   for (int e = ft; e < M; e += 64 * W) {
-    float sum = 0.f;
-#pragma unroll
+    constexpr int kSumUnroll = RUNS * Q > 64 ? 4 : RUNS;
+    sum_t sum = 0;
+#pragma unroll kSumUnroll
     for (int r = 0; r < RUNS; ++r) {
-      const float* wst = all_st + (CLS > 1 ? r * CLS + (e & (CLS - 1)) : r) * (2 * XWAVE);
+      const sum_t* wst = all_st + (CLS > 1 ? r * CLS + (e & (CLS - 1)) : r) * REGION;
       if constexpr (CLS > 1) {
         sum += wst[e / CLS];
       } else {
@@ -435,6 +466,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
         for (int t = 0; t < Q; ++t) sum += wst[t * M + e];
       }
     }
+    if constexpr (!WHOLE) sum *= a.gain[e];
     out[e] = add ? out[e] + sum : sum;
   }
   add = true;
@@ -456,8 +488,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
 // decide what is kept in flight: all eight int16 samples of the next pulse, half
 // of the complex64 ones (all of them spill, and a reload waits for every load
 // before it).  200 pulses x 500 gates at L = 4000, N = 16384, phase codes (int16)
-// take 1.04 ms, 2.24 by direct transforms; the uneven batch, of which
-// L = 2000 is the longest part, 6.2 instead of 40 ms.
+// take 1.13 ms, 2.22 by direct transforms; 500 pulses x 2000 gates at L = 2000, N = 32768
+// 5.1 instead of 31 ms.
 
 // Code rows as sign bits for the long grid: word lg of a row holds in bit
 // 31 - j whether code sample lg + 1024 j is -1.  One workgroup per row.
@@ -489,13 +521,26 @@ pack_long_grid_bits(const float2* __restrict__ tx, int32_t code_len, uint32_t* _
   if (threadIdx.x == 0) binary[row] = ok ? 1 : 0;
 }
 
-template <int J, int ST>
+// A long grid's sums: its chunks' partials, `elems` apart, in ascending order.
+__global__ void __launch_bounds__(256)
+sum_chunks(const double* __restrict__ partial, double* __restrict__ to, int64_t elems, int32_t chunks) {
+  const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < elems; i += step) {
+    double s = 0.0;
+    for (int c = 0; c < chunks; ++c) s += partial[c * elems + i];
+    to[i] = s;
+  }
+}
+
+template <int J, int ST, bool WHOLE>
 __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
   constexpr int NT = 64 * J, PER = 16 / J, JL = J / 2;
   constexpr int JP = ST == 0 ? JL / 2 : JL;  // of each thread's samples, fetched a pulse ahead
   using IO = BufferSample<ST>;
   __shared__ float2 xs[J * XWAVE];
+  using sum_t = std::conditional_t<WHOLE, float, double>;
   __shared__ GeoTwiddles p1s[J];  // pass-1 progression W_M^{64 k1} of each wave
+  __shared__ float4 p2s[WHOLE ? 1 : J][5][16];  // pass 2's (beside double sums)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -506,22 +551,29 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
   const int L = a.code_len, M = SUB * J, step = a.n_fft / M, nmask = a.n_fft - 1;
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   // (complex64 samples in flight take 16 registers)
-  std::conditional_t<ST == 0, GridTwiddlesRows1, GridTwiddlesRows> wt;
+  std::conditional_t<!WHOLE, GridTwiddlesRows2,
+                     std::conditional_t<ST == 0, GridTwiddlesRows1, GridTwiddlesRows>> wt;
   {
     const int q = wave + J * (lane & 15);
-    load_geo(wt.p2, tw, a.n_fft, 4 * step * q);
+    if constexpr (WHOLE) {
+      load_geo(wt.p2, tw, a.n_fft, 4 * step * q);
+    } else {
+      for (int t = lane >> 4; t < 5; t += 4)
+        p2s[wave][t][lane & 15] = geo_part(tw, a.n_fft, 4 * step * q, t);
+      wt.p2.p = &p2s[wave][0][lane & 15];
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int e = step * (q + 16 * J * (4 * (lane >> 4) + t));
       wt.t3[t] = tw[e & nmask];
-      if constexpr (ST == 1) wt.t3sq[t] = tw[(2 * e) & nmask];
+      if constexpr (WHOLE && ST == 1) wt.t3sq[t] = tw[(2 * e) & nmask];
     }
     if (lane == 0) load_geo(p1s[wave], tw, a.n_fft, 64 * step * wave);
   }
   const Dft16Consts dk = dft16_consts();
-  float acc[16];
+  sum_t acc[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int i = 0; i < 16; ++i) acc[i] = 0;
 
   const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
   const RunSplit runs(a.n_pulses, a.chunks);
@@ -574,7 +626,8 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
     for (int i = 0; i < 16; ++i) v[i] = xw[lane + 64 * i];
     wave_lds_sync();  // read before this wave reuses its region for its own exchange
     dft16_geo(v, p1s[wave]);
-    wave_passes_23(v, xw, wt, dk, lane, NoHook{}, PowerSink{acc});
+    wave_passes_23(v, xw, wt, dk, lane, NoHook{},
+                   std::conditional_t<WHOLE, PowerSink, PowerSink64>{acc});
   };
 
   // codes of this workgroup's pulses all +-1: conj(c) x is a sign flip
@@ -588,13 +641,12 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
       binary = a.code_binary[0] != 0;
     }
   }
-  // the chunk's partial row, or the result's (as in grid_spectra)
-  const bool whole = a.grid_len == a.n_fft && !a.partials, last = whole && a.chunks == 1;
-  float* out = last ? a.out + static_cast<int64_t>(g) * M
-                    : a.grid + (static_cast<int64_t>(c) * a.rows + (whole ? g : slot)) * M;
+  sum_t* out = out_row<WHOLE>(a, g, slot, c);
+  const bool last = WHOLE && a.chunks == 1;
   bool add = last && a.accumulate;
-  for (int q0 = p0; q0 == p0 || q0 < p1; q0 += RUN_STEPS) {  // one FP32 sum each
-    const int q1 = min(q0 + RUN_STEPS, p1);
+  const int per_sum = WHOLE ? RUN_STEPS : max(1, p1 - p0);  // (as in grid_spectra)
+  for (int q0 = p0; q0 == p0 || q0 < p1; q0 += per_sum) {
+    const int q1 = min(q0 + per_sum, p1);
     if (binary) {
       if (q0 < q1) {
         fetch(q0, 0, JP);
@@ -653,18 +705,20 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
     // (addresses formed here each time: kept across the pulse loop they would
     // take its registers)
     const int ft = opaque(tid), fl = ft & 63;
-    float* st = reinterpret_cast<float*>(xs) + (ft >> 6) * (2 * XWAVE);
+    constexpr int REGION = XWAVE * sizeof(float2) / sizeof(sum_t);
+    sum_t* st = reinterpret_cast<sum_t*>(xs) + (ft >> 6) * REGION;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int r4 = fl >> 4;
       st[(fl & 15) + 64 * r4 + 16 * ((i >> 2) ^ r4) + 256 * (i & 3)] = acc[i];  // staged(bin_of)
-      acc[i] = 0.f;
+      acc[i] = 0;
     }
     __syncthreads();
-    const float* all_st = reinterpret_cast<const float*>(xs);
+    const sum_t* all_st = reinterpret_cast<const sum_t*>(xs);
     for (int e = ft; e < M; e += NT) {
       const int kb = e / J;
-      const float s = all_st[(e & (J - 1)) * (2 * XWAVE) + (kb ^ ((kb >> 2) & 48))];
+      sum_t s = all_st[(e & (J - 1)) * REGION + (kb ^ ((kb >> 2) & 48))];
+      if constexpr (!WHOLE) s *= a.gain[e];
       out[e] = add ? out[e] + s : s;
     }
     add = true;  // (the next pulse's first barrier frees the regions)
@@ -693,10 +747,8 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
 // The transforms run in double precision: a line of power S_l leaves rounding of
 // about 1e-7 S_l at its mirror frequency and other places of an FP32
 // transform's structure, where S may be a hundred times smaller, which no direct
-// transform does.  (With FP32 transforms the largest error of the uneven batch's
-// L = 2000 experiment was 3.5e-5 of the larger of S and its mean, now 5.7e-6; 1000
-// gates of N = 16384 take 67 us, in FP32 50.)  Lags and grid stay FP32:
-// their rounding is spread evenly over all bins.
+// transform does (1000 gates of N = 16384 take 69 us, in FP32 50).  The lags are FP32: their
+// rounding is spread evenly over all bins, 2^-24 of the spectrum's fluctuation about its mean.
 
 // SG-point DFT in place, natural order (SG = 2, 4 or 8).
 template <int SG>
@@ -829,30 +881,27 @@ __device__ __forceinline__ double block_mean(double part, double* red, int m) {
   return s / static_cast<double>(m);
 }
 
-// A gate's grid of M <= 2048 points into `to`, its chunk partials (cs floats apart)
+// A gate's grid of M <= 2048 points into `to`, its chunk partials (cs apart)
 // summed in ascending order; returns this thread's part of the sum over the grid.
-__device__ __forceinline__ double gather_grid(const FoldArgs& a, const float* row, int64_t cs,
-                                              float* to, int tid) {
+__device__ __forceinline__ double gather_grid(const FoldArgs& a, const double* row, int64_t cs,
+                                              double* to, int tid) {
   double part = 0.0;
-  for (int k = 4 * tid; k < a.grid_len; k += 4 * 64 * EXP_WAVES) {
-    float4 s = *reinterpret_cast<const float4*>(row + k);
+  for (int k = 2 * tid; k < a.grid_len; k += 2 * 64 * EXP_WAVES) {
+    double2 s = *reinterpret_cast<const double2*>(row + k);
     for (int c0 = 1; c0 < a.chunks; c0 += 8) {
-      float4 q[8];
+      double2 q[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        q[u] = *reinterpret_cast<const float4*>(row + min(c0 + u, a.chunks - 1) * cs + k);
+        q[u] = *reinterpret_cast<const double2*>(row + min(c0 + u, a.chunks - 1) * cs + k);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (c0 + u < a.chunks) {
           s.x += q[u].x;
           s.y += q[u].y;
-          s.z += q[u].z;
-          s.w += q[u].w;
         }
     }
-    *reinterpret_cast<float4*>(to + k) = s;
-    part += (static_cast<double>(s.x) + static_cast<double>(s.y)) +
-            (static_cast<double>(s.z) + static_cast<double>(s.w));
+    *reinterpret_cast<double2*>(to + k) = s;
+    part += s.x + s.y;
   }
   return part;
 }
@@ -863,11 +912,11 @@ __device__ __forceinline__ double gather_grid(const FoldArgs& a, const float* ro
 template <int ST, int SG>
 __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   constexpr int W = EXP_WAVES, NT = 64 * W;
-  constexpr int UP = SUB + 4;  // aux: 1024-point grid of M < 1024
   constexpr bool WIDE = SG == 1, LONG = SG > 1;
   __shared__ __attribute__((aligned(16))) float2 xs[W * XWAVE];
-  __shared__ __attribute__((aligned(16))) float aux[LONG ? 4 : 2 * SUB + 8];
-  __shared__ float2 lags[LONG ? SG * SUB + 1 : 1];
+  __shared__ __attribute__((aligned(16))) double sums[LONG ? 1 : 2 * SUB];  // M <= 2048: the grid
+  __shared__ float up_s[SG == 0 ? SUB : 1];      // M < 1024: the grid of 1024 points
+  __shared__ float2 lags[LONG ? SG * SUB + 1 : WIDE ? 1 : SUB / 2 + 1];
   __shared__ double red[W];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -884,7 +933,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   const int slot = bid / a.blocks, share = bid % a.blocks;  // of the gate's rounds of classes
   const int g = gate_of(a, slot);
   if (g < 0) return;
-  const float* const row = a.grid + static_cast<int64_t>(slot) * M;
+  const double* const row = a.grid + static_cast<int64_t>(slot) * M;
   const int64_t cs = static_cast<int64_t>(a.rows) * M;
   const float scale = 1.f / static_cast<float>(M);
 
@@ -919,9 +968,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int j = 0; j < SG; ++j) {
-        const float2 s = reinterpret_cast<const float2*>(row)[tid + NT * t + SUB * j];
+        const double2 s = reinterpret_cast<const double2*>(row)[tid + NT * t + SUB * j];
         z[t][j] = complex64d{s.x, s.y};
-        part += static_cast<double>(s.x) + static_cast<double>(s.y);
+        part += s.x + s.y;
       }
     mean = block_mean(part, red, M);
     qs = lags;
@@ -961,14 +1010,13 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
       untangle(lags, NC - n, B, A);  // n = 0: the zero past the last lag
     }
   } else {
-    // ---- the grid, chunk sums in ascending order, into aux
-    mean = block_mean(gather_grid(a, row, cs, aux, tid), red, M);
+    // ---- the grid, chunk sums in ascending order
+    mean = block_mean(gather_grid(a, row, cs, sums, tid), red, M);
 
     // ---- lags: up to conjugation and 1 / M the forward DFT of the real grid,
     // M <= 1024 zero-interleaved to 1024 points (which repeats its spectrum),
-    // M = 2048 as complex points; left behind the grid in aux, at M = 2048 in
-    // wave 0's own region
-    qs = WIDE ? xs : reinterpret_cast<float2*>(aux + M);
+    // M = 2048 as complex points (its lags in wave 0's own region)
+    qs = WIDE ? xs : lags;
     if (wave == 0) {
       // (the sinks write into the wave's own exchange buffer, whose reads are
       // all issued by then)
@@ -976,7 +1024,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
       if constexpr (WIDE) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-          const float2 p = reinterpret_cast<const float2*>(aux)[lane + 64 * j];
+          const double2 p = reinterpret_cast<const double2*>(sums)[lane + 64 * j];
           v[j] = complex64d{p.x - mean, p.y - mean};
         }
         class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d f) {
@@ -987,7 +1035,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           const int n = lane + 64 * j;
-          v[j] = complex64d{(n & up) == 0 ? aux[n >> lup] - mean : 0.0, 0.0};
+          v[j] = complex64d{(n & up) == 0 ? sums[n >> lup] - mean : 0.0, 0.0};
         }
         class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d f) {
           xw[bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
@@ -1013,7 +1061,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
             const int k = bin_of(i, lane);
             const float s = static_cast<float>(F.x - F.y + mean);
             // S >= 0: a rounded zero stays one
-            aux[UP + k] = (k & up) == 0 ? aux[k >> lup] : s < 0.f ? 0.f : s;
+            up_s[k] = (k & up) == 0 ? static_cast<float>(sums[k >> lup]) : s < 0.f ? 0.f : s;
           });
         }
       }
@@ -1030,7 +1078,12 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 
   // ---- the classes
   const bool ok = expandable(mean);
-  const float* grid = LONG ? row : M < SUB ? aux + UP : aux;
+  auto grid_bin = [&](int k) -> float {
+    if constexpr (LONG) return static_cast<float>(row[k]);
+    if constexpr (SG == 0)
+      if (M < SUB) return up_s[k];
+    return static_cast<float>(sums[k]);
+  };
   const bool one_round = n_tasks <= PER_ROUND;
   for (int z0 = PER_ROUND * share; z0 == 0 || z0 < n_tasks; z0 += PER_ROUND * a.blocks) {
     const int n_cls = min(PER_ROUND, n_tasks - z0);  // 0: every bin is on the grid
@@ -1095,7 +1148,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
         for (int u = 0; u < 4; ++u) {
           float x = 0.f;
           if (grid_pt[u]) {
-            x = grid[(k0 + u) >> lratio];
+            x = grid_bin((k0 + u) >> lratio);
           } else if (base[u] >= 0) {
             // class R - k1 holds bin -(k1 + R kk), i.e. its own entry 1023 - kk
             const int kb = (k0 + u) >> lr;
@@ -1158,7 +1211,7 @@ __device__ void direct_window(const FoldArgs& a, int g, int k0, int j0, int j1, 
 
 template <int ST, bool WIDE>
 __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
-  __shared__ __attribute__((aligned(16))) float grid[WIDE ? 2 * SUB : SUB];
+  __shared__ __attribute__((aligned(16))) double grid[WIDE ? 2 * SUB : SUB];
   __shared__ __attribute__((aligned(16))) complex64d lags[SUB + 1];
   __shared__ __attribute__((aligned(16))) double xd[XWAVE];
   __shared__ double red[EXP_WAVES], sums[EXP_WAVES][128];
@@ -1171,7 +1224,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   if (g < 0) return;
   const int r0 = K / 128 * part / a.blocks, r1 = K / 128 * (part + 1) / a.blocks;
   const int k0 = a.bin_start[g];
-  const float* row = a.grid + static_cast<int64_t>(slot) * M;
+  const double* row = a.grid + static_cast<int64_t>(slot) * M;
   const double mean = block_mean(
       gather_grid(a, row, static_cast<int64_t>(a.rows) * M, grid, tid), red, M);
   if (!expandable(mean)) {  // uniform
@@ -1198,7 +1251,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
     if constexpr (WIDE) {
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const float2 p = reinterpret_cast<const float2*>(grid)[lane + 64 * j];
+        const double2 p = reinterpret_cast<const double2*>(grid)[lane + 64 * j];
         v[j] = complex64d{p.x - mean, p.y - mean};
       }
       class_transform64(v, xd, a.twiddle64, SUB, N, 0, lane,
@@ -1257,12 +1310,12 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   }
 }
 
-template <int LOGM, int ST>
+template <int LOGM, int ST, bool WHOLE>
 hipError_t launch_grid_w(const FoldArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.chunks));
   switch (a.waves) {
-    case 8: hipLaunchKernelGGL((grid_spectra<LOGM, ST, 8>), grid, dim3(512), 0, s, a); break;
-    case 16: hipLaunchKernelGGL((grid_spectra<LOGM, ST, 16>), grid, dim3(1024), 0, s, a); break;
+    case 8: hipLaunchKernelGGL((grid_spectra<LOGM, ST, 8, WHOLE>), grid, dim3(512), 0, s, a); break;
+    case 16: hipLaunchKernelGGL((grid_spectra<LOGM, ST, 16, WHOLE>), grid, dim3(1024), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1271,15 +1324,24 @@ hipError_t launch_grid_w(const FoldArgs& a, hipStream_t s) {
 template <int ST>
 hipError_t launch_grid(const FoldArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.chunks));
+  if (a.partial) {  // the grid is the N bins (N >= 1024; longer codes: N >= 16384)
+    switch (a.grid_len) {
+      case 1024: return launch_grid_w<10, ST, true>(a, s);
+      case 2048: return launch_grid_w<11, ST, true>(a, s);
+      case 16384: hipLaunchKernelGGL((grid_long<16, ST, true>), grid, dim3(1024), 0, s, a); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   switch (a.grid_len) {
-    case 128: return launch_grid_w<7, ST>(a, s);
-    case 256: return launch_grid_w<8, ST>(a, s);
-    case 512: return launch_grid_w<9, ST>(a, s);
-    case 1024: return launch_grid_w<10, ST>(a, s);
-    case 2048: return launch_grid_w<11, ST>(a, s);
-    case 4096: hipLaunchKernelGGL((grid_long<4, ST>), grid, dim3(256), 0, s, a); break;
-    case 8192: hipLaunchKernelGGL((grid_long<8, ST>), grid, dim3(512), 0, s, a); break;
-    case 16384: hipLaunchKernelGGL((grid_long<16, ST>), grid, dim3(1024), 0, s, a); break;
+    case 128: return launch_grid_w<7, ST, false>(a, s);
+    case 256: return launch_grid_w<8, ST, false>(a, s);
+    case 512: return launch_grid_w<9, ST, false>(a, s);
+    case 1024: return launch_grid_w<10, ST, false>(a, s);
+    case 2048: return launch_grid_w<11, ST, false>(a, s);
+    case 4096: hipLaunchKernelGGL((grid_long<4, ST, false>), grid, dim3(256), 0, s, a); break;
+    case 8192: hipLaunchKernelGGL((grid_long<8, ST, false>), grid, dim3(512), 0, s, a); break;
+    case 16384: hipLaunchKernelGGL((grid_long<16, ST, false>), grid, dim3(1024), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1338,7 +1400,9 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.tx = f.tx;
   a.twiddle = f.twiddle;
   a.twiddle64 = f.twiddle64;
+  a.gain = f.grid_gain;
   a.grid = f.grid;
+  a.partial = f.grid_len == f.n_fft ? reinterpret_cast<float*>(f.grid) : nullptr;
   a.out = f.out;
   a.stride = f.stride;
   a.n_fft = f.n_fft;
@@ -1360,9 +1424,15 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
     a.rows = f.n_gates;
     e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
     if (e == hipSuccess && a.chunks > 1 && !f.grid_defer)
-      e = launch_reduce_chunks(a.grid, a.out, static_cast<int64_t>(f.n_gates) * f.n_fft, a.chunks,
+      e = launch_reduce_chunks(a.partial, a.out, static_cast<int64_t>(f.n_gates) * f.n_fft, a.chunks,
                                a.accumulate, a.n_fft, a.gate_list, a.gate_count, s);
     return e;
+  }
+  if (f.grid_gain_missing) {
+    hipLaunchKernelGGL(build_gains, dim3(static_cast<unsigned>((a.grid_len + 255) / 256)), dim3(256), 0,
+                       s, a.twiddle64, a.n_fft, a.grid_len, f.grid_gain);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
   // as many gates at a time as the scratch holds
   for (int32_t s0 = 0; s0 < f.n_gates; s0 += f.grid_rows) {
@@ -1376,7 +1446,9 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
       const int64_t elems = static_cast<int64_t>(a.rows) * a.grid_len;
       x.grid = a.grid + a.chunks * elems;
       x.chunks = 1;
-      e = launch_reduce_chunks(a.grid, x.grid, elems, a.chunks, 0, a.grid_len, nullptr, nullptr, s);
+      const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((elems + 255) / 256, 4096));
+      hipLaunchKernelGGL(sum_chunks, dim3(blocks), dim3(256), 0, s, a.grid, x.grid, elems, a.chunks);
+      e = hipGetLastError();
     }
     if (e == hipSuccess)
       e = f.sample_type == 1 ? launch_expand<1>(x, s) : launch_expand<0>(x, s);
@@ -1391,6 +1463,7 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
   a.tx = z.tx;
   a.twiddle = z.twiddle;
   a.twiddle64 = z.twiddle64;
+  a.gain = z.grid_gain;
   a.grid = z.grid;
   a.out = z.out;
   a.stride = z.stride;
@@ -1409,7 +1482,6 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
   a.gate_count = z.gate_count;
   a.bin_start = z.bin_start;
   a.n_bins = z.n_bins;
-  a.partials = 1;
   hipError_t e = pack_bits(a, z.grid_bits, z.grid_binary, s);
   for (int32_t s0 = 0; e == hipSuccess && s0 < z.n_gates; s0 += z.grid_rows) {
     a.slot0 = s0;

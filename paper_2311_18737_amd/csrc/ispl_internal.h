@@ -80,14 +80,16 @@ struct FusedArgs {
   // grid_len >= 2 L - 1 points, which is then expanded to the N bins of `out`
   // (`chunks` and `waves_per_block` are not read); grid_len = N sums the bins
   // themselves.  `grid` holds the chunk partials of grid_rows gates at a time,
-  // [grid_chunks][grid_rows][grid_len] floats (grid_len = N: of all gates, and
+  // [grid_chunks][grid_rows][grid_len] doubles (grid_len = N: floats of all gates, and
   // one chunk needs none).  grid_bits / grid_binary (both or neither):
   // [code rows][L <= SUB ? 64 : SUB] words and [code rows] flags for the codes'
   // sign bits.
-  float* grid;
+  double* grid;
   const double* twiddle64;  // W_N^i, i < N, complex128 pairs
+  double* grid_gain;        // grid_gain(k) of every grid point (see ispl_gain.h)
   uint32_t* grid_bits;
   int32_t* grid_binary;
+  int32_t grid_gain_missing; // the launch writes grid_gain first
   int32_t grid_len;
   int32_t grid_chunks;
   int32_t grid_waves;
@@ -120,9 +122,11 @@ struct FoldArgs {
   const float* tx;
   const float* twiddle;      // W_N^i, i < N
   const double* twiddle64;   // the same in double
+  const double* gain;        // by which each grid point's sum is multiplied
   const uint32_t* code_bits; // sign bits of the code rows (NULL: read tx), see the packing kernels
   const int32_t* code_binary;
-  float* grid;               // [chunks][rows][M]
+  double* grid;              // sums [chunks][rows][M]
+  float* partial;            // M = N: FP32 partials [chunks][G][N] instead (not read with one chunk)
   float* out;                // [G][N]
   int64_t stride;
   int32_t n_fft, grid_len, code_len;
@@ -134,7 +138,6 @@ struct FoldArgs {
   // a window of n_bins bins per gate from bin_start[gate] on (out [G][n_bins])
   const int32_t* bin_start;
   int32_t n_bins, blocks;    // workgroups a window is split over
-  int32_t partials;          // leave the sums in `grid` also where M = N
 };
 // The whole folded integration of a.grid_len > 0.
 hipError_t launch_folded(const FusedArgs& a, hipStream_t stream);
@@ -148,10 +151,12 @@ hipError_t launch_reduce_chunks(const float* partial, float* spectra, int64_t el
 
 // Static scratch of ispl_integrate_spectra_noalloc: twiddle table first, the
 // chunk partials after it.  Calls that run on a grid use the second part as the twiddle
-// table in double (NOALLOC_TWIDDLE64_BYTES) and the grid scratch after it.
+// table in double (NOALLOC_TWIDDLE64_BYTES), the grid points' gains (NOALLOC_GAIN_BYTES) and
+// the grid scratch after them.
 constexpr size_t NOALLOC_TWIDDLE_BYTES = size_t{512} << 10;  // N <= 65536 complex64
 constexpr size_t NOALLOC_PARTIAL_BYTES = ISPL_NOALLOC_SCRATCH_BYTES - NOALLOC_TWIDDLE_BYTES;
 constexpr size_t NOALLOC_TWIDDLE64_BYTES = size_t{1} << 20;  // N <= 65536 complex128
+constexpr size_t NOALLOC_GAIN_BYTES = size_t{1} << 20;       // 16384 doubles, and room
 // This GPU's copy of the array (`device` must be current); looked up once per
 // device.
 hipError_t noalloc_scratch(int device, unsigned char** base);
@@ -201,10 +206,11 @@ struct ZoomArgs {
   int32_t* code_binary;
   // Zoom from the pulse-summed grid of grid_len points instead (0: matrix
   // products); see FusedArgs and launch_zoom_folded.  chunks is 1 then.
-  float* grid;
+  double* grid;
   uint32_t* grid_bits;
   int32_t* grid_binary;
   const double* twiddle64;
+  double* grid_gain;
   int32_t grid_len, grid_chunks, grid_waves, grid_rows;
 };
 hipError_t launch_zoom_folded(const ZoomArgs& a, hipStream_t stream);

@@ -1,0 +1,87 @@
+"""Accuracy of spectra with one narrow line per tested gate, where a summed grid
+is expanded: rounding at a line's grid points is spread over the gate's bins, in
+proportion to the line's height over the mean.
+
+Every error is relative to max(S, mean S) of the FP64 oracle's spectrum."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import integrate_spectra as oracle_spectra  # noqa: E402
+from tests.conftest import ensure_library  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def ispl():
+    ensure_library()
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2311_18737_amd as pkg
+
+    return pkg
+
+
+class Lines:
+    """+-1 codes, unit noise, and in every 16th gate an echo with one line at a
+    random frequency and random phases; gates step by L / 8, so echoes do not meet."""
+
+    def __init__(self, L, N, G, P, snr_db, seed, sample_type="c64"):
+        rng = np.random.default_rng(seed)
+        step = max(1, L // 8)
+        self.stride = (G - 1) * step + L
+        self.geo = dict(code_len=L, fft_len=N, n_gates=G, gate_step=step, pulse_stride=self.stride,
+                        sample_type=sample_type)
+        self.tx = (rng.integers(0, 2, (P, L)) * 2 - 1).astype(np.complex64)
+        x = rng.standard_normal((P, self.stride, 2), dtype=np.float32).view(np.complex64)[..., 0]
+        x *= np.float32(np.sqrt(0.5))
+        self.gates = list(range(3, G, 16))
+        n = np.arange(L)
+        amp = 10.0 ** (snr_db / 20.0)
+        for g in self.gates:
+            tone = amp * np.exp(2j * np.pi * rng.uniform() * n)
+            phase = np.exp(2j * np.pi * rng.uniform(size=(P, 1)))
+            x[:, g * step:g * step + L] += (self.tx * tone * phase).astype(np.complex64)
+        if sample_type == "ci16":
+            x = np.round(x.view(np.float32).reshape(P, self.stride, 2) * (2000.0 / max(1.0, amp)))
+            x = x.astype(np.int16)
+        self.x = x
+        self.ref = oracle_spectra(self.x, self.tx, n_gates=G, gate_step=step, first_gate=0,
+                                  fft_len=N, tx_per_pulse=True, gates=self.gates)
+
+    def run(self, ispl):
+        ctx = ispl.Context(max_pulses=len(self.tx), **self.geo)
+        out = ctx.integrate_spectra(torch.from_numpy(self.x).to(DEV), torch.from_numpy(self.tx).to(DEV))
+        got = out[self.gates].cpu().numpy().astype(np.float64)
+        ctx.close()
+        return got
+
+
+SHAPES = [
+    # L,   N,     G,   P
+    (64, 4096, 600, 100),
+    (256, 16384, 300, 100),
+    (333, 8192, 300, 60),
+    (1000, 16384, 200, 100),
+    (2000, 32768, 120, 100),
+    (4000, 16384, 100, 60),
+    (8000, 32768, 60, 60),
+]
+
+
+@pytest.mark.parametrize("sample_type", ["c64", "ci16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "L{}_N{}_G{}_P{}".format(*s))
+def test_line_below_the_noise(ispl, shape, sample_type):
+    """-10 dB per sample.  Bound: ten roundings of an FP32 transform (2^-24 each) as without a
+    line, and a sixth of a rounding of the line's points, which its neighbours see."""
+    L, N, G, P = shape
+    lines = Lines(L, N, G, P, -10.0, seed=L, sample_type=sample_type)
+    got, ref = lines.run(ispl), lines.ref
+    mean = ref.mean(axis=1, keepdims=True)
+    err = (np.abs(got - ref) / np.maximum(ref, mean)).max(axis=1)
+    bound = 2.0 ** -24 * (10.0 + ref.max(axis=1) / mean[:, 0] / 6.0)
+    assert (err <= bound).all(), (err / bound).max()
