@@ -41,6 +41,7 @@ struct ispl_ctx {
   uint32_t* grid_bits;  // codes as sign bits, grid_bits_rows rows, and their flags
   int32_t* grid_binary;
   int32_t grid_bits_rows;
+  int32_t* redo;        // number and list of the gates that a call's expansion leaves over
 };
 
 namespace {
@@ -294,6 +295,11 @@ int64_t grid_scratch_bytes(const ispl_config& c, int64_t most_bytes = kGridBytes
   return std::min(most_bytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), (kMaxChunks + 1) * row}));
 }
 
+// Most gates whose sums `bytes` of grid scratch hold at a time.
+int64_t grid_rows_max(const ispl_config& c, int64_t bytes) {
+  return std::min<int64_t>(c.n_gates, bytes / (int64_t{8} * grid_length(c)));
+}
+
 ispl_status validate_config(const ispl_config* c) {
   if (!c) return fail(ISPL_ERR_INVALID_ARG, "config is NULL");
   if (c->abi_version != ISPL_ABI_VERSION)
@@ -449,6 +455,7 @@ struct ispl_zoom {
   uint32_t* grid_bits;    // [grid_bits_rows][64], and the rows' flags behind them
   int32_t* grid_binary;
   int32_t grid_bits_rows;
+  int32_t* redo;          // as a context's
 };
 
 namespace {
@@ -491,7 +498,7 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_pulses) {
 
 static void zoom_free(ispl_zoom* z) {
   void* bufs[] = {z->a_hi,      z->a_lo, z->partial,   z->col_exp,    z->code_bits,
-                  z->code_binary, z->grid, z->grid_bits};
+                  z->code_binary, z->grid, z->grid_bits, z->redo};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
 }
@@ -605,6 +612,9 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
       ctx->grid_gain = ctx->twiddle64 + tw64.size();
       e = hipMemcpy(ctx->grid_gain, gain.data(), gain.size() * sizeof(double), hipMemcpyHostToDevice);
     }
+    if (e == hipSuccess)
+      e = hipMalloc(reinterpret_cast<void**>(&ctx->redo),
+                    sizeof(int32_t) * (1 + grid_rows_max(*cfg, ctx->grid_bytes)));
     const size_t words = grid_bits_words(*cfg);
     ctx->grid_bits_rows = grid_bits_rows(*cfg);
     if (e == hipSuccess)  // the sign bits and their flags in one block
@@ -613,6 +623,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
     if (e != hipSuccess) {
       if (ctx->grid) (void)hipFree(ctx->grid);
       if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
+      if (ctx->redo) (void)hipFree(ctx->redo);
       if (ctx->partial) (void)hipFree(ctx->partial);
       (void)hipFree(ctx->twiddle);
       delete ctx;
@@ -632,6 +643,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
       if (ctx->partial) (void)hipFree(ctx->partial);
       if (ctx->grid) (void)hipFree(ctx->grid);
       if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
+      if (ctx->redo) (void)hipFree(ctx->redo);
       if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
       (void)hipFree(ctx->twiddle);
       delete ctx;
@@ -657,6 +669,7 @@ void ispl_destroy(ispl_ctx* ctx) {
     if (ctx->code_binary) (void)hipFree(ctx->code_binary);
     if (ctx->grid) (void)hipFree(ctx->grid);
     if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
+    if (ctx->redo) (void)hipFree(ctx->redo);
     if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
   }
   delete ctx;
@@ -697,8 +710,9 @@ struct AdaptiveFallback {
 // The adaptive parameters for a context's fallback launches over n_pulses: at
 // most one round of the chip, at most 64 chunks (the reduction reads each
 // chunk's row) of at least kMinChunkPulses pulses.
-static AdaptiveFallback adaptive_plan(const ispl_config& c, int32_t n_pulses, float* partial) {
-  const Plan pl = make_plan(c, n_pulses > 0 ? n_pulses : 1);
+static AdaptiveFallback adaptive_plan(const ispl_config& c, int32_t n_pulses, float* partial,
+                                      int32_t force_rw = 0) {
+  const Plan pl = make_plan(c, n_pulses > 0 ? n_pulses : 1, force_rw);
   int per_cu = kLdsPerCu / ispl::fused_lds_bytes(pl.rw, pl.sub_len);
   if (per_cu * pl.rw > kMaxWavesPerCu) per_cu = kMaxWavesPerCu / pl.rw;
   if (per_cu < 1) per_cu = 1;
@@ -796,6 +810,15 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
       a.grid_bits = ctx->grid_bits;
       a.grid_binary = ctx->grid_binary;
     }
+    const AdaptiveFallback redo = adaptive_plan(c, n_pulses, nullptr, ctx->force_rw);
+    a.redo_count = ctx->redo;
+    a.redo_list = ctx->redo + 1;
+    a.redo_target = redo.target;
+    a.redo_max_chunks = redo.max_chunks;
+    a.redo_rows = static_cast<int32_t>(
+        std::min<int64_t>(redo.rows, ctx->grid_bytes / (int64_t{4} * c.fft_len)));
+    a.code_bits = ctx->code_bits;
+    a.code_binary = ctx->code_binary;
     e = ispl::launch_fused(a, s);
     if (e != hipSuccess) return hip_fail(e, "folded launch");
     if (deferred_chunks) {
@@ -911,6 +934,8 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
     tmp.grid_gain = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
                                               ispl::NOALLOC_TWIDDLE64_BYTES);
     tmp.gain_missing = true;
+    tmp.redo = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(tmp.grid_gain) +
+                                          ispl::NOALLOC_REDO_AT);
     tmp.grid = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
                                          ispl::NOALLOC_TWIDDLE64_BYTES + ispl::NOALLOC_GAIN_BYTES);
   }
@@ -965,6 +990,8 @@ ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
   if (e == hipSuccess && ctx->twiddle64 && zoom_grid_plan(c, c.max_pulses).len > 0) {
     z->grid_bytes = grid_scratch_bytes(c);
     e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes));
+    if (e == hipSuccess)
+      e = hipMalloc(&z->redo, sizeof(int32_t) * (1 + grid_rows_max(c, z->grid_bytes)));
     z->grid_bits_rows = grid_bits_rows(c);
     const size_t words = static_cast<size_t>(z->grid_bits_rows) * grid_bits_words(c);
     if (e == hipSuccess)
@@ -1075,7 +1102,6 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
   GridPlan gp{};
   if (z->grid) gp = zoom_grid_plan(c, n_pulses);
   if (gp.len > 0) {
-    a.chunks = 1;
     a.grid = z->grid;
     a.twiddle64 = z->ctx->twiddle64;
     a.grid_gain = z->ctx->grid_gain;
@@ -1083,6 +1109,8 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
     a.grid_chunks = gp.chunks;
     a.grid_waves = gp.waves;
     a.grid_rows = grid_run(c.n_gates, z->grid_bytes / (int64_t{8} * gp.len * gp.chunks));
+    a.redo_count = z->redo;
+    a.redo_list = z->redo + 1;
     if (packs_bits(c, tx_per_pulse, n_pulses, z->grid_bits_rows)) {
       a.grid_bits = z->grid_bits;
       a.grid_binary = z->grid_binary;

@@ -24,6 +24,7 @@
 // 2000 / 4000: 7e-7 / 1.1e-6 / 1.7e-6 (FP32 sums 3.1e-6 / 7.5e-6 / 1.2e-5, double ones
 // without the gain 2.0e-6 / 5.7e-6 / 1.7e-5); without a line 1.0e-7 to 1.4e-7, direct 4e-7 to 6e-7.
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -286,6 +287,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cls = CLS > 1 ? wave & 1 : 0;
   const int run = wave / CLS;
+  if (a.redo_count && blockIdx.x == 0 && tid == 0) *a.redo_count = 0;  // (the expansion's list)
   const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
   const int c = bid % a.chunks, slot = bid / a.chunks;
   const int g = gate_of(a, slot);
@@ -544,6 +546,7 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (a.redo_count && blockIdx.x == 0 && tid == 0) *a.redo_count = 0;  // (the expansion's list)
   const int bid = a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
   const int c = bid % a.chunks, slot = bid / a.chunks;
   const int g = gate_of(a, slot);
@@ -792,100 +795,52 @@ constexpr int EXP_WAVES = 8;
 constexpr int MIRROR = 1040;   // second staged row of a wave's region
 static_assert(MIRROR + SUB <= 2 * XWAVE, "two rows per region");
 
-// Twiddle i of the table for a wave-uniform i, by a scalar load (the table is
-// constant while a kernel runs).
-__device__ __forceinline__ float2 uniform_twiddle(const float2* tw, int i) {
-  using cptr = const __attribute__((address_space(4))) f32x2*;
-  const f32x2 w = reinterpret_cast<cptr>(reinterpret_cast<uint64_t>(tw))[__builtin_amdgcn_readfirstlane(i)];
-  return make_float2(w.x, w.y);
-}
-
 struct alignas(4) Float4u {
   float v[4];
 };
 
-// Whether the grid's sums can be expanded: finite, and far enough from the ends
-// of the FP32 range that the transforms stay inside it.
-__device__ __forceinline__ bool expandable(double mean) {
-  return mean == 0.0 || (mean > 1e-30 && mean < 1e30);
-}
-
-// The N bins of gate g straight from its pulses, for a grid that cannot be
-// expanded (a power beyond the FP32 range or near its lower end, NaN): bins then
-// come out as the direct transform leaves them.
-template <int ST>
-__device__ void direct_row(const FoldArgs& a, int g, float2* xs, const Dft16Consts& dk, int tid) {
-  using IO = BufferSample<ST>;
-  constexpr int W = EXP_WAVES;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int N = a.n_fft, R = N / SUB, L = a.code_len;
-  const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
-  const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
-  float2* xw = xs + wave * XWAVE;
-  float* xf = reinterpret_cast<float*>(xs);
-  float* out = a.out + static_cast<int64_t>(g) * N;
-  for (int c0 = 0; c0 < R; c0 += W) {
-    const int n_cls = min(W, R - c0), k1 = c0 + wave;
-    __syncthreads();  // the regions are free
-    if (wave < n_cls) {
-      WaveTwiddlesGeo w;
-      load_wave_twiddles(w, tw, N, k1, lane);
-      float acc[16];
+// A gate's grid of m points: its mean and its largest value.
+struct GridStats {
+  double sum = 0.0;
+  float hi = 0.f;
+  __device__ __forceinline__ void add(double v) {
+    sum += v;
+    hi = fmaxf(hi, static_cast<float>(v));
+  }
+  // Over the workgroup, from each thread's part; sum becomes the mean.
+  __device__ __forceinline__ void reduce(double* red, float* red_hi, int m) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll 1
-      for (int p = 0; p < a.n_pulses; ++p) {
-        float2 v[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = make_float2(0.f, 0.f);
-#pragma unroll 1
-        for (int s = 0; s * SUB < L; ++s) {  // 1024 samples at a time, folded by W_R^{k1 s}
-          const auto ds = row_desc(a.samples, static_cast<int64_t>(p) * a.stride + gate_off + SUB * s,
-                                   IO::SIZE, L - SUB * s);
-          const auto dc = row_desc(a.tx, (a.tx_per_pulse ? static_cast<int64_t>(p) * L : 0) + SUB * s,
-                                   8, L - SUB * s);
-          const float2 f = uniform_twiddle(tw, (SUB * k1 * s) & (N - 1));
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const auto x = IO::load(ds, (lane + 64 * j) * IO::SIZE);
-            const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(dc, (lane + 64 * j) * 8, 0, 0);
-            const float2 y = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)), IO::cvt(x));
-            v[j] = s == 0 ? y : cmuladd(v[j], f, y);
-          }
-        }
-        wave_fft_accumulate(v, xw, w, dk, acc, lane);
-      }
-      wave_lds_sync();
-#pragma unroll
-      for (int i = 0; i < 16; ++i) xf[wave * 2 * XWAVE + bin_of(i, lane)] = acc[i];
+    for (int off = 32; off > 0; off >>= 1) {
+      sum += __shfl_xor(sum, off);
+      hi = fmaxf(hi, __shfl_xor(hi, off));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[threadIdx.x >> 6] = sum;
+      red_hi[threadIdx.x >> 6] = hi;
     }
     __syncthreads();
-    for (int k = tid; k < N; k += 64 * W) {
-      const int i = (k & (R - 1)) - c0;
-      if (i < 0 || i >= n_cls) continue;
-      const float s = xf[i * 2 * XWAVE + k / R];
-      out[k] = a.accumulate ? out[k] + s : s;
+    sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < EXP_WAVES; ++i) {
+      sum += red[i];
+      hi = fmaxf(hi, red_hi[i]);
     }
+    sum /= static_cast<double>(m);
   }
-}
+  // Whether the bins may follow from the grid: its points finite, and as FP32.
+  __device__ __forceinline__ bool usable() const { return sum - sum == 0.0 && hi <= FLT_MAX; }
+};
 
-// Mean of a gate's grid of m points from each thread's part of its sum.
-__device__ __forceinline__ double block_mean(double part, double* red, int m) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < EXP_WAVES; ++i) s += red[i];
-  return s / static_cast<double>(m);
+// Leaves gate g to the launches that follow (one thread per gate).
+__device__ __forceinline__ void redo_gate(const FoldArgs& a, int g) {
+  a.redo_list[atomicAdd(a.redo_count, 1)] = g;
 }
 
 // A gate's grid of M <= 2048 points into `to`, its chunk partials (cs apart)
-// summed in ascending order; returns this thread's part of the sum over the grid.
-__device__ __forceinline__ double gather_grid(const FoldArgs& a, const double* row, int64_t cs,
-                                              double* to, int tid) {
-  double part = 0.0;
+// summed in ascending order; returns this thread's part of its statistics.
+__device__ __forceinline__ GridStats gather_grid(const FoldArgs& a, const double* row, int64_t cs,
+                                                 double* to, int tid) {
+  GridStats part;
   for (int k = 2 * tid; k < a.grid_len; k += 2 * 64 * EXP_WAVES) {
     double2 s = *reinterpret_cast<const double2*>(row + k);
     for (int c0 = 1; c0 < a.chunks; c0 += 8) {
@@ -901,7 +856,8 @@ __device__ __forceinline__ double gather_grid(const FoldArgs& a, const double* r
         }
     }
     *reinterpret_cast<double2*>(to + k) = s;
-    part += s.x + s.y;
+    part.add(s.x);
+    part.add(s.y);
   }
   return part;
 }
@@ -909,7 +865,7 @@ __device__ __forceinline__ double gather_grid(const FoldArgs& a, const double* r
 // SG: M / 2048 segments of 1024 lags each way (0: M <= 1024).  Two waves per SIMD:
 // with four (two workgroups on a CU) the double-precision transforms spill, 71
 // against 67 us at 1000 gates of N = 16384.
-template <int ST, int SG>
+template <int SG>
 __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   constexpr int W = EXP_WAVES, NT = 64 * W;
   constexpr bool WIDE = SG == 1, LONG = SG > 1;
@@ -918,6 +874,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   __shared__ float up_s[SG == 0 ? SUB : 1];      // M < 1024: the grid of 1024 points
   __shared__ float2 lags[LONG ? SG * SUB + 1 : WIDE ? 1 : SUB / 2 + 1];
   __shared__ double red[W];
+  __shared__ float red_hi[W];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -957,22 +914,28 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   constexpr int FIRST = WIDE ? 1 : 0, PER_ROUND = W - FIRST;
   auto class_of = [&](int task) { return task + 1 + task / rmask; };
 
+  GridStats st;
   double mean;
   float2* qs;  // (q[n], q[-n]), n < M / 2, and one zero more
   if constexpr (LONG) {
     // ---- the grid (its chunk sums are formed by then), two times SG complex points per thread, and the first pass of the inverse transform:
     // SG-point DFTs over points lg + 1024 j
     complex64d z[2][SG];
-    double part = 0.0;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int j = 0; j < SG; ++j) {
         const double2 s = reinterpret_cast<const double2*>(row)[tid + NT * t + SUB * j];
         z[t][j] = complex64d{s.x, s.y};
-        part += s.x + s.y;
+        st.add(s.x);
+        st.add(s.y);
       }
-    mean = block_mean(part, red, M);
+    st.reduce(red, red_hi, M);
+    if (!st.usable()) {  // uniform
+      if (share == 0 && tid == 0) redo_gate(a, g);
+      return;
+    }
+    mean = st.sum;
     qs = lags;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -1011,7 +974,13 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     }
   } else {
     // ---- the grid, chunk sums in ascending order
-    mean = block_mean(gather_grid(a, row, cs, sums, tid), red, M);
+    st = gather_grid(a, row, cs, sums, tid);
+    st.reduce(red, red_hi, M);
+    if (!st.usable()) {  // uniform
+      if (share == 0 && tid == 0) redo_gate(a, g);
+      return;
+    }
+    mean = st.sum;
 
     // ---- lags: up to conjugation and 1 / M the forward DFT of the real grid,
     // M <= 1024 zero-interleaved to 1024 points (which repeats its spectrum),
@@ -1077,7 +1046,6 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   }
 
   // ---- the classes
-  const bool ok = expandable(mean);
   auto grid_bin = [&](int k) -> float {
     if constexpr (LONG) return static_cast<float>(row[k]);
     if constexpr (SG == 0)
@@ -1125,7 +1093,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
       });
     }
     __syncthreads();
-    if (ok) {
+    {
       // the four bins k = 4 tid + u (+ 4 NT per step) this thread stores: their
       // staged rows, or -1: not of this round, or grid points
       int base[4];
@@ -1168,7 +1136,6 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     }
     if (z0 + PER_ROUND * a.blocks < n_tasks) __syncthreads();
   }
-  if (!ok && share == 0) direct_row<ST>(a, g, xs, dft16_consts(), tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1183,38 +1150,13 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 // of N = 16384: the pulse pass 400 us, the windows 27; by matrix products (each
 // pulse's K L) 1180.  100 x 64: 16.8 us against 23, latency of the two kernels.
 
-// Bins k0 + j, j0 <= j < j1, of gate g straight from its pulses (see direct_row).
-template <int ST>
-__device__ void direct_window(const FoldArgs& a, int g, int k0, int j0, int j1, int tid) {
-  using IO = BufferSample<ST>;
-  const int N = a.n_fft, L = a.code_len;
-  const int64_t gate_off = static_cast<int64_t>(a.first_gate) + static_cast<int64_t>(g) * a.gate_step;
-  float* out = a.out + static_cast<int64_t>(g) * a.n_bins;
-  for (int j = j0 + tid; j < j1; j += 64 * EXP_WAVES) {
-    const complex64d z = twiddle64(a.twiddle64, (k0 + j) & (N - 1));
-    float s = a.accumulate ? out[j] : 0.f;
-    for (int p = 0; p < a.n_pulses; ++p) {
-      const auto ds = row_desc(a.samples, static_cast<int64_t>(p) * a.stride + gate_off, IO::SIZE, L);
-      const auto dc = row_desc(a.tx, a.tx_per_pulse ? static_cast<int64_t>(p) * L : 0, 8, L);
-      complex64d h{0.0, 0.0};
-      for (int n = L - 1; n >= 0; --n) {
-        const u32x2 cr = __builtin_amdgcn_raw_buffer_load_b64(dc, 8 * n, 0, 0);
-        const float2 y = conj_mul(make_float2(__uint_as_float(cr.x), __uint_as_float(cr.y)),
-                                  IO::cvt(IO::load(ds, IO::SIZE * n)));
-        h = cmuladd(complex64d{y.x, y.y}, h, z);
-      }
-      s += static_cast<float>(h.x * h.x + h.y * h.y);
-    }
-    out[j] = s;
-  }
-}
-
-template <int ST, bool WIDE>
+template <bool WIDE>
 __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   __shared__ __attribute__((aligned(16))) double grid[WIDE ? 2 * SUB : SUB];
   __shared__ __attribute__((aligned(16))) complex64d lags[SUB + 1];
   __shared__ __attribute__((aligned(16))) double xd[XWAVE];
   __shared__ double red[EXP_WAVES], sums[EXP_WAVES][128];
+  __shared__ float red_hi[EXP_WAVES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = a.grid_len, N = a.n_fft, L = a.code_len, K = a.n_bins;
@@ -1225,12 +1167,13 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   const int r0 = K / 128 * part / a.blocks, r1 = K / 128 * (part + 1) / a.blocks;
   const int k0 = a.bin_start[g];
   const double* row = a.grid + static_cast<int64_t>(slot) * M;
-  const double mean = block_mean(
-      gather_grid(a, row, static_cast<int64_t>(a.rows) * M, grid, tid), red, M);
-  if (!expandable(mean)) {  // uniform
-    direct_window<ST>(a, g, k0, 128 * r0, 128 * r1, tid);
+  GridStats st = gather_grid(a, row, static_cast<int64_t>(a.rows) * M, grid, tid);
+  st.reduce(red, red_hi, M);
+  if (!st.usable()) {  // uniform
+    if (part == 0 && tid == 0) redo_gate(a, g);
     return;
   }
+  const double mean = st.sum;
 
   // z and z^n0 of the lane's two bins in the run from j0 on (for the first run read
   // before the lags are there)
@@ -1347,7 +1290,6 @@ hipError_t launch_grid(const FoldArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int ST>
 hipError_t launch_expand(FoldArgs a, hipStream_t s) {
   // with fewer gates than compute units a gate's rounds of classes go to several
   // workgroups, each forming the lags (N = 65536, one gate: 93 us by one)
@@ -1357,11 +1299,11 @@ hipError_t launch_expand(FoldArgs a, hipStream_t s) {
   a.blocks = std::max(1, std::min((tasks + per_round - 1) / per_round, 256 / a.rows));
   const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.blocks)), block(64 * EXP_WAVES);
   switch (a.grid_len / (2 * SUB)) {
-    case 0: hipLaunchKernelGGL((expand_grid<ST, 0>), grid, block, 0, s, a); break;
-    case 1: hipLaunchKernelGGL((expand_grid<ST, 1>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((expand_grid<ST, 2>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((expand_grid<ST, 4>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((expand_grid<ST, 8>), grid, block, 0, s, a); break;
+    case 0: hipLaunchKernelGGL((expand_grid<0>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((expand_grid<1>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((expand_grid<2>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((expand_grid<4>), grid, block, 0, s, a); break;
+    case 8: hipLaunchKernelGGL((expand_grid<8>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1382,14 +1324,70 @@ hipError_t pack_bits(FoldArgs& a, uint32_t* bits, int32_t* binary, hipStream_t s
   return hipGetLastError();
 }
 
-template <int ST>
 hipError_t launch_window(const FoldArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.blocks)), block(64 * EXP_WAVES);
   if (a.grid_len > SUB)
-    hipLaunchKernelGGL((expand_window<ST, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((expand_window<true>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((expand_window<ST, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((expand_window<false>), grid, block, 0, s, a);
   return hipGetLastError();
+}
+
+// Spectra of redone gates whose direct launch split its pulses into chunks, from the partials
+// by list slot, the chunks in ascending order.
+__global__ void __launch_bounds__(256)
+sum_redone(FusedArgs a, int zgroups) {
+  const int k = min(max(*a.gate_count, 0), a.n_gates);
+  const int chunks = adaptive_chunks(k, zgroups, a.adapt_target, a.adapt_max_chunks, a.adapt_rows);
+  if (chunks == 1) return;  // written by the launch itself
+  const int64_t n = static_cast<int64_t>(k) * a.n_fft, step = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += step) {
+    float s = 0.f;
+    for (int c = 0; c < chunks; ++c) s += a.adapt_partial[c * n + i];
+    float* dst = a.out + static_cast<int64_t>(a.gate_list[i / a.n_fft]) * a.n_fft + i % a.n_fft;
+    *dst = a.accumulate ? *dst + s : s;
+  }
+}
+
+// The gates that the expansion has left over, by direct transforms: pulses split over as many
+// workgroups as fill the chip for the number of gates there turn out to be, the partials in the
+// grid scratch (no longer read).  With none left over the launches find an empty list: 1.6 us
+// each.  (Recomputed by the gate's expansion workgroup, without a split, one such gate
+// held up a call by 100 times its time.)
+hipError_t redo_direct(const FusedArgs& f, hipStream_t s) {
+  FusedArgs d = f;
+  d.grid_len = 0;
+  d.gate_list = f.redo_list;
+  d.gate_count = f.redo_count;
+  d.chunks = 1;
+  d.adapt_partial = reinterpret_cast<float*>(f.grid);
+  d.adapt_target = f.redo_target;
+  d.adapt_max_chunks = f.redo_max_chunks;
+  d.adapt_rows = f.redo_rows;
+  hipError_t e = hipSuccess;
+  if (d.code_bits) {
+    e = launch_pack_code_bits_if(d.tx, d.tx_per_pulse ? d.n_pulses : 1, d.code_len,
+                                 const_cast<uint16_t*>(d.code_bits),
+                                 const_cast<int32_t*>(d.code_binary), f.redo_count, s);
+    if (e != hipSuccess) return e;
+  }
+  e = launch_fused(d, s);
+  if (e != hipSuccess || d.adapt_max_chunks == 1) return e;
+  const int zgroups = d.sub_len == SUB ? (1 << d.log2_r) / d.waves_per_block : 1 << d.log2_r;
+  hipLaunchKernelGGL(sum_redone, dim3(512), dim3(256), 0, s, d, zgroups);
+  return hipGetLastError();
+}
+
+// The same for zoom windows, by matrix products.
+hipError_t redo_products(const ZoomArgs& z, hipStream_t s) {
+  ZoomArgs d = z;
+  d.grid_len = 0;
+  d.gate_list = z.redo_list;
+  d.gate_count = z.redo_count;
+  const hipError_t e = launch_zoom(d, s, true);
+  if (e != hipSuccess || d.chunks == 1) return e;
+  return launch_reduce_chunks(d.partial, d.out, static_cast<int64_t>(d.n_gates) * d.n_bins, d.chunks,
+                              d.accumulate, d.n_bins, d.gate_list, d.gate_count, s);
 }
 
 }  // namespace
@@ -1418,6 +1416,8 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.accumulate = f.accumulate;
   a.gate_list = f.gate_list;
   a.gate_count = f.gate_count;
+  a.redo_list = f.redo_list;
+  a.redo_count = a.partial ? nullptr : f.redo_count;
   hipError_t e = pack_bits(a, f.grid_bits, f.grid_binary, s);
   if (e != hipSuccess) return e;
   if (a.grid_len == a.n_fft) {  // every bin is on the grid: partials by gate, no expansion
@@ -1451,7 +1451,8 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
       e = hipGetLastError();
     }
     if (e == hipSuccess)
-      e = f.sample_type == 1 ? launch_expand<1>(x, s) : launch_expand<0>(x, s);
+      e = launch_expand(x, s);
+    if (e == hipSuccess) e = redo_direct(f, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1480,6 +1481,8 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
   a.accumulate = z.accumulate;
   a.gate_list = z.gate_list;
   a.gate_count = z.gate_count;
+  a.redo_list = z.redo_list;
+  a.redo_count = z.redo_count;
   a.bin_start = z.bin_start;
   a.n_bins = z.n_bins;
   hipError_t e = pack_bits(a, z.grid_bits, z.grid_binary, s);
@@ -1489,7 +1492,8 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
     // a workgroup or more per gate, up to two per CU (each forms the gate's lags)
     a.blocks = std::max(1, std::min(z.n_bins / 128, 512 / a.rows));
     e = z.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
-    if (e == hipSuccess) e = z.sample_type == 1 ? launch_window<1>(a, s) : launch_window<0>(a, s);
+    if (e == hipSuccess) e = launch_window(a, s);
+    if (e == hipSuccess) e = redo_products(z, s);
   }
   return e;
 }

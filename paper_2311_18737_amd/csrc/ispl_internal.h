@@ -95,6 +95,12 @@ struct FusedArgs {
   int32_t grid_waves;
   int32_t grid_rows;
   int32_t grid_defer;        // grid_len = N: leave the chunk partials in `grid`
+  // Gates whose grid is not expanded run as a direct launch with this list, filled on the
+  // device ([grid_rows] entries; grid_len < N), chunked by the adaptive rule with these
+  // parameters and its partials in `grid`.
+  int32_t* redo_list;
+  int32_t* redo_count;
+  int32_t redo_target, redo_max_chunks, redo_rows;
 };
 
 // Words of one code row in the sign-bit form (one per first-pass thread).
@@ -134,6 +140,8 @@ struct FoldArgs {
   int32_t chunks, waves, tx_per_pulse, accumulate;
   const int32_t* gate_list;
   const int32_t* gate_count;
+  int32_t* redo_list;        // gates left to other launches, and their number
+  int32_t* redo_count;
   int32_t slot0, rows;
   // a window of n_bins bins per gate from bin_start[gate] on (out [G][n_bins])
   const int32_t* bin_start;
@@ -151,18 +159,23 @@ hipError_t launch_reduce_chunks(const float* partial, float* spectra, int64_t el
 
 // Static scratch of ispl_integrate_spectra_noalloc: twiddle table first, the
 // chunk partials after it.  Calls that run on a grid use the second part as the twiddle
-// table in double (NOALLOC_TWIDDLE64_BYTES), the grid points' gains (NOALLOC_GAIN_BYTES) and
-// the grid scratch after them.
+// table in double (NOALLOC_TWIDDLE64_BYTES), the grid points' gains and at NOALLOC_REDO_AT the
+// list of gates to redo (NOALLOC_GAIN_BYTES) and the grid scratch after them.
 constexpr size_t NOALLOC_TWIDDLE_BYTES = size_t{512} << 10;  // N <= 65536 complex64
 constexpr size_t NOALLOC_PARTIAL_BYTES = ISPL_NOALLOC_SCRATCH_BYTES - NOALLOC_TWIDDLE_BYTES;
 constexpr size_t NOALLOC_TWIDDLE64_BYTES = size_t{1} << 20;  // N <= 65536 complex128
-constexpr size_t NOALLOC_GAIN_BYTES = size_t{1} << 20;       // 16384 doubles, and room
+constexpr size_t NOALLOC_GAIN_BYTES = size_t{1} << 20;
+constexpr size_t NOALLOC_REDO_AT = size_t{128} << 10;        // behind 16384 gains
 // This GPU's copy of the array (`device` must be current); looked up once per
 // device.
 hipError_t noalloc_scratch(int device, unsigned char** base);
 // W_N^i, i < n_fft, as the context builds them: into `table` (complex64 pairs) and in
 // double into the NOALLOC_TWIDDLE64_BYTES that follow its NOALLOC_TWIDDLE_BYTES.
 hipError_t launch_build_twiddles(float* table, int32_t n_fft, hipStream_t stream);
+
+// The same unless *count is 0 on the device.
+hipError_t launch_pack_code_bits_if(const float* tx, int32_t rows, int32_t code_len, uint16_t* bits,
+                                    int32_t* binary, const int32_t* count, hipStream_t stream);
 
 hipError_t launch_fill_zero(float* dst, int64_t elems, hipStream_t stream);
 hipError_t launch_fill_zero_rows(float* dst, int32_t n_gates, int32_t n_fft, const int32_t* list,
@@ -205,7 +218,9 @@ struct ZoomArgs {
   uint32_t* code_bits;
   int32_t* code_binary;
   // Zoom from the pulse-summed grid of grid_len points instead (0: matrix
-  // products); see FusedArgs and launch_zoom_folded.  chunks is 1 then.
+  // products); see FusedArgs and launch_zoom_folded.  Gates left over run as products.
+  int32_t* redo_list;        // [grid_rows]
+  int32_t* redo_count;
   double* grid;
   uint32_t* grid_bits;
   int32_t* grid_binary;

@@ -550,7 +550,8 @@ __global__ void __launch_bounds__(1024) fused_spectra_long_dma(FusedArgs a) {
 // the whole row is +-1 + 0i.
 __global__ void __launch_bounds__(1024)
 pack_code_bits(const float2* __restrict__ tx, int32_t code_len, uint16_t* __restrict__ bits,
-               int32_t* __restrict__ binary) {
+               int32_t* __restrict__ binary, const int32_t* __restrict__ count) {
+  if (count && *count <= 0) return;  // no launch reads them
   const int row = blockIdx.x, lg = threadIdx.x;
   const float2* c = tx + static_cast<int64_t>(row) * code_len;
   uint32_t word = 0;
@@ -689,14 +690,9 @@ peak_pick(const float* __restrict__ spectra, int32_t n_gates, int32_t n_fft, int
 // with adaptive chunking the most work items any list length can ask for.
 int64_t fused_blocks(const FusedArgs& a, int zgroups) {
   if (a.adapt_target <= 0) return static_cast<int64_t>(a.n_gates) * zgroups * a.chunks;
-  auto items = [&](int k) {
-    return static_cast<int64_t>(k) * zgroups *
-           adaptive_chunks(k, zgroups, a.adapt_target, a.adapt_max_chunks, a.adapt_rows);
-  };
-  int64_t most = items(a.n_gates);
-  const int kmax = std::min(a.n_gates, a.adapt_target / zgroups + 1);
-  for (int k = 1; k <= kmax; ++k) most = std::max(most, items(k));
-  return most;
+  // k gates take k zgroups workgroups, or while there is room several chunks, within the target
+  const int64_t all = static_cast<int64_t>(a.n_gates) * zgroups;
+  return std::max(all, std::min<int64_t>(a.adapt_target, all * a.adapt_max_chunks));
 }
 
 template <int RW, int ST>
@@ -800,8 +796,13 @@ hipError_t launch_reduce_chunks(const float* partial, float* spectra, int64_t el
 
 hipError_t launch_pack_code_bits(const float* tx, int32_t rows, int32_t code_len,
                                  uint16_t* bits, int32_t* binary, hipStream_t stream) {
+  return launch_pack_code_bits_if(tx, rows, code_len, bits, binary, nullptr, stream);
+}
+
+hipError_t launch_pack_code_bits_if(const float* tx, int32_t rows, int32_t code_len, uint16_t* bits,
+                                    int32_t* binary, const int32_t* count, hipStream_t stream) {
   hipLaunchKernelGGL(pack_code_bits, dim3(static_cast<unsigned>(rows)), dim3(SUB), 0, stream,
-                     reinterpret_cast<const float2*>(tx), code_len, bits, binary);
+                     reinterpret_cast<const float2*>(tx), code_len, bits, binary, count);
   return hipGetLastError();
 }
 

@@ -707,7 +707,8 @@ __global__ void __launch_bounds__(256)
 pulse_prep(const void* __restrict__ samples, int32_t sample_type, const float* __restrict__ tx,
            int64_t stride, int64_t lo, int64_t hi, int32_t code_len, int32_t tx_per_pulse,
            int32_t* __restrict__ exps, int32_t words, uint32_t* __restrict__ bits,
-           int32_t* __restrict__ binary) {
+           int32_t* __restrict__ binary, const int32_t* __restrict__ count) {
+  if (count && *count <= 0) return;  // no gate listed
   const int p = static_cast<int>(blockIdx.x);
   if (exps)
     pulse_exponent_block(samples, sample_type, tx, stride, lo, hi, code_len, tx_per_pulse, p,
@@ -747,7 +748,8 @@ hipError_t launch_zoom(const ZoomArgs& a, hipStream_t stream, bool prep) {
   if (prep && (exps || a.code_bits)) {
     hipLaunchKernelGGL(pulse_prep, dim3(static_cast<unsigned>(a.n_pulses)), dim3(256), 0, stream,
                        a.samples, a.sample_type, a.tx, a.stride, a.row_lo, a.row_hi, a.code_len,
-                       a.tx_per_pulse, exps, a.code_pad / 32, a.code_bits, a.code_binary);
+                       a.tx_per_pulse, exps, a.code_pad / 32, a.code_bits, a.code_binary,
+                       a.gate_list ? a.gate_count : nullptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

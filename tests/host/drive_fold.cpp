@@ -50,7 +50,28 @@ hipError_t launch_fused(const FusedArgs& a, hipStream_t st) {
     const size_t sets = c.grid_chunks + (c.grid_len > 2 * SUB && c.grid_chunks > 1 ? 1 : 0);
     check_range(c.grid, sets * c.grid_rows * c.grid_len * sizeof(*c.grid), "grid sums");
     check_range(c.twiddle64, size_t(c.n_fft) * 16, "double twiddles");
+    check_range(c.grid_gain, size_t(c.grid_len) * 8, "grid gains");
   });
+  // the direct launch of gates that are not expanded, with few of them and with a full list
+  for (int k : {1, a.grid_rows}) {
+    if (a.grid_len == a.n_fft) break;
+    run_on(st, [c, k] {
+      check_range(c.redo_list, size_t(c.grid_rows) * 4, "redo list");
+      check_range(c.redo_count, 4, "redo count");
+      for (int i = 0; i < k; ++i) c.redo_list[i] = i;
+      *c.redo_count = k;
+      check_range(c.grid, size_t(c.redo_rows) * c.n_fft * 4, "redo partials");
+    });
+    FusedArgs d = a;
+    d.grid_len = 0;
+    d.gate_list = a.redo_list;
+    d.gate_count = a.redo_count;
+    d.adapt_partial = reinterpret_cast<float*>(a.grid);
+    d.adapt_target = a.redo_target;
+    d.adapt_max_chunks = a.redo_max_chunks;
+    d.adapt_rows = a.redo_rows;
+    (void)plain_fused(d, st);
+  }
   return hipSuccess;
 }
 
@@ -64,8 +85,13 @@ hipError_t launch_zoom(const ZoomArgs& a, hipStream_t st, bool prep) {
     check_range(c.grid, size_t(c.grid_chunks) * c.grid_rows * c.grid_len * sizeof(*c.grid),
                 "zoom grid sums");
     check_range(c.twiddle64, size_t(c.n_fft) * 16, "double twiddles");
+    check_range(c.grid_gain, size_t(c.grid_len) * 8, "grid gains");
+    check_range(c.redo_list, size_t(c.grid_rows) * 4, "redo list");
+    check_range(c.redo_count, 4, "redo count");
   });
-  return hipSuccess;
+  ZoomArgs d = a;  // the products of gates that are not expanded
+  d.grid_len = 0;
+  return plain_zoom(d, st, true);
 }
 
 }  // namespace ispl
