@@ -103,10 +103,13 @@ ispl_status ispl_create(const ispl_config* cfg, ispl_ctx** out);
  *   n_pulses  0 <= n_pulses <= max_pulses.  With 0 pulses the sum is empty:
  *             spectra is zeroed (accumulate = 0) or left as is (accumulate = 1).
  * Arithmetic: decode, transform, power and accumulation in FP32.  Codes of at
- * most 8192 samples may be summed over the pulses on a grid of 2^m >= 2 L - 1
- * frequencies (where that is estimated to be faster), from which the N bins follow
- * exactly (|X|^2 of L samples has 2 L - 1 coefficients; this step in double precision);
- * S >= 0 as in the direct form.
+ * most 8192 samples may be transformed to a grid of 2^m >= 2 L - 1 frequencies instead
+ * (where that is estimated to be faster), the powers summed over the pulses in double, and
+ * the N bins formed from the sums (|X|^2 of L samples has 2 L - 1 coefficients).  A gate
+ * whose grid holds a line or a gap so strong that its bins would be less exact than the direct
+ * transform's, or infinities or NaN, is then redone by direct transforms, decided on the
+ * device: a call in which every gate has such a line takes up to the time of both (12 % more than
+ * direct transforms at L = 1000, N = 16384).  S >= 0 in either form.
  */
 ispl_status ispl_integrate_spectra(ispl_ctx* ctx, const void* samples,
                                    const float* tx_code, int32_t tx_per_pulse,
@@ -190,10 +193,10 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
  * high and low halves (three split products each, FP32 accumulation);
  * decode, shift and the pulse sum stay FP32.  The result is the same
  * quantity as ispl_integrate_spectra at those bins (Section 2.2, Eqs. 7-8),
- * at the precision of the chosen split.  Codes of at most 1024 samples sum the
- * pulses in FP32 on a grid of 2^m >= 2 L - 1 points instead and take the
- * windows from it in double precision, for either precision (relative error
- * about 1e-7, that of ispl_integrate_spectra).
+ * at the precision of the chosen split.  Codes of at most 1024 samples may be
+ * transformed in FP32 to a grid of 2^m >= 2 L - 1 points instead, the powers summed and the
+ * windows taken from it in double precision, where that is at least as exact as the chosen
+ * split's products (decided per gate on the device; the others run as products).
  */
 typedef enum {
   ISPL_ZOOM_BF16X3 = 0,  /* BF16 hi/lo split: ~16 significant bits per product */

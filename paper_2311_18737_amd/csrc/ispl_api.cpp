@@ -241,7 +241,8 @@ double expand_us(const ispl_config& c, int len) {
   const int rounds = std::max(1, (tasks + per_round - 1) / per_round);
   const int blocks = std::max(1, std::min(rounds, kComputeUnits / c.n_gates));
   const int64_t passes = (static_cast<int64_t>(c.n_gates) * blocks + kComputeUnits - 1) / kComputeUnits;
-  return 4.0 + passes * (6.0 + len / 1024.0 + ((rounds + blocks - 1) / blocks) * (5.0 + c.fft_len / 4300.0));
+  // (with the launches that find no gate to redo)
+  return (c.code_len > 2 * ispl::SUB ? 10.0 : 7.0) + passes * (6.0 + len / 1024.0 + ((rounds + blocks - 1) / blocks) * (5.0 + c.fft_len / 4300.0));
 }
 
 // Estimated time of the direct transform: rounds of its plan's workgroups, a fixed
@@ -269,6 +270,10 @@ int32_t grid_run(int32_t n_gates, int64_t most) {
   return static_cast<int32_t>((n_gates + runs - 1) / runs);
 }
 
+// Fewest pulses of a call that sums on a shorter grid: the spectrum of a single pulse of noise
+// has bins so far below its mean that most gates would be redone.
+constexpr int32_t kMinFoldPulses = 2;
+
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks = 0) {
   GridPlan fold{}, whole{};
   const int len = grid_length(c);
@@ -277,10 +282,11 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks 
   const double whole_us = c.fft_len <= 2 * ispl::SUB || len == c.fft_len
                               ? grid_split(c, c.fft_len, n_pulses, force_chunks, &whole)
                               : 0.0;
-  if (len == c.fft_len) return whole;
+  if (len == c.fft_len || n_pulses < kMinFoldPulses) return whole;
   const double fold_us = grid_split(c, len, n_pulses, force_chunks, &fold) + expand_us(c, len);
-  if (whole.len > 0) return fold_us < whole_us ? fold : whole;
-  return fold_us < direct_us(c, n_pulses) ? fold : GridPlan{};
+  // gates with a strong line are redone, so a call may cost both: folded from a quarter less on
+  if (whole.len > 0) return fold_us < 0.75 * whole_us ? fold : whole;
+  return fold_us < 0.75 * direct_us(c, n_pulses) ? fold : GridPlan{};
 }
 
 // Scratch of a context whose calls run on a grid (0: they never do): the chunk
@@ -490,7 +496,7 @@ ZoomPlan zoom_plan(int32_t n_gates, int32_t n_bins, int32_t n_pulses) {
 GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_pulses) {
   GridPlan gp{};
   const int len = c.code_len <= ispl::SUB ? grid_length(c) : 0;
-  if (len > 0 && n_pulses >= 1) grid_split(c, len, n_pulses, 0, &gp);
+  if (len > 0 && n_pulses >= kMinFoldPulses) grid_split(c, len, n_pulses, 0, &gp);
   return gp;
 }
 

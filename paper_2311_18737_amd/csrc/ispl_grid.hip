@@ -25,6 +25,7 @@
 // without the gain 2.0e-6 / 5.7e-6 / 1.7e-5); without a line 1.0e-7 to 1.4e-7, direct 4e-7 to 6e-7.
 
 #include <float.h>
+#include <math.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -799,36 +800,46 @@ struct alignas(4) Float4u {
   float v[4];
 };
 
-// A gate's grid of m points: its mean and its largest value.
+// A gate's grid of m points: its mean, largest and smallest value.
 struct GridStats {
   double sum = 0.0;
-  float hi = 0.f;
+  float hi = 0.f, lo = FLT_MAX;
   __device__ __forceinline__ void add(double v) {
     sum += v;
     hi = fmaxf(hi, static_cast<float>(v));
+    lo = fminf(lo, static_cast<float>(v));
   }
   // Over the workgroup, from each thread's part; sum becomes the mean.
-  __device__ __forceinline__ void reduce(double* red, float* red_hi, int m) {
+  __device__ __forceinline__ void reduce(double* red, float2* red_ends, int m) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
       sum += __shfl_xor(sum, off);
       hi = fmaxf(hi, __shfl_xor(hi, off));
+      lo = fminf(lo, __shfl_xor(lo, off));
     }
     if ((threadIdx.x & 63) == 0) {
       red[threadIdx.x >> 6] = sum;
-      red_hi[threadIdx.x >> 6] = hi;
+      red_ends[threadIdx.x >> 6] = make_float2(hi, lo);
     }
     __syncthreads();
     sum = 0.0;
 #pragma unroll
     for (int i = 0; i < EXP_WAVES; ++i) {
       sum += red[i];
-      hi = fmaxf(hi, red_hi[i]);
+      hi = fmaxf(hi, red_ends[i].x);
+      lo = fminf(lo, red_ends[i].y);
     }
     sum /= static_cast<double>(m);
   }
-  // Whether the bins may follow from the grid: its points finite, and as FP32.
-  __device__ __forceinline__ bool usable() const { return sum - sum == 0.0 && hi <= FLT_MAX; }
+  // Whether the bins follow from the grid at no more than a direct transform's error.  That is
+  // about 7 roundings of sqrt(S mean S) in a bin of power S, the grid's about that of its largest
+  // point, over the square root of the samples that a bin's rounding averages and whatever the
+  // distance of the bin; so hi^2 <= limit mean lo, the limit as measured (launch_folded).
+  // Infinite and NaN points fail.
+  __device__ __forceinline__ bool usable(float limit) const {
+    const double h = hi;
+    return sum - sum == 0.0 && hi <= FLT_MAX && h * h <= limit * sum * lo;
+  }
 };
 
 // Leaves gate g to the launches that follow (one thread per gate).
@@ -874,7 +885,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   __shared__ float up_s[SG == 0 ? SUB : 1];      // M < 1024: the grid of 1024 points
   __shared__ float2 lags[LONG ? SG * SUB + 1 : WIDE ? 1 : SUB / 2 + 1];
   __shared__ double red[W];
-  __shared__ float red_hi[W];
+  __shared__ float2 red_ends[W];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -914,6 +925,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   constexpr int FIRST = WIDE ? 1 : 0, PER_ROUND = W - FIRST;
   auto class_of = [&](int task) { return task + 1 + task / rmask; };
 
+  // (FP32 lags of so small a spectrum lose bits)
+  auto tiny = [](const GridStats& s) { return s.hi > 0.f && s.hi < 1e-30f; };
   GridStats st;
   double mean;
   float2* qs;  // (q[n], q[-n]), n < M / 2, and one zero more
@@ -930,8 +943,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
         st.add(s.x);
         st.add(s.y);
       }
-    st.reduce(red, red_hi, M);
-    if (!st.usable()) {  // uniform
+    st.reduce(red, red_ends, M);
+    if (!st.usable(a.peak_limit) || tiny(st)) {  // uniform
       if (share == 0 && tid == 0) redo_gate(a, g);
       return;
     }
@@ -975,8 +988,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   } else {
     // ---- the grid, chunk sums in ascending order
     st = gather_grid(a, row, cs, sums, tid);
-    st.reduce(red, red_hi, M);
-    if (!st.usable()) {  // uniform
+    st.reduce(red, red_ends, M);
+    if (!st.usable(a.peak_limit) || tiny(st)) {  // uniform
       if (share == 0 && tid == 0) redo_gate(a, g);
       return;
     }
@@ -1156,7 +1169,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   __shared__ __attribute__((aligned(16))) complex64d lags[SUB + 1];
   __shared__ __attribute__((aligned(16))) double xd[XWAVE];
   __shared__ double red[EXP_WAVES], sums[EXP_WAVES][128];
-  __shared__ float red_hi[EXP_WAVES];
+  __shared__ float2 red_ends[EXP_WAVES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = a.grid_len, N = a.n_fft, L = a.code_len, K = a.n_bins;
@@ -1168,8 +1181,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   const int k0 = a.bin_start[g];
   const double* row = a.grid + static_cast<int64_t>(slot) * M;
   GridStats st = gather_grid(a, row, static_cast<int64_t>(a.rows) * M, grid, tid);
-  st.reduce(red, red_hi, M);
-  if (!st.usable()) {  // uniform
+  st.reduce(red, red_ends, M);
+  if (!st.usable(a.peak_limit)) {  // uniform
     if (part == 0 && tid == 0) redo_gate(a, g);
     return;
   }
@@ -1333,6 +1346,17 @@ hipError_t launch_window(const FoldArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// A grid with points hi, lo and mean is expanded while hi / sqrt(mean lo) <= 12 L^(1/4).
+// Largest errors over max(S, mean S) there and of direct transforms, one line per gate
+// (100 pulses, 60 from L = 4000 on; sets of 40 to 600 gates, complex64), with hi / sqrt(mean lo):
+//   L =   64   24: 3.0e-7, 4.3e-7    41: 5.1e-7, 3.7e-7
+//   L =  256   33: 2.4e-7, 6.3e-7    61: 3.9e-7, 5.8e-7    (8 pulses: 33: 3.6e-7, 5.6e-7)
+//   L = 1000   42: 2.8e-7, 4.8e-7   116: 7.2e-7, 4.5e-7
+//   L = 2000   83: 3.4e-7, 5.1e-7   249: 1.1e-6, 5.3e-7
+//   L = 8000   40: 2.0e-7, 4.2e-7   374: 9.2e-7, 5.3e-7
+// The noise of 2 pulses has 20 to 70, of 100 pulses 2.
+constexpr float kPeakLimit = 144.f;
+
 // Spectra of redone gates whose direct launch split its pulses into chunks, from the partials
 // by list slot, the chunks in ascending order.
 __global__ void __launch_bounds__(256)
@@ -1418,6 +1442,7 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.gate_count = f.gate_count;
   a.redo_list = f.redo_list;
   a.redo_count = a.partial ? nullptr : f.redo_count;
+  a.peak_limit = kPeakLimit * std::sqrt(static_cast<float>(a.code_len));
   hipError_t e = pack_bits(a, f.grid_bits, f.grid_binary, s);
   if (e != hipSuccess) return e;
   if (a.grid_len == a.n_fft) {  // every bin is on the grid: partials by gate, no expansion
@@ -1483,6 +1508,8 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
   a.gate_count = z.gate_count;
   a.redo_list = z.redo_list;
   a.redo_count = z.redo_count;
+  // (BF16 products round 16 times as coarsely)
+  a.peak_limit = (z.precision == 1 ? 1.f : 256.f) * kPeakLimit * std::sqrt(static_cast<float>(a.code_len));
   a.bin_start = z.bin_start;
   a.n_bins = z.n_bins;
   hipError_t e = pack_bits(a, z.grid_bits, z.grid_binary, s);

@@ -142,6 +142,7 @@ struct FoldArgs {
   const int32_t* gate_count;
   int32_t* redo_list;        // gates left to other launches, and their number
   int32_t* redo_count;
+  float peak_limit;          // see GridStats
   int32_t slot0, rows;
   // a window of n_bins bins per gate from bin_start[gate] on (out [G][n_bins])
   const int32_t* bin_start;

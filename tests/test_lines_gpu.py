@@ -85,3 +85,83 @@ def test_line_below_the_noise(ispl, shape, sample_type):
     err = (np.abs(got - ref) / np.maximum(ref, mean)).max(axis=1)
     bound = 2.0 ** -24 * (10.0 + ref.max(axis=1) / mean[:, 0] / 6.0)
     assert (err <= bound).all(), (err / bound).max()
+
+
+@pytest.mark.parametrize("sample_type", ["c64", "ci16"])
+@pytest.mark.parametrize("snr_db", [0.0, 10.0, 20.0, 40.0])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "L{}_N{}_G{}_P{}".format(*s))
+def test_line_above_the_noise(ispl, shape, snr_db, sample_type):
+    """Bins of power S are off by no more than an FP32 transform's rounding, d = 2^-25 x 64 of the
+    gate's mean amplitude (4 deviations of 16 passes of two roundings), however strong the line: 2 d
+    sqrt(S mean S) + d^2 mean S."""
+    L, N, G, P = shape
+    lines = Lines(L, N, G, P, snr_db, seed=L + 1, sample_type=sample_type)
+    got, ref = lines.run(ispl), lines.ref
+    mean = ref.mean(axis=1, keepdims=True)
+    d = 2.0 ** -25 * 64.0
+    bound = 2.0 * d * np.sqrt(ref * np.maximum(ref, mean)) + d * d * mean
+    err = np.abs(got - ref) / bound
+    assert err.max() <= 1.0, err.max()
+
+
+@pytest.mark.parametrize("precision", ["fp16x3", "bf16x3"])
+@pytest.mark.parametrize("snr_db", [-10.0, 0.0, 20.0, 40.0])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] <= 1000],
+                         ids=lambda s: "L{}_N{}_G{}_P{}".format(*s))
+def test_zoom_windows_of_lines(ispl, shape, snr_db, precision):
+    """Windows at, beside and far from a line, as exact as split products: d = 8 x 2^-22 or 8 x 2^-16
+    of the gate's mean amplitude."""
+    L, N, G, P = shape
+    K = 256
+    lines = Lines(L, N, G, P, snr_db, seed=L + 2)
+    ref = lines.ref
+    start = np.zeros(G, dtype=np.int32)
+    for i, g in enumerate(lines.gates):
+        start[g] = int(ref[i].argmax()) - (128, 128, 2 * K, N // 2)[i % 4]
+    ctx = ispl.Context(max_pulses=P, **lines.geo)
+    zoom = ispl.Zoom(ctx, K, precision)
+    out = zoom.spectra(torch.from_numpy(lines.x).to(DEV), torch.from_numpy(lines.tx).to(DEV),
+                       torch.from_numpy(start).to(DEV))
+    got = out[lines.gates].cpu().numpy().astype(np.float64)
+    zoom.close()
+    ctx.close()
+    idx = (start[lines.gates].astype(np.int64)[:, None] + np.arange(K)) % N
+    mean = ref.mean(axis=1, keepdims=True)
+    want = np.take_along_axis(ref, idx, axis=1)
+    d = 8.0 * 2.0 ** (-22 if precision == "fp16x3" else -16)
+    bound = 2.0 * d * np.sqrt(want * np.maximum(want, mean)) + d * d * mean
+    err = np.abs(got - want) / bound
+    assert err.max() <= 1.0, err.max()
+
+
+@pytest.mark.parametrize("shape", [(256, 16384, 300, 100), (1000, 16384, 200, 64)],
+                         ids=lambda s: "L{}_N{}_G{}_P{}".format(*s))
+def test_power_far_below_the_mean(ispl, shape):
+    """Noise filtered to a fifth of the band (after decoding): the stop band, 60 dB down, keeps the
+    accuracy of an FP32 transform."""
+    L, N, G, P = shape
+    rng = np.random.default_rng(L)
+    step = L
+    stride = G * step
+    tx = (rng.integers(0, 2, (P, L)) * 2 - 1).astype(np.complex64)
+    taper = np.blackman(L)
+    f = np.fft.fftfreq(L)
+    keep = np.abs(f) < 0.1
+    y = np.empty((P, G, L), dtype=np.complex64)
+    for p in range(P):
+        z = (rng.standard_normal((G, L)) + 1j * rng.standard_normal((G, L))) * np.where(keep, 1.0, 1e-3)
+        y[p] = np.fft.ifft(z, axis=1) * taper * np.sqrt(L)
+    x = (y * tx[:, None, :]).reshape(P, stride)
+    gates = list(range(0, G, 37))
+    ref = oracle_spectra(x, tx, n_gates=G, gate_step=step, first_gate=0, fft_len=N, tx_per_pulse=True,
+                         gates=gates)
+    ctx = ispl.Context(code_len=L, fft_len=N, n_gates=G, gate_step=step, pulse_stride=stride,
+                       max_pulses=P)
+    out = ctx.integrate_spectra(torch.from_numpy(x).to(DEV), torch.from_numpy(tx).to(DEV))
+    got = out[gates].cpu().numpy().astype(np.float64)
+    ctx.close()
+    mean = ref.mean(axis=1, keepdims=True)
+    assert (ref < 1e-4 * mean).any()
+    d = 2.0 ** -25 * 64.0
+    bound = 2.0 * d * np.sqrt(ref * np.maximum(ref, mean)) + d * d * mean
+    assert (np.abs(got - ref) / bound).max() <= 1.0
