@@ -237,8 +237,7 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force
 double expand_us(const ispl_config& c, int len) {
   const int ratio = c.fft_len / std::max<int>(len, ispl::SUB), half = c.fft_len / ispl::SUB / 2;
   const int tasks = ratio == 1 ? 0 : half - half / ratio;
-  const int per_round = len == 2 * ispl::SUB ? 7 : 8;
-  const int rounds = std::max(1, (tasks + per_round - 1) / per_round);
+  const int rounds = std::max(1, (tasks + 7) / 8);
   const int blocks = std::max(1, std::min(rounds, kComputeUnits / c.n_gates));
   const int64_t passes = (static_cast<int64_t>(c.n_gates) * blocks + kComputeUnits - 1) / kComputeUnits;
   // (with the launches that find no gate to redo)
@@ -270,9 +269,9 @@ int32_t grid_run(int32_t n_gates, int64_t most) {
   return static_cast<int32_t>((n_gates + runs - 1) / runs);
 }
 
-// Fewest pulses of a call that sums on a shorter grid: the spectrum of a single pulse of noise
-// has bins so far below its mean that most gates would be redone.
-constexpr int32_t kMinFoldPulses = 2;
+// Fewest pulses of a call that sums on a shorter grid: the noise of one or two has bins so far
+// below its mean that many gates would be redone.
+constexpr int32_t kMinFoldPulses = 3;
 
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks = 0) {
   GridPlan fold{}, whole{};

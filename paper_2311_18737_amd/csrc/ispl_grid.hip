@@ -21,8 +21,9 @@
 // powers are squared and summed in double (7 to 10 % of the pass; sums of 32 pulses in FP32
 // before that), and a point's sum is multiplied by the known gain of its FP32 twiddles
 // (ispl_gain.h).  Largest error over max(S, mean S) with a line at -10 dB per sample, L = 1000 /
-// 2000 / 4000: 7e-7 / 1.1e-6 / 1.7e-6 (FP32 sums 3.1e-6 / 7.5e-6 / 1.2e-5, double ones
-// without the gain 2.0e-6 / 5.7e-6 / 1.7e-5); without a line 1.0e-7 to 1.4e-7, direct 4e-7 to 6e-7.
+// 2000 / 4000: 4e-7 / 8e-7 / 1.7e-6 (FP32 sums 3.1e-6 / 7.5e-6 / 1.2e-5, double ones
+// without the gain 2.0e-6 / 5.7e-6 / 1.7e-5; direct 5e-7); without a line 1.0e-7 to 1.4e-7, direct
+// 4e-7 to 6e-7.  Gates with a line too strong for that are redone by direct transforms (peak_limit).
 
 #include <float.h>
 #include <math.h>
@@ -751,8 +752,9 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
 // The transforms run in double precision: a line of power S_l leaves rounding of
 // about 1e-7 S_l at its mirror frequency and other places of an FP32
 // transform's structure, where S may be a hundred times smaller, which no direct
-// transform does (1000 gates of N = 16384 take 69 us, in FP32 50).  The lags are FP32: their
-// rounding is spread evenly over all bins, 2^-24 of the spectrum's fluctuation about its mean.
+// transform does (1000 gates of N = 16384 take 69 us, in FP32 50).  The lags are double too (FP32
+// for M = 16384, where they would not fit): with FP32 lags a line at -10 dB left 7e-7 at L = 1000,
+// now 4e-7.
 
 // SG-point DFT in place, natural order (SG = 2, 4 or 8).
 template <int SG>
@@ -834,7 +836,7 @@ struct GridStats {
   // Whether the bins follow from the grid at no more than a direct transform's error.  That is
   // about 7 roundings of sqrt(S mean S) in a bin of power S, the grid's about that of its largest
   // point, over the square root of the samples that a bin's rounding averages and whatever the
-  // distance of the bin; so hi^2 <= limit mean lo, the limit as measured (launch_folded).
+  // distance of the bin; so hi^2 <= limit mean lo, the limit as measured (peak_limit).
   // Infinite and NaN points fail.
   __device__ __forceinline__ bool usable(float limit) const {
     const double h = hi;
@@ -883,7 +885,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   __shared__ __attribute__((aligned(16))) float2 xs[W * XWAVE];
   __shared__ __attribute__((aligned(16))) double sums[LONG ? 1 : 2 * SUB];  // M <= 2048: the grid
   __shared__ float up_s[SG == 0 ? SUB : 1];      // M < 1024: the grid of 1024 points
-  __shared__ float2 lags[LONG ? SG * SUB + 1 : WIDE ? 1 : SUB / 2 + 1];
+  // q[n] and q[-n], n < M / 2, and one zero more (before that a transform's parts); in double
+  // where they fit
+  using lag_t = std::conditional_t<SG == 8, float, double>;
+  __shared__ lag_t qp[LONG ? SG * SUB + 1 : SUB + 1], qm[LONG ? SG * SUB + 1 : SUB + 1];
   __shared__ double red[W];
   __shared__ float2 red_ends[W];
 
@@ -891,7 +896,6 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = a.grid_len, N = a.n_fft, L = a.code_len, R = N / SUB;
   const int lr = __builtin_ctz(R);
-  const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   const double* tw64 = a.twiddle64;
   float* xf = reinterpret_cast<float*>(xs);
   float2* xw = xs + wave * XWAVE;
@@ -903,33 +907,37 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   if (g < 0) return;
   const double* const row = a.grid + static_cast<int64_t>(slot) * M;
   const int64_t cs = static_cast<int64_t>(a.rows) * M;
-  const float scale = 1.f / static_cast<float>(M);
+  const double scale = 1.0 / static_cast<double>(M);
 
-  // The lags n and m = n_cpx - n in place of F[n], F[m] (F: the transform of the
-  // complex points z[2 a] + i z[2 a + 1]); with r = conj(DFT) / M
-  // qs[n] = (q[n], q[-n]) = (Re r + Im r, Re r - Im r).
-  auto untangle = [&](float2* qs, int n, float2 p, float2 m) {
-    float2 f = make_float2(0.f, 0.f);
-    if (n > 0 && n < L) {
-      const float2 E = make_float2(0.5f * (p.x + m.x), 0.5f * (p.y - m.y));
-      const float2 O = make_float2(0.5f * (p.y + m.y), 0.5f * (m.x - p.x));
-      f = cmuladd(E, tw[n * (N / M)], O);
-    }
-    qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
+  // With r = conj(DFT) / M the lags n are q[n] = Re r + Im r, q[-n] = Re r - Im r.
+  auto put_lag = [&](int n, complex64d f) {
+    qp[n] = static_cast<lag_t>(scale * (f.x - f.y));
+    qm[n] = static_cast<lag_t>(scale * (f.x + f.y));
   };
+  // The lags n and m = n_cpx - n in place of F[n], F[m] (F: the transform of the
+  // complex points z[2 a] + i z[2 a + 1]).
+  auto untangle = [&](int n, complex64d p, complex64d m) {
+    complex64d f{0.0, 0.0};
+    if (n > 0 && n < L) {
+      const complex64d E{0.5 * (p.x + m.x), 0.5 * (p.y - m.y)};
+      const complex64d O{0.5 * (p.y + m.y), 0.5 * (m.x - p.x)};
+      f = cmuladd(E, twiddle64(tw64, n * (N / M)), O);
+    }
+    put_lag(n, f);
+  };
+  auto get = [&](int n) { return complex64d{qp[n], qm[n]}; };
 
   // the classes 1 ... R / 2 that do not lie on the grid (multiples of `ratio` do),
-  // one per wave and round; at M = 2048 the lags keep wave 0's region
+  // one per wave and round
   const int ratio = N / max(M, SUB), lratio = __builtin_ctz(ratio), rmask = ratio - 1;
   const int n_tasks = ratio == 1 ? 0 : R / 2 - ((R / 2) >> lratio);
-  constexpr int FIRST = WIDE ? 1 : 0, PER_ROUND = W - FIRST;
+  constexpr int PER_ROUND = W;
   auto class_of = [&](int task) { return task + 1 + task / rmask; };
 
   // (FP32 lags of so small a spectrum lose bits)
-  auto tiny = [](const GridStats& s) { return s.hi > 0.f && s.hi < 1e-30f; };
+  auto tiny = [](const GridStats& s) { return SG == 8 && s.hi > 0.f && s.hi < 1e-30f; };
   GridStats st;
   double mean;
-  float2* qs;  // (q[n], q[-n]), n < M / 2, and one zero more
   if constexpr (LONG) {
     // ---- the grid (its chunk sums are formed by then), two times SG complex points per thread, and the first pass of the inverse transform:
     // SG-point DFTs over points lg + 1024 j
@@ -949,7 +957,6 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
       return;
     }
     mean = st.sum;
-    qs = lags;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
 #pragma unroll
@@ -975,15 +982,17 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     if (wave < SG) {
       wave_lds_sync();
       class_transform64(v, xd, tw64, M / 2, N, wave, lane, [&](int i, complex64d f) {
-        lags[wave + SG * bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
+        const int n = wave + SG * bin_of(i, lane);
+        qp[n] = static_cast<lag_t>(f.x);
+        qm[n] = static_cast<lag_t>(f.y);
       });
     }
     __syncthreads();
     constexpr int NC = SG * SUB;
     for (int n = tid; n <= NC / 2; n += NT) {
-      const float2 A = lags[n], B = lags[n == 0 ? 0 : NC - n];
-      untangle(lags, n, A, B);
-      untangle(lags, NC - n, B, A);  // n = 0: the zero past the last lag
+      const complex64d A = get(n), B = get(n == 0 ? 0 : NC - n);
+      untangle(n, A, B);
+      untangle(NC - n, B, A);  // n = 0: the zero past the last lag
     }
   } else {
     // ---- the grid, chunk sums in ascending order
@@ -997,21 +1006,20 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 
     // ---- lags: up to conjugation and 1 / M the forward DFT of the real grid,
     // M <= 1024 zero-interleaved to 1024 points (which repeats its spectrum),
-    // M = 2048 as complex points (its lags in wave 0's own region)
-    qs = WIDE ? xs : lags;
+    // M = 2048 as complex points
     if (wave == 0) {
-      // (the sinks write into the wave's own exchange buffer, whose reads are
-      // all issued by then)
       complex64d v[16];
+      auto to_lags = [&](int i, complex64d f) {
+        qp[bin_of(i, lane)] = static_cast<lag_t>(f.x);
+        qm[bin_of(i, lane)] = static_cast<lag_t>(f.y);
+      };
       if constexpr (WIDE) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           const double2 p = reinterpret_cast<const double2*>(sums)[lane + 64 * j];
           v[j] = complex64d{p.x - mean, p.y - mean};
         }
-        class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d f) {
-          xw[bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
-        });
+        class_transform64(v, xd, tw64, SUB, N, 0, lane, to_lags);
       } else {
         const int lup = __builtin_ctz(SUB / M), up = (1 << lup) - 1;
 #pragma unroll
@@ -1019,25 +1027,22 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
           const int n = lane + 64 * j;
           v[j] = complex64d{(n & up) == 0 ? sums[n >> lup] - mean : 0.0, 0.0};
         }
-        class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d f) {
-          xw[bin_of(i, lane)] = make_float2(static_cast<float>(f.x), static_cast<float>(f.y));
-        });
+        class_transform64(v, xd, tw64, SUB, N, 0, lane, to_lags);
         wave_lds_sync();
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           const int n = lane + 64 * j;
-          const float2 f = n > 0 && n < L ? xw[n] : make_float2(0.f, 0.f);
-          if (n < M / 2) qs[n] = make_float2(scale * (f.x - f.y), scale * (f.x + f.y));
+          if (n < M / 2) put_lag(n, n > 0 && n < L ? get(n) : complex64d{0.0, 0.0});
         }
-        if (lane == 0) qs[M / 2] = make_float2(0.f, 0.f);
+        if (lane == 0) put_lag(M / 2, complex64d{0.0, 0.0});
         if (M < SUB) {  // class 0
           wave_lds_sync();
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int n = lane + 64 * j, m = SUB - n;
-            const float qp = 64 * j < M / 2 ? qs[n].x : 0.f;
-            const float qm = 64 * (15 - j) < M / 2 ? qs[m].y : 0.f;
-            v[j] = complex64d{static_cast<double>(qp) + static_cast<double>(qm), 0.0};
+            const double rp = 64 * j < M / 2 ? qp[n] : 0.0;
+            const double rm = 64 * (15 - j) < M / 2 ? qm[m] : 0.0;
+            v[j] = complex64d{rp + rm, 0.0};
           }
           class_transform64(v, xd, tw64, SUB, N, 0, lane, [&](int i, complex64d F) {
             const int k = bin_of(i, lane);
@@ -1051,10 +1056,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     if constexpr (WIDE) {
       __syncthreads();
       static_assert(NT == SUB / 2, "a pair of lags per thread, thread 0 also the middle one");
-      const float2 A = xs[tid], B = xs[tid == 0 ? SUB / 2 : SUB - tid];
-      untangle(qs, tid, A, B);
-      untangle(qs, SUB - tid, B, A);  // tid = 0: the zero past the last lag
-      if (tid == 0) untangle(qs, SUB / 2, B, B);
+      const complex64d A = get(tid), B = get(tid == 0 ? SUB / 2 : SUB - tid);
+      untangle(tid, A, B);
+      untangle(SUB - tid, B, A);  // tid = 0: the zero past the last lag
+      if (tid == 0) untangle(SUB / 2, B, B);
     }
   }
 
@@ -1068,9 +1073,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   const bool one_round = n_tasks <= PER_ROUND;
   for (int z0 = PER_ROUND * share; z0 == 0 || z0 < n_tasks; z0 += PER_ROUND * a.blocks) {
     const int n_cls = min(PER_ROUND, n_tasks - z0);  // 0: every bin is on the grid
-    const int task = wave - FIRST;
-    const bool mine = task >= 0 && task < n_cls;
-    const int k1 = mine ? class_of(z0 + task) : 0;
+    const bool mine = wave < n_cls;
+    const int k1 = mine ? class_of(z0 + wave) : 0;
     __syncthreads();  // the lags (first round) are written, the regions free
     if (mine) {
       complex64d v[16];
@@ -1078,9 +1082,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 #pragma unroll
       for (int j = 0; j < 16; ++j) {  // q[n] and q[n - 1024], n = lane + 64 j
         const int n = lane + 64 * j, m = SUB - n;
-        const double qp = LONG || 64 * j < M / 2 ? qs[n].x : 0.f;
-        const double qm = LONG || 64 * (15 - j) < M / 2 ? qs[m].y : 0.f;
-        v[j] = complex64d{fma(r1.x, qm, qp), -r1.y * qm};
+        const double rp = LONG || 64 * j < M / 2 ? qp[n] : 0.0;
+        const double rm = LONG || 64 * (15 - j) < M / 2 ? qm[m] : 0.0;
+        v[j] = complex64d{fma(r1.x, rm, rp), -r1.y * rm};
       }
       if constexpr (LONG) {
 #pragma unroll 1
@@ -1090,9 +1094,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int n = lane + 64 * j + SUB * s, m = SUB * (s + 1) - lane - 64 * j;
-            const double qp = qs[n].x, qm = qs[m].y;
-            v[j].x = fma(b.x, qm, fma(f.x, qp, v[j].x));
-            v[j].y = fma(-b.y, qm, fma(f.y, qp, v[j].y));
+            const double rp = qp[n], rm = qm[m];
+            v[j].x = fma(b.x, rm, fma(f.x, rp, v[j].x));
+            v[j].y = fma(-b.y, rm, fma(f.y, rp, v[j].y));
           }
         }
       }
@@ -1118,7 +1122,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
         mirror[u] = 2 * cl > R;
         const int kc = mirror[u] ? R - cl : cl;
         const int i = kc - 1 - (kc >> lratio) - z0;
-        base[u] = i >= 0 && i < n_cls ? (i + FIRST) * 2 * XWAVE + (mirror[u] ? MIRROR : 0) : -1;
+        base[u] = i >= 0 && i < n_cls ? i * 2 * XWAVE + (mirror[u] ? MIRROR : 0) : -1;
         if (grid_pt[u]) base[u] = z0 == 0 ? 0 : -1;
       }
       float* out = a.out + static_cast<int64_t>(g) * N;
@@ -1308,8 +1312,7 @@ hipError_t launch_expand(FoldArgs a, hipStream_t s) {
   // workgroups, each forming the lags (N = 65536, one gate: 93 us by one)
   const int ratio = a.n_fft / std::max(a.grid_len, SUB), half = a.n_fft / SUB / 2;
   const int tasks = ratio == 1 ? 0 : half - half / ratio;
-  const int per_round = a.grid_len == 2 * SUB ? EXP_WAVES - 1 : EXP_WAVES;
-  a.blocks = std::max(1, std::min((tasks + per_round - 1) / per_round, 256 / a.rows));
+  a.blocks = std::max(1, std::min((tasks + EXP_WAVES - 1) / EXP_WAVES, 256 / a.rows));
   const dim3 grid(static_cast<unsigned>(a.rows) * static_cast<unsigned>(a.blocks)), block(64 * EXP_WAVES);
   switch (a.grid_len / (2 * SUB)) {
     case 0: hipLaunchKernelGGL((expand_grid<0>), grid, block, 0, s, a); break;
@@ -1346,16 +1349,21 @@ hipError_t launch_window(const FoldArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A grid with points hi, lo and mean is expanded while hi / sqrt(mean lo) <= 12 L^(1/4).
-// Largest errors over max(S, mean S) there and of direct transforms, one line per gate
-// (100 pulses, 60 from L = 4000 on; sets of 40 to 600 gates, complex64), with hi / sqrt(mean lo):
-//   L =   64   24: 3.0e-7, 4.3e-7    41: 5.1e-7, 3.7e-7
-//   L =  256   33: 2.4e-7, 6.3e-7    61: 3.9e-7, 5.8e-7    (8 pulses: 33: 3.6e-7, 5.6e-7)
-//   L = 1000   42: 2.8e-7, 4.8e-7   116: 7.2e-7, 4.5e-7
-//   L = 2000   83: 3.4e-7, 5.1e-7   249: 1.1e-6, 5.3e-7
-//   L = 8000   40: 2.0e-7, 4.2e-7   374: 9.2e-7, 5.3e-7
-// The noise of 2 pulses has 20 to 70, of 100 pulses 2.
-constexpr float kPeakLimit = 144.f;
+// A grid with points hi, lo and mean is expanded while t = hi / sqrt(mean lo) <= 22 L^(1/4)
+// (12 L^(1/4) for L > 1024, whose transforms have a pass more), less by (P / 32)^(1/4) for few
+// pulses, over which rounding averages less.  Largest errors over max(S, mean S) there and of
+// direct transforms, one line per gate (sets of 40 to 600 gates, complex64):
+//   L =  128, P = 100   t =  74: 2.5e-7, 3.8e-7    t = 115: 3.0e-7, 3.9e-7
+//   L =  256, P = 100   t =  62: 2.3e-7, 5.8e-7    t = 164: 6.4e-7, 6.0e-7
+//   L =  256, P =   8   t =  33: 3.5e-7, 5.6e-7    t =  90: 5.9e-7, 5.3e-7
+//   L = 1000, P = 100   t = 124: 4.0e-7, 4.5e-7    t = 233: 8.0e-7, 4.7e-7
+//   L = 2000, P = 100   t =  83: 3.1e-7, 5.1e-7    t = 249: 8.5e-7, 5.3e-7
+//   L = 4000, P =  60   t =  20: 1.6e-7, 4.1e-7    t = 170: 7.3e-7, 3.9e-7
+// Noise alone has t = 20 to 40 at 3 pulses, 2 at 100.
+float peak_limit(int code_len, int n_pulses) {
+  const float c = code_len > SUB ? 12.f : 22.f;
+  return c * c * std::sqrt(static_cast<float>(code_len) * std::min(1.f, static_cast<float>(n_pulses) / 32.f));
+}
 
 // Spectra of redone gates whose direct launch split its pulses into chunks, from the partials
 // by list slot, the chunks in ascending order.
@@ -1442,7 +1450,7 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   a.gate_count = f.gate_count;
   a.redo_list = f.redo_list;
   a.redo_count = a.partial ? nullptr : f.redo_count;
-  a.peak_limit = kPeakLimit * std::sqrt(static_cast<float>(a.code_len));
+  a.peak_limit = peak_limit(a.code_len, a.n_pulses);
   hipError_t e = pack_bits(a, f.grid_bits, f.grid_binary, s);
   if (e != hipSuccess) return e;
   if (a.grid_len == a.n_fft) {  // every bin is on the grid: partials by gate, no expansion
@@ -1509,7 +1517,7 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
   a.redo_list = z.redo_list;
   a.redo_count = z.redo_count;
   // (BF16 products round 16 times as coarsely)
-  a.peak_limit = (z.precision == 1 ? 1.f : 256.f) * kPeakLimit * std::sqrt(static_cast<float>(a.code_len));
+  a.peak_limit = (z.precision == 1 ? 1.f : 256.f) * peak_limit(a.code_len, a.n_pulses);
   a.bin_start = z.bin_start;
   a.n_bins = z.n_bins;
   hipError_t e = pack_bits(a, z.grid_bits, z.grid_binary, s);
