@@ -815,13 +815,14 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
       a.grid_bits = ctx->grid_bits;
       a.grid_binary = ctx->grid_binary;
     }
+    // (four rounds of workgroups: with one, 65 gates of two each took one chunk and half the chip)
     const AdaptiveFallback redo = adaptive_plan(c, n_pulses, nullptr, ctx->force_rw);
     a.redo_count = ctx->redo;
     a.redo_list = ctx->redo + 1;
-    a.redo_target = redo.target;
+    a.redo_target = 4 * redo.target;
     a.redo_max_chunks = redo.max_chunks;
     a.redo_rows = static_cast<int32_t>(
-        std::min<int64_t>(redo.rows, ctx->grid_bytes / (int64_t{4} * c.fft_len)));
+        std::min<int64_t>(4 * redo.rows, ctx->grid_bytes / (int64_t{4} * c.fft_len)));
     a.code_bits = ctx->code_bits;
     a.code_binary = ctx->code_binary;
     e = ispl::launch_fused(a, s);
