@@ -461,6 +461,9 @@ struct ispl_zoom {
   int32_t* grid_binary;
   int32_t grid_bits_rows;
   int32_t* redo;          // as a context's
+  bool lines;             // see zoom_grid_plan
+  GridPlan plan;          // of calls of plan_pulses pulses (0: none yet)
+  int32_t plan_pulses;
 };
 
 namespace {
@@ -487,19 +490,47 @@ ZoomPlan zoom_plan(int32_t n_gates, int32_t n_bins, int32_t n_pulses) {
   return z;
 }
 
-// The grid plan of a zoom call, or none (then matrix products): one transform of
-// >= 2 L - 1 points per pulse is less than K L products already for the smallest
-// window.  Measured (pulses x gates, L, N, K: us by products, on the grid):
-// 1 x 64, 256, 16384, 256: 16.8, 13.7; 3 x 300, 1000, 16384, 16384: 8250, 1210;
-// 1000 x 16, 256, 16384, 256: 46, 28; 4000 gates of 1 pulse, L = 16: 119, 94.
-GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_pulses) {
+// Estimated time of a zoom call by matrix products: prep and launches, then rounds of one
+// workgroup per compute unit, each a fixed cost and its steps of 64 samples of a pulse block.
+double products_us(const ispl_config& c, int32_t n_bins, int32_t n_pulses, double* round_us) {
+  const ZoomPlan z = zoom_plan(c.n_gates, n_bins, n_pulses);
+  const int64_t wgs = static_cast<int64_t>(c.n_gates) * (n_bins / (128 * z.rt)) * z.chunks;
+  const int per = (n_pulses + z.chunks - 1) / z.chunks, cols = 32 * z.ct;
+  const int steps = ((per + cols - 1) / cols) * ((c.code_len + 63) / 64);
+  const double step_us = z.ct == 2 ? (z.rt == 2 ? 4.0 : 2.4) : (z.rt == 2 ? 2.4 : 1.7);
+  *round_us = 6.8 + steps * step_us;
+  return (z.chunks > 1 ? 12.0 : 8.0) +
+         static_cast<double>((wgs + kComputeUnits - 1) / kComputeUnits) * *round_us;
+}
+
+// The grid plan of a zoom call, or none (then matrix products): by estimated times, with
+// `lines` (windows of gates chosen for their lines) as if some gates were redone by products.
+// Measured (pulses x gates, L, N, K: us by products, on the grid):
+// 50 x 64, 128, 4096, 128: 16.4, 19.0; 100 x 64, 256, 16384, 256: 25.2, 22.7;
+// 1000 x 64, same: 95.6, 56.5; 100 x 1000, same: 165, 86; 8 x 300, 1000, 16384, 4096: 1300, 325.
+GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, bool lines) {
   GridPlan gp{};
   const int len = c.code_len <= ispl::SUB ? grid_length(c) : 0;
-  if (len > 0 && n_pulses >= kMinFoldPulses) grid_split(c, len, n_pulses, 0, &gp);
-  return gp;
+  if (len == 0 || n_pulses < kMinFoldPulses) return gp;
+  const int runs = n_bins / 128, blocks = std::max(1, std::min(runs, 512 / c.n_gates));
+  const int64_t passes = (static_cast<int64_t>(c.n_gates) * blocks + 511) / 512;
+  double round_us;
+  const double by_products = products_us(c, n_bins, n_pulses, &round_us);
+  const double on_grid = grid_split(c, len, n_pulses, 0, &gp) + 6.0 +
+                         passes * (6.0 + (runs + blocks - 1) / blocks * 0.0147 * c.code_len) +
+                         (lines ? 8.0 + round_us : 0.0);
+  return on_grid < 0.95 * by_products ? gp : GridPlan{};
 }
 
 }  // namespace
+
+static const GridPlan& zoom_plan_of(ispl_zoom* z, int32_t n_pulses) {
+  if (z->plan_pulses != n_pulses) {
+    z->plan = z->grid ? zoom_grid_plan(z->ctx->cfg, z->n_bins, n_pulses, z->lines) : GridPlan{};
+    z->plan_pulses = n_pulses;
+  }
+  return z->plan;
+}
 
 static void zoom_free(ispl_zoom* z) {
   void* bufs[] = {z->a_hi,      z->a_lo, z->partial,   z->col_exp,    z->code_bits,
@@ -953,8 +984,8 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
                         accumulate, stream);
 }
 
-ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
-                             ispl_zoom** out) {
+static ispl_status create_zoom(ispl_ctx* ctx, int32_t n_bins, int32_t precision, bool lines,
+                               ispl_zoom** out) {
   if (!out) return fail(ISPL_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
   if (!ctx) return fail(ISPL_ERR_INVALID_ARG, "context is NULL");
@@ -992,8 +1023,10 @@ ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
                                      static_cast<size_t>(code_pad / 32));
   if (e == hipSuccess)
     e = hipMalloc(&z->code_binary, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
+  z->lines = lines;
   // (a call of fewer pulses gains less from the grid)
-  if (e == hipSuccess && ctx->twiddle64 && zoom_grid_plan(c, c.max_pulses).len > 0) {
+  if (e == hipSuccess && ctx->twiddle64 &&
+      zoom_grid_plan(c, n_bins, c.max_pulses, lines).len > 0) {
     z->grid_bytes = grid_scratch_bytes(c);
     e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes));
     if (e == hipSuccess)
@@ -1018,6 +1051,10 @@ ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
   }
   *out = z;
   return ok();
+}
+
+ispl_status ispl_zoom_create(ispl_ctx* ctx, int32_t n_bins, int32_t precision, ispl_zoom** out) {
+  return create_zoom(ctx, n_bins, precision, false, out);
 }
 
 void ispl_zoom_destroy(ispl_zoom* z) {
@@ -1105,8 +1142,7 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
   a.row_lo = c.first_gate;
   a.row_hi = static_cast<int64_t>(c.first_gate) + static_cast<int64_t>(c.n_gates - 1) * c.gate_step +
              c.code_len;
-  GridPlan gp{};
-  if (z->grid) gp = zoom_grid_plan(c, n_pulses);
+  const GridPlan& gp = zoom_plan_of(z, n_pulses);
   if (gp.len > 0) {
     a.grid = z->grid;
     a.twiddle64 = z->ctx->twiddle64;
@@ -1506,7 +1542,7 @@ ispl_status ispl_lzoom_create(const ispl_config* cfg, ispl_net* net, int32_t win
   // the fine context runs only the fallback, whose chunking is adaptive and
   // whose partials live in the object's own buffer: no scratch of its own
   if (st == ISPL_OK) st = create_ctx(cfg, INT32_MAX, &z->fine);
-  if (st == ISPL_OK) st = ispl_zoom_create(z->fine, window_bins, zoom_precision, &z->zoom);
+  if (st == ISPL_OK) st = create_zoom(z->fine, window_bins, zoom_precision, true, &z->zoom);
   if (st != ISPL_OK) {
     const std::string why = g_last_error;
     lzoom_free(z);
@@ -1600,8 +1636,8 @@ ispl_status ispl_lzoom_peaks(ispl_lzoom* z, const void* samples, const float* tx
     pe.sample_type = c.sample_type;
     pe.code_len = c.code_len;
     pe.tx_per_pulse = tx_per_pulse;
-    // (a zoom from the grid needs neither exponents nor these sign bits)
-    const bool folds = z->zoom->grid && zoom_grid_plan(c, n_pulses).len > 0;
+    // (a zoom from the grid has its own, for gates redone by products)
+    const bool folds = zoom_plan_of(z->zoom, n_pulses).len > 0;
     pe.n_pulses = n_pulses > 0 && !folds ? n_pulses : 0;
     e = ispl::launch_select_and_exponents(z->logits, G, c.fft_len, z->window_bins, z->threshold,
                                           z->bin_start, z->confidence, z->flag, z->zoom_list,
