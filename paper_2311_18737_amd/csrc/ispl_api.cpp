@@ -25,15 +25,15 @@ struct ispl_ctx {
   ispl_config cfg;
   int32_t chunks_max;   // largest chunk count any call may plan
   float* twiddle;       // complex64 pairs, N entries
-  float* partial;       // chunks_max * G * N floats (nullptr when chunks_max == 1)
+  float* partial;       // chunks_max * G * N floats (unused when chunks_max == 1)
   int32_t force_rw;     // tuned plan (0: automatic): waves per workgroup, L <= 1024 only
   int32_t force_chunks; // tuned plan (0: automatic): pulse chunks, <= chunks_max
   int32_t min_chunk_pulses;  // fewest pulses per chunk of an automatic plan
   // codes of L > 2 SUB as sign bits (long-code kernel), max_pulses rows
   uint16_t* code_bits;  // [max_pulses][CODE_BITS_WORDS]
   int32_t* code_binary; // [max_pulses]
-  double* grid;         // folded integration: scratch of grid_bytes (nullptr: never folds)
-  int64_t grid_bytes;
+  double* grid;         // folded integration: scratch of grid_bytes (nullptr: never folds), in
+  int64_t grid_bytes;   // the place of `partial`: a call uses one or the other
   const float* deferred; // where the last call's chunk partials lie that its caller sums
   double* twiddle64;    // the twiddle table in double
   double* grid_gain;    // gains of the grid's points, behind it
@@ -42,6 +42,12 @@ struct ispl_ctx {
   int32_t* grid_binary;
   int32_t grid_bits_rows;
   int32_t* redo;        // number and list of the gates that a call's expansion leaves over
+  struct {              // the grid plan of the last call's form (n_pulses 0: none yet)
+    int32_t n_pulses, force_rw, force_chunks;
+    bool deferred;
+    int32_t len, waves, chunks;
+  } plan;
+  void* zoom_tables;    // the double tables when only a zoom needs them
 };
 
 namespace {
@@ -193,36 +199,44 @@ static_assert(kNoallocGridBytes + ispl::NOALLOC_TWIDDLE64_BYTES + ispl::NOALLOC_
               "the entry point that allocates nothing holds the grid scratch");
 constexpr int64_t kGridChunkBytes = int64_t{32} << 20;  // most of it for several chunks
 
+// What a plan is held to: bytes for chunk partials, a tuned plan's chunks and waves (0: free), and
+// doubles also on a grid of N points (a zoom's).
+struct GridForce {
+  int64_t bytes = kGridChunkBytes;
+  int32_t chunks = 0, waves = 0;
+  bool doubles = false;
+};
+
 // Waves per workgroup and pulse chunks on a grid of `len` points with the
 // least estimated time (us, fitted to measurements), and that time: rounds of
 // workgroups over the chip, each a fixed cost and its steps; a step takes
 // longer the more waves share a SIMD.
-double grid_split(const ispl_config& c, int len, int32_t n_pulses, int32_t force_chunks,
+double grid_split(const ispl_config& c, int len, int32_t n_pulses, const GridForce& force,
                   GridPlan* out) {
   const int classes = len > ispl::SUB ? len / ispl::SUB : 1;
   const int per_step = len < ispl::SUB ? ispl::SUB / len : 1;  // pulses a wave takes at once
-  const int64_t steps = (n_pulses + per_step - 1) / per_step;
+  const uint32_t steps = (static_cast<uint32_t>(n_pulses) + per_step - 1) / per_step;
   // FP32 partials on a grid of the N bins, doubles on a shorter one
-  const int64_t row = int64_t{len == c.fft_len ? 4 : 8} * len * c.n_gates;
+  const int64_t row = int64_t{len == c.fft_len && !force.doubles ? 4 : 8} * len * c.n_gates;
   const bool is_long = classes > 2;  // one wave per bin class, one pulse at a time
   double best = 0.0;
   out->len = 0;
   for (int waves = is_long ? classes : 8; waves <= 16; waves = is_long ? 32 : 2 * waves) {
-    const int runs = waves / classes;
-    int64_t lo = 1, hi = std::min<int64_t>(64, (steps + runs - 1) / runs);
-    hi = std::max<int64_t>(1, std::min(hi, kGridChunkBytes / row));
-    if (force_chunks > 0) {
-      lo = hi = std::min<int64_t>(force_chunks, kMaxChunks);
-      if (len == c.fft_len) lo = hi = std::max<int64_t>(1, std::min(hi, kGridChunkBytes / row));
-    }
-    for (int64_t chunks = lo; chunks <= hi; ++chunks) {
-      const int64_t wgs = chunks * c.n_gates, per_cu = kMaxWavesPerCu / waves;
-      const int64_t rounds = (wgs + kComputeUnits * per_cu - 1) / (kComputeUnits * per_cu);
-      const int64_t resident = std::min(per_cu, (wgs + kComputeUnits - 1) / kComputeUnits);
-      const int64_t iters = (steps + chunks * runs - 1) / (chunks * runs);
+    if (!is_long && (force.waves == 8 || force.waves == 16) && waves != force.waves) continue;
+    const uint32_t runs = static_cast<uint32_t>(waves / classes), per_cu = kMaxWavesPerCu / waves;
+    // what the scratch holds (of a long grid the sums too)
+    const int64_t held = force.bytes / row - (is_long && len != c.fft_len ? 1 : 0);
+    const uint32_t most = static_cast<uint32_t>(std::max<int64_t>(1, std::min<int64_t>(64, held)));
+    const uint32_t lo = force.chunks > 0 ? std::min<uint32_t>(force.chunks, most) : 1;
+    const uint32_t hi = force.chunks > 0 ? lo : std::max(1u, std::min(most, (steps + runs - 1) / runs));
+    const double chunk_us = row / 2e6 + 0.1, sum_us = len == c.fft_len || is_long ? 4.0 : 0.0;
+    for (uint32_t chunks = lo; chunks <= hi; ++chunks) {  // (32-bit divisions: most of the planning)
+      const uint32_t wgs = chunks * static_cast<uint32_t>(c.n_gates);  // many gates: one chunk
+      const uint32_t rounds = (wgs + kComputeUnits * per_cu - 1) / (kComputeUnits * per_cu);
+      const uint32_t resident = std::min(per_cu, (wgs + kComputeUnits - 1) / kComputeUnits);
+      const uint32_t iters = (steps + chunks * runs - 1) / (chunks * runs);
       const double step_us = std::max(1.6, 0.85 * static_cast<double>(resident * waves) / 4);
-      const double us = rounds * (iters * step_us + 3.0) + chunks * (row / 2e6 + 0.1) +
-                        (chunks > 1 && (len == c.fft_len || is_long) ? 4.0 : 0.0);
+      const double us = rounds * (iters * step_us + 3.0) + chunks * chunk_us + (chunks > 1 ? sum_us : 0.0);
       if (out->len == 0 || us < best) {
         *out = GridPlan{len, waves, static_cast<int>(chunks)};
         best = us;
@@ -256,7 +270,7 @@ double direct_us(const ispl_config& c, int32_t n_pulses) {
   const int64_t resident = std::min(per_cu, (pl.blocks + kComputeUnits - 1) / kComputeUnits);
   const double pulse_us = is_long ? 3.2 + 0.4e-3 * c.code_len
                                   : std::max(1.5, 0.235 * static_cast<double>(resident * pl.rw));
-  const int iters = (n_pulses + pl.chunks - 1) / pl.chunks;
+  const int64_t iters = (static_cast<int64_t>(n_pulses) + pl.chunks - 1) / pl.chunks;
   return 2.0 + rounds * ((is_long ? 12.0 : 2.5 + 0.5 * pl.rw) + iters * pulse_us) +
          (pl.chunks > 1 ? 4.0 + 2e-7 * pl.chunks * c.n_gates * c.fft_len * 4.0 : 0.0);
 }
@@ -273,31 +287,31 @@ int32_t grid_run(int32_t n_gates, int64_t most) {
 // below its mean that many gates would be redone.
 constexpr int32_t kMinFoldPulses = 3;
 
-GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, int32_t force_chunks = 0) {
+GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, const GridForce& force = {}) {
   GridPlan fold{}, whole{};
   const int len = grid_length(c);
   if (len == 0 || n_pulses < 1) return fold;
   // a grid of all the bins needs no expansion
   const double whole_us = c.fft_len <= 2 * ispl::SUB || len == c.fft_len
-                              ? grid_split(c, c.fft_len, n_pulses, force_chunks, &whole)
+                              ? grid_split(c, c.fft_len, n_pulses, force, &whole)
                               : 0.0;
   if (len == c.fft_len || n_pulses < kMinFoldPulses) return whole;
-  const double fold_us = grid_split(c, len, n_pulses, force_chunks, &fold) + expand_us(c, len);
+  const double fold_us = grid_split(c, len, n_pulses, force, &fold) + expand_us(c, len);
   // gates with a strong line are redone, so a call may cost both: folded from a quarter less on
   if (whole.len > 0) return fold_us < 0.75 * whole_us ? fold : whole;
   return fold_us < 0.75 * direct_us(c, n_pulses) ? fold : GridPlan{};
 }
 
-// Scratch of a context whose calls run on a grid (0: they never do): the chunk
-// partials of every gate when they fit, else of as many gates as do (any chunk
-// count of a plan fits for one gate, and a long grid's sums).
-int64_t grid_scratch_bytes(const ispl_config& c, int64_t most_bytes = kGridBytes) {
-  const int64_t len = grid_length(c);
-  if (len == 0) return 0;
-  // the larger row of its grids
-  const int64_t row = std::max<int64_t>(8 * len, c.fft_len <= 2 * ispl::SUB ? 4 * c.fft_len : 0);
-  const int64_t all = row * c.n_gates;
-  return std::min(most_bytes, std::max({all, std::min(kMaxChunks * all, kGridChunkBytes), (kMaxChunks + 1) * row}));
+// Scratch of calls whose longest runs on a grid by `pl` (of none: 0): its partials and sums, of
+// as many gates as fit when they are too many; and up to 16 MiB, or the spectra of as many chunks
+// as there can be, for the partials of gates that are redone.
+int64_t grid_scratch_bytes(const ispl_config& c, const GridPlan& pl, int64_t most_bytes = kGridBytes) {
+  if (pl.len == 0) return 0;
+  if (pl.len == c.fft_len) return std::max<int64_t>(8, int64_t{4} * pl.len * c.n_gates * pl.chunks);
+  const int64_t sets = pl.chunks + (pl.len > 2 * ispl::SUB && pl.chunks > 1 ? 1 : 0);
+  const int64_t redo = int64_t{4} * c.fft_len * c.n_gates * std::max(1, c.max_pulses / kMinChunkPulses);
+  return std::min(most_bytes, std::max({int64_t{8} * pl.len * c.n_gates * sets,
+                                        std::min(redo, int64_t{16} << 20), int64_t{16} * pl.len}));
 }
 
 // Most gates whose sums `bytes` of grid scratch hold at a time.
@@ -491,16 +505,17 @@ ZoomPlan zoom_plan(int32_t n_gates, int32_t n_bins, int32_t n_pulses) {
 }
 
 // Estimated time of a zoom call by matrix products: prep and launches, then rounds of one
-// workgroup per compute unit, each a fixed cost and its steps of 64 samples of a pulse block.
+// workgroup per compute unit, each its steps of 64 samples of a pulse block.
 double products_us(const ispl_config& c, int32_t n_bins, int32_t n_pulses, double* round_us) {
   const ZoomPlan z = zoom_plan(c.n_gates, n_bins, n_pulses);
   const int64_t wgs = static_cast<int64_t>(c.n_gates) * (n_bins / (128 * z.rt)) * z.chunks;
-  const int per = (n_pulses + z.chunks - 1) / z.chunks, cols = 32 * z.ct;
-  const int steps = ((per + cols - 1) / cols) * ((c.code_len + 63) / 64);
+  const int64_t per = (static_cast<int64_t>(n_pulses) + z.chunks - 1) / z.chunks, cols = 32 * z.ct;
+  const int64_t steps = ((per + cols - 1) / cols) * ((c.code_len + 63) / 64);
   const double step_us = z.ct == 2 ? (z.rt == 2 ? 4.0 : 2.4) : (z.rt == 2 ? 2.4 : 1.7);
-  *round_us = 6.8 + steps * step_us;
-  return (z.chunks > 1 ? 12.0 : 8.0) +
-         static_cast<double>((wgs + kComputeUnits - 1) / kComputeUnits) * *round_us;
+  const int64_t rounds = (wgs + kComputeUnits - 1) / kComputeUnits;
+  *round_us = static_cast<double>(steps) * step_us;
+  return (z.chunks > 1 ? 12.0 : 8.0) + static_cast<double>(rounds) * *round_us +
+         6.8 * static_cast<double>(rounds - 1);
 }
 
 // The grid plan of a zoom call, or none (then matrix products): by estimated times, with
@@ -508,17 +523,21 @@ double products_us(const ispl_config& c, int32_t n_bins, int32_t n_pulses, doubl
 // Measured (pulses x gates, L, N, K: us by products, on the grid):
 // 50 x 64, 128, 4096, 128: 16.4, 19.0; 100 x 64, 256, 16384, 256: 25.2, 22.7;
 // 1000 x 64, same: 95.6, 56.5; 100 x 1000, same: 165, 86; 8 x 300, 1000, 16384, 4096: 1300, 325.
-GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, bool lines) {
+GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, bool lines,
+                        int64_t bytes = kGridChunkBytes) {
   GridPlan gp{};
   const int len = c.code_len <= ispl::SUB ? grid_length(c) : 0;
   if (len == 0 || n_pulses < kMinFoldPulses) return gp;
   const int runs = n_bins / 128, blocks = std::max(1, std::min(runs, 512 / c.n_gates));
   const int64_t passes = (static_cast<int64_t>(c.n_gates) * blocks + 511) / 512;
+  GridForce force;
+  force.bytes = std::min(kGridChunkBytes, bytes);
+  force.doubles = true;
   double round_us;
   const double by_products = products_us(c, n_bins, n_pulses, &round_us);
-  const double on_grid = grid_split(c, len, n_pulses, 0, &gp) + 6.0 +
+  const double on_grid = grid_split(c, len, n_pulses, force, &gp) + 6.0 +
                          passes * (6.0 + (runs + blocks - 1) / blocks * 0.0147 * c.code_len) +
-                         (lines ? 8.0 + round_us : 0.0);
+                         (lines ? 15.0 + round_us : 0.0);
   return on_grid < 0.95 * by_products ? gp : GridPlan{};
 }
 
@@ -526,7 +545,8 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, 
 
 static const GridPlan& zoom_plan_of(ispl_zoom* z, int32_t n_pulses) {
   if (z->plan_pulses != n_pulses) {
-    z->plan = z->grid ? zoom_grid_plan(z->ctx->cfg, z->n_bins, n_pulses, z->lines) : GridPlan{};
+    z->plan = z->grid ? zoom_grid_plan(z->ctx->cfg, z->n_bins, n_pulses, z->lines, z->grid_bytes)
+                      : GridPlan{};
     z->plan_pulses = n_pulses;
   }
   return z->plan;
@@ -534,7 +554,7 @@ static const GridPlan& zoom_plan_of(ispl_zoom* z, int32_t n_pulses) {
 
 static void zoom_free(ispl_zoom* z) {
   void* bufs[] = {z->a_hi,      z->a_lo, z->partial,   z->col_exp,    z->code_bits,
-                  z->code_binary, z->grid, z->grid_bits, z->redo};
+                  z->code_binary, z->grid};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
 }
@@ -586,9 +606,30 @@ static ispl_status check_device(int32_t device) {
   return ISPL_OK;
 }
 
+// The twiddles and the gains of the grid points in double, as they lie in memory.
+static std::vector<double> double_tables(const ispl_config& c) {
+  std::vector<double> t = twiddle_table(c.fft_len);
+  const size_t n = t.size();
+  const int32_t len = grid_length(c);
+  t.resize(n + len);
+  for (int32_t k = 0; k < len; ++k) t[n + k] = ispl::grid_gain(t.data(), c.fft_len, len, k);
+  return t;
+}
+
+static void ctx_free(ispl_ctx* ctx) {
+  // (partial and grid share one block, the tables and the sign bits another)
+  void* bufs[] = {ctx->grid ? static_cast<void*>(ctx->grid) : ctx->partial,
+                  ctx->twiddle64 && !ctx->zoom_tables ? static_cast<void*>(ctx->twiddle64) : ctx->twiddle,
+                  ctx->zoom_tables, ctx->code_bits, ctx->code_binary};
+  for (void* b : bufs)
+    if (b) (void)hipFree(b);
+  delete ctx;
+}
+
 // A context whose automatic plans keep at least min_chunk_pulses pulses per
-// chunk (ispl_create: kMinChunkPulses).
-static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, ispl_ctx** out) {
+// chunk (ispl_create: kMinChunkPulses); `folds` false: only gate lists with adaptive chunks.
+static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, bool folds,
+                              ispl_ctx** out) {
   if (!out) return fail(ISPL_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
   ispl_status st = validate_config(cfg);
@@ -604,69 +645,67 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
   ctx->cfg = *cfg;
   ctx->min_chunk_pulses = min_chunk_pulses;
   const Plan worst = make_plan(*cfg, cfg->max_pulses, 0, 0, min_chunk_pulses);
+  // (a call of fewer pulses gains less from a grid)
+  const GridPlan gp = folds ? grid_plan(*cfg, cfg->max_pulses) : GridPlan{};
+  folds = gp.len > 0;
 
-  const std::vector<double> tw64 = twiddle_table(cfg->fft_len);
-  const std::vector<float> tw(tw64.begin(), tw64.end());  // rounded
-  e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle), tw.size() * sizeof(float));
-  if (e != hipSuccess) {
-    delete ctx;
-    return fail(ISPL_ERR_OUT_OF_MEMORY, "twiddle table: %s", hipGetErrorString(e));
+  // one block: double tables when there is a grid, the FP32 table, then the grid pass's sign bits
+  // with their flags and the list of gates to redo
+  std::vector<double> tables;
+  if (folds)
+    tables = double_tables(*cfg);
+  else
+    tables = twiddle_table(cfg->fft_len);
+  const size_t n = 2 * static_cast<size_t>(cfg->fft_len), head = folds ? tables.size() : 0;
+  std::vector<unsigned char> image(head * sizeof(double) + n * sizeof(float));
+  std::memcpy(image.data(), tables.data(), head * sizeof(double));
+  for (size_t i = 0; i < n; ++i) {
+    const float w = static_cast<float>(tables[i]);
+    std::memcpy(image.data() + head * sizeof(double) + i * sizeof(float), &w, sizeof w);
   }
-  e = hipMemcpy(ctx->twiddle, tw.data(), tw.size() * sizeof(float), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    (void)hipFree(ctx->twiddle);
-    delete ctx;
-    return hip_fail(e, "twiddle upload");
-  }
+  size_t bytes = image.size();
+  const size_t words = grid_bits_words(*cfg);
+  const int32_t bit_rows = grid_bits_rows(*cfg);
+  int64_t redo_rows = 0;
   // A plan's chunk count is its unclamped count capped at n_pulses, so the
   // plan for max_pulses has the largest one and bounds the partial buffer.
   const int32_t cmax = worst.chunks;
   ctx->chunks_max = cmax;
-  if (cmax > 1) {
-    const size_t bytes = static_cast<size_t>(cmax) * cfg->n_gates * cfg->fft_len * sizeof(float);
-    e = hipMalloc(reinterpret_cast<void**>(&ctx->partial), bytes);
+  const int64_t partials = cmax > 1 ? int64_t{4} * cmax * cfg->n_gates * cfg->fft_len : 0;
+  if (folds) {
+    ctx->grid_bytes = std::max(grid_scratch_bytes(*cfg, gp), std::min(partials, kGridBytes));
+    redo_rows = grid_rows_max(*cfg, ctx->grid_bytes);
+    bytes += sizeof(uint32_t) * (static_cast<size_t>(bit_rows) * (words + 1) + 1 + redo_rows);
+  }
+  unsigned char* base = nullptr;
+  e = hipMalloc(reinterpret_cast<void**>(&base), bytes);
+  if (e != hipSuccess) {
+    delete ctx;
+    return fail(ISPL_ERR_OUT_OF_MEMORY, "tables (%zu bytes): %s", bytes, hipGetErrorString(e));
+  }
+  ctx->twiddle = reinterpret_cast<float*>(base + head * sizeof(double));
+  if (folds) {
+    ctx->twiddle64 = reinterpret_cast<double*>(base);
+    ctx->grid_gain = ctx->twiddle64 + n;
+    ctx->grid_bits_rows = bit_rows;
+    ctx->grid_bits = reinterpret_cast<uint32_t*>(base + image.size());
+    ctx->grid_binary = reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(bit_rows) * words);
+    ctx->redo = ctx->grid_binary + bit_rows;
+  }
+  e = hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    ctx_free(ctx);
+    return hip_fail(e, "twiddle upload");
+  }
+  if (partials > 0 || folds) {
+    const size_t size = static_cast<size_t>(std::max(partials, ctx->grid_bytes));
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->partial), size);
     if (e != hipSuccess) {
-      (void)hipFree(ctx->twiddle);
-      delete ctx;
-      return fail(ISPL_ERR_OUT_OF_MEMORY, "chunk partials (%zu bytes): %s", bytes,
+      ctx_free(ctx);
+      return fail(ISPL_ERR_OUT_OF_MEMORY, "chunk partials (%zu bytes): %s", size,
                   hipGetErrorString(e));
     }
-  }
-  ctx->grid_bytes = grid_scratch_bytes(*cfg);
-  if (ctx->grid_bytes > 0) {
-    e = hipMalloc(reinterpret_cast<void**>(&ctx->grid), static_cast<size_t>(ctx->grid_bytes));
-    if (e == hipSuccess)
-      e = hipMalloc(reinterpret_cast<void**>(&ctx->twiddle64),
-                    (tw64.size() + grid_length(*cfg)) * sizeof(double));
-    if (e == hipSuccess)
-      e = hipMemcpy(ctx->twiddle64, tw64.data(), tw64.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) {
-      std::vector<double> gain(grid_length(*cfg));
-      for (size_t k = 0; k < gain.size(); ++k)
-        gain[k] = ispl::grid_gain(tw64.data(), cfg->fft_len, static_cast<int32_t>(gain.size()),
-                                  static_cast<int32_t>(k));
-      ctx->grid_gain = ctx->twiddle64 + tw64.size();
-      e = hipMemcpy(ctx->grid_gain, gain.data(), gain.size() * sizeof(double), hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess)
-      e = hipMalloc(reinterpret_cast<void**>(&ctx->redo),
-                    sizeof(int32_t) * (1 + grid_rows_max(*cfg, ctx->grid_bytes)));
-    const size_t words = grid_bits_words(*cfg);
-    ctx->grid_bits_rows = grid_bits_rows(*cfg);
-    if (e == hipSuccess)  // the sign bits and their flags in one block
-      e = hipMalloc(reinterpret_cast<void**>(&ctx->grid_bits),
-                    static_cast<size_t>(ctx->grid_bits_rows) * (words + 1) * sizeof(uint32_t));
-    if (e != hipSuccess) {
-      if (ctx->grid) (void)hipFree(ctx->grid);
-      if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
-      if (ctx->redo) (void)hipFree(ctx->redo);
-      if (ctx->partial) (void)hipFree(ctx->partial);
-      (void)hipFree(ctx->twiddle);
-      delete ctx;
-      return fail(ISPL_ERR_OUT_OF_MEMORY, "grid scratch: %s", hipGetErrorString(e));
-    }
-    ctx->grid_binary =
-        reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(ctx->grid_bits_rows) * words);
+    if (folds) ctx->grid = reinterpret_cast<double*>(ctx->partial);
   }
   if (cfg->code_len > 2 * ispl::SUB) {  // the long-code kernel reads binary codes as sign bits
     const size_t rows = static_cast<size_t>(cfg->max_pulses);
@@ -675,14 +714,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
     if (e == hipSuccess)
       e = hipMalloc(reinterpret_cast<void**>(&ctx->code_binary), rows * sizeof(int32_t));
     if (e != hipSuccess) {
-      if (ctx->code_bits) (void)hipFree(ctx->code_bits);
-      if (ctx->partial) (void)hipFree(ctx->partial);
-      if (ctx->grid) (void)hipFree(ctx->grid);
-      if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
-      if (ctx->redo) (void)hipFree(ctx->redo);
-      if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
-      (void)hipFree(ctx->twiddle);
-      delete ctx;
+      ctx_free(ctx);
       return fail(ISPL_ERR_OUT_OF_MEMORY, "code sign bits: %s", hipGetErrorString(e));
     }
   }
@@ -691,7 +723,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
 }
 
 ispl_status ispl_create(const ispl_config* cfg, ispl_ctx** out) {
-  return create_ctx(cfg, kMinChunkPulses, out);
+  return create_ctx(cfg, kMinChunkPulses, true, out);
 }
 
 void ispl_destroy(ispl_ctx* ctx) {
@@ -699,16 +731,8 @@ void ispl_destroy(ispl_ctx* ctx) {
   {
     DeviceGuard guard(ctx->cfg.device);
     (void)hipDeviceSynchronize();
-    if (ctx->partial) (void)hipFree(ctx->partial);
-    if (ctx->twiddle) (void)hipFree(ctx->twiddle);
-    if (ctx->code_bits) (void)hipFree(ctx->code_bits);
-    if (ctx->code_binary) (void)hipFree(ctx->code_binary);
-    if (ctx->grid) (void)hipFree(ctx->grid);
-    if (ctx->grid_bits) (void)hipFree(ctx->grid_bits);
-    if (ctx->redo) (void)hipFree(ctx->redo);
-    if (ctx->twiddle64) (void)hipFree(ctx->twiddle64);
+    ctx_free(ctx);
   }
-  delete ctx;
 }
 
 // Arguments of one integration against the geometry c (nothing is launched).
@@ -761,6 +785,29 @@ static AdaptiveFallback adaptive_plan(const ispl_config& c, int32_t n_pulses, fl
 }
 
 static int32_t adaptive_zgroups(const ispl_config& c) { return make_plan(c, 1).zgroups; }
+
+// The grid plan of a context's calls of n_pulses, kept from one to the next.  `deferred`: the caller
+// sums chunk partials (no accumulation, no list), on a grid of all the bins (100 pulses of 64
+// gates at N = 1024 take 13.9 us, 16.4 by the direct kernel).
+static GridPlan ctx_grid_plan(ispl_ctx* ctx, int32_t n_pulses, bool deferred) {
+  auto& p = ctx->plan;
+  if (p.n_pulses != n_pulses || p.deferred != deferred || p.force_rw != ctx->force_rw ||
+      p.force_chunks != ctx->force_chunks) {
+    const ispl_config& c = ctx->cfg;
+    GridForce force;
+    force.bytes = std::min(kGridChunkBytes, ctx->grid_bytes);
+    GridPlan gp{};
+    if (!deferred) {
+      force.chunks = ctx->force_chunks;
+      force.waves = ctx->force_rw;
+      gp = grid_plan(c, n_pulses, force);
+    } else if (c.fft_len <= 2 * ispl::SUB) {
+      grid_split(c, c.fft_len, n_pulses, force, &gp);
+    }
+    p = {n_pulses, ctx->force_rw, ctx->force_chunks, deferred, gp.len, gp.waves, gp.chunks};
+  }
+  return GridPlan{p.len, p.waves, p.chunks};
+}
 
 // With deferred_chunks non-NULL a pulse-chunked plan leaves its partial
 // spectra in the context's scratch ([C][G][N]) instead of reducing them into
@@ -821,13 +868,8 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
   a.waves_per_block = pl.rw;
   a.gate_list = gate_list;
   a.gate_count = gate_count;
-  GridPlan gp{};
-  if (ctx->grid && !adapt && !deferred_chunks) gp = grid_plan(c, n_pulses, ctx->force_chunks);
-  // chunk partials that the caller sums: on a grid of all the bins (100 pulses of 64
-  // gates at N = 1024 take 13.9 us, 16.4 by the direct kernel)
-  if (ctx->grid && deferred_chunks && !adapt && !gate_list && !accumulate &&
-      c.fft_len <= 2 * ispl::SUB && grid_length(c) > 0)
-    grid_split(c, c.fft_len, n_pulses, 0, &gp);
+  const GridPlan gp = ctx->grid && !adapt ? ctx_grid_plan(ctx, n_pulses, deferred_chunks != nullptr)
+                                          : GridPlan{};
   if (gp.len > 0) {
     a.out = spectra;
     a.chunks = 1;
@@ -841,7 +883,9 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     a.grid_waves = gp.waves;
     // (a long grid's chunk partials are summed behind them)
     const int64_t sets = gp.chunks + (gp.len > 2 * ispl::SUB && gp.chunks > 1 ? 1 : 0);
-    a.grid_rows = grid_run(c.n_gates, ctx->grid_bytes / (int64_t{8} * gp.len * sets));
+    a.grid_rows = gp.len == c.fft_len
+                      ? c.n_gates
+                      : grid_run(c.n_gates, ctx->grid_bytes / (int64_t{8} * gp.len * sets));
     if (packs_bits(c, tx_per_pulse, n_pulses, ctx->grid_bits_rows)) {
       a.grid_bits = ctx->grid_bits;
       a.grid_binary = ctx->grid_binary;
@@ -965,8 +1009,12 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
   tmp.partial = pl.chunks > 1 ? reinterpret_cast<float*>(base + ispl::NOALLOC_TWIDDLE_BYTES)
                               : nullptr;
   tmp.min_chunk_pulses = kMinChunkPulses;
-  tmp.grid_bytes = grid_scratch_bytes(*cfg, kNoallocGridBytes);
-  if (tmp.grid_bytes > 0) {
+  // the grid scratch of such a context, which bounds its plans (its partials share it)
+  const GridPlan gp = grid_plan(*cfg, cfg->max_pulses);
+  if (gp.len > 0) {
+    const int64_t worst = make_plan(*cfg, cfg->max_pulses).chunks;
+    tmp.grid_bytes = std::min(kNoallocGridBytes, std::max(grid_scratch_bytes(*cfg, gp),
+                                                          worst > 1 ? worst * row_bytes : 0));
     tmp.twiddle64 = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES);
     tmp.grid_gain = reinterpret_cast<double*>(base + ispl::NOALLOC_TWIDDLE_BYTES +
                                               ispl::NOALLOC_TWIDDLE64_BYTES);
@@ -1025,17 +1073,29 @@ static ispl_status create_zoom(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
     e = hipMalloc(&z->code_binary, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
   z->lines = lines;
   // (a call of fewer pulses gains less from the grid)
-  if (e == hipSuccess && ctx->twiddle64 &&
-      zoom_grid_plan(c, n_bins, c.max_pulses, lines).len > 0) {
-    z->grid_bytes = grid_scratch_bytes(c);
-    e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes));
-    if (e == hipSuccess)
-      e = hipMalloc(&z->redo, sizeof(int32_t) * (1 + grid_rows_max(c, z->grid_bytes)));
+  const GridPlan gp = zoom_grid_plan(c, n_bins, c.max_pulses, lines);
+  if (e == hipSuccess && gp.len > 0) {  // sums, sign bits with their flags and the list in one block
+    z->grid_bytes = std::min(kGridBytes, int64_t{8} * gp.len * c.n_gates * gp.chunks);
     z->grid_bits_rows = grid_bits_rows(c);
     const size_t words = static_cast<size_t>(z->grid_bits_rows) * grid_bits_words(c);
-    if (e == hipSuccess)
-      e = hipMalloc(&z->grid_bits, sizeof(uint32_t) * (words + static_cast<size_t>(z->grid_bits_rows)));
-    z->grid_binary = reinterpret_cast<int32_t*>(z->grid_bits + words);
+    const size_t ints = words + z->grid_bits_rows + 1 + grid_rows_max(c, z->grid_bytes);
+    e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes) + sizeof(int32_t) * ints);
+    if (e == hipSuccess) {
+      z->grid_bits = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(z->grid) + z->grid_bytes);
+      z->grid_binary = reinterpret_cast<int32_t*>(z->grid_bits + words);
+      z->redo = z->grid_binary + z->grid_bits_rows;
+    }
+    if (e == hipSuccess && !ctx->twiddle64) {  // a context without a grid of its own
+      const std::vector<double> tables = double_tables(c);
+      e = hipMalloc(&ctx->zoom_tables, tables.size() * sizeof(double));
+      if (e == hipSuccess)
+        e = hipMemcpy(ctx->zoom_tables, tables.data(), tables.size() * sizeof(double),
+                      hipMemcpyHostToDevice);
+      if (e == hipSuccess) {
+        ctx->twiddle64 = static_cast<double*>(ctx->zoom_tables);
+        ctx->grid_gain = ctx->twiddle64 + 2 * static_cast<size_t>(c.fft_len);
+      }
+    }
   }
   if (e != hipSuccess) {
     zoom_free(z);
@@ -1538,10 +1598,10 @@ ispl_status ispl_lzoom_create(const ispl_config* cfg, ispl_net* net, int32_t win
   cc.fft_len = ispl::NET_LEN;
   // the coarse transforms are short: chunks of 4 pulses give enough waves to
   // fill the chip on small workloads, and the network sums the partials
-  st = create_ctx(&cc, 4, &z->coarse);
+  st = create_ctx(&cc, 4, true, &z->coarse);
   // the fine context runs only the fallback, whose chunking is adaptive and
   // whose partials live in the object's own buffer: no scratch of its own
-  if (st == ISPL_OK) st = create_ctx(cfg, INT32_MAX, &z->fine);
+  if (st == ISPL_OK) st = create_ctx(cfg, INT32_MAX, false, &z->fine);
   if (st == ISPL_OK) st = create_zoom(z->fine, window_bins, zoom_precision, true, &z->zoom);
   if (st != ISPL_OK) {
     const std::string why = g_last_error;
