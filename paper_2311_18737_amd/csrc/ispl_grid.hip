@@ -1368,7 +1368,7 @@ float peak_limit(int code_len, int n_pulses) {
 // Spectra of redone gates whose direct launch split its pulses into chunks, from the partials
 // by list slot, the chunks in ascending order.
 __global__ void __launch_bounds__(256)
-sum_redone(FusedArgs a, int zgroups) {
+sum_redone(DirectArgs a, int zgroups) {
   const int k = min(max(*a.gate_count, 0), a.n_gates);
   const int chunks = adaptive_chunks(k, zgroups, a.adapt_target, a.adapt_max_chunks, a.adapt_rows);
   if (chunks == 1) return;  // written by the launch itself
@@ -1406,7 +1406,7 @@ hipError_t redo_direct(const FusedArgs& f, hipStream_t s) {
   e = launch_fused(d, s);
   if (e != hipSuccess || d.adapt_max_chunks == 1) return e;
   const int zgroups = d.sub_len == SUB ? (1 << d.log2_r) / d.waves_per_block : 1 << d.log2_r;
-  hipLaunchKernelGGL(sum_redone, dim3(512), dim3(256), 0, s, d, zgroups);
+  hipLaunchKernelGGL(sum_redone, dim3(512), dim3(256), 0, s, static_cast<const DirectArgs&>(d), zgroups);
   return hipGetLastError();
 }
 

@@ -41,8 +41,8 @@ ISPL_HOST_DEVICE inline int adaptive_chunks(int k, int zgroups, int target, int 
   return c > 1 ? c : 1;
 }
 
-// Geometry and plan of one fused launch.
-struct FusedArgs {
+// Geometry and plan of one launch of direct transforms (the kernels' argument).
+struct DirectArgs {
   const void* samples;     // [P][stride] ci16 or c64
   const float* tx;         // complex64 pairs, [P][L] or [L]
   const float* twiddle;    // complex64 pairs, W_N^i for i < N
@@ -76,6 +76,10 @@ struct FusedArgs {
   // launch_pack_code_bits for the same tx; NULL = always read tx.
   const uint16_t* code_bits;     // [rows][SUB]: bit j of word lg is code[lg + SUB j] == -1
   const int32_t* code_binary;    // [rows]: 1 when every code of the row is +-1 + 0i
+};
+
+// The same with a call's folded integration.
+struct FusedArgs : DirectArgs {
   // Folded integration (grid_len 0 = off): the pulses are summed on a grid of
   // grid_len >= 2 L - 1 points, which is then expanded to the N bins of `out`
   // (`chunks` and `waves_per_block` are not read); grid_len = N sums the bins
@@ -183,7 +187,8 @@ hipError_t launch_fill_zero_rows(float* dst, int32_t n_gates, int32_t n_fft, con
                                  const int32_t* count, hipStream_t stream);
 
 // Zoom DFT of a K-bin window per gate on the matrix cores.
-struct ZoomArgs {
+// Geometry and plan of one launch of zoom products (the kernels' argument).
+struct ProductArgs {
   const void* samples;      // [P][stride] ci16 or c64
   const float* tx;          // complex64 pairs, [P][L] or [L]
   const float* twiddle;     // complex64 pairs, W_N^i for i < N
@@ -218,6 +223,10 @@ struct ZoomArgs {
   // set when code[32 w + b] == -1, and per row 1 when the whole row is +-1.
   uint32_t* code_bits;
   int32_t* code_binary;
+};
+
+// The same with a call's grid.
+struct ZoomArgs : ProductArgs {
   // Zoom from the pulse-summed grid of grid_len points instead (0: matrix
   // products); see FusedArgs and launch_zoom_folded.  Gates left over run as products.
   int32_t* redo_list;        // [grid_rows]

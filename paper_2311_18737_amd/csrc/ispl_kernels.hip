@@ -45,7 +45,7 @@ namespace {
 // Gate of work slot `slot`: the slot itself, or the slot-th entry of a gate
 // list.  Returns -1 for slots past the list's device-side count and for
 // entries outside [0, n_gates), whose workgroups then do nothing.
-__device__ __forceinline__ int slot_gate(const FusedArgs& a, int slot) {
+__device__ __forceinline__ int slot_gate(const DirectArgs& a, int slot) {
   if (!a.gate_list) return slot;
   if (slot >= *a.gate_count) return -1;
   const int g = a.gate_list[slot];
@@ -54,7 +54,7 @@ __device__ __forceinline__ int slot_gate(const FusedArgs& a, int slot) {
 
 // Listed launches keep the hardware order, which deals the active (leading)
 // slots round-robin over all XCDs; full launches use the XCD-contiguous order.
-__device__ __forceinline__ int work_id(const FusedArgs& a) {
+__device__ __forceinline__ int work_id(const DirectArgs& a) {
   return a.gate_list ? static_cast<int>(blockIdx.x) : xcd_block_id();
 }
 
@@ -68,7 +68,7 @@ struct WorkItem {
   int g, zg, c, chunks, slot, rows;
 };
 
-__device__ __forceinline__ WorkItem work_item(const FusedArgs& a, int zgroups) {
+__device__ __forceinline__ WorkItem work_item(const DirectArgs& a, int zgroups) {
   WorkItem w;
   int bid = work_id(a);
   if (a.adapt_target > 0) {
@@ -94,7 +94,7 @@ __device__ __forceinline__ WorkItem work_item(const FusedArgs& a, int zgroups) {
 // Output row of a work item: the gate's row of `out` with one chunk, else
 // the chunk's partial row (chunk-major [C][G][N] in `out`, or [C][k][N] by
 // list slot in adapt_partial).
-__device__ __forceinline__ float* out_row(const FusedArgs& a, const WorkItem& w) {
+__device__ __forceinline__ float* out_row(const DirectArgs& a, const WorkItem& w) {
   if (w.chunks == 1) return a.out + static_cast<int64_t>(w.g) * a.n_fft;
   if (a.adapt_target > 0)
     return a.adapt_partial + (static_cast<int64_t>(w.c) * w.rows + w.slot) * a.n_fft;
@@ -110,7 +110,7 @@ __device__ __forceinline__ float* out_row(const FusedArgs& a, const WorkItem& w)
 // pre-twiddles.  F4 (with K0, L <= 256): each lane's samples 4..15 are zero,
 // so they are neither fetched nor decoded and pass 1 starts from four inputs.
 template <int RW, int ST, bool PF = false, bool K0 = false, bool F4 = false>
-__global__ void __launch_bounds__(64 * RW) fused_spectra(FusedArgs a) {
+__global__ void __launch_bounds__(64 * RW) fused_spectra(DirectArgs a) {
   static_assert(!K0 || RW == 1, "bin class 0 alone: one-wave workgroups at N = 1024");
   static_assert(!F4 || K0, "four non-zero inputs only in bin class 0");
   constexpr int NT = 64 * RW;
@@ -271,7 +271,7 @@ __device__ __forceinline__ void two_point_pass(float2 (&v)[16], float2 y0, float
 // is bin k1 + R kk with kk = wave + 16 kb, kb = ka + 16 (4 row + t) + 256 kd.
 // Staged through LDS in bin order (the caller has passed a barrier after its
 // last use of xs), then stored as runs of R-strided bins.
-__device__ __forceinline__ void store_long_bins(const FusedArgs& a, const WorkItem& w,
+__device__ __forceinline__ void store_long_bins(const DirectArgs& a, const WorkItem& w,
                                                 float2* xs, const float (&acc)[16], int tid,
                                                 int k1, int R) {
   const int lane = tid & 63, wave = tid >> 6;
@@ -292,7 +292,7 @@ __device__ __forceinline__ void store_long_bins(const FusedArgs& a, const WorkIt
 }
 
 // Whether every code row of pulses [p0, p1) is binary (sign bits usable).
-__device__ __forceinline__ bool range_binary(const FusedArgs& a, int p0, int p1) {
+__device__ __forceinline__ bool range_binary(const DirectArgs& a, int p0, int p1) {
   if (!a.code_bits) return false;
   if (!a.tx_per_pulse) return a.code_binary[0] != 0;
   int all = 1;
@@ -305,7 +305,7 @@ __device__ __forceinline__ bool range_binary(const FusedArgs& a, int p0, int p1)
 // pulse ranges whose codes are not all binary (fused_spectra_long_dma runs the
 // others, from the same grid).
 template <int ST, bool TWO, bool K0>
-__global__ void __launch_bounds__(1024) fused_spectra_long(FusedArgs a) {
+__global__ void __launch_bounds__(1024) fused_spectra_long(DirectArgs a) {
   using IO = SampleIO<ST>;
   __shared__ float2 xs[16 * XWAVE];
 
@@ -447,7 +447,7 @@ __device__ __forceinline__ void wait_vmem_ops() { asm volatile("s_waitcnt vmcnt(
 // the pulse ranges whose code rows are all binary (fused_spectra_long runs the
 // others, from the same grid).
 template <int ST, bool K0>
-__global__ void __launch_bounds__(1024) fused_spectra_long_dma(FusedArgs a) {
+__global__ void __launch_bounds__(1024) fused_spectra_long_dma(DirectArgs a) {
   using IO = SampleIO<ST>;
   using raw_t = typename IO::raw_t;
   constexpr int SB = static_cast<int>(sizeof(raw_t));
@@ -688,7 +688,7 @@ peak_pick(const float* __restrict__ spectra, int32_t n_gates, int32_t n_fft, int
 
 // Workgroups of a fused launch: every (gate, bin group, chunk) work item, or
 // with adaptive chunking the most work items any list length can ask for.
-int64_t fused_blocks(const FusedArgs& a, int zgroups) {
+int64_t fused_blocks(const DirectArgs& a, int zgroups) {
   if (a.adapt_target <= 0) return static_cast<int64_t>(a.n_gates) * zgroups * a.chunks;
   // k gates take k zgroups workgroups, or while there is room several chunks, within the target
   const int64_t all = static_cast<int64_t>(a.n_gates) * zgroups;
@@ -696,7 +696,7 @@ int64_t fused_blocks(const FusedArgs& a, int zgroups) {
 }
 
 template <int RW, int ST>
-hipError_t launch_fused_t(const FusedArgs& a, hipStream_t stream) {
+hipError_t launch_fused_t(const DirectArgs& a, hipStream_t stream) {
   const int zgroups = (1 << a.log2_r) / RW;
   const int64_t blocks = fused_blocks(a, zgroups);
   // one-wave workgroups prefetch when the launch has at most two waves per SIMD
@@ -725,7 +725,7 @@ hipError_t launch_fused_t(const FusedArgs& a, hipStream_t stream) {
 }
 
 template <int ST>
-hipError_t launch_fused_long_t(const FusedArgs& a, hipStream_t stream) {
+hipError_t launch_fused_long_t(const DirectArgs& a, hipStream_t stream) {
   const int64_t blocks = fused_blocks(a, 1 << a.log2_r);
   const dim3 grid(static_cast<unsigned>(blocks)), block(1024);
   const bool two = a.code_len <= 2 * SUB, k0 = a.log2_r == 0;
@@ -754,7 +754,7 @@ hipError_t launch_fused_long_t(const FusedArgs& a, hipStream_t stream) {
 }
 
 template <int ST>
-hipError_t launch_fused_st(const FusedArgs& a, hipStream_t stream) {
+hipError_t launch_fused_st(const DirectArgs& a, hipStream_t stream) {
   if (a.sub_len == 16 * SUB) return launch_fused_long_t<ST>(a, stream);
   switch (a.waves_per_block) {
     case 1: return launch_fused_t<1, ST>(a, stream);

@@ -195,7 +195,7 @@ __device__ __forceinline__ int b_slot(int ks, int ln) { return ln ^ ((8 * ks + 4
 // Item context of pulse block pb: pulse pb + pc past p1 reads the first pulse
 // of the range instead (valid loads, zeroed when stored).
 template <int PREC>
-__device__ __forceinline__ void item_of(const ZoomArgs& a, Item& it, int pb, int pc, int p0,
+__device__ __forceinline__ void item_of(const ProductArgs& a, Item& it, int pb, int pc, int p0,
                                         int p1, int64_t gate_off, int words) {
   const int p = pb + pc;
   const int pr = p < p1 ? p : p0;
@@ -221,7 +221,7 @@ __device__ __forceinline__ float2 shift_twiddle(const float2* tws, const float2*
 // lies wholly inside [0, L) or wholly past it and is one 16- or 32-byte
 // access).
 template <int ST, bool VEC>
-__device__ __forceinline__ void fetch_samples(const ZoomArgs& a, typename RawSample<ST>::type (&x)[8],
+__device__ __forceinline__ void fetch_samples(const ProductArgs& a, typename RawSample<ST>::type (&x)[8],
                                               const Item& it, int nb) {
   const int L = a.code_len;
   if constexpr (VEC) {
@@ -244,7 +244,7 @@ __device__ __forceinline__ void fetch_samples(const ZoomArgs& a, typename RawSam
 }
 
 template <int ST, bool VEC>
-__device__ __forceinline__ void fetch_chunk(const ZoomArgs& a, ChunkRegs<ST>& r, const Item& it,
+__device__ __forceinline__ void fetch_chunk(const ProductArgs& a, ChunkRegs<ST>& r, const Item& it,
                                             int nb, uint32_t k0, const float2* tws) {
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   const uint32_t nmask = static_cast<uint32_t>(a.n_fft - 1);
@@ -271,7 +271,7 @@ __device__ __forceinline__ void fetch_chunk(const ZoomArgs& a, ChunkRegs<ST>& r,
 }
 
 template <int ST, bool VEC>
-__device__ __forceinline__ void fetch_bits(const ZoomArgs& a, BitRegs<ST>& r, const Item& it,
+__device__ __forceinline__ void fetch_bits(const ProductArgs& a, BitRegs<ST>& r, const Item& it,
                                            int nb) {
   fetch_samples<ST, VEC>(a, r.x, it, nb);
   r.bits = it.bitp[nb >> 5] >> (nb & 31);  // bit s of the group in bit s
@@ -391,7 +391,7 @@ __device__ __forceinline__ void put_bits(const BitRegs<ST>& r, const Item& it, c
 }
 
 // True (wave-uniform) when the code rows of pulses [p0, p1) are all +-1.
-__device__ __forceinline__ bool rows_binary(const ZoomArgs& a, int p0, int p1, int lane) {
+__device__ __forceinline__ bool rows_binary(const ProductArgs& a, int p0, int p1, int lane) {
   if (!a.tx_per_pulse) return a.code_binary[0] != 0;
   bool ok = true;
   for (int p = p0 + lane; p < p1; p += 64) ok = ok && a.code_binary[p] != 0;
@@ -425,7 +425,7 @@ __device__ __forceinline__ int zoom_xcd_id(int b, int nblk) {
 // A-operand order) are refilled in place, each product's right after its
 // multiplies, one k-step ahead.
 template <int PREC, int ST, int RT, int CT>
-__global__ void __launch_bounds__(ZTA) zoom_spectra(ZoomArgs a) {
+__global__ void __launch_bounds__(ZTA) zoom_spectra(ProductArgs a) {
   constexpr int NCOL = 32 * CT;
   constexpr int BG = 4 * RT;                   // bin tiles per workgroup
   constexpr int CG = ZW / BG;                  // matrix waves per bin tile
@@ -717,7 +717,7 @@ pulse_prep(const void* __restrict__ samples, int32_t sample_type, const float* _
 }
 
 template <int PREC, int ST, int RT>
-hipError_t launch_zoom_rt(const ZoomArgs& a, int ct, hipStream_t stream) {
+hipError_t launch_zoom_rt(const ProductArgs& a, int ct, hipStream_t stream) {
   const unsigned blocks =
       static_cast<unsigned>(a.n_gates) * (a.n_bins / (128 * RT)) * static_cast<unsigned>(a.chunks);
   if (ct == 1)
@@ -730,13 +730,13 @@ hipError_t launch_zoom_rt(const ZoomArgs& a, int ct, hipStream_t stream) {
 }
 
 template <int PREC, int ST>
-hipError_t launch_zoom_st(const ZoomArgs& a, hipStream_t stream) {
+hipError_t launch_zoom_st(const ProductArgs& a, hipStream_t stream) {
   return a.row_tiles == 2 ? launch_zoom_rt<PREC, ST, 2>(a, a.col_tiles, stream)
                           : launch_zoom_rt<PREC, ST, 1>(a, a.col_tiles, stream);
 }
 
 template <int PREC>
-hipError_t launch_zoom_t(const ZoomArgs& a, hipStream_t stream) {
+hipError_t launch_zoom_t(const ProductArgs& a, hipStream_t stream) {
   return a.sample_type == 1 ? launch_zoom_st<PREC, 1>(a, stream) : launch_zoom_st<PREC, 0>(a, stream);
 }
 
