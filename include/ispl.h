@@ -412,6 +412,9 @@ void ispl_destroy(ispl_ctx* ctx);
  *   ispl_batch_get_plan / set_plan  the plan in use (waves 0 and chunks 0 mean
  *                       the automatic choice; waves only for modes with
  *                       L <= 1024: a power of two <= min(16, N/1024)).
+ *                       A mode summed on a grid takes 8 or 16 waves from the
+ *                       plan (others: automatic) and as many of its chunks as
+ *                       its scratch holds.
  * Waves per workgroup change no result between shapes that share a twiddle
  * factorization (eight-wave workgroups use a geometric form of the inner
  * passes' twiddles, every other shape the direct form) and only the rounding

@@ -2057,10 +2057,17 @@ ispl_status ispl_batch_tune(ispl_batch* b, const ispl_batch_io* io, int32_t tria
   for (int m : by_work) {
     if (st != ISPL_OK) break;
     const ispl_config& c = b->ctx[m]->cfg;
-    const Plan auto_pl = make_plan(c, io[m].n_pulses > 0 ? io[m].n_pulses : 1);
+    Plan auto_pl = make_plan(c, io[m].n_pulses > 0 ? io[m].n_pulses : 1);
     std::vector<std::pair<int, int>> cands;  // (waves, chunks)
-    if (c.code_len <= ispl::SUB)
+    const GridPlan gp = b->ctx[m]->grid && io[m].n_pulses > 0 ? grid_plan(c, io[m].n_pulses) : GridPlan{};
+    if (gp.len > 0) {  // summed on a grid, whose workgroups have 8 or 16 waves
+      auto_pl.chunks = gp.chunks;
+      auto_pl.rw = 0;
+      if (c.code_len <= ispl::SUB)
+        for (int w = 8; w <= 16 && w <= c.fft_len / ispl::SUB; w *= 2) cands.push_back({w, 0});
+    } else if (c.code_len <= ispl::SUB) {
       for (int w = auto_pl.rw; w >= 1 && w >= auto_pl.rw / 4; w /= 2) cands.push_back({w, 0});
+    }
     cands.push_back({0, 1});
     if (auto_pl.chunks > 2) cands.push_back({0, auto_pl.chunks / 2});
     if (2 * auto_pl.chunks <= b->ctx[m]->chunks_max) cands.push_back({0, 2 * auto_pl.chunks});

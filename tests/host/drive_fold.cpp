@@ -15,6 +15,7 @@
 
 static int g_fail = 0;
 static long g_folded = 0, g_packed = 0;
+static std::set<std::pair<int, int>> g_plans;  // (waves, chunks) of folded launches
 #define CHECK(cond)                                                        \
   do {                                                                     \
     if (!(cond)) {                                                         \
@@ -38,6 +39,7 @@ static void check_bits(const uint32_t* bits, const int32_t* binary, int code_len
 hipError_t launch_fused(const FusedArgs& a, hipStream_t st) {
   if (a.grid_len == 0) return plain_fused(a, st);
   ++g_folded;
+  g_plans.insert({a.grid_waves, a.grid_chunks});
   FusedArgs c = a;
   run_on(st, [c] {
     check_bits(c.grid_bits, c.grid_binary, c.code_len, c.tx_per_pulse, c.n_pulses);
@@ -200,7 +202,46 @@ static void more_codes_than_rows(int L, int N, int G, int P) {
   free_all();
 }
 
+// The tuner's and a set plan's waves and chunks reach a mode that is summed on a grid.
+static void tuned_modes() {
+  const ispl_config c = config(300, 16384, 40, 400);
+  ispl_batch* b = nullptr;
+  CHECK(ispl_batch_create(&c, 1, &b) == ISPL_OK);
+  if (!b) return;
+  ispl_batch_io io{};
+  io.samples = dev<void>(size_t(400) * c.pulse_stride * 4);
+  io.tx_code = dev<float>(size_t(400) * c.code_len * 8);
+  io.tx_per_pulse = 1;
+  io.n_pulses = 400;
+  io.spectra = dev<float>(size_t(c.n_gates) * c.fft_len * 4);
+  auto waves = [] {
+    std::set<int> w;
+    for (const auto& p : g_plans) w.insert(p.first);
+    return w;
+  };
+  ispl_batch_plan plan{};
+  for (int w : {8, 16}) {
+    g_plans.clear();
+    CHECK(ispl_batch_get_plan(b, &plan) == ISPL_OK);
+    plan.waves[0] = w;
+    CHECK(ispl_batch_set_plan(b, &plan) == ISPL_OK);
+    CHECK(ispl_batch_integrate(b, &io, 0, 0, nullptr) == ISPL_OK);
+    CHECK(waves() == std::set<int>{w});
+  }
+  plan.waves[0] = 0;
+  CHECK(ispl_batch_set_plan(b, &plan) == ISPL_OK);
+  g_plans.clear();
+  float ms = 0.f;
+  CHECK(ispl_batch_tune(b, &io, 1, &plan, &ms) == ISPL_OK);
+  CHECK((waves() == std::set<int>{8, 16}));
+  CHECK(g_plans.size() > 2);  // and other chunk counts
+  CHECK(ispl_batch_set_plan(b, &plan) == ISPL_OK);
+  ispl_batch_destroy(b);
+  free_all();
+}
+
 int main() {
+  tuned_modes();
   const int shapes[][4] = {{16, 1024, 64, 700},   {256, 1024, 64, 100}, {300, 16384, 900, 60},
                            {600, 4096, 9000, 9},  {1000, 16384, 37, 90}, {1000, 65536, 2, 400},
                            {1024, 2048, 300, 40}, {33, 65536, 1, 64},    {128, 4096, 200, 500}};
