@@ -255,7 +255,7 @@ double expand_us(const ispl_config& c, int len) {
   const int blocks = std::max(1, std::min(rounds, kComputeUnits / c.n_gates));
   const int64_t passes = (static_cast<int64_t>(c.n_gates) * blocks + kComputeUnits - 1) / kComputeUnits;
   // (with the launches that find no gate to redo)
-  return (c.code_len > 2 * ispl::SUB ? 10.0 : 7.0) + passes * (6.0 + len / 1024.0 + ((rounds + blocks - 1) / blocks) * (5.0 + c.fft_len / 4300.0));
+  return (c.code_len > 2 * ispl::SUB ? 7.0 : 4.0) + passes * (6.0 + len / 1024.0 + ((rounds + blocks - 1) / blocks) * (5.0 + c.fft_len / 4300.0));
 }
 
 // Estimated time of the direct transform: rounds of its plan's workgroups, a fixed
@@ -297,9 +297,9 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, const GridForce& forc
                               : 0.0;
   if (len == c.fft_len || n_pulses < kMinFoldPulses) return whole;
   const double fold_us = grid_split(c, len, n_pulses, force, &fold) + expand_us(c, len);
-  // gates with a strong line are redone, so a call may cost both: folded from a quarter less on
-  if (whole.len > 0) return fold_us < 0.75 * whole_us ? fold : whole;
-  return fold_us < 0.75 * direct_us(c, n_pulses) ? fold : GridPlan{};
+  // gates with a strong line are redone, so a call may cost both: folded from a fifth less on
+  if (whole.len > 0) return fold_us < 0.8 * whole_us ? fold : whole;
+  return fold_us < 0.8 * direct_us(c, n_pulses) ? fold : GridPlan{};
 }
 
 // Scratch of calls whose longest runs on a grid by `pl` (of none: 0): its partials and sums, of
@@ -506,7 +506,8 @@ ZoomPlan zoom_plan(int32_t n_gates, int32_t n_bins, int32_t n_pulses) {
 
 // Estimated time of a zoom call by matrix products: prep and launches, then rounds of one
 // workgroup per compute unit, each its steps of 64 samples of a pulse block.
-double products_us(const ispl_config& c, int32_t n_bins, int32_t n_pulses, double* round_us) {
+double products_us(const ispl_config& c, int32_t n_bins, int32_t precision, int32_t n_pulses,
+                   double* round_us) {
   const ZoomPlan z = zoom_plan(c.n_gates, n_bins, n_pulses);
   const int64_t wgs = static_cast<int64_t>(c.n_gates) * (n_bins / (128 * z.rt)) * z.chunks;
   const int64_t per = (static_cast<int64_t>(n_pulses) + z.chunks - 1) / z.chunks, cols = 32 * z.ct;
@@ -514,7 +515,8 @@ double products_us(const ispl_config& c, int32_t n_bins, int32_t n_pulses, doubl
   const double step_us = z.ct == 2 ? (z.rt == 2 ? 4.0 : 2.4) : (z.rt == 2 ? 2.4 : 1.7);
   const int64_t rounds = (wgs + kComputeUnits - 1) / kComputeUnits;
   *round_us = static_cast<double>(steps) * step_us;
-  return (z.chunks > 1 ? 12.0 : 8.0) + static_cast<double>(rounds) * *round_us +
+  return (precision == ISPL_ZOOM_FP16X3 ? 8.0 : 5.0) + (z.chunks > 1 ? 4.0 : 0.0) +
+         static_cast<double>(rounds) * *round_us +
          6.8 * static_cast<double>(rounds - 1);
 }
 
@@ -523,8 +525,8 @@ double products_us(const ispl_config& c, int32_t n_bins, int32_t n_pulses, doubl
 // Measured (pulses x gates, L, N, K: us by products, on the grid):
 // 50 x 64, 128, 4096, 128: 16.4, 19.0; 100 x 64, 256, 16384, 256: 25.2, 22.7;
 // 1000 x 64, same: 95.6, 56.5; 100 x 1000, same: 165, 86; 8 x 300, 1000, 16384, 4096: 1300, 325.
-GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, bool lines,
-                        int64_t bytes = kGridChunkBytes) {
+GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t precision, int32_t n_pulses,
+                        bool lines, int64_t bytes = kGridChunkBytes) {
   GridPlan gp{};
   const int len = c.code_len <= ispl::SUB ? grid_length(c) : 0;
   if (len == 0 || n_pulses < kMinFoldPulses) return gp;
@@ -534,7 +536,7 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, 
   force.bytes = std::min(kGridChunkBytes, bytes);
   force.doubles = true;
   double round_us;
-  const double by_products = products_us(c, n_bins, n_pulses, &round_us);
+  const double by_products = products_us(c, n_bins, precision, n_pulses, &round_us);
   const double on_grid = grid_split(c, len, n_pulses, force, &gp) + 6.0 +
                          passes * (6.0 + (runs + blocks - 1) / blocks * 0.0147 * c.code_len) +
                          (lines ? 15.0 + round_us : 0.0);
@@ -545,7 +547,7 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t n_pulses, 
 
 static const GridPlan& zoom_plan_of(ispl_zoom* z, int32_t n_pulses) {
   if (z->plan_pulses != n_pulses) {
-    z->plan = z->grid ? zoom_grid_plan(z->ctx->cfg, z->n_bins, n_pulses, z->lines, z->grid_bytes)
+    z->plan = z->grid ? zoom_grid_plan(z->ctx->cfg, z->n_bins, z->precision, n_pulses, z->lines, z->grid_bytes)
                       : GridPlan{};
     z->plan_pulses = n_pulses;
   }
@@ -1073,7 +1075,7 @@ static ispl_status create_zoom(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
     e = hipMalloc(&z->code_binary, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
   z->lines = lines;
   // (a call of fewer pulses gains less from the grid)
-  const GridPlan gp = zoom_grid_plan(c, n_bins, c.max_pulses, lines);
+  const GridPlan gp = zoom_grid_plan(c, n_bins, precision, c.max_pulses, lines);
   if (e == hipSuccess && gp.len > 0) {  // sums, sign bits with their flags and the list in one block
     z->grid_bytes = std::min(kGridBytes, int64_t{8} * gp.len * c.n_gates * gp.chunks);
     z->grid_bits_rows = grid_bits_rows(c);
