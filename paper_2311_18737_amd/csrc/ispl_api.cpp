@@ -520,8 +520,17 @@ double products_us(const ispl_config& c, int32_t n_bins, int32_t precision, int3
          6.8 * static_cast<double>(rounds - 1);
 }
 
+// Whether a call's FP16 products scale each gate's samples by themselves, for which every gate is read
+// once more: calls of up to 4 M samples (a few us); the others by pulse, so that a gate far weaker
+// than the pulse's strongest loses bits.
+constexpr int64_t kGateExpSamples = int64_t{1} << 22;
+bool by_gate(const ispl_config& c, int32_t n_pulses) {
+  return static_cast<int64_t>(n_pulses) * c.n_gates <= kGateExpSamples / c.code_len;
+}
+
 // The grid plan of a zoom call, or none (then matrix products): by estimated times, with
-// `lines` (windows of gates chosen for their lines) as if some gates were redone by products.
+// `lines` (windows of gates chosen for their lines) as if some gates were redone by products; FP16
+// products scaled by pulse only for those.
 // Measured (pulses x gates, L, N, K: us by products, on the grid):
 // 50 x 64, 128, 4096, 128: 16.4, 19.0; 100 x 64, 256, 16384, 256: 25.2, 22.7;
 // 1000 x 64, same: 95.6, 56.5; 100 x 1000, same: 165, 86; 8 x 300, 1000, 16384, 4096: 1300, 325.
@@ -540,7 +549,9 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t precision,
   const double on_grid = grid_split(c, len, n_pulses, force, &gp) + 6.0 +
                          passes * (6.0 + (runs + blocks - 1) / blocks * 0.0147 * c.code_len) +
                          (lines ? 15.0 + round_us : 0.0);
-  return on_grid < 0.95 * by_products ? gp : GridPlan{};
+  const bool on = on_grid < 0.95 * by_products ||
+                  (precision == ISPL_ZOOM_FP16X3 && !lines && !by_gate(c, n_pulses));
+  return on ? gp : GridPlan{};
 }
 
 }  // namespace
@@ -1067,7 +1078,9 @@ static ispl_status create_zoom(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
     e = hipMalloc(&z->partial, sizeof(float) * static_cast<size_t>(z->chunks_max) * c.n_gates *
                                    static_cast<size_t>(n_bins));
   if (e == hipSuccess && precision == ISPL_ZOOM_FP16X3)
-    e = hipMalloc(&z->col_exp, sizeof(int32_t) * static_cast<size_t>(c.max_pulses));
+    e = hipMalloc(&z->col_exp, sizeof(int32_t) * static_cast<size_t>(std::max<int64_t>(
+                                   c.max_pulses, std::min(int64_t{c.max_pulses} * c.n_gates,
+                                                          kGateExpSamples / c.code_len))));
   if (e == hipSuccess)
     e = hipMalloc(&z->code_bits, sizeof(uint32_t) * static_cast<size_t>(c.max_pulses) *
                                      static_cast<size_t>(code_pad / 32));
@@ -1199,6 +1212,7 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
   a.col_tiles = zp.ct;
   a.partial = z->partial;
   a.col_exp = z->col_exp;
+  a.gate_exps = by_gate(c, n_pulses) ? 1 : 0;
   a.code_bits = z->code_bits;
   a.code_binary = z->code_binary;
   a.row_lo = c.first_gate;
@@ -1688,6 +1702,9 @@ ispl_status ispl_lzoom_peaks(ispl_lzoom* z, const void* samples, const float* tx
     pe.samples = samples;
     pe.tx = tx_code;
     pe.exps = z->zoom->precision == ISPL_ZOOM_FP16X3 ? z->zoom->col_exp : nullptr;
+    pe.gate_exps = by_gate(c, n_pulses) ? 1 : 0;
+    pe.first_gate = c.first_gate;
+    pe.gate_step = c.gate_step;
     pe.bits = z->zoom->code_bits;
     pe.binary = z->zoom->code_binary;
     pe.bit_words = z->zoom->code_pad / 32;

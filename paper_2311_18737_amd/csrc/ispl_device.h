@@ -19,6 +19,18 @@ __device__ __forceinline__ float2 load_any_sample(const void* base, int32_t samp
   return reinterpret_cast<const float2*>(base)[i];
 }
 
+// The exponent of a column whose largest |x|^2 and |c|^2 are mx and mc (see below).
+__device__ __forceinline__ int column_exponent(float mx, float mc) {
+  int e = 0;
+  const float m = sqrtf(mx) * sqrtf(mc);
+  if (m > 0.f && isfinite(m)) {
+    int ex;
+    frexpf(m, &ex);  // m < 2^ex
+    e = 14 - ex;
+  }
+  return max(-60, min(60, e));
+}
+
 // FP16 column exponent of pulse p, computed by one workgroup of 256 threads:
 // the e with max|x| max|c| 2^e < 2^14 over the samples [lo, hi) of the pulse
 // row that some gate reads and over the pulse's code, so that no split FP16
@@ -73,15 +85,51 @@ __device__ __forceinline__ void pulse_exponent_block(const void* __restrict__ sa
   if (threadIdx.x == 0) {
     mx = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
     mc = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
-    int e = 0;
-    const float m = sqrtf(mx) * sqrtf(mc);
-    if (m > 0.f && isfinite(m)) {
-      int ex;
-      frexpf(m, &ex);  // m < 2^ex
-      e = 14 - ex;
-    }
-    exps[p] = max(-60, min(60, e));
+    exps[p] = column_exponent(mx, mc);
   }
+}
+
+// The same for each gate by itself, exps[n_gates p + g], so that a gate far weaker than the strongest
+// of its pulse keeps its bits: the gates 8 group ... 8 group + 7 of pulse p, two per wave.
+__device__ __forceinline__ void gate_exponents_block(const void* __restrict__ samples,
+                                                     int32_t sample_type,
+                                                     const float* __restrict__ tx, int64_t stride,
+                                                     int32_t first_gate, int32_t gate_step,
+                                                     int32_t n_gates, int32_t code_len,
+                                                     int32_t tx_per_pulse, int p, int group,
+                                                     int32_t* __restrict__ exps) {
+  const int lane = threadIdx.x & 63, g0 = 8 * group + 2 * static_cast<int>(threadIdx.x >> 6);
+  if (g0 >= n_gates) return;  // whole waves, no barrier
+  const float2* txp = reinterpret_cast<const float2*>(tx) +
+                      (tx_per_pulse ? static_cast<int64_t>(p) * code_len : 0);
+  const int64_t at0 = static_cast<int64_t>(p) * stride + first_gate + static_cast<int64_t>(g0) * gate_step;
+  const int64_t at1 = g0 + 1 < n_gates ? at0 + gate_step : at0;
+  float mc = 0.f, m0 = 0.f, m1 = 0.f;
+  constexpr int U = 4;
+  for (int n0 = lane; n0 < code_len; n0 += 64 * U) {
+    float2 c[U], x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // (past the end the last sample again)
+      const int n = min(n0 + 64 * u, code_len - 1);
+      c[u] = txp[n];
+      x[u] = load_any_sample(samples, sample_type, at0 + n);
+      y[u] = load_any_sample(samples, sample_type, at1 + n);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mc = fmaxf(mc, c[u].x * c[u].x + c[u].y * c[u].y);
+      m0 = fmaxf(m0, x[u].x * x[u].x + x[u].y * x[u].y);
+      m1 = fmaxf(m1, y[u].x * y[u].x + y[u].y * y[u].y);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    mc = fmaxf(mc, __shfl_xor(mc, off));
+    m0 = fmaxf(m0, __shfl_xor(m0, off));
+    m1 = fmaxf(m1, __shfl_xor(m1, off));
+  }
+  if (lane < 2 && g0 + lane < n_gates)
+    exps[static_cast<int64_t>(n_gates) * p + g0 + lane] = column_exponent(lane == 0 ? m0 : m1, mc);
 }
 
 // Sign bits of pulse p's code for the zoom DFT, by one workgroup of 256

@@ -1410,12 +1410,15 @@ hipError_t redo_direct(const FusedArgs& f, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The same for zoom windows, by matrix products.
+// The same for zoom windows, by matrix products (their codes as complex numbers: a pass over all of
+// them less).
 hipError_t redo_products(const ZoomArgs& z, hipStream_t s) {
   ZoomArgs d = z;
   d.grid_len = 0;
   d.gate_list = z.redo_list;
   d.gate_count = z.redo_count;
+  d.code_bits = nullptr;
+  d.code_binary = nullptr;
   const hipError_t e = launch_zoom(d, s, true);
   if (e != hipSuccess || d.chunks == 1) return e;
   return launch_reduce_chunks(d.partial, d.out, static_cast<int64_t>(d.n_gates) * d.n_bins, d.chunks,

@@ -198,6 +198,7 @@ struct ProductArgs {
   float* out;               // [G][K]
   float* partial;           // [chunks][G][K] when chunks > 1
   int32_t* col_exp;         // [P] per-pulse FP16 exponents (written by the launch)
+  int32_t gate_exps;        // or [P][G], one for each gate of a pulse
   int64_t stride;
   int64_t row_lo, row_hi;   // samples of a pulse row that some gate reads
   int32_t n_fft;            // N
@@ -314,6 +315,7 @@ struct PulseExpArgs {
   uint32_t* bits;          // NULL: no code sign bits
   int32_t* binary;
   int64_t stride, lo, hi;  // rows and the span [lo, hi) some gate reads
+  int32_t gate_exps, first_gate, gate_step;  // exponents of each gate (see ProductArgs)
   int32_t sample_type, code_len, tx_per_pulse, n_pulses, bit_words;
 };
 // select_windows and, in the same launch, the zoom's per-pulse pass: FP16

@@ -189,7 +189,8 @@ select_windows(const float* __restrict__ logits, int32_t n_gates, int32_t fine_l
 }
 
 // The window decision (workgroups g < n_gates) and, in the same launch, the
-// zoom DFT's per-pulse FP16 exponents (workgroup n_gates + p for pulse p).
+// zoom DFT's per-pulse pass (workgroup n_gates + p for pulse p; with exponents of each gate, one for
+// every eight gates of a pulse).
 __global__ void __launch_bounds__(NT)
 select_and_exponents(const float* __restrict__ logits, int32_t n_gates, int32_t fine_len,
                      int32_t window_bins, float threshold, int32_t* __restrict__ bin_start,
@@ -202,12 +203,16 @@ select_and_exponents(const float* __restrict__ logits, int32_t n_gates, int32_t 
     select_window_block(b, logits, n_gates, fine_len, window_bins, threshold, bin_start,
                         confidence, flag, zoom_list, fallback_list, counts, done);
   } else {
-    if (pe.exps)
+    const int groups = pe.exps && pe.gate_exps ? (n_gates + 7) / 8 : 1;
+    const int p = (b - n_gates) / groups, group = (b - n_gates) % groups;
+    if (pe.exps && pe.gate_exps)
+      gate_exponents_block(pe.samples, pe.sample_type, pe.tx, pe.stride, pe.first_gate, pe.gate_step,
+                           n_gates, pe.code_len, pe.tx_per_pulse, p, group, pe.exps);
+    else if (pe.exps)
       pulse_exponent_block(pe.samples, pe.sample_type, pe.tx, pe.stride, pe.lo, pe.hi,
-                           pe.code_len, pe.tx_per_pulse, b - n_gates, pe.exps);
-    if (pe.bits)
-      code_bits_block(pe.tx, pe.code_len, pe.tx_per_pulse, pe.bit_words, b - n_gates, pe.bits,
-                      pe.binary);
+                           pe.code_len, pe.tx_per_pulse, p, pe.exps);
+    if (pe.bits && group == 0)
+      code_bits_block(pe.tx, pe.code_len, pe.tx_per_pulse, pe.bit_words, p, pe.bits, pe.binary);
   }
 }
 
@@ -376,7 +381,8 @@ hipError_t launch_select_and_exponents(const float* logits, int32_t n_gates, int
                                        float* confidence, int32_t* flag, int32_t* zoom_list,
                                        int32_t* fallback_list, int32_t* counts, int32_t* done,
                                        const PulseExpArgs& pe, hipStream_t s) {
-  const unsigned blocks = static_cast<unsigned>(n_gates) + static_cast<unsigned>(pe.n_pulses);
+  const unsigned groups = pe.exps && pe.gate_exps ? static_cast<unsigned>(n_gates + 7) / 8 : 1u;
+  const unsigned blocks = static_cast<unsigned>(n_gates) + groups * static_cast<unsigned>(pe.n_pulses);
   hipLaunchKernelGGL(select_and_exponents, dim3(blocks), dim3(NT), 0, s, logits, n_gates,
                      fine_len, window_bins, threshold, bin_start, confidence, flag, zoom_list,
                      fallback_list, counts, done, pe);

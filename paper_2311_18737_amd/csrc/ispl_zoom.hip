@@ -35,6 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ispl_device.h"
@@ -192,18 +193,23 @@ struct Item {
 // spreads the 16 lanes of each quarter wave's store over 16 bank groups.
 __device__ __forceinline__ int b_slot(int ks, int ln) { return ln ^ ((8 * ks + 4 * (ln >> 5)) & 15); }
 
+// The FP16 exponent of a pulse's column in gate g's products.
+__device__ __forceinline__ int col_exponent(const ProductArgs& a, int p, int g) {
+  return a.col_exp[a.gate_exps ? static_cast<int64_t>(a.n_gates) * p + g : p];
+}
+
 // Item context of pulse block pb: pulse pb + pc past p1 reads the first pulse
 // of the range instead (valid loads, zeroed when stored).
 template <int PREC>
 __device__ __forceinline__ void item_of(const ProductArgs& a, Item& it, int pb, int pc, int p0,
-                                        int p1, int64_t gate_off, int words) {
+                                        int p1, int g, int64_t gate_off, int words) {
   const int p = pb + pc;
   const int pr = p < p1 ? p : p0;
   it.rowp = static_cast<int64_t>(pr) * a.stride + gate_off;
   const int64_t row = a.tx_per_pulse ? pr : 0;
   it.txp = reinterpret_cast<const float2*>(a.tx) + row * a.code_len;
   it.bitp = a.code_bits ? a.code_bits + row * words : nullptr;
-  const int e = PREC == 1 ? a.col_exp[pr] : 0;
+  const int e = PREC == 1 ? col_exponent(a, pr, g) : 0;
   it.scale = PREC == 1 && p < p1 ? ldexpf(1.f, e) : 1.f;
 }
 
@@ -499,7 +505,7 @@ __global__ void __launch_bounds__(ZTA) zoom_spectra(ProductArgs a) {
       ChunkRegs<ST> r;
       Item it;
       for (int pb = p0; pb < p1; pb += NCOL) {
-        if (item) item_of<PREC>(a, it, pb, pc, p0, p1, gate_off, words);
+        if (item) item_of<PREC>(a, it, pb, pc, p0, p1, g, gate_off, words);
         const bool full_block = pb + NCOL <= p1;
         for (int ch = 0; ch < nchunks; ++ch) {
           if (item) {
@@ -529,12 +535,12 @@ __global__ void __launch_bounds__(ZTA) zoom_spectra(ProductArgs a) {
       BitRegs<ST> ra, rb;  // first halves in ra, second halves in rb
       Item it, itn;
       if (item) {
-        item_of<PREC>(a, it, p0, pc, p0, p1, gate_off, words);
+        item_of<PREC>(a, it, p0, pc, p0, p1, g, gate_off, words);
         fetch_bits<ST, VEC>(a, ra, it, 8 * q);
       }
       for (int pb = p0; pb < p1; pb += NCOL) {
         const bool has_next = pb + NCOL < p1;
-        if (item && has_next) item_of<PREC>(a, itn, pb + NCOL, pc, p0, p1, gate_off, words);
+        if (item && has_next) item_of<PREC>(a, itn, pb + NCOL, pc, p0, p1, g, gate_off, words);
         const bool full_block = pb + NCOL <= p1;
         for (int ch = 0; ch < nchunks; ++ch) {
           if (item) {
@@ -657,7 +663,7 @@ __global__ void __launch_bounds__(ZTA) zoom_spectra(ProductArgs a) {
 #pragma unroll
     for (int c = 0; c < CTW; ++c) {
       const int pcol = pb + 32 * (ct0 + c) + (lane & 31);
-      const float un = (PREC == 1 && pcol < p1) ? ldexpf(1.f, -2 * a.col_exp[pcol]) : 1.f;
+      const float un = (PREC == 1 && pcol < p1) ? ldexpf(1.f, -2 * col_exponent(a, pcol, g)) : 1.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const float re = acc[0][c][i] - acc[2][c][i], im = acc[0][c][i] + acc[1][c][i];
@@ -701,19 +707,23 @@ __global__ void __launch_bounds__(ZTA) zoom_spectra(ProductArgs a) {
   }
 }
 
-// Per-pulse pass, one workgroup per pulse: FP16 exponents (exps != NULL)
-// and code sign bits (bits != NULL).
+// Per-pulse pass, one workgroup per pulse (and eight gates, with exponents of each gate): FP16
+// exponents (exps != NULL) and code sign bits (bits != NULL).
 __global__ void __launch_bounds__(256)
 pulse_prep(const void* __restrict__ samples, int32_t sample_type, const float* __restrict__ tx,
            int64_t stride, int64_t lo, int64_t hi, int32_t code_len, int32_t tx_per_pulse,
            int32_t* __restrict__ exps, int32_t words, uint32_t* __restrict__ bits,
-           int32_t* __restrict__ binary, const int32_t* __restrict__ count) {
+           int32_t* __restrict__ binary, int32_t gate_exps, int32_t first_gate, int32_t gate_step,
+           const int32_t* __restrict__ count) {
   if (count && *count <= 0) return;  // no gate listed
-  const int p = static_cast<int>(blockIdx.x);
-  if (exps)
+  const int p = static_cast<int>(blockIdx.x), group = static_cast<int>(blockIdx.y);
+  if (exps && gate_exps > 0)
+    gate_exponents_block(samples, sample_type, tx, stride, first_gate, gate_step, gate_exps, code_len,
+                         tx_per_pulse, p, group, exps);
+  else if (exps)
     pulse_exponent_block(samples, sample_type, tx, stride, lo, hi, code_len, tx_per_pulse, p,
                          exps);
-  if (bits) code_bits_block(tx, code_len, tx_per_pulse, words, p, bits, binary);
+  if (bits && group == 0) code_bits_block(tx, code_len, tx_per_pulse, words, p, bits, binary);
 }
 
 template <int PREC, int ST, int RT>
@@ -746,9 +756,12 @@ hipError_t launch_zoom(const ZoomArgs& a, hipStream_t stream, bool prep) {
   if (a.grid_len > 0) return launch_zoom_folded(a, stream);
   int32_t* exps = a.precision == 1 ? a.col_exp : nullptr;
   if (prep && (exps || a.code_bits)) {
-    hipLaunchKernelGGL(pulse_prep, dim3(static_cast<unsigned>(a.n_pulses)), dim3(256), 0, stream,
+    const int gate_exps = exps && a.gate_exps ? a.n_gates : 0;
+    const dim3 grid(static_cast<unsigned>(a.n_pulses), static_cast<unsigned>(std::max(1, (gate_exps + 7) / 8)));
+    hipLaunchKernelGGL(pulse_prep, grid, dim3(256), 0, stream,
                        a.samples, a.sample_type, a.tx, a.stride, a.row_lo, a.row_hi, a.code_len,
-                       a.tx_per_pulse, exps, a.code_pad / 32, a.code_bits, a.code_binary,
+                       a.tx_per_pulse, exps, a.code_pad / 32, a.code_bits, a.code_binary, gate_exps,
+                       a.first_gate, a.gate_step,
                        a.gate_list ? a.gate_count : nullptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -165,3 +165,38 @@ def test_power_far_below_the_mean(ispl, shape):
     d = 2.0 ** -25 * 64.0
     bound = 2.0 * d * np.sqrt(ref * np.maximum(ref, mean)) + d * d * mean
     assert (np.abs(got - ref) / bound).max() <= 1.0
+
+
+@pytest.mark.parametrize("case", [
+    # L,   N,    G,  P,  K,   type, per-pulse codes
+    (100, 4096, 24, 20, 128, "c64", True),
+    (256, 16384, 40, 60, 256, "c64", False),
+    (130, 2048, 70, 33, 384, "c64", True),
+    (2000, 16384, 9, 25, 128, "c64", True),
+], ids=lambda c: "L{}_N{}_G{}_P{}_K{}_{}_{}".format(*c))
+def test_zoom_of_gates_far_apart_in_power(ispl, case):
+    """Gates from 0 to -160 dB side by side in every pulse: each one's window keeps the FP16 split's
+    accuracy relative to its own mean."""
+    L, N, G, P, K, st, per = case
+    rng = np.random.default_rng(L)
+    stride = G * L
+    tx = (rng.integers(0, 2, (P if per else 1, L)) * 2 - 1).astype(np.complex64)
+    scale = 10.0 ** (-8.0 * rng.permutation(G) / (G - 1))
+    x = rng.standard_normal((P, G, L, 2)).view(np.complex128)[..., 0] * scale[None, :, None]
+    x = x.reshape(P, stride).astype(np.complex64)
+    ref = oracle_spectra(x, tx, n_gates=G, gate_step=L, first_gate=0, fft_len=N, tx_per_pulse=per)
+    start = rng.integers(0, N, G).astype(np.int32)
+    ctx = ispl.Context(code_len=L, fft_len=N, n_gates=G, gate_step=L, pulse_stride=stride,
+                       sample_type=st, max_pulses=P)
+    zoom = ispl.Zoom(ctx, K, "fp16x3")
+    out = zoom.spectra(torch.from_numpy(x).to(DEV), torch.from_numpy(tx).to(DEV),
+                       torch.from_numpy(start).to(DEV))
+    got = out.cpu().numpy().astype(np.float64)
+    zoom.close()
+    ctx.close()
+    idx = (start.astype(np.int64)[:, None] + np.arange(K)) % N
+    mean = ref.mean(axis=1, keepdims=True)
+    want = np.take_along_axis(ref, idx, axis=1)
+    d = 8.0 * 2.0 ** -22
+    bound = 2.0 * d * np.sqrt(want * np.maximum(want, mean)) + d * d * mean
+    assert (np.abs(got - want) / bound).max() <= 1.0
