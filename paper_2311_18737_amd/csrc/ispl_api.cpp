@@ -158,12 +158,14 @@ Plan make_plan(const ispl_config& c, int32_t n_pulses, int32_t force_rw = 0,
 
 // Folded integration: fewest points of a grid that holds |X|^2 of an L-sample
 // row, a power of two >= 2 L - 1 (at least 128), or 0 when the N bins are fewer
-// or the code has no grid kernel.
+// or the code has no grid kernel.  Grids of 16384 points only as all the bins: a shorter one gained
+// 1.66 times at most (100 pulses x 250 gates, L = 8000, N = 32768: direct 1238 us, 745), and lines
+// from -18 dB per sample on would have such a code's gates redone.
 int grid_length(const ispl_config& c) {
   if (c.code_len > 8 * ispl::SUB) return 0;
   int m = 128;
   while (m < 2 * c.code_len - 1) m *= 2;
-  return m <= c.fft_len ? m : 0;
+  return m <= c.fft_len && (m <= 8 * ispl::SUB || m == c.fft_len) ? m : 0;
 }
 
 // Fewest pulse-gate transforms whose launch first packs the codes into sign
@@ -662,14 +664,15 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
   const GridPlan gp = folds ? grid_plan(*cfg, cfg->max_pulses) : GridPlan{};
   folds = gp.len > 0;
 
-  // one block: double tables when there is a grid, the FP32 table, then the grid pass's sign bits
+  // one block: double tables when there is a shorter grid, the FP32 table, then the grid pass's sign bits
   // with their flags and the list of gates to redo
   std::vector<double> tables;
-  if (folds)
+  const bool doubles = folds && grid_length(*cfg) < cfg->fft_len;
+  if (doubles)
     tables = double_tables(*cfg);
   else
     tables = twiddle_table(cfg->fft_len);
-  const size_t n = 2 * static_cast<size_t>(cfg->fft_len), head = folds ? tables.size() : 0;
+  const size_t n = 2 * static_cast<size_t>(cfg->fft_len), head = doubles ? tables.size() : 0;
   std::vector<unsigned char> image(head * sizeof(double) + n * sizeof(float));
   std::memcpy(image.data(), tables.data(), head * sizeof(double));
   for (size_t i = 0; i < n; ++i) {
@@ -697,9 +700,11 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
     return fail(ISPL_ERR_OUT_OF_MEMORY, "tables (%zu bytes): %s", bytes, hipGetErrorString(e));
   }
   ctx->twiddle = reinterpret_cast<float*>(base + head * sizeof(double));
-  if (folds) {
+  if (doubles) {
     ctx->twiddle64 = reinterpret_cast<double*>(base);
     ctx->grid_gain = ctx->twiddle64 + n;
+  }
+  if (folds) {
     ctx->grid_bits_rows = bit_rows;
     ctx->grid_bits = reinterpret_cast<uint32_t*>(base + image.size());
     ctx->grid_binary = reinterpret_cast<int32_t*>(ctx->grid_bits + static_cast<size_t>(bit_rows) * words);

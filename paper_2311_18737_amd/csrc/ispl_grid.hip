@@ -752,11 +752,10 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
 // The transforms run in double precision: a line of power S_l leaves rounding of
 // about 1e-7 S_l at its mirror frequency and other places of an FP32
 // transform's structure, where S may be a hundred times smaller, which no direct
-// transform does (1000 gates of N = 16384 take 69 us, in FP32 50).  The lags are double too (FP32
-// for M = 16384, where they would not fit): with FP32 lags a line at -10 dB left 7e-7 at L = 1000,
-// now 4e-7.
+// transform does (1000 gates of N = 16384 take 69 us, in FP32 50).  The lags are double too: with
+// FP32 lags a line at -10 dB left 7e-7 at L = 1000, now 4e-7.
 
-// SG-point DFT in place, natural order (SG = 2, 4 or 8).
+// SG-point DFT in place, natural order (SG = 2 or 4).
 template <int SG>
 __device__ __forceinline__ void dft_small64(complex64d (&z)[SG]) {
   auto add = [](complex64d a, complex64d b) { return complex64d{a.x + b.x, a.y + b.y}; };
@@ -772,18 +771,9 @@ __device__ __forceinline__ void dft_small64(complex64d (&z)[SG]) {
     const complex64d a = z[0], b = z[1];
     z[0] = add(a, b);
     z[1] = sub(a, b);
-  } else if constexpr (SG == 4) {
-    four(z[0], z[1], z[2], z[3]);
   } else {
-    constexpr double r2 = 0.70710678118654752440;  // cos(pi / 4)
-    complex64d e0 = z[0], e1 = z[2], e2 = z[4], e3 = z[6], o0 = z[1], o1 = z[3], o2 = z[5], o3 = z[7];
-    four(e0, e1, e2, e3);
-    four(o0, o1, o2, o3);
-    o1 = complex64d{r2 * (o1.x + o1.y), r2 * (o1.y - o1.x)};   // W_8
-    o2 = complex64d{o2.y, -o2.x};                              // -i
-    o3 = complex64d{r2 * (o3.y - o3.x), -r2 * (o3.x + o3.y)};  // W_8^3
-    z[0] = add(e0, o0), z[4] = sub(e0, o0), z[1] = add(e1, o1), z[5] = sub(e1, o1);
-    z[2] = add(e2, o2), z[6] = sub(e2, o2), z[3] = add(e3, o3), z[7] = sub(e3, o3);
+    static_assert(SG == 4, "two or four segments");
+    four(z[0], z[1], z[2], z[3]);
   }
 }
 
@@ -885,10 +875,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   __shared__ __attribute__((aligned(16))) float2 xs[W * XWAVE];
   __shared__ __attribute__((aligned(16))) double sums[LONG ? 1 : 2 * SUB];  // M <= 2048: the grid
   __shared__ float up_s[SG == 0 ? SUB : 1];      // M < 1024: the grid of 1024 points
-  // q[n] and q[-n], n < M / 2, and one zero more (before that a transform's parts); in double
-  // where they fit
-  using lag_t = std::conditional_t<SG == 8, float, double>;
-  __shared__ lag_t qp[LONG ? SG * SUB + 1 : SUB + 1], qm[LONG ? SG * SUB + 1 : SUB + 1];
+  // q[n] and q[-n], n < M / 2, and one zero more (before that a transform's parts)
+  __shared__ double qp[LONG ? SG * SUB + 1 : SUB + 1], qm[LONG ? SG * SUB + 1 : SUB + 1];
   __shared__ double red[W];
   __shared__ float2 red_ends[W];
 
@@ -911,8 +899,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 
   // With r = conj(DFT) / M the lags n are q[n] = Re r + Im r, q[-n] = Re r - Im r.
   auto put_lag = [&](int n, complex64d f) {
-    qp[n] = static_cast<lag_t>(scale * (f.x - f.y));
-    qm[n] = static_cast<lag_t>(scale * (f.x + f.y));
+    qp[n] = scale * (f.x - f.y);
+    qm[n] = scale * (f.x + f.y);
   };
   // The lags n and m = n_cpx - n in place of F[n], F[m] (F: the transform of the
   // complex points z[2 a] + i z[2 a + 1]).
@@ -934,8 +922,6 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
   constexpr int PER_ROUND = W;
   auto class_of = [&](int task) { return task + 1 + task / rmask; };
 
-  // (FP32 lags of so small a spectrum lose bits)
-  auto tiny = [](const GridStats& s) { return SG == 8 && s.hi > 0.f && s.hi < 1e-30f; };
   GridStats st;
   double mean;
   if constexpr (LONG) {
@@ -952,7 +938,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
         st.add(s.y);
       }
     st.reduce(red, red_ends, M);
-    if (!st.usable(a.peak_limit) || tiny(st)) {  // uniform
+    if (!st.usable(a.peak_limit)) {  // uniform
       if (share == 0 && tid == 0) redo_gate(a, g);
       return;
     }
@@ -983,8 +969,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
       wave_lds_sync();
       class_transform64(v, xd, tw64, M / 2, N, wave, lane, [&](int i, complex64d f) {
         const int n = wave + SG * bin_of(i, lane);
-        qp[n] = static_cast<lag_t>(f.x);
-        qm[n] = static_cast<lag_t>(f.y);
+        qp[n] = f.x;
+        qm[n] = f.y;
       });
     }
     __syncthreads();
@@ -998,7 +984,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     // ---- the grid, chunk sums in ascending order
     st = gather_grid(a, row, cs, sums, tid);
     st.reduce(red, red_ends, M);
-    if (!st.usable(a.peak_limit) || tiny(st)) {  // uniform
+    if (!st.usable(a.peak_limit)) {  // uniform
       if (share == 0 && tid == 0) redo_gate(a, g);
       return;
     }
@@ -1010,8 +996,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     if (wave == 0) {
       complex64d v[16];
       auto to_lags = [&](int i, complex64d f) {
-        qp[bin_of(i, lane)] = static_cast<lag_t>(f.x);
-        qm[bin_of(i, lane)] = static_cast<lag_t>(f.y);
+        qp[bin_of(i, lane)] = f.x;
+        qm[bin_of(i, lane)] = f.y;
       };
       if constexpr (WIDE) {
 #pragma unroll
@@ -1301,7 +1287,6 @@ hipError_t launch_grid(const FoldArgs& a, hipStream_t s) {
     case 2048: return launch_grid_w<11, ST, false>(a, s);
     case 4096: hipLaunchKernelGGL((grid_long<4, ST, false>), grid, dim3(256), 0, s, a); break;
     case 8192: hipLaunchKernelGGL((grid_long<8, ST, false>), grid, dim3(512), 0, s, a); break;
-    case 16384: hipLaunchKernelGGL((grid_long<16, ST, false>), grid, dim3(1024), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1319,7 +1304,6 @@ hipError_t launch_expand(FoldArgs a, hipStream_t s) {
     case 1: hipLaunchKernelGGL((expand_grid<1>), grid, block, 0, s, a); break;
     case 2: hipLaunchKernelGGL((expand_grid<2>), grid, block, 0, s, a); break;
     case 4: hipLaunchKernelGGL((expand_grid<4>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((expand_grid<8>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
