@@ -41,11 +41,12 @@ struct ispl_ctx {
   uint32_t* grid_bits;  // codes as sign bits, grid_bits_rows rows, and their flags
   int32_t* grid_binary;
   int32_t grid_bits_rows;
-  int32_t* redo;        // number and list of the gates that a call's expansion leaves over
+  int32_t* redo;        // number and list of the gates that a call's expansion leaves over, and
+                        // flags of those found early
   struct {              // the grid plan of the last call's form (n_pulses 0: none yet)
     int32_t n_pulses, force_rw, force_chunks;
     bool deferred;
-    int32_t len, waves, chunks;
+    int32_t len, waves, chunks, probe;
   } plan;
   void* zoom_tables;    // the double tables when only a zoom needs them
 };
@@ -190,6 +191,7 @@ struct GridPlan {
   int len;     // 0: the direct transform
   int waves;   // per workgroup
   int chunks;  // pulse chunks, each a workgroup per gate
+  int probe;   // pulses of the first of two passes (0: one pass)
 };
 
 // Most grid scratch of a context (2000 gates of L = 2000 in one run: in two 5.6 ms, 5.1 in one),
@@ -240,7 +242,7 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, const GridFor
       const double step_us = std::max(1.6, 0.85 * static_cast<double>(resident * waves) / 4);
       const double us = rounds * (iters * step_us + 3.0) + chunks * chunk_us + (chunks > 1 ? sum_us : 0.0);
       if (out->len == 0 || us < best) {
-        *out = GridPlan{len, waves, static_cast<int>(chunks)};
+        *out = GridPlan{len, waves, static_cast<int>(chunks), 0};
         best = us;
       }
     }
@@ -289,6 +291,17 @@ int32_t grid_run(int32_t n_gates, int64_t most) {
 // below its mean that many gates would be redone.
 constexpr int32_t kMinFoldPulses = 3;
 
+// Pulses after which a long call looks for gates that will be redone, whose other pulses it then
+// leaves out (0: not at all): a sixteenth, from 100 us on a grid on.  Measured (us; no gate has a
+// line: one pass, two passes; all have one at 0 dB: direct, one pass and direct, two passes and direct):
+// 500 pulses x 600 gates, L = 480, N = 8192: 367, 398; 2057, 2668, 2169
+// 500 x 500, 1000, 16384: 616, 628; 3131, 3884, 3243
+// 250 x 500, 2000, 32768: 992, 1023; 3999, 4925, 4127
+// 200 x 500, 4000, 16384: 1329, 1370; 2295, 3591, 2508
+int32_t probe_pulses(int32_t n_pulses, double grid_us) {
+  return n_pulses >= 64 && grid_us >= 100.0 ? std::max(16, n_pulses / 16) : 0;
+}
+
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, const GridForce& force = {}) {
   GridPlan fold{}, whole{};
   const int len = grid_length(c);
@@ -298,10 +311,12 @@ GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, const GridForce& forc
                               ? grid_split(c, c.fft_len, n_pulses, force, &whole)
                               : 0.0;
   if (len == c.fft_len || n_pulses < kMinFoldPulses) return whole;
-  const double fold_us = grid_split(c, len, n_pulses, force, &fold) + expand_us(c, len);
-  // gates with a strong line are redone, so a call may cost both: folded from a fifth less on
-  if (whole.len > 0) return fold_us < 0.8 * whole_us ? fold : whole;
-  return fold_us < 0.8 * direct_us(c, n_pulses) ? fold : GridPlan{};
+  const double grid_us = grid_split(c, len, n_pulses, force, &fold), fold_us = grid_us + expand_us(c, len);
+  fold.probe = probe_pulses(n_pulses, grid_us);
+  // gates with a strong line are redone, so a call may cost both: folded from a fifth less on, with
+  // few pulses, whose noise alone comes near the limit, from half
+  const double most = (whole.len > 0 ? whole_us : direct_us(c, n_pulses)) * (n_pulses < 16 ? 0.5 : 0.8);
+  return fold_us < most ? fold : whole;
 }
 
 // Scratch of calls whose longest runs on a grid by `pl` (of none: 0): its partials and sums, of
@@ -548,7 +563,9 @@ GridPlan zoom_grid_plan(const ispl_config& c, int32_t n_bins, int32_t precision,
   force.doubles = true;
   double round_us;
   const double by_products = products_us(c, n_bins, precision, n_pulses, &round_us);
-  const double on_grid = grid_split(c, len, n_pulses, force, &gp) + 6.0 +
+  const double grid_us = grid_split(c, len, n_pulses, force, &gp);
+  gp.probe = probe_pulses(n_pulses, grid_us);
+  const double on_grid = grid_us + 6.0 +
                          passes * (6.0 + (runs + blocks - 1) / blocks * 0.0147 * c.code_len) +
                          (lines ? 15.0 + round_us : 0.0);
   const bool on = on_grid < 0.95 * by_products ||
@@ -691,7 +708,7 @@ static ispl_status create_ctx(const ispl_config* cfg, int32_t min_chunk_pulses, 
   if (folds) {
     ctx->grid_bytes = std::max(grid_scratch_bytes(*cfg, gp), std::min(partials, kGridBytes));
     redo_rows = grid_rows_max(*cfg, ctx->grid_bytes);
-    bytes += sizeof(uint32_t) * (static_cast<size_t>(bit_rows) * (words + 1) + 1 + redo_rows);
+    bytes += sizeof(uint32_t) * (static_cast<size_t>(bit_rows) * (words + 1) + 1 + 2 * redo_rows);
   }
   unsigned char* base = nullptr;
   e = hipMalloc(reinterpret_cast<void**>(&base), bytes);
@@ -822,9 +839,9 @@ static GridPlan ctx_grid_plan(ispl_ctx* ctx, int32_t n_pulses, bool deferred) {
     } else if (c.fft_len <= 2 * ispl::SUB) {
       grid_split(c, c.fft_len, n_pulses, force, &gp);
     }
-    p = {n_pulses, ctx->force_rw, ctx->force_chunks, deferred, gp.len, gp.waves, gp.chunks};
+    p = {n_pulses, ctx->force_rw, ctx->force_chunks, deferred, gp.len, gp.waves, gp.chunks, gp.probe};
   }
-  return GridPlan{p.len, p.waves, p.chunks};
+  return GridPlan{p.len, p.waves, p.chunks, p.probe};
 }
 
 // With deferred_chunks non-NULL a pulse-chunked plan leaves its partial
@@ -912,6 +929,8 @@ static ispl_status integrate_impl(ispl_ctx* ctx, const void* samples, const floa
     const AdaptiveFallback redo = adaptive_plan(c, n_pulses, nullptr, ctx->force_rw);
     a.redo_count = ctx->redo;
     a.redo_list = ctx->redo + 1;
+    a.redo_early = ctx->redo + 1 + a.grid_rows;
+    a.probe_pulses = gp.probe;
     a.redo_target = 4 * redo.target;
     a.redo_max_chunks = redo.max_chunks;
     a.redo_rows = static_cast<int32_t>(
@@ -1098,7 +1117,7 @@ static ispl_status create_zoom(ispl_ctx* ctx, int32_t n_bins, int32_t precision,
     z->grid_bytes = std::min(kGridBytes, int64_t{8} * gp.len * c.n_gates * gp.chunks);
     z->grid_bits_rows = grid_bits_rows(c);
     const size_t words = static_cast<size_t>(z->grid_bits_rows) * grid_bits_words(c);
-    const size_t ints = words + z->grid_bits_rows + 1 + grid_rows_max(c, z->grid_bytes);
+    const size_t ints = words + z->grid_bits_rows + 1 + 2 * grid_rows_max(c, z->grid_bytes);
     e = hipMalloc(&z->grid, static_cast<size_t>(z->grid_bytes) + sizeof(int32_t) * ints);
     if (e == hipSuccess) {
       z->grid_bits = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(z->grid) + z->grid_bytes);
@@ -1234,6 +1253,8 @@ static ispl_status zoom_impl(ispl_zoom* z, const void* samples, const float* tx_
     a.grid_rows = grid_run(c.n_gates, z->grid_bytes / (int64_t{8} * gp.len * gp.chunks));
     a.redo_count = z->redo;
     a.redo_list = z->redo + 1;
+    a.redo_early = z->redo + 1 + a.grid_rows;
+    a.probe_pulses = gp.probe;
     if (packs_bits(c, tx_per_pulse, n_pulses, z->grid_bits_rows)) {
       a.grid_bits = z->grid_bits;
       a.grid_binary = z->grid_binary;

@@ -294,6 +294,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
   const int c = bid % a.chunks, slot = bid / a.chunks;
   const int g = gate_of(a, slot);
   if (g < 0) return;
+  if constexpr (!WHOLE)
+    if (a.skip && a.skip[slot] != 0) return;
   const int L = a.code_len;
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   // pass-2 column k1 of this lane (bins k1 + (M / 64) (kc + 16 kd)) and its
@@ -375,8 +377,7 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
     }
   }
   sum_t* out = out_row<WHOLE>(a, g, slot, c);
-  const bool last = WHOLE && a.chunks == 1;
-  bool add = last && a.accumulate;
+  bool add = WHOLE ? a.chunks == 1 && a.accumulate : a.add != 0;
   // at most RUN_STEPS steps go into one FP32 sum (the same number of sums for
   // every run, which meet at its end), all into one double
   const int per_sum = WHOLE ? RUN_STEPS : max(1, runs.longest());
@@ -553,6 +554,8 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
   const int c = bid % a.chunks, slot = bid / a.chunks;
   const int g = gate_of(a, slot);
   if (g < 0) return;
+  if constexpr (!WHOLE)
+    if (a.skip && a.skip[slot] != 0) return;
   const int L = a.code_len, M = SUB * J, step = a.n_fft / M, nmask = a.n_fft - 1;
   const float2* __restrict__ tw = reinterpret_cast<const float2*>(a.twiddle);
   // (complex64 samples in flight take 16 registers)
@@ -647,8 +650,7 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
     }
   }
   sum_t* out = out_row<WHOLE>(a, g, slot, c);
-  const bool last = WHOLE && a.chunks == 1;
-  bool add = last && a.accumulate;
+  bool add = WHOLE ? a.chunks == 1 && a.accumulate : a.add != 0;
   const int per_sum = WHOLE ? RUN_STEPS : max(1, p1 - p0);  // (as in grid_spectra)
   for (int q0 = p0; q0 == p0 || q0 < p1; q0 += per_sum) {
     const int q1 = min(q0 + per_sum, p1);
@@ -834,6 +836,11 @@ struct GridStats {
   }
 };
 
+// Whether the gate's sums end with the probe's pulses.
+__device__ __forceinline__ bool left_out(const FoldArgs& a, int slot) {
+  return a.skip && a.skip[slot] != 0;
+}
+
 // Leaves gate g to the launches that follow (one thread per gate).
 __device__ __forceinline__ void redo_gate(const FoldArgs& a, int g) {
   a.redo_list[atomicAdd(a.redo_count, 1)] = g;
@@ -863,6 +870,42 @@ __device__ __forceinline__ GridStats gather_grid(const FoldArgs& a, const double
     part.add(s.y);
   }
   return part;
+}
+
+// After the first pulses of a long call: the gates whose largest point stands so far above the mean
+// that they will be redone: hi <= 0.9 sqrt(limit) mean here, hi <= sqrt(limit mean lo) at the end, with
+// lo about 0.8 mean.  (A gate left out that could have been expanded costs more than one summed for
+// nothing: at 0.7, 500 gates of L = 1000 with -10 dB lines took 3793 us, without a probe 619.)  One
+// workgroup per gate.
+__global__ void __launch_bounds__(64 * EXP_WAVES) probe_grid(FoldArgs a, int32_t* __restrict__ skip) {
+  __shared__ double red[EXP_WAVES];
+  __shared__ float2 red_ends[EXP_WAVES];
+  const int slot = blockIdx.x, M = a.grid_len;
+  if (gate_of(a, slot) < 0) return;
+  const double* row = a.grid + static_cast<int64_t>(slot) * M;
+  const int64_t cs = static_cast<int64_t>(a.rows) * M;
+  GridStats st;
+  for (int k = 2 * static_cast<int>(threadIdx.x); k < M; k += 2 * 64 * EXP_WAVES) {
+    double2 s = make_double2(0.0, 0.0);
+    for (int c0 = 0; c0 < a.chunks; c0 += 8) {
+      double2 q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        q[u] = *reinterpret_cast<const double2*>(row + min(c0 + u, a.chunks - 1) * cs + k);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (c0 + u < a.chunks) {
+          s.x += q[u].x;
+          s.y += q[u].y;
+        }
+    }
+    st.add(s.x);
+    st.add(s.y);
+  }
+  st.reduce(red, red_ends, M);
+  constexpr double MARGIN = 0.9;
+  const double h = st.hi, most = MARGIN * st.sum;
+  if (threadIdx.x == 0) skip[slot] = h * h <= a.peak_limit * most * most ? 0 : 1;
 }
 
 // SG: M / 2048 segments of 1024 lags each way (0: M <= 1024).  Two waves per SIMD:
@@ -938,7 +981,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
         st.add(s.y);
       }
     st.reduce(red, red_ends, M);
-    if (!st.usable(a.peak_limit)) {  // uniform
+    if (!st.usable(a.peak_limit) || left_out(a, slot)) {  // uniform
       if (share == 0 && tid == 0) redo_gate(a, g);
       return;
     }
@@ -984,7 +1027,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
     // ---- the grid, chunk sums in ascending order
     st = gather_grid(a, row, cs, sums, tid);
     st.reduce(red, red_ends, M);
-    if (!st.usable(a.peak_limit)) {  // uniform
+    if (!st.usable(a.peak_limit) || left_out(a, slot)) {  // uniform
       if (share == 0 && tid == 0) redo_gate(a, g);
       return;
     }
@@ -1172,7 +1215,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {
   const double* row = a.grid + static_cast<int64_t>(slot) * M;
   GridStats st = gather_grid(a, row, static_cast<int64_t>(a.rows) * M, grid, tid);
   st.reduce(red, red_ends, M);
-  if (!st.usable(a.peak_limit)) {  // uniform
+  if (!st.usable(a.peak_limit) || left_out(a, slot)) {  // uniform
     if (part == 0 && tid == 0) redo_gate(a, g);
     return;
   }
@@ -1307,6 +1350,34 @@ hipError_t launch_expand(FoldArgs a, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// A run of gates summed on the grid; with probe > 0 in two passes, the second without the gates
+// whose first `probe` pulses show a line too strong (a.skip then tells the expansion).
+hipError_t sum_grid(FoldArgs& a, int sample_type, int probe, int32_t* early, hipStream_t s) {
+  if (probe <= 0 || probe >= a.n_pulses)
+    return sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+  FoldArgs first = a, rest = a;
+  first.n_pulses = probe;
+  first.skip = nullptr;
+  hipError_t e = sample_type == 1 ? launch_grid<1>(first, s) : launch_grid<0>(first, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(probe_grid, dim3(static_cast<unsigned>(a.rows)), dim3(64 * EXP_WAVES), 0, s, a, early);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  rest.n_pulses = a.n_pulses - probe;
+  rest.samples = static_cast<const char*>(a.samples) + probe * a.stride * (sample_type == 1 ? 4 : 8);
+  if (a.tx_per_pulse) {
+    rest.tx = a.tx + static_cast<int64_t>(2) * probe * a.code_len;
+    if (a.code_bits) {
+      rest.code_bits = a.code_bits + static_cast<int64_t>(probe) * (a.code_len > SUB ? SUB : 64);
+      rest.code_binary = a.code_binary + probe;
+    }
+  }
+  rest.skip = early;
+  rest.add = 1;
+  a.skip = early;
+  return sample_type == 1 ? launch_grid<1>(rest, s) : launch_grid<0>(rest, s);
 }
 
 // Sign bits of the call's code rows, if it has room for them.
@@ -1458,7 +1529,7 @@ hipError_t launch_folded(const FusedArgs& f, hipStream_t s) {
   for (int32_t s0 = 0; s0 < f.n_gates; s0 += f.grid_rows) {
     a.slot0 = s0;
     a.rows = std::min(f.n_gates - s0, f.grid_rows);
-    e = f.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+    e = sum_grid(a, f.sample_type, f.probe_pulses, f.redo_early, s);
     FoldArgs x = a;
     if (e == hipSuccess && a.grid_len > 2 * SUB && a.chunks > 1) {
       // a long grid's chunk partials by a launch of their own, behind them (the expansion's
@@ -1513,7 +1584,7 @@ hipError_t launch_zoom_folded(const ZoomArgs& z, hipStream_t s) {
     a.rows = std::min(z.n_gates - s0, z.grid_rows);
     // a workgroup or more per gate, up to two per CU (each forms the gate's lags)
     a.blocks = std::max(1, std::min(z.n_bins / 128, 512 / a.rows));
-    e = z.sample_type == 1 ? launch_grid<1>(a, s) : launch_grid<0>(a, s);
+    e = sum_grid(a, z.sample_type, z.probe_pulses, z.redo_early, s);
     if (e == hipSuccess) e = launch_window(a, s);
     if (e == hipSuccess) e = redo_products(z, s);
   }

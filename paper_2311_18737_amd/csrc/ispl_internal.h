@@ -104,7 +104,10 @@ struct FusedArgs : DirectArgs {
   // parameters and its partials in `grid`.
   int32_t* redo_list;
   int32_t* redo_count;
+  int32_t* redo_early;       // [grid_rows] with probe_pulses
   int32_t redo_target, redo_max_chunks, redo_rows;
+  int32_t probe_pulses;      // pulses summed before gates that are to be redone are first looked
+                             // for, which the others' pass then leaves out (0: not before its end)
 };
 
 // Words of one code row in the sign-bit form (one per first-pass thread).
@@ -147,6 +150,8 @@ struct FoldArgs {
   int32_t* redo_list;        // gates left to other launches, and their number
   int32_t* redo_count;
   float peak_limit;          // see GridStats
+  const int32_t* skip;       // [rows] gates found so after the probe's pulses, or NULL
+  int32_t add;               // onto the sums in `grid`
   int32_t slot0, rows;
   // a window of n_bins bins per gate from bin_start[gate] on (out [G][n_bins])
   const int32_t* bin_start;
@@ -232,6 +237,8 @@ struct ZoomArgs : ProductArgs {
   // products); see FusedArgs and launch_zoom_folded.  Gates left over run as products.
   int32_t* redo_list;        // [grid_rows]
   int32_t* redo_count;
+  int32_t* redo_early;
+  int32_t probe_pulses;
   double* grid;
   uint32_t* grid_bits;
   int32_t* grid_binary;

@@ -60,6 +60,7 @@ hipError_t launch_fused(const FusedArgs& a, hipStream_t st) {
     run_on(st, [c, k] {
       check_range(c.redo_list, size_t(c.grid_rows) * 4, "redo list");
       check_range(c.redo_count, 4, "redo count");
+      check_range(c.redo_early, size_t(c.grid_rows) * 4, "early flags");
       for (int i = 0; i < k; ++i) c.redo_list[i] = i;
       *c.redo_count = k;
       check_range(c.grid, size_t(c.redo_rows) * c.n_fft * 4, "redo partials");
@@ -90,6 +91,7 @@ hipError_t launch_zoom(const ZoomArgs& a, hipStream_t st, bool prep) {
     check_range(c.grid_gain, size_t(c.grid_len) * 8, "grid gains");
     check_range(c.redo_list, size_t(c.grid_rows) * 4, "redo list");
     check_range(c.redo_count, 4, "redo count");
+    check_range(c.redo_early, size_t(c.grid_rows) * 4, "early flags");
   });
   ZoomArgs d = a;  // the products of gates that are not expanded
   d.grid_len = 0;

@@ -167,6 +167,64 @@ def test_power_far_below_the_mean(ispl, shape):
     assert (np.abs(got - ref) / bound).max() <= 1.0
 
 
+@pytest.mark.parametrize("when", ["always", "late", "early"])
+@pytest.mark.parametrize("case", [
+    # L,    N,     G,   P,   type, per-pulse codes
+    (1000, 16384, 400, 200, "c64", True),
+    (1000, 16384, 400, 201, "ci16", False),
+    (300, 8192, 900, 333, "ci16", True),
+    (4000, 16384, 260, 130, "ci16", True),
+    (2000, 32768, 300, 129, "c64", False),
+    (6000, 32768, 130, 100, "c64", True),
+], ids=lambda c: "L{}_N{}_G{}_P{}_{}_{}".format(*c))
+def test_long_calls_of_mixed_gates(ispl, case, when):
+    """Calls long enough that gates with strong lines are looked for after their first pulses: lines
+    of 5 to 30 dB in some gates, in all pulses, only in the last half or only in the first tenth;
+    every tested gate, with and without a line, as exact as by an FP32 transform.  Listed gates and
+    accumulation give the same rows."""
+    L, N, G, P, st, per = case
+    rng = np.random.default_rng(L + P)
+    step = max(1, L // 8)
+    stride = 5 + (G - 1) * step + L
+    tx = (rng.integers(0, 2, (P if per else 1, L)) * 2 - 1).astype(np.complex64)
+    x = rng.standard_normal((P, stride, 2), dtype=np.float32).view(np.complex64)[..., 0]
+    x *= np.float32(np.sqrt(0.5))
+    pulses = {"always": slice(0, P), "late": slice(P // 2, P), "early": slice(0, P // 10)}[when]
+    n = np.arange(L)
+    hot = list(range(7, G, 40))
+    for i, g in enumerate(hot):
+        tone = 10.0 ** ((5.0 + 25.0 * i / len(hot)) / 20.0) * np.exp(2j * np.pi * rng.uniform() * n)
+        at = 5 + g * step
+        x[pulses, at:at + L] += (tx[pulses] if per else tx) * tone.astype(np.complex64)
+    if st == "ci16":
+        x = np.round(x.view(np.float32).reshape(P, stride, 2) * 200.0).astype(np.int16)
+    gates = sorted(hot[:6] + [g + 20 for g in hot[:6] if g + 20 < G])
+    ref = oracle_spectra(x, tx, n_gates=G, gate_step=step, first_gate=5, fft_len=N, tx_per_pulse=per,
+                         gates=gates)
+    ctx = ispl.Context(code_len=L, fft_len=N, n_gates=G, gate_step=step, first_gate=5,
+                       pulse_stride=stride, sample_type=st, max_pulses=P)
+    xs, xt = torch.from_numpy(x).to(DEV), torch.from_numpy(tx).to(DEV)
+    out = ctx.integrate_spectra(xs, xt)
+    got = out[gates].cpu().numpy().astype(np.float64)
+    mean = ref.mean(axis=1, keepdims=True)
+    d = 2.0 ** -25 * 64.0
+    bound = 2.0 * d * np.sqrt(ref * np.maximum(ref, mean)) + d * d * mean
+    assert (np.abs(got - ref) / bound).max() <= 1.0
+    again = ctx.integrate_spectra(xs, xt, out=out.clone(), accumulate=True)
+    np.testing.assert_allclose(again.cpu().numpy(), 2 * out.cpu().numpy(), rtol=1e-6)
+    lst = torch.tensor(gates[::-1], dtype=torch.int32, device=DEV)
+    part = torch.full((G, N), -1.0, device=DEV)
+    lst = torch.cat([lst, torch.zeros(G - len(gates), dtype=torch.int32, device=DEV)])
+    ctx.integrate_spectra(xs, xt, out=part,
+                          gates=(lst, torch.tensor([len(gates)], dtype=torch.int32, device=DEV)))
+    listed = part[gates].cpu().numpy().astype(np.float64)
+    assert (np.abs(listed - ref) / bound).max() <= 1.0
+    rest = torch.ones(G, dtype=torch.bool, device=DEV)
+    rest[gates] = False
+    assert bool((part[rest] == -1.0).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("case", [
     # L,   N,    G,  P,  K,   type, per-pulse codes
     (100, 4096, 24, 20, 128, "c64", True),
