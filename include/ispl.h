@@ -29,11 +29,11 @@
  *   - Nothing throws or aborts across this ABI.
  *   - A context is not thread-safe: one thread at a time per context.  A
  *     context and the objects built on it (zoom, learned zoom) own scratch
- *     (pulse-chunk partials, FP16 exponents, code sign bits) that every call
- *     reuses, so calls on one context or object must not overlap on
+ *     (pulse-chunk partials or summed grids, lists of gates, FP16 exponents,
+ *     code sign bits) that every call reuses, so calls on one context or object must not overlap on
  *     different streams either.
  *   - Results are bit-identical from run to run for the same context,
- *     arguments and device (no atomics, fixed reduction order).
+ *     arguments and device (fixed reduction order).
  */
 #ifndef ISPL_H
 #define ISPL_H
@@ -82,8 +82,9 @@ typedef struct {
   int32_t device;       /* HIP device ordinal */
 } ispl_config;
 
-/* Validates `cfg`, selects `cfg->device`, builds the twiddle table and the
- * scratch buffers the plan needs, and returns a new context in *out.
+/* Validates `cfg`, selects `cfg->device`, builds the twiddle tables and the
+ * scratch buffers the plan needs (up to 128 MiB of partials or summed grids,
+ * and 64 MiB of code sign bits), and returns a new context in *out.
  * Config errors are reported before the device is touched.  Returns
  * ISPL_ERR_DEVICE when the device is missing or is not gfx950. */
 ispl_status ispl_create(const ispl_config* cfg, ispl_ctx** out);
@@ -103,13 +104,14 @@ ispl_status ispl_create(const ispl_config* cfg, ispl_ctx** out);
  *   n_pulses  0 <= n_pulses <= max_pulses.  With 0 pulses the sum is empty:
  *             spectra is zeroed (accumulate = 0) or left as is (accumulate = 1).
  * Arithmetic: decode, transform, power and accumulation in FP32.  Codes of at
- * most 8192 samples may be transformed to a grid of 2^m >= 2 L - 1 frequencies instead
- * (where that is estimated to be faster), the powers summed over the pulses in double, and
- * the N bins formed from the sums (|X|^2 of L samples has 2 L - 1 coefficients).  A gate
- * whose grid holds a line or a gap so strong that its bins would be less exact than the direct
- * transform's, or infinities or NaN, is then redone by direct transforms, decided on the
- * device: a call in which every gate has such a line takes up to the time of both (12 % more than
- * direct transforms at L = 1000, N = 16384).  S >= 0 in either form.
+ * most 4096 samples may be transformed to a grid of 2^m >= 2 L - 1 frequencies
+ * instead (where that is estimated to be faster), the powers summed over the
+ * pulses in double, and the N bins formed from the sums (|X|^2 of L samples has
+ * 2 L - 1 coefficients).  A gate whose grid holds a line or a gap so strong that
+ * its bins would be less exact than the direct transform's, or infinities or
+ * NaN, is redone by direct transforms, decided on the device: a call in which
+ * every gate has such a line takes 3 to 19 % longer than direct transforms
+ * alone (measured at L = 256 to 4000).  S >= 0 in either form.
  */
 ispl_status ispl_integrate_spectra(ispl_ctx* ctx, const void* samples,
                                    const float* tx_code, int32_t tx_per_pulse,
@@ -165,13 +167,14 @@ ispl_status ispl_find_plasma_line_gates(ispl_ctx* ctx, const float* spectra, int
  *             as for ispl_integrate_spectra (caller-owned device buffers).
  * The twiddle table and the pulse-chunk partial spectra live in a static
  * device array of ISPL_NOALLOC_SCRATCH_BYTES bytes (512 KiB of twiddles, 64
- * MiB of partials) that the library holds on every GPU it runs on until the
+ * MiB of partials, or a summed grid and its tables) that the library holds on every GPU it runs on until the
  * process ends; the table is rebuilt on `stream` by every call (one small
  * launch).  The launch plan is ispl_create's automatic plan, whose partials
  * never exceed 64 MiB (fewer than four workgroup slots of the chip per chunk
  * row); a plan that needed more would be rejected with ISPL_ERR_UNSUPPORTED
  * before anything is queued.  Results equal those of ispl_integrate_spectra
- * (the same plan, the same kernels).  Every call on one GPU shares that GPU's
+ * (the same plan, the same kernels; where the scratch bounds the chunks, up to
+ * the order of the pulse sum).  Every call on one GPU shares that GPU's
  * array, which keeps the last call's contents: calls that overlap on one GPU
  * (on different streams, or from different threads) race and give wrong
  * results.  The first call on a device looks up its copy of the array
@@ -197,10 +200,13 @@ ispl_status ispl_integrate_spectra_noalloc(const ispl_config* cfg, const void* s
  * transformed in FP32 to a grid of 2^m >= 2 L - 1 points instead, the powers summed and the
  * windows taken from it in double precision, where that is at least as exact as the chosen
  * split's products (decided per gate on the device; the others run as products).
+ * The choice of grid or products is by estimated time; FP16 calls above 4 M
+ * samples, whose products would scale all gates of a pulse alike, take the grid.
  */
 typedef enum {
   ISPL_ZOOM_BF16X3 = 0,  /* BF16 hi/lo split: ~16 significant bits per product */
-  ISPL_ZOOM_FP16X3 = 1   /* FP16 hi/lo split with per-pulse power-of-two scaling: ~22 bits */
+  ISPL_ZOOM_FP16X3 = 1   /* FP16 hi/lo split, ~22 bits, scaled by a power of two per pulse and
+                            gate (calls of up to 4 M samples of all gates) or per pulse */
 } ispl_zoom_precision;
 
 typedef struct ispl_zoom ispl_zoom; /* opaque; must not outlive its context */
@@ -316,10 +322,10 @@ ispl_status ispl_net_select(ispl_net* net, const float* logits, int32_t n_gates,
 /*
  * Learned zoom: peak frequency of every gate without the full-resolution
  * spectrum of every gate.  One call runs, on `stream`, what these calls
- * compute one after another (in six launches, seven with a zoom from the grid):
+ * compute one after another:
  *   1. ispl_integrate_spectra at N_c = 1024 (the coarse spectra; its pulses
- *      are split into chunks of at least 4, so the coarse sums may differ
- *      from a context's own in rounding);
+ *      may be split into more chunks than a context's, so the coarse sums may
+ *      differ from a context's own in rounding);
  *   2. the network's features and BF16 logits;
  *   3. ispl_net_select with (cfg->fft_len, window_bins, threshold);
  *   4. ispl_zoom_spectra_gates over the zoomed gates (window_bins bins from
@@ -342,7 +348,8 @@ ispl_status ispl_net_select(ispl_net* net, const float* logits, int32_t n_gates,
  * be on cfg->device; its current parameters are used at every call.  The
  * object owns two contexts, a zoom object, [n_gates] x (2 * 1024 +
  * window_bins + fft_len) floats of buffers and up to 16 MiB of fallback
- * chunk partials.  Not thread-safe, and calls on
+ * chunk partials; the coarse context and the zoom their grid scratch, as
+ * ispl_create and ispl_zoom_create say.  Not thread-safe, and calls on
  * one object must not overlap on different streams (it owns the scratch and
  * the decision's completion counter).  Capturable in a HIP graph (it neither
  * allocates nor synchronises).
@@ -488,7 +495,8 @@ ispl_status ispl_stream_submit(ispl_stream* st, int32_t slot, int32_t n_pulses,
 ispl_status ispl_stream_sync(ispl_stream* st);
 
 /* Launch plan of the direct N-point transform for n_pulses pulses with this config
- * (calls that sum on a shorter grid plan that launch by themselves); host-only (no device call), for tests and tooling.  Fills, when non-NULL:
+ * (calls that sum on a grid plan that launch by themselves); host-only (no device
+ * call), for tests and tooling.  Fills, when non-NULL:
  * chunks = number of pulse chunks integrated side by side (1 = no partial
  * buffers), waves_per_block, blocks = workgroups of the fused launch. */
 ispl_status ispl_plan(const ispl_config* cfg, int32_t n_pulses, int32_t* chunks,

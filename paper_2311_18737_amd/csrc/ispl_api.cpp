@@ -294,10 +294,10 @@ constexpr int32_t kMinFoldPulses = 3;
 // Pulses after which a long call looks for gates that will be redone, whose other pulses it then
 // leaves out (0: not at all): a sixteenth, from 100 us on a grid on.  Measured (us; no gate has a
 // line: one pass, two passes; all have one at 0 dB: direct, one pass and direct, two passes and direct):
-// 500 pulses x 600 gates, L = 480, N = 8192: 367, 398; 2057, 2668, 2169
-// 500 x 500, 1000, 16384: 616, 628; 3131, 3884, 3243
-// 250 x 500, 2000, 32768: 992, 1023; 3999, 4925, 4127
-// 200 x 500, 4000, 16384: 1329, 1370; 2295, 3591, 2508
+// 500 pulses x 600 gates, L = 480, N = 8192: 367, 396; 2057, 2668, 2190
+// 500 x 500, 1000, 16384: 616, 642; 3131, 3884, 3342
+// 250 x 500, 2000, 32768: 992, 1022; 3999, 4925, 4157
+// 200 x 500, 4000, 16384: 1329, 1373; 2295, 3591, 2498
 int32_t probe_pulses(int32_t n_pulses, double grid_us) {
   return n_pulses >= 64 && grid_us >= 100.0 ? std::max(16, n_pulses / 16) : 0;
 }

@@ -59,8 +59,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // barrier): each takes its own run of pulses, and the workgroup's sums meet in
 // LDS at the end.
 //
-// What bounds it is VALU issue (M = 2048: 580 VALU instructions per wave and
-// pulse at 0.30 per SIMD and cycle).  Register-only probes at four waves per
+// What bounds it is VALU issue (M = 2048: 600 VALU instructions per wave and
+// pulse, 32 of them in double, at 0.29 per SIMD and cycle; a fifth of the waves' time goes to LDS).  Register-only probes at four waves per
 // SIMD: two-operand (4-byte) instructions issue at 0.43 per cycle, three-operand
 // ones (8 bytes) at 0.34, and conversions, shifts and anything reading a scalar
 // register at 0.22, a v_permlane swap at 0.12.  Hence pass 3's exchange between
@@ -480,7 +480,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Grid pass, 1024 < L <= 8192: M = 1024 J points, J = 4, 8 or 16 >= L / 512.
+// Grid pass, L > 1024: M = 1024 J points, J = 4 or 8 >= L / 512, and J = 16 where
+// those are all the bins (L <= 8192).
 //
 // A workgroup of J waves transforms one pulse at a time.  With n = lg + 1024 j
 // the first pass is a J-point DFT over j for every lg < 1024 (half of its inputs
@@ -489,7 +490,8 @@ __global__ void __launch_bounds__(64 * W, 4) grid_spectra(FoldArgs a) {
 // W_M^{k1 lg} gives bins k1 + J kb.  The factors are a geometric progression in
 // every pass, so none costs a multiplication of its own.
 //
-// VALU issue bounds it like the short grid, with two barriers a pulse; registers
+// Two barriers a pulse and the exchange bound it (J = 8, int16: 29 % of the waves' time waits for
+// LDS, VALU issue 0.19 per SIMD and cycle); registers
 // decide what is kept in flight: all eight int16 samples of the next pulse, half
 // of the complex64 ones (all of them spill, and a reload waits for every load
 // before it).  200 pulses x 500 gates at L = 4000, N = 16384, phase codes (int16)
@@ -754,7 +756,7 @@ __global__ void __launch_bounds__(64 * J, 4) grid_long(FoldArgs a) {
 // The transforms run in double precision: a line of power S_l leaves rounding of
 // about 1e-7 S_l at its mirror frequency and other places of an FP32
 // transform's structure, where S may be a hundred times smaller, which no direct
-// transform does (1000 gates of N = 16384 take 69 us, in FP32 50).  The lags are double too: with
+// transform does (1000 gates of N = 16384 take 71 us, in FP32 50).  The lags are double too: with
 // FP32 lags a line at -10 dB left 7e-7 at L = 1000, now 4e-7.
 
 // SG-point DFT in place, natural order (SG = 2 or 4).
@@ -1193,8 +1195,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, 2) expand_grid(FoldArgs a) {
 // (the lag is one broadcast LDS read for eight multiply-adds), the eighths
 // meet in LDS.  4 K L double multiply-adds a gate are little beside a transform
 // of N points and need no window-sized table.  1000 pulses x 1000 gates, L = 256, K = 256
-// of N = 16384: the pulse pass 400 us, the windows 27; by matrix products (each
-// pulse's K L) 1180.  100 x 64: 16.8 us against 23, latency of the two kernels.
+// of N = 16384: the pulse pass 430 us, the windows 30; by matrix products (each
+// pulse's K L) 1150.  Small calls are faster by products (the rule of the zoom plans).
 
 template <bool WIDE>
 __global__ void __launch_bounds__(64 * EXP_WAVES, 4) expand_window(FoldArgs a) {

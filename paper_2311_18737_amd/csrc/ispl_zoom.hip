@@ -1,5 +1,6 @@
-// Zoom DFT on the matrix cores (gfx950 MFMA), for codes of more than 1024 samples and
-// those too long for a grid of 2 L - 1 <= N points (the others: ispl_grid.hip): a window of K bins of the
+// Zoom DFT on the matrix cores (gfx950 MFMA), for codes of more than 1024 samples or
+// too long for a grid of 2 L - 1 <= N points, for small calls, and for the gates that a
+// grid leaves over (the others: ispl_grid.hip): a window of K bins of the
 // N-point spectrum of every gate, S[g][j] = sum_p |Z_{p,g}[j]|^2 with
 //
 //   Z_{p,g}[j] = sum_{n < L} y'_{p,g}[n] W_N^{j n},
@@ -15,9 +16,9 @@
 // Precision: both operands are split into a high and a low 16-bit part
 // (BF16 or FP16) and D = A_hi B_hi + A_hi B_lo + A_lo B_hi accumulates in
 // FP32; the dropped A_lo B_lo term and the split residuals are about 2^-16
-// (BF16) or 2^-22 (FP16) of each product.  FP16 columns (pulses) are scaled by a
-// power of two that puts the largest decoded sample of the pulse below 2^14
-// (no overflow, yr + yi stays below 2^15; low parts stay normal) and the
+// (BF16) or 2^-22 (FP16) of each product.  FP16 columns (a gate's pulses) are scaled by a
+// power of two that puts the largest decoded sample of the pulse in that gate, in large
+// calls of the pulse in all gates, below 2^14 (no overflow, yr + yi stays below 2^15; low parts stay normal) and the
 // scale is removed exactly before the pulse sum.  Decode, shift and pulse
 // integration run in FP32.
 //
