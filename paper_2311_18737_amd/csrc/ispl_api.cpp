@@ -292,14 +292,15 @@ int32_t grid_run(int32_t n_gates, int64_t most) {
 constexpr int32_t kMinFoldPulses = 3;
 
 // Pulses after which a long call looks for gates that will be redone, whose other pulses it then
-// leaves out (0: not at all): a sixteenth, from 100 us on a grid on.  Measured (us; no gate has a
+// leaves out (0: not at all): a sixteenth, but 16, in calls of 128 pulses and 100 us on a grid or
+// more (in one of 64 x 1000 gates, L = 1000, N = 16384, they cost 27 of 240 us).  Measured (us; no gate has a
 // line: one pass, two passes; all have one at 0 dB: direct, one pass and direct, two passes and direct):
 // 500 pulses x 600 gates, L = 480, N = 8192: 367, 396; 2057, 2668, 2190
 // 500 x 500, 1000, 16384: 616, 642; 3131, 3884, 3342
 // 250 x 500, 2000, 32768: 992, 1022; 3999, 4925, 4157
 // 200 x 500, 4000, 16384: 1329, 1373; 2295, 3591, 2498
 int32_t probe_pulses(int32_t n_pulses, double grid_us) {
-  return n_pulses >= 64 && grid_us >= 100.0 ? std::max(16, n_pulses / 16) : 0;
+  return n_pulses >= 128 && grid_us >= 100.0 ? std::max(16, n_pulses / 16) : 0;
 }
 
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, const GridForce& force = {}) {
