@@ -25,8 +25,10 @@ METRIC = "range-gate spectra/s at N=16384 + % HBM roofline; learned-zoom vs plai
 WORKLOAD = "realistic"
 PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector peak (published)
 PEAK_HBM_GBS = 8000.0      # MI355X HBM3E (published)
-KERNEL_SRC = os.path.join(ROOT, "paper_2311_18737_amd", "csrc", "ispl_kernels.hip")
-PMC_SUMMARY = os.path.join(ROOT, "profiles", "fused_spectra_realistic_hbm_traffic.txt")
+# the headline integration's kernels (decode, grid transform, expansion), and their HBM counters
+KERNEL_SRC = [os.path.join(ROOT, "paper_2311_18737_amd", "csrc", name)
+              for name in ("ispl_grid.hip", "ispl_fft.h", "ispl_fft64.h")]
+PMC_SUMMARY = os.path.join(ROOT, "profiles", "folded_realistic_hbm_traffic.txt")
 
 
 def log(msg):
@@ -56,14 +58,25 @@ def algorithmic_bytes(cfg, bytes_per_sample: int) -> float:
     return float(rows + codes + spectra)
 
 
+def grid_points(n_fft: int, code_len: int) -> int:
+    """Points of the transform that a long integration takes per pulse and gate: |X|^2 of L
+    samples on 2^m >= 2 L - 1 frequencies, the N bins following once per gate, or all N where
+    that grid is not shorter or has more than 8192 points."""
+    grid = max(128, 1 << (2 * code_len - 2).bit_length())
+    return grid if grid <= min(n_fft, 8192) else n_fft
+
+
 def kernel_source_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in KERNEL_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic():
-    """HBM bytes per fused launch from the committed rocprofv3 counter summary,
-    or None when it is absent or was taken on a different kernel source."""
+    """HBM bytes of one integration (all its launches) from the committed rocprofv3 counter
+    summary, or None when it is absent or was taken on a different kernel source."""
     if not os.path.exists(PMC_SUMMARY):
         return None
     text = open(PMC_SUMMARY).read()
@@ -226,7 +239,7 @@ def small_workload(steps: int, seed: int, dev):
         ctx.find_plasma_line(S, out_bins=bins, want_power=False, stream=stream)
 
     out = {"workload": "small: 100 pulses x 64 gates, code length 256, FFT N=1024, complex64",
-           "plan": ispl.plan(cfg.n_pulses, max_pulses=cfg.n_pulses, **geo)}
+           "direct_plan": ispl.plan(cfg.n_pulses, max_pulses=cfg.n_pulses, **geo)}
     for name, fn in (("context", step), ("noalloc", noalloc_step)):
         for _ in range(3):
             fn()
@@ -247,11 +260,14 @@ def small_workload(steps: int, seed: int, dev):
 
 
 def zoom_study(steps: int, seed: int, dev):
-    """Matrix-core zoom DFT on the small workload (100 pulses x 64 gates,
-    L = 256): (a) a 512-bin window at N = 1024 around every gate's true line,
-    BF16 and FP16 split precision, error against the FP64 oracle; (b) a 256-bin
-    window at N = 16384 resolution, timed against the plain path computing
-    the whole 16384-bin spectrum of the same data."""
+    """Zoom DFT on the small workload (100 pulses x 64 gates, L = 256): (a) a
+    512-bin window at N = 1024 around every gate's true line, BF16 and FP16
+    split precision, error against the FP64 oracle; (b) a 256-bin window at
+    N = 16384 resolution, timed against the plain path computing the whole
+    16384-bin spectrum of the same data.  The library takes a window by
+    matrix products of the split or from the pulse-summed grid (in FP32 and
+    double, whatever the split), by estimated time; where both precisions
+    show the same error, both came from the grid."""
     import numpy as np
     import torch
 
@@ -584,7 +600,7 @@ def main():
     ap.add_argument("--paper-steps", type=int, default=5,
                     help="timed runs of the paper's Section 4 workload (0 = skip)")
     ap.add_argument("--zoom-steps", type=int, default=10,
-                    help="timed runs of the matrix-core zoom DFT study (0 = skip)")
+                    help="timed runs of the zoom DFT study (0 = skip)")
     ap.add_argument("--batch-steps", type=int, default=5,
                     help="timed runs of the uneven-batch study at full size (0 = skip)")
     ap.add_argument("--stream-reps", type=int, default=3,
@@ -644,7 +660,7 @@ def main():
         if ev is not None:
             ev[2].record(stream)
 
-    log(f"plan {plan}; warmup {args.warmup}")
+    log(f"direct plan {plan}; warmup {args.warmup}")
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
@@ -674,9 +690,7 @@ def main():
 
     units = cfg.n_pulses * cfg.n_gates
     t_kernel = float(np.mean(integ_ms)) / 1e3
-    # what the launch transforms: |X|^2 of L samples on a grid of 2^m >= 2 L - 1 points
-    # per pulse and gate (the N bins follow once per gate), or N points if fewer
-    grid = min(cfg.fft_len, max(128, 1 << (2 * cfg.code_len - 2).bit_length()))
+    grid = grid_points(cfg.fft_len, cfg.code_len)
     flops = units * flops_per_spectrum(grid, cfg.code_len)
     achieved_tflops = flops / t_kernel / 1e12
     bps = 4 if cfg.sample_type == "ci16" else 8
@@ -718,7 +732,7 @@ def main():
                         "2 kHz line width",
             "n_pulses": cfg.n_pulses, "n_gates": cfg.n_gates, "code_len": cfg.code_len,
             "fft_len": cfg.fft_len, "gate_step": cfg.gate_step, "sample_type": cfg.sample_type,
-            "parallelism": "single GPU", "plan": plan,
+            "parallelism": "single GPU", "grid_points": grid, "direct_plan": plan,
         },
         "roofline": {
             "bound": "alu",
