@@ -258,3 +258,94 @@ def test_zoom_of_gates_far_apart_in_power(ispl, case):
     d = 8.0 * 2.0 ** -22
     bound = 2.0 * d * np.sqrt(want * np.maximum(want, mean)) + d * d * mean
     assert (np.abs(got - want) / bound).max() <= 1.0
+
+
+@pytest.mark.parametrize("sample_type", ["c64", "ci16"])
+def test_lines_in_every_slice(ispl, sample_type):
+    """More gates than the grid scratch holds, in calls that look for lines early: lines of 15 dB in
+    gates of the first and the last slice, in whole calls and in listed ones."""
+    L, N, G, P, step = 3000, 16384, 2200, 130, 2
+    rng = np.random.default_rng(7)
+    stride = (G - 1) * step + L
+    tx = (rng.integers(0, 2, (P, L)) * 2 - 1).astype(np.complex64)
+    x = rng.standard_normal((P, stride, 2), dtype=np.float32).view(np.complex64)[..., 0]
+    hot = [5, 1090, 1110, 2190]
+    n = np.arange(L)
+    for g in hot:
+        tone = 10.0 ** (15.0 / 20.0) * np.exp(2j * np.pi * rng.uniform() * n)
+        x[:, g * step:g * step + L] += (tx * tone).astype(np.complex64)
+    if sample_type == "ci16":
+        x = np.round(x.view(np.float32).reshape(P, stride, 2) * 200.0).astype(np.int16)
+    gates = sorted(hot + [0, 6, 1099, 1100, 1101, 2199])
+    ref = oracle_spectra(x, tx, n_gates=G, gate_step=step, first_gate=0, fft_len=N, tx_per_pulse=True,
+                         gates=gates)
+    mean = ref.mean(axis=1, keepdims=True)
+    d = 2.0 ** -25 * 64.0
+    bound = 2.0 * d * np.sqrt(ref * np.maximum(ref, mean)) + d * d * mean
+    ctx = ispl.Context(code_len=L, fft_len=N, n_gates=G, gate_step=step, pulse_stride=stride,
+                       sample_type=sample_type, max_pulses=P)
+    xs, xt = torch.from_numpy(x).to(DEV), torch.from_numpy(tx).to(DEV)
+    out = ctx.integrate_spectra(xs, xt)
+    got = out[gates].cpu().numpy().astype(np.float64)
+    assert (np.abs(got - ref) / bound).max() <= 1.0
+    # the tested gates last in a list of most
+    order = np.concatenate([np.setdiff1d(np.arange(0, G, 1), gates)[: G - 100], gates]).astype(np.int32)
+    lst = torch.zeros(G, dtype=torch.int32, device=DEV)
+    lst[:len(order)] = torch.from_numpy(order).to(DEV)
+    count = torch.tensor([len(order)], dtype=torch.int32, device=DEV)
+    part = torch.zeros_like(out)
+    ctx.integrate_spectra(xs, xt, out=part, gates=(lst, count))
+    got = part[gates].cpu().numpy().astype(np.float64)
+    rest = np.setdiff1d(np.arange(G), order)
+    ctx.close()
+    assert (np.abs(got - ref) / bound).max() <= 1.0
+    assert not part[rest.tolist()].any()
+
+
+@pytest.mark.parametrize("case", [
+    # L,   N,     G,   P,   K,   type, per-pulse codes
+    (256, 16384, 1000, 400, 256, "c64", True),
+    (700, 8192, 400, 301, 128, "ci16", False),
+], ids=lambda c: "L{}_N{}_G{}_P{}_K{}_{}_{}".format(*c))
+def test_zoom_of_long_calls_of_mixed_gates(ispl, case):
+    """Windows of calls that look for lines early: lines of 30 dB in some gates, all calls and listed
+    ones, at the FP16 split's accuracy."""
+    L, N, G, P, K, st, per = case
+    rng = np.random.default_rng(L + G)
+    step, hot = 3, [2, G // 2, G - 1]
+    stride = (G - 1) * step + L
+    tx = (rng.integers(0, 2, (P if per else 1, L)) * 2 - 1).astype(np.complex64)
+    x = rng.standard_normal((P, stride, 2), dtype=np.float32).view(np.complex64)[..., 0]
+    freq = rng.uniform(size=G)
+    for g in hot:
+        tone = 10.0 ** (30.0 / 20.0) * np.exp(2j * np.pi * freq[g] * np.arange(L))
+        x[:, g * step:g * step + L] += (tx * tone).astype(np.complex64)
+    if st == "ci16":
+        x = np.round(x.view(np.float32).reshape(P, stride, 2) * 100.0).astype(np.int16)
+    start = (np.round(freq * N).astype(np.int64) - K // 2).astype(np.int32)
+    gates = sorted(hot + [0, 1, 3, G // 2 + 1, G - 2])
+    ref = oracle_spectra(x, tx, n_gates=G, gate_step=step, first_gate=0, fft_len=N, tx_per_pulse=per,
+                         gates=gates)
+    mean = ref.mean(axis=1, keepdims=True)
+    want = np.take_along_axis(ref, (start[gates].astype(np.int64)[:, None] + np.arange(K)) % N, axis=1)
+    d = 8.0 * 2.0 ** -22
+    bound = 2.0 * d * np.sqrt(want * np.maximum(want, mean)) + d * d * mean
+    ctx = ispl.Context(code_len=L, fft_len=N, n_gates=G, gate_step=step, pulse_stride=stride,
+                       sample_type=st, max_pulses=P)
+    zoom = ispl.Zoom(ctx, K, "fp16x3")
+    args = (torch.from_numpy(x).to(DEV), torch.from_numpy(tx).to(DEV), torch.from_numpy(start).to(DEV))
+    out = zoom.spectra(*args)
+    got = out[gates].cpu().numpy().astype(np.float64)
+    lst = torch.zeros(G, dtype=torch.int32, device=DEV)
+    lst[:len(gates)] = torch.tensor(gates[::-1], dtype=torch.int32, device=DEV)
+    count = torch.tensor([len(gates)], dtype=torch.int32, device=DEV)
+    part = torch.full_like(out, -1.0)
+    zoom.spectra(*args, out=part, gates=(lst, count))
+    listed = part[gates].cpu().numpy().astype(np.float64)
+    rest = torch.ones(G, dtype=torch.bool, device=DEV)
+    rest[gates] = False
+    assert bool((part[rest] == -1.0).all())
+    zoom.close()
+    ctx.close()
+    assert (np.abs(got - want) / bound).max() <= 1.0
+    assert (np.abs(listed - want) / bound).max() <= 1.0
