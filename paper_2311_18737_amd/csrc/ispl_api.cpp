@@ -223,6 +223,9 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, const GridFor
   // FP32 partials on a grid of the N bins, doubles on a shorter one
   const int64_t row = int64_t{len == c.fft_len && !force.doubles ? 4 : 8} * len * c.n_gates;
   const bool is_long = classes > 2;  // one wave per bin class, one pulse at a time
+  // (steps of 3.4 to 4.9 us with two to four workgroups on a CU for J = 4, 4.0 and 5.4 with one and
+  // two for J = 8, 5.5 for J = 16: int16; c64 a tenth more)
+  const double long_us = classes == 4 ? 2.1 : 2.7;
   double best = 0.0;
   out->len = 0;
   for (int waves = is_long ? classes : 8; waves <= 16; waves = is_long ? 32 : 2 * waves) {
@@ -239,7 +242,8 @@ double grid_split(const ispl_config& c, int len, int32_t n_pulses, const GridFor
       const uint32_t rounds = (wgs + kComputeUnits * per_cu - 1) / (kComputeUnits * per_cu);
       const uint32_t resident = std::min(per_cu, (wgs + kComputeUnits - 1) / kComputeUnits);
       const uint32_t iters = (steps + chunks * runs - 1) / (chunks * runs);
-      const double step_us = std::max(1.6, 0.85 * static_cast<double>(resident * waves) / 4);
+      const double step_us = is_long ? long_us + 1.35 * (classes / 8.0) * resident
+                                     : std::max(1.6, 0.85 * static_cast<double>(resident * waves) / 4);
       const double us = rounds * (iters * step_us + 3.0) + chunks * chunk_us + (chunks > 1 ? sum_us : 0.0);
       if (out->len == 0 || us < best) {
         *out = GridPlan{len, waves, static_cast<int>(chunks), 0};
@@ -303,21 +307,58 @@ int32_t probe_pulses(int32_t n_pulses, double grid_us) {
   return n_pulses >= 128 && grid_us >= 100.0 ? std::max(16, n_pulses / 16) : 0;
 }
 
+// Estimated times of a call at N <= 2048 on a grid of all its bins (by plan `pl`, complex codes)
+// and by direct transforms: the steps of a wave's run, and the SIMD's share of all steps.  Fitted to 800
+// calls of 1 to 1000 pulses x 1 to 2000 gates, c64 and int16, +-1 and complex codes (8 and 5 % rms).
+// The grid for all of them was up to 2.1 times slower than direct transforms (2 pulses x 1143 gates,
+// L = 524, N = 2048: 28.5 us, 13.8; 236 x 1802, L = 921, phase codes: 1303, 961); the faster by these
+// is in the mean 1.36 times faster than direct (1.38 if always right).
+double whole_us(const ispl_config& c, int32_t n_pulses, const GridPlan& pl) {
+  const bool two = pl.len > ispl::SUB, ci16 = c.sample_type == ISPL_SAMPLES_CI16;
+  const int64_t runs = static_cast<int64_t>(pl.chunks) * (two ? pl.waves / 2 : pl.waves);
+  const double iters = static_cast<double>((n_pulses + runs - 1) / runs), mb = 4e-6 * c.n_gates * pl.len;
+  const double waves = static_cast<double>(pl.chunks) * c.n_gates * pl.waves / 1024.0;  // per SIMD
+  const double rounds = std::max(1.0, std::ceil(waves / 4.0));
+  if (!two)
+    return 1.3 + (pl.chunks > 1 ? 2.3 + (0.23 + 0.5 * mb) * pl.chunks : 0.0) +
+           rounds * (2.4 + iters * (ci16 ? 1.6 : 1.77)) + waves * (0.11 + 0.36 * iters);
+  const double step_us = (ci16 ? 2.35 : 3.06) + 0.9 * std::max(0, c.code_len - 512) / 512.0;
+  return 1.9 + (pl.chunks > 1 ? 2.0 + 0.26 * pl.chunks : 0.0) + rounds * (3.2 + iters * step_us) +
+         waves * (0.68 + 0.47 * iters);
+}
+
+// (With L <= 256 a quarter of the samples of each N = 1024 transform.)
+double direct_short_us(const ispl_config& c, int32_t n_pulses) {
+  const Plan pl = make_plan(c, n_pulses);
+  const bool two = c.fft_len > ispl::SUB, few = c.code_len <= 256;
+  const double iters = static_cast<double>((static_cast<int64_t>(n_pulses) + pl.chunks - 1) / pl.chunks);
+  const double waves = static_cast<double>(pl.blocks) * pl.rw / 1024.0, mb = 4e-6 * c.n_gates * c.fft_len;
+  return 3.5 + 0.45 * mb + (pl.chunks > 1 ? 1.75 + (0.22 + 0.62 * mb) * pl.chunks : 0.0) +
+         std::max(1.0, waves / 4.0) * iters * (two ? 1.6 : few ? 1.07 : 1.65) +
+         waves * iters * (two ? 0.63 : few ? 0.41 : 0.52);
+}
+
 GridPlan grid_plan(const ispl_config& c, int32_t n_pulses, const GridForce& force = {}) {
   GridPlan fold{}, whole{};
   const int len = grid_length(c);
   if (len == 0 || n_pulses < 1) return fold;
+  const bool is_short = c.fft_len <= 2 * ispl::SUB;
+  double others_us = is_short ? direct_short_us(c, n_pulses) : direct_us(c, n_pulses);
   // a grid of all the bins needs no expansion
-  const double whole_us = c.fft_len <= 2 * ispl::SUB || len == c.fft_len
-                              ? grid_split(c, c.fft_len, n_pulses, force, &whole)
-                              : 0.0;
+  if (is_short || len == c.fft_len) {
+    const double split_us = grid_split(c, c.fft_len, n_pulses, force, &whole);
+    // (of 16384 bins always: 656 pulses x 260 gates, two rounds of one workgroup a CU, at L = 6611
+    // 7597 us, direct 6083)
+    const double us = is_short ? whole_us(c, n_pulses, whole) : split_us;
+    if (us >= 0.93 * others_us) whole = GridPlan{};
+    others_us = std::min(others_us, us);
+  }
   if (len == c.fft_len || n_pulses < kMinFoldPulses) return whole;
   const double grid_us = grid_split(c, len, n_pulses, force, &fold), fold_us = grid_us + expand_us(c, len);
   fold.probe = probe_pulses(n_pulses, grid_us);
   // gates with a strong line are redone, so a call may cost both: folded from a fifth less on, with
   // few pulses, whose noise alone comes near the limit, from half
-  const double most = (whole.len > 0 ? whole_us : direct_us(c, n_pulses)) * (n_pulses < 16 ? 0.5 : 0.8);
-  return fold_us < most ? fold : whole;
+  return fold_us < others_us * (n_pulses < 16 ? 0.5 : 0.8) ? fold : whole;
 }
 
 // Scratch of calls whose longest runs on a grid by `pl` (of none: 0): its partials and sums, of
