@@ -89,6 +89,31 @@ __device__ __forceinline__ void pulse_exponent_block(const void* __restrict__ sa
   }
 }
 
+// Largest |c|^2 and |x|^2 of a lane's samples of two gates at0 and at1 (the type known, so that all
+// loads of a step are in flight).
+template <int ST>
+__device__ __forceinline__ void gate_maxima(const void* __restrict__ samples,
+                                            const float2* __restrict__ txp, int64_t at0, int64_t at1,
+                                            int32_t code_len, int lane, float& mc, float& m0, float& m1) {
+  constexpr int U = 4;
+  for (int n0 = lane; n0 < code_len; n0 += 64 * U) {
+    float2 c[U], x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // (past the end the last sample again)
+      const int n = min(n0 + 64 * u, code_len - 1);
+      c[u] = txp[n];
+      x[u] = load_any_sample(samples, ST, at0 + n);
+      y[u] = load_any_sample(samples, ST, at1 + n);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mc = fmaxf(mc, c[u].x * c[u].x + c[u].y * c[u].y);
+      m0 = fmaxf(m0, x[u].x * x[u].x + x[u].y * x[u].y);
+      m1 = fmaxf(m1, y[u].x * y[u].x + y[u].y * y[u].y);
+    }
+  }
+}
+
 // The same for each gate by itself, exps[n_gates p + g], so that a gate far weaker than the strongest
 // of its pulse keeps its bits: the gates 8 group ... 8 group + 7 of pulse p, two per wave.
 __device__ __forceinline__ void gate_exponents_block(const void* __restrict__ samples,
@@ -105,23 +130,10 @@ __device__ __forceinline__ void gate_exponents_block(const void* __restrict__ sa
   const int64_t at0 = static_cast<int64_t>(p) * stride + first_gate + static_cast<int64_t>(g0) * gate_step;
   const int64_t at1 = g0 + 1 < n_gates ? at0 + gate_step : at0;
   float mc = 0.f, m0 = 0.f, m1 = 0.f;
-  constexpr int U = 4;
-  for (int n0 = lane; n0 < code_len; n0 += 64 * U) {
-    float2 c[U], x[U], y[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {  // (past the end the last sample again)
-      const int n = min(n0 + 64 * u, code_len - 1);
-      c[u] = txp[n];
-      x[u] = load_any_sample(samples, sample_type, at0 + n);
-      y[u] = load_any_sample(samples, sample_type, at1 + n);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      mc = fmaxf(mc, c[u].x * c[u].x + c[u].y * c[u].y);
-      m0 = fmaxf(m0, x[u].x * x[u].x + x[u].y * x[u].y);
-      m1 = fmaxf(m1, y[u].x * y[u].x + y[u].y * y[u].y);
-    }
-  }
+  if (sample_type == 1)
+    gate_maxima<1>(samples, txp, at0, at1, code_len, lane, mc, m0, m1);
+  else
+    gate_maxima<0>(samples, txp, at0, at1, code_len, lane, mc, m0, m1);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     mc = fmaxf(mc, __shfl_xor(mc, off));

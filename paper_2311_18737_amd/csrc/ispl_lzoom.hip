@@ -188,9 +188,13 @@ select_windows(const float* __restrict__ logits, int32_t n_gates, int32_t fine_l
                       done);
 }
 
-// The window decision (workgroups g < n_gates) and, in the same launch, the
-// zoom DFT's per-pulse pass (workgroup n_gates + p for pulse p; with exponents of each gate, one for
-// every eight gates of a pulse).
+// Workgroups of a pulse in the zoom DFT's per-pulse pass: one; with exponents of each gate one for every
+// eight gates, and one for the code's bits.
+__host__ __device__ inline int prep_groups(int32_t n_gates, const PulseExpArgs& pe) {
+  return pe.exps && pe.gate_exps ? (n_gates + 7) / 8 + (pe.bits ? 1 : 0) : 1;
+}
+
+// The window decision (workgroups g < n_gates) and, in the same launch, that pass.
 __global__ void __launch_bounds__(NT)
 select_and_exponents(const float* __restrict__ logits, int32_t n_gates, int32_t fine_len,
                      int32_t window_bins, float threshold, int32_t* __restrict__ bin_start,
@@ -203,15 +207,19 @@ select_and_exponents(const float* __restrict__ logits, int32_t n_gates, int32_t 
     select_window_block(b, logits, n_gates, fine_len, window_bins, threshold, bin_start,
                         confidence, flag, zoom_list, fallback_list, counts, done);
   } else {
-    const int groups = pe.exps && pe.gate_exps ? (n_gates + 7) / 8 : 1;
+    const int eights = (n_gates + 7) / 8, groups = prep_groups(n_gates, pe);
     const int p = (b - n_gates) / groups, group = (b - n_gates) % groups;
-    if (pe.exps && pe.gate_exps)
-      gate_exponents_block(pe.samples, pe.sample_type, pe.tx, pe.stride, pe.first_gate, pe.gate_step,
-                           n_gates, pe.code_len, pe.tx_per_pulse, p, group, pe.exps);
-    else if (pe.exps)
+    if (pe.exps && pe.gate_exps) {
+      if (group < eights) {
+        gate_exponents_block(pe.samples, pe.sample_type, pe.tx, pe.stride, pe.first_gate, pe.gate_step,
+                             n_gates, pe.code_len, pe.tx_per_pulse, p, group, pe.exps);
+        return;
+      }
+    } else if (pe.exps) {
       pulse_exponent_block(pe.samples, pe.sample_type, pe.tx, pe.stride, pe.lo, pe.hi,
                            pe.code_len, pe.tx_per_pulse, p, pe.exps);
-    if (pe.bits && group == 0)
+    }
+    if (pe.bits)
       code_bits_block(pe.tx, pe.code_len, pe.tx_per_pulse, pe.bit_words, p, pe.bits, pe.binary);
   }
 }
@@ -381,7 +389,7 @@ hipError_t launch_select_and_exponents(const float* logits, int32_t n_gates, int
                                        float* confidence, int32_t* flag, int32_t* zoom_list,
                                        int32_t* fallback_list, int32_t* counts, int32_t* done,
                                        const PulseExpArgs& pe, hipStream_t s) {
-  const unsigned groups = pe.exps && pe.gate_exps ? static_cast<unsigned>(n_gates + 7) / 8 : 1u;
+  const unsigned groups = static_cast<unsigned>(prep_groups(n_gates, pe));
   const unsigned blocks = static_cast<unsigned>(n_gates) + groups * static_cast<unsigned>(pe.n_pulses);
   hipLaunchKernelGGL(select_and_exponents, dim3(blocks), dim3(NT), 0, s, logits, n_gates,
                      fine_len, window_bins, threshold, bin_start, confidence, flag, zoom_list,
