@@ -16,6 +16,7 @@
 static int g_fail = 0;
 static long g_folded = 0, g_packed = 0;
 static std::set<std::pair<int, int>> g_plans;  // (waves, chunks) of folded launches
+static int g_grid_len = 0, g_chunks = 0;       // of the last launch (0: direct)
 #define CHECK(cond)                                                        \
   do {                                                                     \
     if (!(cond)) {                                                         \
@@ -37,6 +38,8 @@ static void check_bits(const uint32_t* bits, const int32_t* binary, int code_len
 }
 
 hipError_t launch_fused(const FusedArgs& a, hipStream_t st) {
+  g_grid_len = a.grid_len;
+  g_chunks = a.grid_chunks;
   if (a.grid_len == 0) return plain_fused(a, st);
   ++g_folded;
   g_plans.insert({a.grid_waves, a.grid_chunks});
@@ -171,6 +174,25 @@ static void folded_calls(int L, int N, int G, int P) {
   free_all();
 }
 
+// What a call of this many pulses sums on: a grid of `len` points in at least `chunks` pulse chunks,
+// or 0 for direct transforms.
+static void plan_of(int L, int N, int G, int P, int len, int chunks) {
+  const ispl_config c = config(L, N, G, P);
+  const void* x = dev<void>(size_t(P) * c.pulse_stride * 4);
+  const float* tx = dev<float>(size_t(P) * L * 8);
+  float* out = dev<float>(size_t(G) * N * 4);
+  ispl_ctx* ctx = nullptr;
+  CHECK(ispl_create(&c, &ctx) == ISPL_OK);
+  if (!ctx) return;
+  g_grid_len = -1;
+  CHECK(ispl_integrate_spectra(ctx, x, tx, 1, P, out, 0, nullptr) == ISPL_OK);
+  if (g_grid_len != len || (len > 0 && g_chunks < chunks))
+    fprintf(stderr, "L %d N %d G %d P %d: grid %d, %d chunks\n", L, N, G, P, g_grid_len, g_chunks);
+  CHECK(g_grid_len == len && (len == 0 || g_chunks >= chunks));
+  ispl_destroy(ctx);
+  free_all();
+}
+
 // A context allocates for the pulses it may sum side by side, not for every
 // pulse that a call may pass.
 static void generous_max_pulses(int L, int N) {
@@ -251,6 +273,15 @@ int main() {
   const int longer[][4] = {{1025, 16384, 300, 64}, {2000, 32768, 600, 40}, {4096, 16384, 500, 20},
                            {8192, 65536, 1, 90},   {5000, 16384, 30, 30}};
   for (const auto& s : longer) folded_calls(s[0], s[1], s[2], s[3]);
+  // the faster form as measured
+  plan_of(256, 1024, 64, 100, 1024, 2);
+  plan_of(524, 2048, 1143, 2, 0, 0);
+  plan_of(999, 2048, 1061, 14, 0, 0);
+  plan_of(114, 1024, 1254, 1, 0, 0);
+  plan_of(595, 2048, 1, 150, 2048, 2);
+  plan_of(3943, 16384, 162, 200, 8192, 2);
+  plan_of(6611, 16384, 260, 656, 0, 0);
+  plan_of(5525, 16384, 43, 13, 16384, 2);
   generous_max_pulses(16, 1024);
   generous_max_pulses(1000, 16384);
   generous_max_pulses(2000, 16384);
