@@ -707,9 +707,16 @@ __global__ void __launch_bounds__(ZTA) zoom_spectra(ProductArgs a) {
   }
 }
 
-// Per-pulse pass: code sign bits (bits != NULL) and FP16 exponents, EXPS = 1 of each pulse by its one
-// workgroup, 2 of each gate by one for every eight gates of a pulse (and one for the bits).
-template <int EXPS>
+// Per-pulse pass of BF16 products: code sign bits.
+__global__ void __launch_bounds__(256)
+pulse_bits(const float* __restrict__ tx, int32_t code_len, int32_t tx_per_pulse, int32_t words,
+           uint32_t* __restrict__ bits, int32_t* __restrict__ binary) {
+  code_bits_block(tx, code_len, tx_per_pulse, words, static_cast<int>(blockIdx.x), bits, binary);
+}
+
+// That of FP16 products: exponents, BY_GATE of each gate by one workgroup for every eight gates of a pulse
+// (and one for the bits) or of each pulse by its one workgroup, and sign bits (bits != NULL).
+template <bool BY_GATE>
 __global__ void __launch_bounds__(256)
 pulse_prep(const void* __restrict__ samples, int32_t sample_type, const float* __restrict__ tx,
            int64_t stride, int64_t lo, int64_t hi, int32_t code_len, int32_t tx_per_pulse,
@@ -718,13 +725,13 @@ pulse_prep(const void* __restrict__ samples, int32_t sample_type, const float* _
            const int32_t* __restrict__ count) {
   if (count && *count <= 0) return;  // no gate listed
   const int p = static_cast<int>(blockIdx.x), group = static_cast<int>(blockIdx.y);
-  if constexpr (EXPS == 2) {
+  if constexpr (BY_GATE) {
     if (group < (n_gates + 7) / 8) {
       gate_exponents_block(samples, sample_type, tx, stride, first_gate, gate_step, n_gates, code_len,
                            tx_per_pulse, p, group, exps);
       return;
     }
-  } else if constexpr (EXPS == 1) {
+  } else {
     pulse_exponent_block(samples, sample_type, tx, stride, lo, hi, code_len, tx_per_pulse, p,
                          exps);
   }
@@ -761,12 +768,17 @@ hipError_t launch_zoom(const ZoomArgs& a, hipStream_t stream, bool prep) {
   if (a.grid_len > 0) return launch_zoom_folded(a, stream);
   int32_t* exps = a.precision == 1 ? a.col_exp : nullptr;
   if (prep && (exps || a.code_bits)) {
-    const int groups = exps && a.gate_exps ? (a.n_gates + 7) / 8 + (a.code_bits ? 1 : 0) : 1;
-    const auto kernel = !exps ? pulse_prep<0> : a.gate_exps ? pulse_prep<2> : pulse_prep<1>;
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.n_pulses), static_cast<unsigned>(groups)),
-                       dim3(256), 0, stream, a.samples, a.sample_type, a.tx, a.stride, a.row_lo, a.row_hi,
-                       a.code_len, a.tx_per_pulse, exps, a.code_pad / 32, a.code_bits, a.code_binary,
-                       a.n_gates, a.first_gate, a.gate_step, a.gate_list ? a.gate_count : nullptr);
+    const dim3 rows(static_cast<unsigned>(a.n_pulses));
+    const int groups = (a.n_gates + 7) / 8 + (a.code_bits ? 1 : 0);
+    if (!exps)
+      hipLaunchKernelGGL(pulse_bits, rows, dim3(256), 0, stream, a.tx, a.code_len, a.tx_per_pulse,
+                         a.code_pad / 32, a.code_bits, a.code_binary);
+    else
+      hipLaunchKernelGGL(a.gate_exps ? pulse_prep<true> : pulse_prep<false>,
+                         a.gate_exps ? dim3(rows.x, static_cast<unsigned>(groups)) : rows, dim3(256), 0,
+                         stream, a.samples, a.sample_type, a.tx, a.stride, a.row_lo, a.row_hi,
+                         a.code_len, a.tx_per_pulse, exps, a.code_pad / 32, a.code_bits, a.code_binary,
+                         a.n_gates, a.first_gate, a.gate_step, a.gate_list ? a.gate_count : nullptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
